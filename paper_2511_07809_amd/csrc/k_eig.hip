@@ -356,147 +356,6 @@ __global__ void k_rank1_update(double* __restrict__ Y, const double* __restrict_
   Y[idx] -= scale_m * m[i] * t[c];
 }
 
-// Right-looking Cholesky of the p x p matrix G + shift * max(diag) * I in
-// place (lower triangle); one block.  info[0] != 0 on a non-positive pivot.
-__global__ void __launch_bounds__(1024) k_cholesky(double* __restrict__ G, int p, double shift_rel,
-                                                   int* __restrict__ info) {
-  __shared__ double sh_shift;
-  __shared__ int sh_fail;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  if (tid == 0) {
-    double mx = 0.0;
-    for (int i = 0; i < p; ++i) mx = fmax(mx, G[(size_t)i * p + i]);
-    sh_shift = shift_rel * mx;
-    sh_fail = 0;
-  }
-  __syncthreads();
-  for (int i = tid; i < p; i += nt) G[(size_t)i * p + i] += sh_shift;
-  __threadfence_block();
-  __syncthreads();
-  for (int j = 0; j < p; ++j) {
-    if (tid == 0) {
-      const double d = G[(size_t)j * p + j];
-      if (!(d > 0.0)) {
-        sh_fail = 1;
-        G[(size_t)j * p + j] = 1.0;
-      } else {
-        G[(size_t)j * p + j] = sqrt(d);
-      }
-    }
-    __threadfence_block();
-    __syncthreads();
-    const double djj = G[(size_t)j * p + j];
-    for (int i = j + 1 + tid; i < p; i += nt) G[(size_t)i * p + j] /= djj;
-    __threadfence_block();
-    __syncthreads();
-    const int rem = p - j - 1;
-    for (int idx = tid; idx < rem * rem; idx += nt) {
-      const int i = j + 1 + idx / rem, k = j + 1 + idx % rem;
-      if (k <= i) G[(size_t)i * p + k] -= G[(size_t)i * p + j] * G[(size_t)k * p + j];
-    }
-    __threadfence_block();
-    __syncthreads();
-  }
-  if (tid == 0 && sh_fail) atomicOr(info, 1);
-}
-
-// The same factorisation with the matrix held in LDS (p <= kLdsP): two
-// barriers per column instead of round trips through global memory.
-constexpr int kLdsP = 128;
-__global__ void __launch_bounds__(1024) k_cholesky_lds(double* __restrict__ G, int p,
-                                                       double shift_rel, int* __restrict__ info) {
-  __shared__ double A[kLdsP * kLdsP];
-  __shared__ double red[1024];
-  __shared__ int sh_fail;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  double mx = 0.0;
-  for (int idx = tid; idx < p * p; idx += nt) {
-    const double v = G[idx];
-    A[idx] = v;
-    if (idx / p == idx % p) mx = fmax(mx, v);
-  }
-  red[tid] = mx;
-  if (tid == 0) sh_fail = 0;
-  __syncthreads();
-  for (int w = nt / 2; w > 0; w >>= 1) {
-    if (tid < w) red[tid] = fmax(red[tid], red[tid + w]);
-    __syncthreads();
-  }
-  const double shift = shift_rel * red[0];
-  for (int i = tid; i < p; i += nt) A[i * p + i] += shift;
-  __syncthreads();
-  for (int j = 0; j < p; ++j) {
-    const double d = A[j * p + j];
-    const double sq = d > 0.0 ? sqrt(d) : 1.0;
-    for (int i = j + 1 + tid; i < p; i += nt) A[i * p + j] /= sq;
-    __syncthreads();
-    if (tid == 0) {
-      if (!(d > 0.0)) sh_fail = 1;
-      A[j * p + j] = sq;
-    }
-    // trailing lower triangle (j < k <= i < p), threads as a 32 x 32 grid
-    for (int i = j + 1 + (tid >> 5); i < p; i += 32) {
-      const double aij = A[i * p + j];
-      for (int k = j + 1 + (tid & 31); k <= i; k += 32) A[i * p + k] -= aij * A[k * p + j];
-    }
-    __syncthreads();
-  }
-  for (int idx = tid; idx < p * p; idx += nt) G[idx] = A[idx];
-  if (tid == 0 && sh_fail) atomicOr(info, 1);
-}
-
-// Binv = (L^-1)^T: wave c computes column c of X = L^-1 by forward
-// substitution, x_i = (delta_ic - sum_{c <= k < i} L[i][k] x_k) / L[i][i].
-// Lane l keeps x_k for k = c + l + 64 j in registers; each row's sum is
-// split over the lanes and added by a butterfly (every lane gets the same
-// value), and row i + 1 of L is loaded while row i is reduced (staging L
-// in LDS measured no faster).  p <= 512.
-constexpr int kInvJ = 8;
-__global__ void __launch_bounds__(256) k_tri_inverse_waves(const double* __restrict__ G, int p,
-                                                           double* __restrict__ Binv) {
-  const int lane = threadIdx.x & 63;
-  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (c >= p) return;                          // the whole wave
-  double xr[kInvJ], ln[kInvJ];
-#pragma unroll
-  for (int j = 0; j < kInvJ; ++j) xr[j] = 0.0;
-  auto load_row = [&](int i, double (&l)[kInvJ]) {
-#pragma unroll
-    for (int j = 0; j < kInvJ; ++j) {
-      const int k = c + lane + 64 * j;
-      l[j] = k < i ? G[(size_t)i * p + k] : 0.0;
-    }
-  };
-  load_row(c, ln);
-  double diag = G[(size_t)c * p + c];
-  for (int i = c; i < p; ++i) {
-    double lc[kInvJ];
-#pragma unroll
-    for (int j = 0; j < kInvJ; ++j) lc[j] = ln[j];
-    const double dg = diag;
-    if (i + 1 < p) {
-      load_row(i + 1, ln);
-      diag = G[(size_t)(i + 1) * p + i + 1];
-    }
-    double part = 0.0;
-#pragma unroll
-    for (int j = 0; j < kInvJ; ++j) part += lc[j] * xr[j];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
-    const double xi = ((i == c ? 1.0 : 0.0) - part) / dg;
-    const int t = i - c;
-#pragma unroll
-    for (int j = 0; j < kInvJ; ++j)
-      if (lane == (t & 63) && j == (t >> 6)) xr[j] = xi;
-  }
-  for (int k = lane; k < c; k += 64) Binv[(size_t)c * p + k] = 0.0;
-#pragma unroll
-  for (int j = 0; j < kInvJ; ++j) {
-    const int k = c + lane + 64 * j;
-    if (k < p) Binv[(size_t)c * p + k] = xr[j];
-  }
-}
-
 // Cyclic Jacobi with the round-robin parallel ordering: in each round the
 // m/2 disjoint pairs (circle method) are rotated at once, so every pair of
 // indices is visited once per sweep.  A pair is rotated only while its
@@ -614,7 +473,7 @@ __global__ void __launch_bounds__(1024) k_jacobi(double* __restrict__ A, double*
 // rotation accumulator Z is in LDS as well (p <= kLdsPZ, the two matrices
 // fill the 160 KB), and Z's array doubles as the reduction scratch before Z
 // is formed and after it is written out; otherwise Z stays in global memory.
-constexpr int kLdsPZ = 100;
+constexpr int kLdsP = 128, kLdsPZ = 100;
 template <bool ZL>
 __global__ void __launch_bounds__(1024) k_jacobi_lds(double* __restrict__ Ag, double* __restrict__ Zg,
                                                  double* __restrict__ ev, int p,
@@ -913,24 +772,6 @@ hipError_t launch_m2_apply(const double* S2, const double* m, const double* t, c
 hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, hipStream_t s) {
   const int splits = (V + 2047) / 2048;
   return gemm(true, p, p, V, A, p, B, p, G, p, 1.0, splits, s);
-}
-
-hipError_t launch_cholesky(double* G, int p, double shift_rel, int* info, hipStream_t s) {
-  if (p <= kLdsP)
-    hipLaunchKernelGGL(k_cholesky_lds, dim3(1), dim3(1024), 0, s, G, p, shift_rel, info);
-  else
-    hipLaunchKernelGGL(k_cholesky, dim3(1), dim3(1024), 0, s, G, p, shift_rel, info);
-  return hipGetLastError();
-}
-
-// Y (V x p) <- Y L^-T, written to Out; Binv is p x p scratch.
-hipError_t launch_trsm_right_into(const double* Y, const double* G, double* Binv, double* Out, int V,
-                                  int p, hipStream_t s) {
-  if (p > 64 * kInvJ) return hipErrorInvalidValue;   // a lane keeps kInvJ entries of a column
-  hipLaunchKernelGGL(k_tri_inverse_waves, dim3((p + 3) / 4), dim3(256), 0, s, G, p, Binv);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return gemm(false, V, p, p, Y, p, Binv, p, Out, p, 1.0, 1, s);
 }
 
 hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s) {

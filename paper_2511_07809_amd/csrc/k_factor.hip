@@ -1,0 +1,303 @@
+// Cholesky factor and triangular inverse of the refresh's p x p Gram matrices
+// on the FP64 matrix cores: G + shift I = R^T R (R upper), Binv = R^-1, so
+// that Q = Y Binv is orthonormal.
+//
+// Bound: a chain of p pivots.  Each costs a reciprocal square root and a
+// rank-one update; only the 16 pivots of a diagonal tile have to be taken one
+// at a time, so a single wave does those in registers and everything else of
+// the block step (the tile row of R, the trailing update, the inverse) is
+// 16 x 16 x 16 products on v_mfma_f64_16x16x4f64.
+//
+// Tiles are kept in the accumulator layout of that instruction: register r of
+// lane l holds entry (4 r + l / 16, l % 16), which is entry r * 64 + l of the
+// row-major tile.  With the upper factor no product needs a transpose:
+//   row of R  : R_kj = R_kk^-T A_kj      B operand = accumulators of A_kj
+//   trailing  : A_ij -= R_ki^T R_kj      both operands = tiles as stored
+//   inverse   : L^-1 (= Binv^T), block column i, Y_ii = R_ii^-T,
+//               Y_ji = -R_jj^-T sum_k R_kj^T Y_ki, again both as stored
+// since lane l supplies A[l % 16][4 s + l / 16] and B[4 s + l / 16][l % 16] in
+// step s.  R_kk^-T is stored by columns, where entry s * 64 + l is the A
+// operand.
+#include "tlda_internal.h"
+
+namespace tlda {
+namespace {
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int kTile = 16, kTileE = kTile * kTile, kMaxNb = 32;   // p <= 512
+
+__device__ __forceinline__ int tile_at(int i, int j) { return j * (j + 1) / 2 + i; }   // i <= j
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+// Orders this wave's LDS stores before its later LDS loads by other lanes.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ doublex4 load_tile(const double* t, int lane) {
+  return doublex4{t[lane], t[64 + lane], t[128 + lane], t[192 + lane]};
+}
+__device__ __forceinline__ void store_tile(double* t, int lane, doublex4 v) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) t[r * 64 + lane] = v[r];
+}
+
+// acc += op(a) b over 16 terms, operands as in the file comment
+__device__ __forceinline__ doublex4 tile_mfma(doublex4 a, doublex4 b, doublex4 acc) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+  return acc;
+}
+
+// One wave: the Cholesky factor of the 16 x 16 tile `a` (row-major in LDS)
+// and the inverse of its transpose.  Lanes 0-15 (and 32-47) hold a column of
+// the tile, lanes 16-31 a column of the identity, and both take the same
+// elimination, which turns the identity into R^-T.  A pivot that is not
+// positive is taken as one and reported.
+__device__ inline bool factor_tile(const double* a, int lane, double* r_out, double* rinvt_cols) {
+  const int c = lane & 15;
+  const bool ident = (lane >> 4) & 1;
+  double v[kTile];
+#pragma unroll
+  for (int i = 0; i < kTile; ++i) v[i] = ident ? (i == c ? 1.0 : 0.0) : a[i * kTile + c];
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < kTile; ++j) {
+    const double d = lane_value(v[j], j);
+    const bool pos = d > 0.0;
+    ok = ok && pos;
+    v[j] *= pos ? 1.0 / sqrt(d) : 1.0;
+    if (!pos && lane == j) v[j] = 1.0;
+#pragma unroll
+    for (int i = j + 1; i < kTile; ++i) v[i] = fma(-lane_value(v[j], i), v[j], v[i]);
+  }
+  wave_sync();
+  if (lane < 16) {
+#pragma unroll
+    for (int i = 0; i < kTile; ++i) r_out[i * kTile + c] = i <= c ? v[i] : 0.0;
+  } else if (lane < 32) {
+#pragma unroll
+    for (int i = 0; i < kTile; ++i) rinvt_cols[c * kTile + i] = v[i];
+  }
+  return ok;
+}
+
+// Entry (gi, gj) of the symmetric matrix padded to whole tiles by the
+// identity, read from the upper triangle.
+__device__ __forceinline__ double padded(const double* G, int p, int gi, int gj, double shift) {
+  const int a = min(gi, gj), b = max(gi, gj);
+  if (b >= p) return a == b ? 1.0 : 0.0;
+  return G[(size_t)a * p + b] + (a == b ? shift : 0.0);
+}
+
+// One wave: block column i of L^-1 = R^-T from the tiles of R and of the
+// diagonal inverses, written to Binv = R^-1 (row-major, p x p; the part below
+// the diagonal is left alone).  y: this column's own tiles (nb of them).
+__device__ inline void inverse_column(const double* tiles, const double* dinv, int nb, int i, int p,
+                                      double* y, double* Binv, int lane) {
+  const int row = lane >> 4, col = lane & 15;
+  for (int j = i; j < nb; ++j) {
+    doublex4 v;
+    if (j == i) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = dinv[i * kTileE + col * kTile + 4 * r + row];
+    } else {
+      // two accumulators: consecutive products do not wait for one another
+      doublex4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
+      int k = i;
+      for (; k + 1 < j; k += 2) {
+        s0 = tile_mfma(load_tile(tiles + (size_t)tile_at(k, j) * kTileE, lane),
+                       load_tile(y + k * kTileE, lane), s0);
+        s1 = tile_mfma(load_tile(tiles + (size_t)tile_at(k + 1, j) * kTileE, lane),
+                       load_tile(y + (k + 1) * kTileE, lane), s1);
+      }
+      if (k < j)
+        s0 = tile_mfma(load_tile(tiles + (size_t)tile_at(k, j) * kTileE, lane),
+                       load_tile(y + k * kTileE, lane), s0);
+      s0 = -(s0 + s1);
+      v = tile_mfma(load_tile(dinv + j * kTileE, lane), s0, doublex4{0.0, 0.0, 0.0, 0.0});
+    }
+    store_tile(y + j * kTileE, lane, v);
+    __threadfence_block();   // the next rows of this column read it back
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int gr = i * kTile + col, gc = j * kTile + 4 * r + row;
+      if (gr < p && gc < p && gr <= gc) Binv[(size_t)gr * p + gc] = v[r];
+    }
+  }
+}
+
+// The largest nb whose nb (nb + 1) / 2 tiles are at most n.
+constexpr int panel_tiles(int n) {
+  int nb = 1;
+  while ((nb + 1) * (nb + 2) / 2 <= n) ++nb;
+  return nb;
+}
+
+// One block of NW waves; tile t = tile_at(i, j) belongs to wave t % NW.
+// SLOTS > 0: a wave's tiles stay in registers (NW SLOTS >= the tile count;
+// at most two waves per SIMD, so that a tile being factored fits beside
+// them); SLOTS == 0: they live in `tiles`, each touched by its own wave alone.
+// INV: the block goes on to the inverse (few tiles: a second launch would
+// cost more than the columns of the other compute units save).
+template <int NW, int SLOTS, bool INV>
+__global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, int p,
+                                               double shift_rel, double* tiles, double* dinv,
+                                               double* ytiles, double* Binv,
+                                               int* __restrict__ info) {
+  __shared__ double panel[(SLOTS == 0 ? kMaxNb : panel_tiles(NW * SLOTS)) * kTileE];
+  __shared__ double diag[kTileE], dcols[kTileE];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (p + kTile - 1) / kTile, nt = nb * (nb + 1) / 2;
+  const int row = lane >> 4, col = lane & 15;
+  double mx = 0.0;
+  for (int i = lane; i < p; i += 64) mx = fmax(mx, G[(size_t)i * p + i]);
+  for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+  const double shift = shift_rel * mx;
+
+  constexpr int R = SLOTS > 0 ? SLOTS : 1;
+  doublex4 acc[R];
+  int ti[R], tj[R];
+  auto first_load = [&](int t, int& i, int& j, doublex4& v) {
+    j = 0;
+    while ((j + 1) * (j + 2) / 2 <= t) ++j;
+    i = t - j * (j + 1) / 2;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      v[r] = padded(G, p, i * kTile + 4 * r + row, j * kTile + col, shift);
+  };
+  if (SLOTS > 0) {
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+      const int t = wave + NW * s;
+      if (t < nt) first_load(t, ti[s], tj[s], acc[s]);
+      else ti[s] = tj[s] = -1;
+    }
+  } else {
+    for (int t = wave; t < nt; t += NW) {
+      int i, j;
+      doublex4 v;
+      first_load(t, i, j, v);
+      store_tile(tiles + (size_t)t * kTileE, lane, v);
+    }
+    __threadfence_block();
+  }
+
+  for (int k = 0; k < nb; ++k) {
+    const int tk = tile_at(k, k);
+    if (tk % NW == wave) {   // its owner factors the diagonal tile
+      doublex4 d = {0.0, 0.0, 0.0, 0.0};
+      if (SLOTS > 0) {
+#pragma unroll
+        for (int s = 0; s < R; ++s)
+          if (wave + NW * s == tk) d = acc[s];
+      } else {
+        d = load_tile(tiles + (size_t)tk * kTileE, lane);
+      }
+      store_tile(diag, lane, d);
+      wave_sync();
+      const bool ok = factor_tile(diag, lane, tiles + (size_t)tk * kTileE, dcols);
+      if (!ok && lane == 0) atomicOr(info, 1);
+      wave_sync();
+      store_tile(dinv + k * kTileE, lane, load_tile(dcols, lane));
+    }
+    __syncthreads();
+    // row k of R: R_kj = R_kk^-T A_kj
+    const doublex4 da = load_tile(dcols, lane);
+    const doublex4 zero = {0.0, 0.0, 0.0, 0.0};
+    if (SLOTS > 0) {
+#pragma unroll
+      for (int s = 0; s < R; ++s)
+        if (ti[s] == k && tj[s] > k) {
+          const doublex4 v = tile_mfma(da, acc[s], zero);
+          store_tile(panel + tj[s] * kTileE, lane, v);
+          store_tile(tiles + (size_t)(wave + NW * s) * kTileE, lane, v);
+        }
+    } else {
+      for (int j = k + 1; j < nb; ++j) {
+        const int t = tile_at(k, j);
+        if (t % NW != wave) continue;
+        const doublex4 v = tile_mfma(da, load_tile(tiles + (size_t)t * kTileE, lane), zero);
+        store_tile(panel + j * kTileE, lane, v);
+        store_tile(tiles + (size_t)t * kTileE, lane, v);
+      }
+    }
+    __syncthreads();
+    // trailing tiles: A_ij -= R_ki^T R_kj
+    if (SLOTS > 0) {
+#pragma unroll
+      for (int s = 0; s < R; ++s)
+        if (ti[s] > k)
+          acc[s] = tile_mfma(-load_tile(panel + ti[s] * kTileE, lane),
+                             load_tile(panel + tj[s] * kTileE, lane), acc[s]);
+    } else {
+      for (int j = k + 1; j < nb; ++j)
+        for (int i = k + 1; i <= j; ++i) {
+          const int t = tile_at(i, j);
+          if (t % NW != wave) continue;
+          double* tp = tiles + (size_t)t * kTileE;
+          store_tile(tp, lane, tile_mfma(-load_tile(panel + i * kTileE, lane),
+                                         load_tile(panel + j * kTileE, lane),
+                                         load_tile(tp, lane)));
+        }
+    }
+  }
+  if (INV) {
+    __threadfence_block();
+    __syncthreads();
+    for (int i = wave; i < nb; i += NW)
+      inverse_column(tiles, dinv, nb, i, p, ytiles + (size_t)i * nb * kTileE, Binv, lane);
+  }
+}
+
+// One wave per block column of the inverse.
+__global__ void __launch_bounds__(64) k_tri_inverse(const double* __restrict__ tiles,
+                                                    const double* __restrict__ dinv, int p,
+                                                    double* ytiles, double* __restrict__ Binv) {
+  const int nb = (p + kTile - 1) / kTile, i = blockIdx.x;
+  inverse_column(tiles, dinv, nb, i, p, ytiles + (size_t)i * nb * kTileE, Binv, threadIdx.x);
+}
+
+}  // namespace
+
+size_t chol_scratch_doubles(int p) {
+  const size_t nb = (p + kTile - 1) / kTile;
+  return (nb * (nb + 1) / 2 + nb + nb * nb) * kTileE;
+}
+
+// Binv (p x p; its part below the diagonal must hold zeros, which stay)
+// becomes R^-1 of G + shift_rel max diag(G) I = R^T R; *info |= 1 on a pivot
+// that is not positive.  scratch: chol_scratch_doubles(p).
+hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
+                               double* Binv, int* info, hipStream_t s) {
+  const int nb = (p + kTile - 1) / kTile;
+  if (p < 1 || nb > kMaxNb) return hipErrorInvalidValue;
+  double* tiles = scratch;
+  double* dinv = tiles + (size_t)nb * (nb + 1) / 2 * kTileE;
+  double* ytiles = dinv + (size_t)nb * kTileE;
+#define TLDA_CHOL(nw, slots, inv)                                                             \
+  hipLaunchKernelGGL((k_chol<nw, slots, inv>), dim3(1), dim3(64 * nw), 0, s, G, p, shift_rel, \
+                     tiles, dinv, ytiles, Binv, info)
+  if (nb <= 5) {
+    TLDA_CHOL(4, 4, true);
+    return hipGetLastError();
+  }
+  if (nb <= 9) TLDA_CHOL(8, 6, false);
+  else if (nb <= 13) TLDA_CHOL(8, 12, false);
+  else TLDA_CHOL(16, 0, false);
+#undef TLDA_CHOL
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_tri_inverse, dim3(nb), dim3(64), 0, s, tiles, dinv, p, ytiles, Binv);
+  return hipGetLastError();
+}
+
+}  // namespace tlda

@@ -257,6 +257,7 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
   tlda::EigScratch& e = c->eig;
   if (e.p == p && e.Q) return TLDA_OK;
   dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.t); dfree(e.Binv);
+  dfree(e.fac);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   e.p = 0;
   e.part_chunks = 0;
@@ -268,6 +269,8 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
   HIP_OK(c, dalloc(&e.G, (size_t)p * p));
   HIP_OK(c, dalloc(&e.Z, (size_t)p * p));
   HIP_OK(c, dalloc(&e.Binv, (size_t)p * p));
+  HIP_OK(c, launch_zero(e.Binv, sizeof(double) * p * p, c->stream));
+  HIP_OK(c, dalloc(&e.fac, tlda::chol_scratch_doubles(p)));
   HIP_OK(c, dalloc(&e.ev, (size_t)p));
   HIP_OK(c, dalloc(&e.t, (size_t)p));
   HIP_OK(c, dalloc(&e.sel, D + (size_t)p * D));
@@ -293,11 +296,11 @@ tlda_status orthonormalise(tlda_ctx* c, const double* in, double* tmp, double* o
   tlda::EigScratch& e = c->eig;
   const int V = c->cfg.V, p = e.p;
   HIP_OK(c, tlda::launch_gram(in, in, e.G, V, p, c->stream));
-  HIP_OK(c, tlda::launch_cholesky(e.G, p, 1e-12, e.info, c->stream));
-  HIP_OK(c, tlda::launch_trsm_right_into(in, e.G, e.Binv, tmp, V, p, c->stream));
+  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 1e-12, e.fac, e.Binv, e.info, c->stream));
+  HIP_OK(c, tlda::launch_block_product(in, e.Binv, tmp, V, p, c->stream));
   HIP_OK(c, tlda::launch_gram(tmp, tmp, e.G, V, p, c->stream));
-  HIP_OK(c, tlda::launch_cholesky(e.G, p, 0.0, e.info, c->stream));
-  HIP_OK(c, tlda::launch_trsm_right_into(tmp, e.G, e.Binv, out, V, p, c->stream));
+  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 0.0, e.fac, e.Binv, e.info, c->stream));
+  HIP_OK(c, tlda::launch_block_product(tmp, e.Binv, out, V, p, c->stream));
   return TLDA_OK;
 }
 
@@ -576,6 +579,7 @@ void destroy_all(tlda_ctx* c) {
   delete[] c->t_stop;
   tlda::EigScratch& e = c->eig;
   dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.t); dfree(e.Binv);
+  dfree(e.fac);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   dfree(c->cp.partial); dfree(c->cp.R1); dfree(c->cp.phi0); dfree(c->cp.grad); dfree(c->cp.X);
   dfree(c->cp.gsq);

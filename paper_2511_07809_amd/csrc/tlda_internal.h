@@ -81,7 +81,8 @@ struct EigScratch {
   double* Z = nullptr;     // [p][p]  eigenvectors of the projected matrix
   double* ev = nullptr;    // [p]
   double* t = nullptr;     // [p]     M1^T Q
-  double* Binv = nullptr;  // [p][p]  inverse-transpose Cholesky factor
+  double* Binv = nullptr;  // [p][p]  inverse of the upper Cholesky factor (zeros below)
+  double* fac = nullptr;   // tiles of the factorisation (chol_scratch_doubles)
   double* sel = nullptr;   // [D + p*D] selected Ritz values and vectors
   double* mcand = nullptr; // [V]     M1 of the refresh in progress
   int* info = nullptr;     // [4]     device status words
@@ -293,9 +294,11 @@ hipError_t launch_m2_apply(const double* S2, const double* m, const double* t, c
 hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, hipStream_t s);
 hipError_t launch_vecT_mat(const double* m, const double* Q, double* t, int V, int p,
                            hipStream_t s);
-hipError_t launch_cholesky(double* G, int p, double shift_rel, int* info, hipStream_t s);
-hipError_t launch_trsm_right_into(const double* Y, const double* G, double* Binv, double* Out, int V,
-                                  int p, hipStream_t s);
+// Binv <- R^-1 with G + shift_rel max diag(G) I = R^T R (R upper; p <= 512);
+// *info |= 1 on a pivot that is not positive
+size_t chol_scratch_doubles(int p);
+hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
+                               double* Binv, int* info, hipStream_t s);
 hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s);
 // Out (V x p) = Q (V x p) Z (p x p)
 hipError_t launch_block_product(const double* Q, const double* Z, double* Out, int V, int p,
