@@ -14,45 +14,33 @@ thread_local EigEnv g_eig_env;
 namespace {
 
 // ---------------------------------------------------------------------------
-// Dense FP64 GEMM: C = alpha * op(A) * B (+ C when accumulating through
-// atomics for split-K).  op(A) is A (M x Kd, row-major, lda) or A^T where A is
-// stored Kd x M.  B is Kd x N row-major (ldb), C is M x N row-major (ldc).
-// 64 x 64 output tile per 256-thread block, 4 x 4 register tile per thread,
-// K step 16 staged through LDS.  grid.z splits Kd into chunks of k_chunk
-// rows; with more than one chunk the tile is added to C with FP64 atomics.
+// Dense FP64 GEMM on the vector ALUs (a second route to check the matrix
+// cores' against): C (M x N) = A (M x Kd) B, all row-major.  64 x 64 output
+// tile per 256-thread block, 4 x 4 register tile per thread, K step 16 staged
+// through LDS.
 // ---------------------------------------------------------------------------
-// (c_stride_z != 0: chunk z writes its own tile to C + z * c_stride_z.)
-template <bool TRANS_A>
 __global__ void __launch_bounds__(256) k_gemm64(int M, int N, int Kd, const double* __restrict__ A,
                                                 int lda, const double* __restrict__ B, int ldb,
-                                                double* __restrict__ C, int ldc, double alpha,
-                                                int k_chunk, int atomic_out, size_t c_stride_z) {
-  C += blockIdx.z * c_stride_z;
+                                                double* __restrict__ C, int ldc) {
   __shared__ double As[16][64 + 2];
   __shared__ double Bs[16][64 + 2];
   const int tid = threadIdx.x;
   const int tx = tid & 15, ty = tid >> 4;
   const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
-  const int kbeg = blockIdx.z * k_chunk;
-  const int kend = min(Kd, kbeg + k_chunk);
   double acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
 
-  for (int k0 = kbeg; k0 < kend; k0 += 16) {
+  for (int k0 = 0; k0 < Kd; k0 += 16) {
     // A tile: 64 rows x 16 k  ->  As[k][row]
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int idx = tid + e * 256;
-      int r, kk;
-      if (TRANS_A) { kk = idx >> 6; r = idx & 63; }   // consecutive threads along M
-      else { r = idx >> 4; kk = idx & 15; }           // consecutive threads along K
+      const int r = idx >> 4, kk = idx & 15;
       const int gr = row0 + r, gk = k0 + kk;
-      double v = 0.0;
-      if (gr < M && gk < kend) v = TRANS_A ? A[(size_t)gk * lda + gr] : A[(size_t)gr * lda + gk];
-      As[kk][r] = v;
+      As[kk][r] = gr < M && gk < Kd ? A[(size_t)gr * lda + gk] : 0.0;
     }
     // B tile: 16 k x 64 cols
 #pragma unroll
@@ -60,7 +48,7 @@ __global__ void __launch_bounds__(256) k_gemm64(int M, int N, int Kd, const doub
       const int idx = tid + e * 256;
       const int kk = idx >> 6, c = idx & 63;
       const int gk = k0 + kk, gc = col0 + c;
-      Bs[kk][c] = (gk < kend && gc < N) ? B[(size_t)gk * ldb + gc] : 0.0;
+      Bs[kk][c] = (gk < Kd && gc < N) ? B[(size_t)gk * ldb + gc] : 0.0;
     }
     __syncthreads();
 #pragma unroll
@@ -84,9 +72,7 @@ __global__ void __launch_bounds__(256) k_gemm64(int M, int N, int Kd, const doub
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int gc = col0 + tx + 16 * j;
-      if (gc >= N) continue;
-      if (atomic_out) unsafeAtomicAdd(&C[(size_t)gr * ldc + gc], alpha * acc[i][j]);
-      else C[(size_t)gr * ldc + gc] = alpha * acc[i][j];
+      if (gc < N) C[(size_t)gr * ldc + gc] = acc[i][j];
     }
   }
 }
@@ -260,74 +246,12 @@ hipError_t dgemm_mfma(int M, int N, int K, const double* A, int lda, const doubl
   return hipGetLastError();
 }
 
-// Out[e] = alpha * sum_z part[z][e] over nz chunks: four lanes per entry,
-// lane c adding the c-th quarter of the chunks in chunk order, the quarters
-// then combined as (q0 + q1) + (q2 + q3) (a fixed order, so the sum is
-// deterministic).  A lane issues the loads of 16 chunks before adding them;
-// the last batch loads from chunk indexes clamped into its quarter and adds
-// only the chunks that exist.
-__global__ void k_sum_partials(const double* __restrict__ part, int nz, size_t mn, int N, int ldc,
-                               double alpha, double* __restrict__ C) {
-  constexpr int kU = 16;
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t e = t >> 2;
-  const int c = (int)(t & 3);
-  const bool in = e < mn;
-  const size_t ec = in ? e : mn - 1;
-  const int per = (nz + 3) / 4;
-  const int z0 = min(c * per, nz), z1 = min(z0 + per, nz);
-  double s = 0.0;
-  for (int z = z0; z < z1; z += kU) {
-    double v[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) v[u] = part[(size_t)min(z + u, z1 - 1) * mn + ec];
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-      if (z + u < z1) s += v[u];
-  }
-  s += __shfl_xor(s, 1, 64);                    // (q0 + q1), (q2 + q3)
-  s += __shfl_xor(s, 2, 64);                    // (q0 + q1) + (q2 + q3)
-  if (in && c == 0) C[(e / N) * ldc + e % N] = alpha * s;
-}
-
-hipError_t gemm(bool transA, int M, int N, int Kd, const double* A, int lda, const double* B,
-                int ldb, double* C, int ldc, double alpha, int splits, hipStream_t s) {
-  if (transA && g_eig_env.part != nullptr && (size_t)M * N <= g_eig_env.part_mn &&
-      g_eig_env.part_chunks > 0) {
-    // A^T B over many rows: row chunks of at least 64 write their own
-    // partials, then one pass adds them in order (no atomics)
-    int nz = (Kd + 63) / 64;
-    if (nz > g_eig_env.part_chunks) nz = g_eig_env.part_chunks;
-    if (nz < 1) nz = 1;
-    const int chunk = ((Kd + nz - 1) / nz + 15) / 16 * 16;
-    nz = (Kd + chunk - 1) / chunk;
-    const size_t mn = (size_t)M * N;
-    dim3 grid((N + 63) / 64, (M + 63) / 64, nz);
-    hipLaunchKernelGGL(k_gemm64<true>, grid, dim3(256), 0, s, M, N, Kd, A, lda, B, ldb,
-                       g_eig_env.part, N, 1.0, chunk, 0, mn);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)((4 * mn + 255) / 256)), dim3(256), 0, s,
-                       g_eig_env.part, nz, mn, N, ldc, alpha, C);
-    return hipGetLastError();
-  }
-  if (!transA && g_eig_env.route == 0) return dgemm_mfma(M, N, Kd, A, lda, B, ldb, C, ldc, alpha, s);
-  if (splits < 1) splits = 1;
-  int chunk = (Kd + splits - 1) / splits;
-  chunk = (chunk + 15) / 16 * 16;
-  splits = (Kd + chunk - 1) / chunk;
-  dim3 grid((N + 63) / 64, (M + 63) / 64, splits);
-  const int atomic_out = splits > 1 ? 1 : 0;
-  if (atomic_out) {
-    hipError_t e = launch_zero(C, (size_t)M * ldc * sizeof(double), s);
-    if (e != hipSuccess) return e;
-  }
-  if (transA)
-    hipLaunchKernelGGL(k_gemm64<true>, grid, dim3(256), 0, s, M, N, Kd, A, lda, B, ldb, C, ldc,
-                       alpha, chunk, atomic_out, (size_t)0);
-  else
-    hipLaunchKernelGGL(k_gemm64<false>, grid, dim3(256), 0, s, M, N, Kd, A, lda, B, ldb, C, ldc,
-                       alpha, chunk, atomic_out, (size_t)0);
+// C (M x N) = A (M x Kd) B: the matrix cores, or the vector-ALU tile kernel.
+hipError_t gemm(int M, int N, int Kd, const double* A, int lda, const double* B, int ldb, double* C,
+                int ldc, hipStream_t s) {
+  if (g_eig_env.route == 0) return dgemm_mfma(M, N, Kd, A, lda, B, ldb, C, ldc, 1.0, s);
+  hipLaunchKernelGGL(k_gemm64, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, s, M, N, Kd, A,
+                     lda, B, ldb, C, ldc);
   return hipGetLastError();
 }
 
@@ -345,15 +269,6 @@ __global__ void k_random_block(double* __restrict__ Q, int V, int p, uint64_t se
   if (idx >= (size_t)V * p) return;
   const uint64_t r = splitmix64(seed * 0x100000001B3ull + idx);
   Q[idx] = (double)(r >> 11) * (1.0 / 9007199254740992.0) * 2.0 - 1.0;
-}
-
-// Y[i][c] -= scale_m * m[i] * t[c]   (the -M1 M1^T part of M2~ applied to Q)
-__global__ void k_rank1_update(double* __restrict__ Y, const double* __restrict__ m,
-                               const double* __restrict__ t, int V, int p, double scale_m) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)V * p) return;
-  const int i = (int)(idx / p), c = (int)(idx % p);
-  Y[idx] -= scale_m * m[i] * t[c];
 }
 
 // Cyclic Jacobi with the round-robin parallel ordering: in each round the
@@ -752,26 +667,9 @@ hipError_t launch_random_block(double* Q, int V, int p, uint64_t seed, hipStream
   return hipGetLastError();
 }
 
-hipError_t launch_vecT_mat(const double* m, const double* Q, double* t, int V, int p,
+hipError_t launch_m2_apply(const double* M2, const double* Q, double* Y, int V, int p,
                            hipStream_t s) {
-  // t (1 x p) = m^T Q as a GEMM with op(A) = m^T
-  const int splits = (V + 4095) / 4096;
-  return gemm(true, 1, p, V, m, 1, Q, p, t, p, 1.0, splits, s);
-}
-
-hipError_t launch_m2_apply(const double* S2, const double* m, const double* t, const double* Q,
-                           double* Y, int V, int p, double scale_s, double scale_m,
-                           hipStream_t s) {
-  hipError_t e = gemm(false, V, p, V, S2, V, Q, p, Y, p, scale_s, 1, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_rank1_update, dim3(blocks_for((size_t)V * p, 256)), dim3(256), 0, s, Y, m,
-                     t, V, p, scale_m);
-  return hipGetLastError();
-}
-
-hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, hipStream_t s) {
-  const int splits = (V + 2047) / 2048;
-  return gemm(true, p, p, V, A, p, B, p, G, p, 1.0, splits, s);
+  return gemm(V, p, V, M2, V, Q, p, Y, p, s);
 }
 
 hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s) {
@@ -792,7 +690,7 @@ hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hip
 
 hipError_t launch_block_product(const double* Q, const double* Z, double* Out, int V, int p,
                                 hipStream_t s) {
-  return gemm(false, V, p, p, Q, p, Z, p, Out, p, 1.0, 1, s);
+  return gemm(V, p, p, Q, p, Z, p, Out, p, s);
 }
 
 hipError_t launch_ritz_vectors(const double* Q, const double* Z, const double* ev, int V, int p,
@@ -802,7 +700,7 @@ hipError_t launch_ritz_vectors(const double* Q, const double* Z, const double* e
   hipLaunchKernelGGL(k_select_top, dim3(1), dim3(256), 0, s, Z, ev, p, D, Zs, eigD);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = gemm(false, V, D, p, Q, p, Zs, D, U, D, 1.0, 1, s);
+  e = gemm(V, D, p, Q, p, Zs, D, U, D, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_sign_fix, dim3(D), dim3(256), 0, s, U, V, D);
   return hipGetLastError();

@@ -1,7 +1,9 @@
-// Cholesky factor and triangular inverse of the refresh's p x p Gram matrices
-// on the FP64 matrix cores: G + shift I = R^T R (R upper), Binv = R^-1, so
+// The refresh's orthonormalisation on the FP64 matrix cores: Gram products of
+// tall blocks (k_gram, below), and the Cholesky factor and triangular inverse
+// of the p x p Gram matrix, G + shift I = R^T R (R upper), Binv = R^-1, so
 // that Q = Y Binv is orthonormal.
 //
+// Factor and inverse.
 // Bound: a chain of p pivots.  Each costs a reciprocal square root and a
 // rank-one update; only the 16 pivots of a diagonal tile have to be taken one
 // at a time, so a single wave does those in registers and everything else of
@@ -266,6 +268,149 @@ __global__ void __launch_bounds__(64) k_tri_inverse(const double* __restrict__ t
   inverse_column(tiles, dinv, nb, i, p, ytiles + (size_t)i * nb * kTileE, Binv, threadIdx.x);
 }
 
+// ---------------------------------------------------------------------------
+// G = A^T B for tall row-major blocks A, B (V x p).  Lane l of a step over
+// four rows v needs A[v + l / 16][16 i + l % 16] and B[v + l / 16][16 j +
+// l % 16]: 128-byte row segments straight from memory, no staging.  A block
+// takes one unit of at most kGramN tiles of one tile row (one A operand feeds
+// them all) and one chunk of the rows, its four waves every fourth group of
+// four rows; the waves' tiles are added in LDS, the chunks' in chunk order by
+// k_gram_sum, so the sum's order is fixed.  SYM (B = A, or A^T B symmetric by
+// construction): only tiles i <= j are formed, and mirrored.
+// Bound: the matrix cores, 2 V p (p + 16) / 2 flops when symmetric; a wider
+// unit would spill, a narrower one reads more operand bytes per product.
+// ---------------------------------------------------------------------------
+constexpr int kGramN = 7, kGramWaves = 4;
+
+// Unit u of nb tile columns: tile row i, first column j0, n tiles.
+__host__ __device__ inline int gram_units(int nb, bool sym) {
+  int u = 0;
+  for (int i = 0; i < nb; ++i) u += ((sym ? nb - i : nb) + kGramN - 1) / kGramN;
+  return u;
+}
+__device__ inline void gram_unit(int u, int nb, bool sym, int& i, int& j0, int& n) {
+  for (i = 0;; ++i) {
+    const int len = sym ? nb - i : nb, parts = (len + kGramN - 1) / kGramN;
+    if (u < parts) {
+      const int a = u * len / parts, b = (u + 1) * len / parts;
+      j0 = (sym ? i : 0) + a;
+      n = b - a;
+      return;
+    }
+    u -= parts;
+  }
+}
+// tiles of the (upper) result, numbered by unit order within a tile row
+__host__ __device__ inline int gram_tile(int i, int j, int nb, bool sym) {
+  return sym ? i * nb - i * (i - 1) / 2 + (j - i) : i * nb + j;
+}
+inline int gram_tiles(int nb, bool sym) { return sym ? nb * (nb + 1) / 2 : nb * nb; }
+
+__global__ void __launch_bounds__(64 * kGramWaves) k_gram(const double* __restrict__ A,
+                                                          const double* __restrict__ B, int V,
+                                                          int p, int chunk, bool sym,
+                                                          double* __restrict__ part) {
+  __shared__ double red[kGramWaves - 1][kGramN * kTileE];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (p + kTile - 1) / kTile;
+  int i, j0, n;
+  gram_unit(blockIdx.x, nb, sym, i, j0, n);
+  const int v0 = blockIdx.y * chunk, v1 = min(V, v0 + chunk);
+  const int row = lane >> 4, col = lane & 15;
+  const int ca = min(i * kTile + col, p - 1);
+  doublex4 acc[kGramN];
+#pragma unroll
+  for (int q = 0; q < kGramN; ++q) acc[q] = doublex4{0.0, 0.0, 0.0, 0.0};
+  // Operands of the next four rows are loaded while the current ones are
+  // multiplied, all from clamped addresses: columns past p only reach entries
+  // that are not stored, and rows past the chunk are taken out by a zero A
+  // operand when it is used (a select at the load would wait for it).
+  double a, b[kGramN];
+  bool in;
+  auto load = [&](int v) {
+    const int r = v + row;
+    in = r < v1;
+    const size_t o = (size_t)min(r, V - 1) * p;
+    a = A[o + ca];
+#pragma unroll
+    for (int q = 0; q < kGramN; ++q)
+      b[q] = B[o + min((j0 + min(q, n - 1)) * kTile + col, p - 1)];
+  };
+  int v = v0 + 4 * wave;
+  if (v < v1) load(v);
+  for (; v < v1; v += 4 * kGramWaves) {
+    const double ac = in ? a : 0.0;
+    double bc[kGramN];
+#pragma unroll
+    for (int q = 0; q < kGramN; ++q) bc[q] = b[q];
+    if (v + 4 * kGramWaves < v1) load(v + 4 * kGramWaves);
+#pragma unroll
+    for (int q = 0; q < kGramN; ++q)
+      if (q < n) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ac, bc[q], acc[q], 0, 0, 0);
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int q = 0; q < kGramN; ++q)
+      if (q < n) store_tile(red[wave - 1] + q * kTileE, lane, acc[q]);
+  }
+  __syncthreads();
+  if (wave == 0) {
+    double* out = part + (size_t)blockIdx.y * (sym ? nb * (nb + 1) / 2 : nb * nb) * kTileE;
+#pragma unroll
+    for (int q = 0; q < kGramN; ++q)
+      if (q < n) {
+        doublex4 s = acc[q];
+#pragma unroll
+        for (int w = 0; w < kGramWaves - 1; ++w) s += load_tile(red[w] + q * kTileE, lane);
+        store_tile(out + (size_t)gram_tile(i, j0 + q, nb, sym) * kTileE, lane, s);
+      }
+  }
+}
+
+// G (p x p) from nz chunks of tiles: four lanes per entry, lane c adding the
+// c-th quarter of the chunks in chunk order, the quarters combined as
+// (q0 + q1) + (q2 + q3).  A lane issues the loads of 8 chunks before adding
+// them; the last batch loads from chunk indexes clamped into its quarter and
+// adds only the chunks that exist.
+__global__ void __launch_bounds__(256) k_gram_sum(const double* __restrict__ part, int nz, int nt,
+                                                  int p, bool sym, double* __restrict__ G) {
+  constexpr int kU = 8;
+  const int nb = (p + kTile - 1) / kTile;
+  const int e = blockIdx.x * 64 + (threadIdx.x >> 2);   // 64 entries per block: within one tile
+  const int c = threadIdx.x & 3;
+  const int t = e / kTileE;
+  const size_t stride = (size_t)nt * kTileE;
+  const int per = (nz + 3) / 4;
+  const int z0 = min(c * per, nz), z1 = min(z0 + per, nz);
+  double s = 0.0;
+  for (int z = z0; z < z1; z += kU) {
+    double v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = part[(size_t)min(z + u, z1 - 1) * stride + e];
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (z + u < z1) s += v[u];
+  }
+  s += __shfl_xor(s, 1, 64);
+  s += __shfl_xor(s, 2, 64);
+  int i = 0, j;
+  if (sym) {
+    int k = t;
+    while (k >= nb - i) k -= nb - i++;
+    j = i + k;
+  } else {
+    i = t / nb;
+    j = t % nb;
+  }
+  const int w = e % kTileE;
+  const int gi = i * kTile + w / kTile, gj = j * kTile + w % kTile;
+  if (c == 0 && gi < p && gj < p) {
+    G[(size_t)gi * p + gj] = s;
+    if (sym && i != j) G[(size_t)gj * p + gi] = s;
+  }
+}
+
 }  // namespace
 
 size_t chol_scratch_doubles(int p) {
@@ -297,6 +442,33 @@ hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double*
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_tri_inverse, dim3(nb), dim3(64), 0, s, tiles, dinv, p, ytiles, Binv);
+  return hipGetLastError();
+}
+
+// Row chunks of the Gram product: enough blocks for four waves per SIMD of the
+// 256 compute units (1024), chunks of at least 64 rows.
+static int gram_chunks(int V, int nb, bool sym) {
+  const int want = 1024 / gram_units(nb, sym), most = (V + 63) / 64;
+  return want < 1 ? 1 : want < most ? want : most;
+}
+
+size_t gram_scratch_doubles(int V, int p, bool sym) {
+  const int nb = (p + kTile - 1) / kTile;
+  return (size_t)gram_chunks(V, nb, sym) * gram_tiles(nb, sym) * kTileE;
+}
+
+hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
+                       double* part, hipStream_t s) {
+  const int nb = (p + kTile - 1) / kTile, nt = gram_tiles(nb, sym);
+  int nz = gram_chunks(V, nb, sym);
+  const int step = 4 * kGramWaves;
+  const int chunk = ((V + nz - 1) / nz + step - 1) / step * step;
+  nz = (V + chunk - 1) / chunk;
+  hipLaunchKernelGGL(k_gram, dim3(gram_units(nb, sym), nz), dim3(64 * kGramWaves), 0, s, A, B, V, p,
+                     chunk, sym, part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_gram_sum, dim3(nt * (kTileE / 64)), dim3(256), 0, s, part, nz, nt, p, sym, G);
   return hipGetLastError();
 }
 

@@ -178,12 +178,14 @@ __global__ void __launch_bounds__(256) k_add_counts(const int* __restrict__ bloc
   }
 }
 
-// The FP64 symmetric S2 of the refresh's products from the packed upper
-// triangle of the fixed-point accumulator: a 32 x 32 tile of the upper
-// triangle is converted row-wise, written in place and, through LDS,
-// transposed into the lower triangle, so reads and writes are coalesced.
+// The FP64 matrix of the refresh's products from the packed upper triangle of
+// the fixed-point accumulator: M2[i][j] = a S2[i][j] - b m_i m_j, so that the
+// products need no separate mean term.  A 32 x 32 tile of the upper triangle
+// is converted row-wise, written in place and, through LDS, transposed into
+// the lower triangle, so reads and writes are coalesced.
 __global__ void __launch_bounds__(256) k_fx_symmetric(const unsigned long long* __restrict__ acc,
-                                                      int V, double* __restrict__ S2) {
+                                                      const double* __restrict__ m, int V,
+                                                      double a, double b, double* __restrict__ M2) {
   __shared__ double tile[32][33];
   const int bi = blockIdx.y, bj = blockIdx.x;     // source tile (bi, bj) of the upper triangle
   if (bi > bj) return;
@@ -192,15 +194,15 @@ __global__ void __launch_bounds__(256) k_fx_symmetric(const unsigned long long* 
     const int gi = bi * 32 + r, gj = bj * 32 + tx;
     double v = 0.0;
     if (gi < V && gj < V && gi <= gj) {
-      v = fx_value(acc + 2 * tri_index(gi, gj, V));
-      S2[(size_t)gi * V + gj] = v;
+      v = fma(a, fx_value(acc + 2 * tri_index(gi, gj, V)), -b * (m[gi] * m[gj]));
+      M2[(size_t)gi * V + gj] = v;
     }
     tile[r][tx] = v;
   }
   __syncthreads();
   for (int r = ty; r < 32; r += 8) {
     const int gi = bj * 32 + r, gj = bi * 32 + tx;   // destination (gi, gj), gi > gj
-    if (gi < V && gj < V && gj < gi) S2[(size_t)gi * V + gj] = tile[tx][r];
+    if (gi < V && gj < V && gj < gi) M2[(size_t)gi * V + gj] = tile[tx][r];
   }
 }
 
@@ -263,9 +265,10 @@ hipError_t launch_accumulate(const tlda_csr_batch& b, int V, const Moments& m, i
   return hipGetLastError();
 }
 
-hipError_t launch_fx_symmetric(const unsigned long long* acc, int V, double* S2, hipStream_t s) {
+hipError_t launch_fx_symmetric(const unsigned long long* acc, const double* m, int V, double a,
+                               double b, double* M2, hipStream_t s) {
   const int nt = (V + 31) / 32;
-  hipLaunchKernelGGL(k_fx_symmetric, dim3(nt, nt), dim3(32, 8), 0, s, acc, V, S2);
+  hipLaunchKernelGGL(k_fx_symmetric, dim3(nt, nt), dim3(32, 8), 0, s, acc, m, V, a, b, M2);
   return hipGetLastError();
 }
 

@@ -256,11 +256,10 @@ tlda_status ensure_acc(tlda_ctx* c) {
 tlda_status ensure_eig(tlda_ctx* c, int p) {
   tlda::EigScratch& e = c->eig;
   if (e.p == p && e.Q) return TLDA_OK;
-  dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.t); dfree(e.Binv);
+  dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
   dfree(e.fac);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   e.p = 0;
-  e.part_chunks = 0;
   e.ws_doubles = 0;
   e.warm = nullptr;
   const size_t V = c->cfg.V, D = c->cfg.D;
@@ -272,15 +271,11 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
   HIP_OK(c, launch_zero(e.Binv, sizeof(double) * p * p, c->stream));
   HIP_OK(c, dalloc(&e.fac, tlda::chol_scratch_doubles(p)));
   HIP_OK(c, dalloc(&e.ev, (size_t)p));
-  HIP_OK(c, dalloc(&e.t, (size_t)p));
   HIP_OK(c, dalloc(&e.sel, D + (size_t)p * D));
   HIP_OK(c, dalloc(&e.mcand, V));
   HIP_OK(c, dalloc(&e.info, 4));
-  // the Gram products split their V rows into chunks of at least 64 rows
-  const int chunks = (int)std::min<size_t>(tlda::kSplitMax, (V + 63) / 64);
-  HIP_OK(c, dalloc(&e.part, (size_t)chunks * p * p));
-  e.part_chunks = chunks;
-  // K-split partials of the S2 product on the matrix cores (V x p each)
+  HIP_OK(c, dalloc(&e.part, tlda::gram_scratch_doubles((int)V, p, true)));
+  // K-split partials of the M2 product on the matrix cores (V x p each)
   const int splits = tlda::dgemm_splits((int)V, p, (int)V, c->num_cu > 0 ? c->num_cu : 256);
   if (splits > 1) {
     HIP_OK(c, dalloc(&e.ws, (size_t)splits * V * p));
@@ -295,24 +290,12 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
 tlda_status orthonormalise(tlda_ctx* c, const double* in, double* tmp, double* out) {
   tlda::EigScratch& e = c->eig;
   const int V = c->cfg.V, p = e.p;
-  HIP_OK(c, tlda::launch_gram(in, in, e.G, V, p, c->stream));
+  HIP_OK(c, tlda::launch_gram(in, in, e.G, V, p, true, e.part, c->stream));
   HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 1e-12, e.fac, e.Binv, e.info, c->stream));
   HIP_OK(c, tlda::launch_block_product(in, e.Binv, tmp, V, p, c->stream));
-  HIP_OK(c, tlda::launch_gram(tmp, tmp, e.G, V, p, c->stream));
+  HIP_OK(c, tlda::launch_gram(tmp, tmp, e.G, V, p, true, e.part, c->stream));
   HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 0.0, e.fac, e.Binv, e.info, c->stream));
   HIP_OK(c, tlda::launch_block_product(tmp, e.Binv, out, V, p, c->stream));
-  return TLDA_OK;
-}
-
-// M2~ Q = (alpha0+1)(S2 Q / N - M1 (M1^T Q)) into Y; for classic-moment
-// contexts M2 Q = (alpha0+1) S2 Q / N - alpha0 M1 (M1^T Q).
-tlda_status apply_m2(tlda_ctx* c, const double* Q, double* Y, double N) {
-  tlda::EigScratch& e = c->eig;
-  const int V = c->cfg.V, p = e.p;
-  const double a1 = c->cfg.alpha0 + 1.0;
-  const double am = is_classic(c) ? c->cfg.alpha0 : a1;
-  HIP_OK(c, tlda::launch_vecT_mat(e.mcand, Q, e.t, V, p, c->stream));
-  HIP_OK(c, tlda::launch_m2_apply(c->mom.S2, e.mcand, e.t, Q, Y, V, p, a1 / N, am, c->stream));
   return TLDA_OK;
 }
 
@@ -324,6 +307,7 @@ tlda_status save_prev(tlda_ctx* c) {
     HIP_OK(c, dalloc(&c->wh.Uprev, V * D));
     HIP_OK(c, dalloc(&c->wh.eigprev, D));
     HIP_OK(c, dalloc(&c->wh.C, D * D));
+    HIP_OK(c, dalloc(&c->wh.part, tlda::gram_scratch_doubles((int)V, (int)D, false)));
   }
   HIP_OK(c, hipMemcpyAsync(c->wh.Uprev, c->wh.U, sizeof(double) * V * D, hipMemcpyDeviceToDevice,
                            c->stream));
@@ -333,14 +317,11 @@ tlda_status save_prev(tlda_ctx* c) {
   return TLDA_OK;
 }
 
-// The refresh's product environment: its matrix-core or vector route, the
-// Gram-split and K-split scratch of this context.
+// The refresh's product environment: its matrix-core or vector route and the
+// K-split scratch of this context.
 tlda::EigEnv eig_env(const tlda_ctx* c) {
   tlda::EigEnv env;
   env.route = c->tune.gemm_route == 1 ? 1 : 0;
-  env.part = c->eig.part;
-  env.part_mn = c->eig.part ? (size_t)c->eig.p * c->eig.p : 0;
-  env.part_chunks = c->eig.part_chunks;
   env.ws = c->eig.ws;
   env.ws_doubles = c->eig.ws_doubles;
   env.num_cu = c->num_cu > 0 ? c->num_cu : 256;
@@ -365,9 +346,13 @@ tlda_status refresh(tlda_ctx* c, bool warm) {
                          : (c->cfg.eig_iters > 0 ? c->cfg.eig_iters : 60);
   const double N = (double)counts[0];
   HIP_OK(c, launch_zero(e.info, 4 * sizeof(int), c->stream));
-  if (c->mom.S2 == nullptr) HIP_OK(c, dalloc(&c->mom.S2, (size_t)V * V));
+  if (c->mom.M2 == nullptr) HIP_OK(c, dalloc(&c->mom.M2, (size_t)V * V));
   HIP_OK(c, tlda::launch_mean(c->mom.fsum, c->mom.counts, e.mcand, V, c->stream));
-  HIP_OK(c, tlda::launch_fx_symmetric(c->mom.acc, V, c->mom.S2, c->stream));
+  // M2~ = (alpha0+1)(S2 / N - M1 M1^T); for classic-moment contexts
+  // M2 = (alpha0+1) S2 / N - alpha0 M1 M1^T
+  const double a1 = c->cfg.alpha0 + 1.0;
+  HIP_OK(c, tlda::launch_fx_symmetric(c->mom.acc, e.mcand, V, a1 / N,
+                                      is_classic(c) ? c->cfg.alpha0 : a1, c->mom.M2, c->stream));
   double* q = e.Q;
   double* y = e.Y;
   if (warm) {
@@ -383,16 +368,14 @@ tlda_status refresh(tlda_ctx* c, bool warm) {
     std::swap(q, y);   // q: orthonormal block
   }
   for (int it = 0; it < iters; ++it) {
-    st = apply_m2(c, q, y, N);
-    if (st != TLDA_OK) return st;
+    HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, c->stream));
     st = orthonormalise(c, y, q, y);   // y -> tmp q -> y
     if (st != TLDA_OK) return st;
     std::swap(q, y);
   }
   // Rayleigh-Ritz: H = Q^T M2~ Q, eigenpairs by Jacobi, U = Q Z_top
-  st = apply_m2(c, q, y, N);
-  if (st != TLDA_OK) return st;
-  HIP_OK(c, tlda::launch_gram(q, y, e.G, V, p, c->stream));
+  HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, c->stream));
+  HIP_OK(c, tlda::launch_gram(q, y, e.G, V, p, true, e.part, c->stream));
   HIP_OK(c, tlda::launch_jacobi(e.G, e.Z, e.ev, p, e.info, c->stream));
   HIP_OK(c, tlda::launch_ritz_vectors(q, e.Z, e.ev, V, p, D, y, e.sel, c->stream));
   int info[4] = {0, 0, 0, 0};
@@ -571,14 +554,15 @@ void destroy_all(tlda_ctx* c) {
   if (!c) return;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   dfree(c->mom.counts); dfree(c->mom.totals); dfree(c->mom.fsum); dfree(c->mom.acc);
-  dfree(c->mom.S2);
+  dfree(c->mom.M2);
   dfree(c->wh.W); dfree(c->wh.U); dfree(c->wh.eig); dfree(c->wh.m); dfree(c->wh.W32);
   dfree(c->wh.mw32); dfree(c->wh.W16); dfree(c->wh.mw16);
   dfree(c->wh.Uprev); dfree(c->wh.eigprev); dfree(c->wh.C);
+  dfree(c->wh.part);
   delete[] c->t_start;
   delete[] c->t_stop;
   tlda::EigScratch& e = c->eig;
-  dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.t); dfree(e.Binv);
+  dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
   dfree(e.fac);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   dfree(c->cp.partial); dfree(c->cp.R1); dfree(c->cp.phi0); dfree(c->cp.grad); dfree(c->cp.X);
@@ -750,7 +734,7 @@ tlda_status tlda_update_moments(tlda_ctx* c, const tlda_csr_batch* b, uint32_t f
   }
   if (flags & TLDA_RELEASE) {
     HIP_OK(c, hipStreamSynchronize(c->stream));
-    dfree(c->mom.S2);
+    dfree(c->mom.M2);
     dfree(c->mom.acc);
     HIP_OK(c, launch_zero(c->mom.counts, 2 * sizeof(unsigned long long), c->stream));
     HIP_OK(c, launch_zero(c->mom.totals, V * sizeof(unsigned long long), c->stream));
@@ -1073,8 +1057,7 @@ tlda_status tlda_rebase_phi(tlda_ctx* c, float* Phi) {
   CHECK_ARG(c, c->wh.ready && c->wh.prev_ready, TLDA_ERR_STATE,
             "no previous whitening to rebase from");
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
-  tlda::EigScope scope(eig_env(c));
-  HIP_OK(c, tlda::launch_gram(c->wh.U, c->wh.Uprev, c->wh.C, V, D, c->stream));
+  HIP_OK(c, tlda::launch_gram(c->wh.U, c->wh.Uprev, c->wh.C, V, D, false, c->wh.part, c->stream));
   HIP_OK(c, tlda::launch_rebase(c->wh.C, c->wh.eig, c->wh.eigprev, D, K, Phi, c->stream));
   return TLDA_OK;
 }

@@ -44,14 +44,14 @@ struct StageSlot {
 
 // Moment accumulators.  fsum and acc hold exact 128-bit fixed-point sums
 // ({lo, hi} pairs of 64-bit words, value hi + lo 2^-64), so the moments do
-// not depend on the order documents are added in; S2 is the FP64 symmetric
-// matrix the refresh forms from acc (k_fx_symmetric) for its products.
+// not depend on the order documents are added in; M2 is the FP64 symmetric
+// matrix the refresh forms from them (k_fx_symmetric) for its products.
 struct Moments {
   unsigned long long* counts = nullptr;  // [0] N kept, [1] dropped
   unsigned long long* totals = nullptr;  // [V] token totals of kept documents
   unsigned long long* fsum = nullptr;    // [V][2] sum of f over kept documents
   unsigned long long* acc = nullptr;     // [V (V + 1) / 2][2] packed upper triangle of sum f f^T
-  double* S2 = nullptr;                  // [V][V] FP64 symmetric copy, formed at each refresh
+  double* M2 = nullptr;                  // [V][V] FP64 second moment, formed at each refresh
 };
 // 64-bit words of the packed fixed-point accumulator of a V-word vocabulary
 inline size_t tri_words(int V) { return (size_t)V * (V + 1); }
@@ -71,6 +71,7 @@ struct Whitening {
   double* Uprev = nullptr;   // [V][D]
   double* eigprev = nullptr; // [D]
   double* C = nullptr;       // [D][D] U^T Uprev
+  double* part = nullptr;    // its row-chunk partials
 };
 
 struct EigScratch {
@@ -80,16 +81,14 @@ struct EigScratch {
   double* G = nullptr;     // [p][p]  Gram / projected matrix
   double* Z = nullptr;     // [p][p]  eigenvectors of the projected matrix
   double* ev = nullptr;    // [p]
-  double* t = nullptr;     // [p]     M1^T Q
   double* Binv = nullptr;  // [p][p]  inverse of the upper Cholesky factor (zeros below)
   double* fac = nullptr;   // tiles of the factorisation (chol_scratch_doubles)
   double* sel = nullptr;   // [D + p*D] selected Ritz values and vectors
   double* mcand = nullptr; // [V]     M1 of the refresh in progress
   int* info = nullptr;     // [4]     device status words
   double* warm = nullptr;  // Q or Y: the orthonormal block the last refresh converged to
-  double* part = nullptr;  // [part_chunks][p][p] partial sums of the Gram products
-  int part_chunks = 0;     // min(kSplitMax, ceil(V / 64)): the most row chunks gemm() uses
-  double* ws = nullptr;    // [splits][V][p] K-split partials of the S2 product
+  double* part = nullptr;  // row-chunk partials of the Gram products (gram_scratch_doubles)
+  double* ws = nullptr;    // [splits][V][p] K-split partials of the M2 product
   size_t ws_doubles = 0;
 };
 
@@ -233,15 +232,8 @@ extern thread_local KernelTimer g_main_timer;
 // refresh or rebase (EigScope).  route 0: C = A B on the FP64 matrix cores
 // (k_dgemm_mfma), with a K split over ws (splits x M x N doubles) when the
 // grid would not fill the device; route 1: the vector-ALU tile kernel.
-// The transposed products A^T B over many rows (the refresh's Gram products)
-// split their rows into up to kSplitMax chunks, each writing its own M x N
-// partial to `part`, added in chunk order afterwards (deterministic).
-constexpr int kSplitMax = 256;
 struct EigEnv {
   int route = 0;
-  double* part = nullptr;     // part_chunks * part_mn doubles
-  size_t part_mn = 0;         // largest M * N the scratch serves
-  int part_chunks = 0;        // row chunks the scratch holds (at most kSplitMax)
   double* ws = nullptr;       // K-split workspace of the matrix-core product
   size_t ws_doubles = 0;
   int num_cu = 256;
@@ -278,8 +270,9 @@ hipError_t launch_validate_csr(const tlda_csr_batch& b, int V, int* err, hipStre
 // instead of f f^T
 hipError_t launch_accumulate(const tlda_csr_batch& b, int V, const Moments& m, int* block_counts,
                              bool classic, hipStream_t s);   // adds into m.acc, m.fsum, m.totals
-// S2 (V x V, FP64, symmetric) from the packed fixed-point accumulator
-hipError_t launch_fx_symmetric(const unsigned long long* acc, int V, double* S2, hipStream_t s);
+// M2 = a S2 - b m m^T (V x V, FP64, symmetric) from the packed fixed-point accumulator of S2
+hipError_t launch_fx_symmetric(const unsigned long long* acc, const double* m, int V, double a,
+                               double b, double* M2, hipStream_t s);
 // col[j] = col16[j], val[j] = val16[j] for j < nnz (compact staging)
 hipError_t launch_widen_u16(const uint16_t* col16, const uint16_t* val16, size_t nnz,
                             int32_t* col, float* val, hipStream_t s);
@@ -288,12 +281,13 @@ hipError_t launch_mean(const unsigned long long* fsum, const unsigned long long*
                        hipStream_t s);
 // eigen-solver building blocks (FP64)
 hipError_t launch_random_block(double* Q, int V, int p, uint64_t seed, hipStream_t s);
-hipError_t launch_m2_apply(const double* S2, const double* m, const double* t, const double* Q,
-                           double* Y, int V, int p, double scale_s, double scale_m,
+hipError_t launch_m2_apply(const double* M2, const double* Q, double* Y, int V, int p,
                            hipStream_t s);
-hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, hipStream_t s);
-hipError_t launch_vecT_mat(const double* m, const double* Q, double* t, int V, int p,
-                           hipStream_t s);
+// G (p x p) = A^T B for V x p blocks; sym: A^T B is symmetric, only its upper
+// tiles are formed.  part: gram_scratch_doubles(V, p, sym) doubles
+size_t gram_scratch_doubles(int V, int p, bool sym);
+hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
+                       double* part, hipStream_t s);
 // Binv <- R^-1 with G + shift_rel max diag(G) I = R^T R (R upper; p <= 512);
 // *info |= 1 on a pivot that is not positive
 size_t chol_scratch_doubles(int p);
