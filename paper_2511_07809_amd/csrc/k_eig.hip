@@ -78,178 +78,219 @@ __global__ void __launch_bounds__(256) k_gemm64(int M, int N, int Kd, const doub
 }
 
 // ---------------------------------------------------------------------------
-// Dense FP64 GEMM on the matrix cores: C = alpha * A * B (row-major; A is
-// M x K, B is K x N), v_mfma_f64_16x16x4f64 with FP64 accumulation.
-// Block: 8 waves over a 128-row x 16 NT-column tile of C (NT 16-column
-// tiles, at most 8: wider products take several column blocks, and two
-// blocks fit on a CU); wave (wr, wc) owns rows 32 wr .. 32 wr + 31 (two
-// 16-row MFMA tiles) and column half wc (tiles 0 .. NT0 - 1 or NT0 .. NT - 1).
-// K advances 16 at a time through double-buffered LDS: the next K tile is
-// loaded into registers while the current one is multiplied (loads are
-// unconditional, from clamped addresses, with out-of-range entries zeroed by
-// selects, so none of them waits on another).  For the tall products (C = S2
-// times the subspace block, V rows) the 128-row tile reads each row block of
-// B once per 128 rows of A: B's traffic is N / 128 of A's.  grid.z splits K
-// into chunks whose C tiles go to their own slice of a workspace
-// (c_stride_z apart); k_sum_splits adds the slices in order.
-// Operand layout of the instruction: lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16]; accumulator register r of lane l is D[4 r + l / 16][l % 16].
+// Dense FP64 GEMM on the matrix cores: C (M x N) = A (M x K) B, row-major,
+// v_mfma_f64_16x16x4f64 (lane l supplies A[l % 16][l / 16] and B[l / 16][l %
+// 16]; accumulator register r of lane l is D[4 r + l / 16][l % 16]).
+//
+// Bound: the matrix cores (78.6 TFLOP/s FP64; 72 on a large library product
+// here).  Block: 8 waves over a tile of 128 rows x 16 NT columns, NT <= 13, so
+// that the refresh's products up to p = 208 read the V x V matrix once and
+// compute no more than a tile's padding; a wave owns 16 rows and every column
+// tile (one A operand feeds NT products; a 2 x NT / 2 split reads LDS less,
+// which is not what bounds, and divides odd NT unevenly).  K advances 16 at a
+// time through double-buffered LDS, A's slab with the reduction index
+// leading, whose stride of 144 makes every operand read free of bank
+// conflicts; the next slab is loaded into registers while the current one is
+// multiplied (buffer loads from 32-bit offsets kept for the whole tile; rows
+// of A past K are zeroed when they are stored, after the matrix work).
+// SYM: A is symmetric, so its slab is read along its rows, as it lies in LDS.
+// Work is dealt out in slabs: the tiles' slabs in a row, cut into gridDim.x
+// equal runs, so that every compute unit ends together whatever M is.  A run
+// that covers a tile writes C; the pieces of a divided tile go to ws, piece
+// (block + tile), and k_dgemm_sum adds them in order.
 // ---------------------------------------------------------------------------
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-constexpr int kDgBM = 128, kDgBK = 16, kDgThreads = 512;
+constexpr int kDgBM = 128, kDgBK = 16, kDgThreads = 512, kDgMaxNT = 13;
+constexpr int kDgLdA = kDgBM + 16;
 
-template <int NT>
-__global__ void __launch_bounds__(kDgThreads, 4) k_dgemm_mfma(
-    int M, int N, int K, int k_chunk, const double* __restrict__ A, int lda,
-    const double* __restrict__ B, int ldb, double* __restrict__ C, int ldc, size_t c_stride_z,
-    double alpha) {
-  constexpr int BNC = 16 * NT, LDA_S = kDgBK + 1, LDB_S = BNC + 2;
-  constexpr int NT0 = (NT + 1) / 2;
+struct DgPlan {
+  int gx, gy, nt;         // column and row tiles, 16-column tiles per block
+  int slabs;              // K slabs per tile
+  int blocks;
+  long long total() const { return (long long)gx * gy * slabs; }
+  size_t ws() const {     // doubles of the pieces
+    return blocks == gx * gy ? 0 : (size_t)(blocks + gx * gy) * kDgBM * 16 * nt;
+  }
+};
+// One round of resident blocks (two on a CU while the tile leaves room), runs
+// of at least 4 slabs; short products (K < 256) take whole tiles, whose pieces
+// would cost more than the rows left over.
+DgPlan dgemm_plan(int M, int N, int K, int num_cu) {
+  DgPlan d;
+  const int tiles = (N + 15) / 16;
+  d.gx = (tiles + kDgMaxNT - 1) / kDgMaxNT;
+  d.nt = (tiles + d.gx - 1) / d.gx;
+  d.gy = (M + kDgBM - 1) / kDgBM;
+  d.slabs = (K + kDgBK - 1) / kDgBK;
+  const long long slots = (long long)num_cu * (d.nt <= 7 ? 2 : 1);
+  const long long most = d.total() / 4 > 1 ? d.total() / 4 : 1;
+  d.blocks = K < 256 ? d.gx * d.gy : (int)(slots < most ? slots : most);
+  return d;
+}
+
+// Buffer descriptor of the doubles p .. end (an operand's slab starts at p; a
+// lane's offset in it fits 32 bits, and reads past `end` give zero).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slab(const double* p, const double* end) {
+  const size_t bytes = (size_t)(end - p) * sizeof(double);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), 0,
+                                           (int)(uint32_t)(bytes < 0xfffffff0u ? bytes : 0xfffffff0u),
+                                           0x00020000);
+}
+
+template <int NT, bool SYM>
+__global__ void __launch_bounds__(kDgThreads, NT <= 7 ? 4 : 2) k_dgemm_mfma(
+    int M, int N, int K, int gx, int slabs, long long total, const double* __restrict__ A, int lda,
+    const double* __restrict__ B, int ldb, double* __restrict__ C, int ldc,
+    double* __restrict__ ws) {
+  constexpr int BNC = 16 * NT, LDB_S = 16 * (NT | 1);
   constexpr int A_PER = kDgBM * kDgBK / kDgThreads;
   constexpr int B_PER = (kDgBK * BNC + kDgThreads - 1) / kDgThreads;
-  __shared__ double As[2][kDgBM * LDA_S];
+  __shared__ double As[2][kDgBK * kDgLdA];
   __shared__ double Bs[2][kDgBK * LDB_S];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave & 3, wc = wave >> 2;
-  const int ct0 = wc ? NT0 : 0;
-  const int nct = wc ? NT - NT0 : NT0;
-  const int row0 = blockIdx.y * kDgBM, col0 = blockIdx.x * BNC;
-  const int kbeg = blockIdx.z * k_chunk;
-  const int kend = min(K, kbeg + k_chunk);
-  C += blockIdx.z * c_stride_z;
-  doublex4 acc[2][NT0];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  long long s0 = blockIdx.x * total / gridDim.x;
+  const long long s1 = (blockIdx.x + 1) * total / gridDim.x;
+  while (s0 < s1) {
+    const int tile = (int)(s0 / slabs);
+    const int kt0 = (int)(s0 - (long long)tile * slabs);
+    const int kt1 = (int)min((long long)slabs, kt0 + (s1 - s0));
+    s0 += kt1 - kt0;
+    const int row0 = tile / gx * kDgBM, col0 = tile % gx * BNC;
+    doublex4 acc[NT];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int j = 0; j < NT0; ++j) acc[t][j] = doublex4{0.0, 0.0, 0.0, 0.0};
-  // raw loaded values and which of them are in range: the selects happen
-  // when the tile is stored to LDS, after the matrix work, so nothing waits
-  // for the loads before then
-  double ra[A_PER], rb[B_PER];
-  unsigned am = 0, bm = 0;
-  auto load = [&](int k0) {
-    am = bm = 0;
+    for (int j = 0; j < NT; ++j) acc[j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double ra[A_PER], rb[B_PER];
+    int oa[A_PER], ob[B_PER];
 #pragma unroll
     for (int i = 0; i < A_PER; ++i) {
       const int e = tid + i * kDgThreads;
-      const int gr = row0 + e / kDgBK, gk = k0 + e % kDgBK;
-      const bool in = gr < M && gk < kend;
-      ra[i] = A[in ? (size_t)gr * lda + gk : 0];
-      am |= (in ? 1u : 0u) << i;
+      const int r = min(SYM ? e % kDgBM : e / kDgBK, M - 1 - row0);
+      const int k = SYM ? e / kDgBM : e % kDgBK;
+      oa[i] = 8 * (SYM ? k * lda + r : r * lda + k);
     }
 #pragma unroll
     for (int i = 0; i < B_PER; ++i) {
-      const int e = tid + i * kDgThreads;
-      const int gk = k0 + e / BNC, gc = col0 + e % BNC;
-      const bool in = e < kDgBK * BNC && gk < kend && gc < N;
-      rb[i] = B[in ? (size_t)gk * ldb + gc : 0];
-      bm |= (in ? 1u : 0u) << i;
+      const int e = min(tid + i * kDgThreads, kDgBK * BNC - 1);
+      ob[i] = 8 * (e / BNC * ldb + min(e % BNC, N - 1 - col0));
     }
-  };
-  auto store = [&](int buf) {
+    auto load = [&](int k0) {
+      const auto rsa = slab(SYM ? A + (size_t)k0 * lda + row0 : A + (size_t)row0 * lda + k0,
+                            A + (size_t)(SYM ? K - 1 : M - 1) * lda + (SYM ? M : K));
+      const auto rsb = slab(B + (size_t)k0 * ldb + col0, B + (size_t)(K - 1) * ldb + N);
 #pragma unroll
-    for (int i = 0; i < A_PER; ++i) {
-      const int e = tid + i * kDgThreads;
-      As[buf][(e / kDgBK) * LDA_S + e % kDgBK] = ((am >> i) & 1u) ? ra[i] : 0.0;
-    }
+      for (int i = 0; i < A_PER; ++i)
+        ra[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsa, oa[i], 0, 0));
 #pragma unroll
-    for (int i = 0; i < B_PER; ++i) {
-      const int e = tid + i * kDgThreads;
-      if (e < kDgBK * BNC) Bs[buf][(e / BNC) * LDB_S + e % BNC] = ((bm >> i) & 1u) ? rb[i] : 0.0;
-    }
-  };
-  const int nk = (kend - kbeg + kDgBK - 1) / kDgBK;
-  load(kbeg);
-  store(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) load(kbeg + (kt + 1) * kDgBK);
-    const double* as = As[cur] + (wr * 32 + (lane & 15)) * LDA_S + (lane >> 4);
-    const double* bs = Bs[cur] + (lane >> 4) * LDB_S + ct0 * 16 + (lane & 15);
+      for (int i = 0; i < B_PER; ++i)
+        rb[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsb, ob[i], 0, 0));
+    };
+    auto store = [&](int buf, int k0) {
 #pragma unroll
-    for (int ks = 0; ks < kDgBK / 4; ++ks) {
-      const double a0 = as[4 * ks], a1 = as[16 * LDA_S + 4 * ks];
+      for (int i = 0; i < A_PER; ++i) {
+        const int e = tid + i * kDgThreads;
+        const int r = SYM ? e % kDgBM : e / kDgBK, k = SYM ? e / kDgBM : e % kDgBK;
+        As[buf][k * kDgLdA + r] = k0 + k < K ? ra[i] : 0.0;
+      }
 #pragma unroll
-      for (int j = 0; j < NT0; ++j)
-        if (j < nct) {
-          const double b = bs[4 * ks * LDB_S + j * 16];
-          acc[0][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b, acc[0][j], 0, 0, 0);
-          acc[1][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b, acc[1][j], 0, 0, 0);
-        }
-    }
-    if (kt + 1 < nk) store(cur ^ 1);
+      for (int i = 0; i < B_PER; ++i) {
+        const int e = tid + i * kDgThreads;
+        if (e < kDgBK * BNC) Bs[buf][(e / BNC) * LDB_S + e % BNC] = rb[i];
+      }
+    };
+    load(kt0 * kDgBK);
+    store(0, kt0 * kDgBK);
     __syncthreads();
-  }
+    for (int kt = kt0; kt < kt1; ++kt) {
+      const int cur = (kt - kt0) & 1;
+      if (kt + 1 < kt1) load((kt + 1) * kDgBK);
+      const double* as = As[cur] + (lane >> 4) * kDgLdA + wave * 16 + (lane & 15);
+      const double* bs = Bs[cur] + (lane >> 4) * LDB_S + (lane & 15);
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+      for (int ks = 0; ks < kDgBK / 4; ++ks) {
+        const double a = as[4 * ks * kDgLdA];
 #pragma unroll
-    for (int j = 0; j < NT0; ++j) {
-      if (j >= nct) continue;
-      const int col = col0 + (ct0 + j) * 16 + (lane & 15);
+        for (int j = 0; j < NT; ++j)
+          acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bs[4 * ks * LDB_S + j * 16], acc[j], 0,
+                                                        0, 0);
+      }
+      if (kt + 1 < kt1) store(cur ^ 1, (kt + 1) * kDgBK);
+      __syncthreads();
+    }
+    const bool whole = kt1 - kt0 == slabs;
+    double* piece = ws + (size_t)(whole ? 0 : blockIdx.x + tile) * kDgBM * BNC;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int c = j * 16 + (lane & 15);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = row0 + wr * 32 + t * 16 + 4 * r + (lane >> 4);
-        if (row < M && col < N) C[(size_t)row * ldc + col] = alpha * acc[t][j][r];
+        const int rr = wave * 16 + 4 * r + (lane >> 4);
+        if (!whole) piece[rr * BNC + c] = acc[j][r];
+        else if (row0 + rr < M && col0 + c < N)
+          C[(size_t)(row0 + rr) * ldc + col0 + c] = acc[j][r];
       }
     }
-}
-
-// C[r][c] = alpha * sum_z ws[z][r][c] in order z = 0 .. nz - 1 (ws slices M x N).
-__global__ void k_sum_splits(const double* __restrict__ ws, int nz, int M, int N,
-                             double* __restrict__ C, int ldc, double alpha) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t mn = (size_t)M * N;
-  if (e >= mn) return;
-  double s = 0.0;
-  for (int z = 0; z < nz; ++z) s += ws[(size_t)z * mn + e];
-  C[(e / N) * ldc + e % N] = alpha * s;
-}
-
-template <int NT>
-hipError_t launch_dgemm_nt(dim3 grid, int M, int N, int K, int chunk, const double* A, int lda,
-                           const double* B, int ldb, double* C, int ldc, size_t cz, double alpha,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_dgemm_mfma<NT>, grid, dim3(kDgThreads), 0, s, M, N, K, chunk, A, lda, B,
-                     ldb, C, ldc, cz, alpha);
-  return hipGetLastError();
-}
-
-hipError_t dgemm_mfma(int M, int N, int K, const double* A, int lda, const double* B, int ldb,
-                      double* C, int ldc, double alpha, hipStream_t s) {
-  const int gx = (N + 127) / 128;                     // column blocks of at most 8 tiles
-  const int NT = ((N + gx - 1) / gx + 15) / 16;
-  const int BNC = 16 * NT;
-  const int gy = (M + kDgBM - 1) / kDgBM;
-  int splits = dgemm_splits(M, N, K, g_eig_env.num_cu);
-  if (splits > 1 && (g_eig_env.ws == nullptr || (size_t)splits * M * N > g_eig_env.ws_doubles))
-    splits = 1;
-  int chunk = ((K + splits - 1) / splits + kDgBK - 1) / kDgBK * kDgBK;
-  splits = (K + chunk - 1) / chunk;
-  double* out = splits > 1 ? g_eig_env.ws : C;
-  const int ldo = splits > 1 ? N : ldc;
-  const size_t cz = splits > 1 ? (size_t)M * N : 0;
-  const double al = splits > 1 ? 1.0 : alpha;
-  const dim3 grid(gx, gy, splits);
-  hipError_t e = hipErrorInvalidValue;
-  switch (NT) {
-#define TLDA_DG(n) \
-  case n: e = launch_dgemm_nt<n>(grid, M, N, K, chunk, A, lda, B, ldb, out, ldo, cz, al, s); break;
-    TLDA_DG(1) TLDA_DG(2) TLDA_DG(3) TLDA_DG(4) TLDA_DG(5) TLDA_DG(6) TLDA_DG(7) TLDA_DG(8)
-#undef TLDA_DG
-    default: break;
   }
-  if (e != hipSuccess || splits == 1) return e;
-  const size_t mn = (size_t)M * N;
-  hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, s,
-                     g_eig_env.ws, splits, M, N, C, ldc, alpha);
+}
+
+// The divided tiles of k_dgemm_mfma: block (x, tile) adds its entries' pieces
+// in block order, 8 loads in flight.
+__global__ void __launch_bounds__(256) k_dgemm_sum(const double* __restrict__ ws, int M, int N,
+                                                   int bnc, int gx, int slabs, int blocks,
+                                                   double* __restrict__ C, int ldc) {
+  constexpr int kU = 8;
+  const int tile = blockIdx.y;
+  const long long total = (long long)gridDim.y * slabs, s = (long long)tile * slabs;
+  // the block of slab s starts at or before it: b total / blocks < s + 1
+  const int b0 = (int)(((s + 1) * blocks - 1) / total);
+  const int b1 = (int)(((s + slabs) * blocks - 1) / total);
+  if (b0 == b1) return;
+  const size_t per = (size_t)kDgBM * bnc;
+  const int e = blockIdx.x * 256 + threadIdx.x;          // kDgBM * bnc is a multiple of 256
+  const double* p = ws + (size_t)(b0 + tile) * per + e;
+  double sum = 0.0;
+  for (int b = 0; b <= b1 - b0; b += kU) {
+    double v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = p[(size_t)min(b + u, b1 - b0) * per];
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (b + u <= b1 - b0) sum += v[u];
+  }
+  const int row = tile / gx * kDgBM + e / bnc, col = tile % gx * bnc + e % bnc;
+  if (row < M && col < N) C[(size_t)row * ldc + col] = sum;
+}
+
+template <bool SYM>
+hipError_t dgemm_mfma(int M, int N, int K, const double* A, int lda, const double* B, int ldb,
+                      double* C, int ldc, hipStream_t s) {
+  DgPlan d = dgemm_plan(M, N, K, g_eig_env.num_cu);
+  if (d.ws() > g_eig_env.ws_doubles) d.blocks = d.gx * d.gy;
+  switch (d.nt) {
+#define TLDA_DG(n)                                                                                \
+  case n:                                                                                         \
+    hipLaunchKernelGGL((k_dgemm_mfma<n, SYM>), dim3(d.blocks), dim3(kDgThreads), 0, s, M, N, K,   \
+                       d.gx, d.slabs, d.total(), A, lda, B, ldb, C, ldc, g_eig_env.ws);           \
+    break;
+    TLDA_DG(1) TLDA_DG(2) TLDA_DG(3) TLDA_DG(4) TLDA_DG(5) TLDA_DG(6) TLDA_DG(7) TLDA_DG(8)
+    TLDA_DG(9) TLDA_DG(10) TLDA_DG(11) TLDA_DG(12) TLDA_DG(13)
+#undef TLDA_DG
+    default: return hipErrorInvalidValue;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || d.blocks == d.gx * d.gy) return e;
+  hipLaunchKernelGGL(k_dgemm_sum, dim3(kDgBM * 16 * d.nt / 256, d.gx * d.gy), dim3(256), 0, s,
+                     g_eig_env.ws, M, N, 16 * d.nt, d.gx, d.slabs, d.blocks, C, ldc);
   return hipGetLastError();
 }
 
 // C (M x N) = A (M x Kd) B: the matrix cores, or the vector-ALU tile kernel.
+// sym: A is symmetric.
 hipError_t gemm(int M, int N, int Kd, const double* A, int lda, const double* B, int ldb, double* C,
-                int ldc, hipStream_t s) {
-  if (g_eig_env.route == 0) return dgemm_mfma(M, N, Kd, A, lda, B, ldb, C, ldc, 1.0, s);
+                int ldc, bool sym, hipStream_t s) {
+  if (g_eig_env.route == 0)
+    return sym ? dgemm_mfma<true>(M, N, Kd, A, lda, B, ldb, C, ldc, s)
+               : dgemm_mfma<false>(M, N, Kd, A, lda, B, ldb, C, ldc, s);
   hipLaunchKernelGGL(k_gemm64, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, s, M, N, Kd, A,
                      lda, B, ldb, C, ldc);
   return hipGetLastError();
@@ -669,7 +710,7 @@ hipError_t launch_random_block(double* Q, int V, int p, uint64_t seed, hipStream
 
 hipError_t launch_m2_apply(const double* M2, const double* Q, double* Y, int V, int p,
                            hipStream_t s) {
-  return gemm(V, p, V, M2, V, Q, p, Y, p, s);
+  return gemm(V, p, V, M2, V, Q, p, Y, p, true, s);
 }
 
 hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s) {
@@ -690,7 +731,7 @@ hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hip
 
 hipError_t launch_block_product(const double* Q, const double* Z, double* Out, int V, int p,
                                 hipStream_t s) {
-  return gemm(V, p, p, Q, p, Z, p, Out, p, s);
+  return gemm(V, p, p, Q, p, Z, p, Out, p, false, s);
 }
 
 hipError_t launch_ritz_vectors(const double* Q, const double* Z, const double* ev, int V, int p,
@@ -700,7 +741,7 @@ hipError_t launch_ritz_vectors(const double* Q, const double* Z, const double* e
   hipLaunchKernelGGL(k_select_top, dim3(1), dim3(256), 0, s, Z, ev, p, D, Zs, eigD);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = gemm(V, D, p, Q, p, Zs, D, U, D, s);
+  e = gemm(V, D, p, Q, p, Zs, D, U, D, false, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_sign_fix, dim3(D), dim3(256), 0, s, U, V, D);
   return hipGetLastError();
@@ -722,24 +763,8 @@ hipError_t launch_from_injected(const double* W, int V, int D, double* U, double
   return hipGetLastError();
 }
 
-int dgemm_splits(int M, int N, int K, int num_cu) {
-  // blocks resident at once: two 8-wave blocks per CU; the time of a product
-  // goes as (rounds of resident blocks) / splits, so pick the split count in
-  // 1 .. 8 (chunks of at least 1024) with the fewest rounds per split,
-  // the smallest count on ties
-  const long long blocks = (long long)((N + 127) / 128) * ((M + kDgBM - 1) / kDgBM);
-  const long long slots = 2LL * num_cu;
-  if (K < 2048 || blocks <= 0) return 1;
-  int best = 1;
-  double best_t = (double)((blocks + slots - 1) / slots);
-  for (int sp = 2; sp <= 8 && K / sp >= 1024; ++sp) {
-    const double t = (double)((blocks * sp + slots - 1) / slots) / sp;
-    if (t < best_t - 1e-9) {
-      best_t = t;
-      best = sp;
-    }
-  }
-  return best;
+size_t dgemm_ws_doubles(int M, int N, int K, int num_cu) {
+  return dgemm_plan(M, N, K, num_cu).ws();
 }
 
 }  // namespace tlda

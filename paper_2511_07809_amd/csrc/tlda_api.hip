@@ -275,11 +275,13 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
   HIP_OK(c, dalloc(&e.mcand, V));
   HIP_OK(c, dalloc(&e.info, 4));
   HIP_OK(c, dalloc(&e.part, tlda::gram_scratch_doubles((int)V, p, true)));
-  // K-split partials of the M2 product on the matrix cores (V x p each)
-  const int splits = tlda::dgemm_splits((int)V, p, (int)V, c->num_cu > 0 ? c->num_cu : 256);
-  if (splits > 1) {
-    HIP_OK(c, dalloc(&e.ws, (size_t)splits * V * p));
-    e.ws_doubles = (size_t)splits * V * p;
+  // pieces of the products: M2 times the block, and the block times a p x p matrix
+  const int cu = c->num_cu > 0 ? c->num_cu : 256;
+  const size_t ws = std::max(tlda::dgemm_ws_doubles((int)V, p, (int)V, cu),
+                             tlda::dgemm_ws_doubles((int)V, p, p, cu));
+  if (ws > 0) {
+    HIP_OK(c, dalloc(&e.ws, ws));
+    e.ws_doubles = ws;
   }
   e.p = p;
   return TLDA_OK;
@@ -317,8 +319,8 @@ tlda_status save_prev(tlda_ctx* c) {
   return TLDA_OK;
 }
 
-// The refresh's product environment: its matrix-core or vector route and the
-// K-split scratch of this context.
+// The refresh's product environment: its matrix-core or vector route and this
+// context's workspace.
 tlda::EigEnv eig_env(const tlda_ctx* c) {
   tlda::EigEnv env;
   env.route = c->tune.gemm_route == 1 ? 1 : 0;

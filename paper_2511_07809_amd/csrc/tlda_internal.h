@@ -88,7 +88,7 @@ struct EigScratch {
   int* info = nullptr;     // [4]     device status words
   double* warm = nullptr;  // Q or Y: the orthonormal block the last refresh converged to
   double* part = nullptr;  // row-chunk partials of the Gram products (gram_scratch_doubles)
-  double* ws = nullptr;    // [splits][V][p] K-split partials of the M2 product
+  double* ws = nullptr;    // pieces of the product with M2 (dgemm_ws_doubles)
   size_t ws_doubles = 0;
 };
 
@@ -229,12 +229,12 @@ struct KernelTimer {
 extern thread_local KernelTimer g_main_timer;
 
 // Environment of the refresh's dense FP64 products, set by the API around a
-// refresh or rebase (EigScope).  route 0: C = A B on the FP64 matrix cores
-// (k_dgemm_mfma), with a K split over ws (splits x M x N doubles) when the
-// grid would not fill the device; route 1: the vector-ALU tile kernel.
+// refresh (EigScope).  route 0: the FP64 matrix cores (k_dgemm_mfma), with ws
+// for the pieces of tiles that several blocks share; route 1: the vector-ALU
+// tile kernel.
 struct EigEnv {
   int route = 0;
-  double* ws = nullptr;       // K-split workspace of the matrix-core product
+  double* ws = nullptr;       // workspace of the matrix-core products
   size_t ws_doubles = 0;
   int num_cu = 256;
 };
@@ -244,10 +244,8 @@ struct EigScope {
   explicit EigScope(const EigEnv& e) : prev(g_eig_env) { g_eig_env = e; }
   ~EigScope() { g_eig_env = prev; }
 };
-// K-split count of the matrix-core product C (M x N) = A (M x K) B: the count
-// in 1 .. 8 (chunks of at least 1024) that fills the rounds of resident
-// blocks best.
-int dgemm_splits(int M, int N, int K, int num_cu);
+// Workspace (doubles) of the matrix-core product C (M x N) = A (M x K) B.
+size_t dgemm_ws_doubles(int M, int N, int K, int num_cu);
 
 template <typename... Params, typename... Args>
 inline void launch_main(void (*kernel)(Params...), dim3 grid, dim3 block, unsigned shmem,
