@@ -358,7 +358,7 @@ const char* tlda_mlp_last_error(const tlda_mlp* mlp);
 tlda_status tlda_mlp_set_params(tlda_mlp* mlp, const float* host_params);
 tlda_status tlda_mlp_get_params(tlda_mlp* mlp, float* host_params);
 /* theta_out [n_rows][k_out] = softmax(...) of X [n_rows][d_in] (device
- * float), in chunks of max_batch rows. */
+ * float), any number of rows. */
 tlda_status tlda_mlp_forward(tlda_mlp* mlp, const float* X, int64_t n_rows, float* theta_out);
 /* Gradients of the mean cross-entropy of X against T [n_rows][k_out] (device
  * float, rows on the simplex), 1 <= n_rows <= max_batch: grads_out (device

@@ -3,18 +3,31 @@
 // output), standing in for the per-document simplex-constrained solve of the
 // inference step, which stays as its judge and fallback.
 //
-// Every layer is one tiled GEMM on BF16 matrix cores (v_mfma_f32_16x16x32_bf16,
-// FP32 accumulation) with the bias, activation or activation-derivative
-// applied in its epilogue; weights are FP32 masters with BF16 copies,
-// activations are stored in BF16 and pre-activations in FP32 (for GELU').
-// Training minimises the mean cross-entropy against solve outputs by Adam.
 //   forward : Z1 = X W1 + b1, H1 = gelu(Z1), Z2 = H1 W2 + b2, H2 = gelu(Z2),
 //             Z3 = H2 W3 + b3, P = softmax(Z3)
 //   backward: dZ3 = (P - T)/B, dW3 = H2^T dZ3, dZ2 = (dZ3 W3^T) gelu'(Z2),
 //             dW2 = H1^T dZ2, dZ1 = (dZ2 W2^T) gelu'(Z1), dW1 = X^T dZ1,
 //             db = column sums of dZ
-// gelu(z) = z Phi(z), Phi(z) = (1 + erf(z / sqrt 2)) / 2, from the device
-// math library's erff and expf.
+// Products run on BF16 matrix cores (v_mfma_f32_16x16x32_bf16, FP32
+// accumulation); weights are FP32 masters with BF16 copies, activations and
+// dZ are rounded to BF16, pre-activations stay FP32.  gelu(z) = z Phi(z),
+// Phi(z) = (1 + erf(z / sqrt 2)) / 2, from the device math library's erff and
+// expf.  Training minimises the mean cross-entropy against solve outputs by
+// Adam.
+//
+// One block takes a tile of documents through every layer, so activations
+// stay on the chip.  A layer is the transposed product Z^T = W^T A^T: the
+// weights are the matrix core's A operand and come straight from the caches
+// in fragment order, the activations are its B operand (16 documents by 32
+// consecutive features, one 16-byte LDS read).  A wave owns 32 output
+// features at a time as two 16-row products; row m of product t stands for
+// feature 8 (m / 4) + 4 t + m % 4 of the 32, so that the accumulators of a
+// lane are 8 consecutive features of one document: one 16-byte LDS store,
+// and the next layer's operand with its reduction index in natural order.
+// Bound: the vector ALUs (the GELUs, two error functions' worth of code per
+// hidden unit and document), then the weights' path out of the caches, which
+// is why a block takes 64 documents where there are enough of them: one
+// weight fragment then feeds four products.
 #include <algorithm>
 #include <cmath>
 
@@ -23,14 +36,11 @@
 namespace tlda {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kTileM = 64, kTileN = 64, kTileK = 32, kLdsK = kTileK + 8;
+constexpr int kThreads = 512, kWaves = kThreads / 64;
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-enum { kEpiBiasGelu = 0, kEpiBias = 1, kEpiStore = 2, kEpiDGelu = 3 };
 
 __device__ __forceinline__ uint16_t to_bf16(float f) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -38,392 +48,696 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
   const b16x2 h = __builtin_convertvector((f32x2{f, 0.f}), b16x2);
   return (uint16_t)(__builtin_bit_cast(uint32_t, h) & 0xffffu);
 }
+__device__ __forceinline__ uint32_t to_bf16x2(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), b16x2));
+}
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-__device__ __forceinline__ float gelu(float z) {
-  return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
-}
-__device__ __forceinline__ float gelu_grad(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) +
-         z * expf(-0.5f * z * z) * 0.39894228040143268f;
+__host__ __device__ inline int pad32(int n) { return (n + 31) / 32 * 32; }
+
+// Place of weight (k, o) (input k, output o) in the fragments of a product
+// whose reduction index is k: 32 x 32 blocks, output blocks outermost; in a
+// block product t, then lane (row m = feature as in the file comment, group
+// q), then 8 consecutive k.
+__host__ __device__ inline size_t frag_at(int k, int o, int k_pad) {
+  const int oo = o & 31, kk = k & 31;
+  const int t = (oo >> 2) & 1, m = 4 * (oo >> 3) + (oo & 3);
+  const size_t block = (size_t)(o >> 5) * (k_pad >> 5) + (k >> 5);
+  return ((block * 2 + t) * 64 + (kk >> 3) * 16 + m) * 8 + (kk & 7);
 }
 
-// C[M][N] = op(A) op(B) with op(A)[m][k] = TA ? A[k*lda + m] : A[m*lda + k]
-// (A in FP32 when AF32, else BF16) and op(B)[k][n] = TB ? B[n*ldb + k] :
-// B[k*ldb + n] (BF16).  One 64 x 64 tile per block; each wave owns a 32 x 32
-// quarter (2 x 2 matrix-core tiles).  Operand tiles go through LDS with the
-// reduction index contiguous, which is what the matrix core's A and B
-// fragments need.
-// grid.z splits the reduction (kEpiStore only): block z takes rows
-// z k_chunk .. of the reduction index and writes its partial to
-// Cf + z c_stride_z (k_sum_slices then adds the partials in order).
-template <bool TA, bool TB, bool AF32, int EPI>
-__global__ void __launch_bounds__(kThreads) k_gemm(int M, int N, int Kd, const void* __restrict__ Av,
-                                                  int lda, const uint16_t* __restrict__ B, int ldb,
-                                                  const float* __restrict__ bias,
-                                                  float* __restrict__ Cf, uint16_t* __restrict__ Cb,
-                                                  int ldc, const float* __restrict__ Zaux,
-                                                  int k_chunk, size_t c_stride_z) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[kTileM * kLdsK];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[kTileN * kLdsK];
+// The encoder's device copies of its parameters: BF16 fragments of W1, W2, W3
+// (forward: reduction over the input) and of W2, W3 with input and output
+// exchanged (backward), all padded to 32 by zeros, and the padded biases.
+struct Frags {
+  uint16_t *w1, *w2, *w3, *t2, *t3;
+  float *b1, *b2, *b3;
+};
+inline size_t frag_halves(int D, int H, int K) {
+  const size_t d = pad32(D), h = pad32(H), k = pad32(K);
+  return d * h + 2 * h * h + 2 * h * k;
+}
+inline size_t bias_floats(int H, int K) { return 2 * (size_t)pad32(H) + pad32(K); }
+inline Frags frags_of(const tlda_mlp& m) {
+  const size_t d = pad32(m.d_in), h = pad32(m.hidden), k = pad32(m.k_out);
+  Frags f;
+  f.w1 = m.wfrag;
+  f.w2 = f.w1 + d * h;
+  f.w3 = f.w2 + h * h;
+  f.t2 = f.w3 + h * k;
+  f.t3 = f.t2 + h * h;
+  f.b1 = m.bpad;
+  f.b2 = f.b1 + h;
+  f.b3 = f.b2 + h;
+  return f;
+}
+
+// Writes parameter e's value into the copies.
+__device__ inline void put_param(const Frags& f, int D, int H, int K, size_t e, float v) {
+  const size_t n1 = (size_t)D * H, n2 = n1 + H, n3 = n2 + (size_t)H * H, n4 = n3 + H,
+               n5 = n4 + (size_t)H * K;
+  if (e < n1) {
+    f.w1[frag_at((int)(e / H), (int)(e % H), pad32(D))] = to_bf16(v);
+  } else if (e < n2) {
+    f.b1[e - n1] = v;
+  } else if (e < n3) {
+    const int i = (int)((e - n2) / H), o = (int)((e - n2) % H);
+    f.w2[frag_at(i, o, pad32(H))] = to_bf16(v);
+    f.t2[frag_at(o, i, pad32(H))] = to_bf16(v);
+  } else if (e < n4) {
+    f.b2[e - n3] = v;
+  } else if (e < n5) {
+    const int i = (int)((e - n4) / K), o = (int)((e - n4) % K);
+    f.w3[frag_at(i, o, pad32(H))] = to_bf16(v);
+    f.t3[frag_at(o, i, pad32(K))] = to_bf16(v);
+  } else {
+    f.b3[e - n5] = v;
+  }
+}
+
+__global__ void __launch_bounds__(256) k_refresh(const float* __restrict__ p, int D, int H, int K,
+                                                 size_t n, Frags f) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) put_param(f, D, H, K, i, p[i]);
+}
+
+// Output features 32 tp .. 32 tp + 31 of NT x 16 documents: acc[t][n][r] of
+// lane (l16, q) is feature 32 tp + 8 q + 4 t + r of document 16 n + l16.
+// w: the layer's fragments, ks_n blocks of 32 inputs; act: LDS, lda halves a
+// document.
+template <int NT>
+__device__ __forceinline__ void layer(const uint16_t* __restrict__ w, int tp, int ks_n,
+                                      const uint16_t* act, int lda, int lane,
+                                      floatx4 (&acc)[2][NT]) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[t][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const u32x4* wp = reinterpret_cast<const u32x4*>(w) + (size_t)tp * ks_n * 128 + lane;
+  const uint16_t* ap = act + (lane & 15) * lda + 8 * (lane >> 4);
+#pragma unroll 4
+  for (int ks = 0; ks < ks_n; ++ks) {
+    const u32x4 a0 = wp[ks * 128], a1 = wp[ks * 128 + 64];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const u32x4 b = *reinterpret_cast<const u32x4*>(ap + n * 16 * lda + ks * 32);
+      acc[0][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a0),
+                                                          __builtin_bit_cast(bf16x8, b),
+                                                          acc[0][n], 0, 0, 0);
+      acc[1][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a1),
+                                                          __builtin_bit_cast(bf16x8, b),
+                                                          acc[1][n], 0, 0, 0);
+    }
+  }
+}
+
+// The 8 values of a lane as one LDS store (v[4 t + r]).
+__device__ __forceinline__ void store_act(uint16_t* act, int lda, int tp, int doc, int q,
+                                          const float (&v)[8]) {
+  const u32x4 h = {to_bf16x2(v[0], v[1]), to_bf16x2(v[2], v[3]), to_bf16x2(v[4], v[5]),
+                   to_bf16x2(v[6], v[7])};
+  *reinterpret_cast<u32x4*>(act + doc * lda + tp * 32 + 8 * q) = h;
+}
+
+__device__ __forceinline__ float phi_cdf2(float z) { return 1.0f + erff(z * 0.70710678118654752f); }
+
+// rows x D floats from X (row-major, contiguous) to LDS documents in BF16;
+// documents from `rows` on and features from D on (to Dp) are zeros.
+__device__ inline void load_rows(const float* __restrict__ X, int rows, int docs, int D, int Dp,
+                                 uint16_t* act, int lda) {
+  for (int e = threadIdx.x; e < docs * Dp; e += kThreads) {
+    const int r = e / Dp, d = e - r * Dp;
+    act[r * lda + d] = r < rows && d < D ? to_bf16(X[(size_t)r * D + d]) : (uint16_t)0;
+  }
+}
+
+// Softmax of the logits of one document over four lanes (j = 0 .. 3, lane j
+// holding entries j, j + 4, ...): p[i] replaces z[i].  Entries l, l + 64, ..
+// are added first and the 64 sums pairwise at distances 32, 16, 8, 4, 2, 1.
+// Returns log sum exp.  K <= 256.
+__device__ inline float softmax_row(float* z, int K, int j) {
+  float mx = -INFINITY;
+  for (int i = j; i < K; i += 4) mx = fmaxf(mx, z[i]);
+  mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
+  mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
+  float s[16];
+#pragma unroll
+  for (int m = 0; m < 16; ++m) {
+    s[m] = 0.f;
+    for (int i = j + 4 * m; i < K; i += 64) {
+      const float v = expf(z[i] - mx);
+      z[i] = v;
+      s[m] += v;
+    }
+  }
+#pragma unroll
+  for (int d = 8; d > 0; d >>= 1)
+#pragma unroll
+    for (int m = 0; m < d; ++m) s[m] += s[m + d];
+  float sum = s[0];
+  sum += __shfl_xor(sum, 2, 64);
+  sum += __shfl_xor(sum, 1, 64);
+  const float inv = 1.0f / sum;
+  for (int i = j; i < K; i += 4) z[i] *= inv;
+  return mx + logf(sum);
+}
+
+// theta = softmax(...) for a tile of 16 NT documents.  LDS: two activation
+// buffers of 16 NT documents, lda halves each (lda >= every padded width and
+// 2 (K padded) + 8, for the logits in FP32).
+template <int NT>
+__global__ void __launch_bounds__(kThreads) k_forward(const float* __restrict__ X, int64_t n_rows,
+                                                      int D, int H, int K, int lda, Frags f,
+                                                      float* __restrict__ theta) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  constexpr int docs = 16 * NT;
+  uint16_t* buf[2] = {lds, lds + docs * lda};
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Dp = pad32(D), Hp = pad32(H), Kp = pad32(K);
+  const int64_t row0 = (int64_t)blockIdx.x * docs;
+  const int rows = (int)min((int64_t)docs, n_rows - row0);
+  load_rows(X + row0 * D, rows, docs, D, Dp, buf[0], lda);
+  __syncthreads();
+#pragma unroll
+  for (int l = 0; l < 2; ++l) {   // hidden layers
+    const uint16_t* w = l == 0 ? f.w1 : f.w2;
+    const float* bias = l == 0 ? f.b1 : f.b2;
+    for (int tp = wave; tp < Hp / 32; tp += kWaves) {
+      floatx4 acc[2][NT];
+      layer<NT>(w, tp, (l == 0 ? Dp : Hp) / 32, buf[l], lda, lane, acc);
+      const float* bp = bias + tp * 32 + 8 * q;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        float h[8];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float z = acc[t][n][r] + bp[4 * t + r];
+            h[4 * t + r] = 0.5f * z * phi_cdf2(z);
+          }
+        store_act(buf[1 - l], lda, tp, n * 16 + l16, q, h);
+      }
+    }
+    __syncthreads();
+  }
+  float* logits = reinterpret_cast<float*>(buf[1]);
+  const int ldl = lda / 2;
+  for (int tp = wave; tp < Kp / 32; tp += kWaves) {
+    floatx4 acc[2][NT];
+    layer<NT>(f.w3, tp, Hp / 32, buf[0], lda, lane, acc);
+    const float* bp = f.b3 + tp * 32 + 8 * q;
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          logits[(n * 16 + l16) * ldl + tp * 32 + 8 * q + 4 * t + r] = acc[t][n][r] + bp[4 * t + r];
+  }
+  __syncthreads();
+  if (tid < 4 * docs) softmax_row(logits + (tid >> 2) * ldl, K, tid & 3);
+  __syncthreads();
+  float* out = theta + row0 * K;
+  for (int e = tid; e < rows * K; e += kThreads) {
+    const int r = e / K;
+    out[e] = logits[r * ldl + e - r * K];
+  }
+}
+
+// Features of the tile's 16 documents, transposed to [feature][ld] at column
+// col0: two 16-byte stores per feature.
+__device__ inline void store_transposed(const uint16_t* act, int lda, int width,
+                                        uint16_t* __restrict__ out, size_t ld, size_t col0) {
+  for (int f = threadIdx.x; f < width; f += kThreads) {
+    u32x4 v[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      v[i >> 2][i & 3] = (uint32_t)act[2 * i * lda + f] | ((uint32_t)act[(2 * i + 1) * lda + f] << 16);
+    u32x4* p = reinterpret_cast<u32x4*>(out + (size_t)f * ld + col0);
+    p[0] = v[0];
+    p[1] = v[1];
+  }
+}
+
+// What the weight gradients read, transposed: [feature][ld], the rows of
+// gradient chunk z at columns z chunk_pad .. (zeros behind its rows).
+struct TrainTiles {
+  uint16_t *x, *h1, *h2, *d1, *d2, *d3;
+  size_t ld;
+  int chunk, chunk_pad;
+};
+
+// Forward and backward of 16 documents of one gradient chunk: block (x, z)
+// takes rows 16 x .. of chunk z.  The wave that computes a hidden unit's
+// pre-activation also computes its dZ, in the same lane, so gelu' waits in
+// registers (PP: blocks of 32 hidden units per wave).
+// LDS: three activation buffers of 16 x lda halves (X, then dZ2; H1; H2, then
+// dZ1), dZ3 (16 x ldk) and the logits.
+template <int PP>
+__global__ void __launch_bounds__(kThreads) k_train(const float* __restrict__ X,
+                                                    const float* __restrict__ T, int n, int D,
+                                                    int H, int K, int lda, Frags f, TrainTiles o,
+                                                    float inv_b, float* __restrict__ row_loss) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  const int Dp = pad32(D), Hp = pad32(H), Kp = pad32(K);
+  const int ldk = Kp + 8, ldl = Kp + 4;
+  uint16_t* bx = lds;
+  uint16_t* b1 = bx + 16 * lda;
+  uint16_t* b2 = b1 + 16 * lda;
+  uint16_t* b3 = b2 + 16 * lda;
+  float* logits = reinterpret_cast<float*>(b3 + 16 * ldk);
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int in_chunk = 16 * blockIdx.x;
+  const int row0 = blockIdx.y * o.chunk + in_chunk;
+  const int rows = max(0, min(min(16, o.chunk - in_chunk), n - row0));
+  const size_t col0 = (size_t)blockIdx.y * o.chunk_pad + in_chunk;
+  float g1[PP][8], g2[PP][8];
+
+  load_rows(X + (size_t)row0 * D, rows, 16, D, Dp, bx, lda);
+  __syncthreads();
+  auto hidden = [&](const uint16_t* w, const float* bias, int ks, const uint16_t* in, uint16_t* out,
+                    float (&g)[PP][8]) {
+#pragma unroll
+    for (int pp = 0; pp < PP; ++pp) {
+      const int tp = wave + pp * kWaves;
+      if (tp >= Hp / 32) break;
+      floatx4 acc[2][1];
+      layer<1>(w, tp, ks, in, lda, lane, acc);
+      const float* bp = bias + tp * 32 + 8 * q;
+      float h[8];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float z = acc[t][0][r] + bp[4 * t + r];
+          const float c2 = phi_cdf2(z);
+          h[4 * t + r] = 0.5f * z * c2;
+          g[pp][4 * t + r] = 0.5f * c2 + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+        }
+      store_act(out, lda, tp, l16, q, h);
+    }
+  };
+  hidden(f.w1, f.b1, Dp / 32, bx, b1, g1);
+  store_transposed(bx, lda, D, o.x, o.ld, col0);
+  __syncthreads();
+  hidden(f.w2, f.b2, Hp / 32, b1, b2, g2);
+  store_transposed(b1, lda, H, o.h1, o.ld, col0);
+  __syncthreads();
+  for (int tp = wave; tp < Kp / 32; tp += kWaves) {
+    floatx4 acc[2][1];
+    layer<1>(f.w3, tp, Hp / 32, b2, lda, lane, acc);
+    const float* bp = f.b3 + tp * 32 + 8 * q;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        logits[l16 * ldl + tp * 32 + 8 * q + 4 * t + r] = acc[t][0][r] + bp[4 * t + r];
+  }
+  store_transposed(b2, lda, H, o.h2, o.ld, col0);
+  __syncthreads();
+  if (tid < 64) {   // four lanes a document: P, dZ3 = (P - T) / B and the cross-entropy
+    const int doc = tid >> 2, j = tid & 3;
+    const bool in = doc < rows;
+    float* z = logits + doc * ldl;
+    const float* t = T + (size_t)(row0 + doc) * K;
+    float ce[16];   // sum t (lse - z) = sum t lse - t z, added as the softmax sum is
+    float zk[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) zk[m] = j + 4 * m < K ? z[j + 4 * m] : 0.f;
+    float keep[3][16];
+    if (K > 64) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+          const int i = j + 4 * m + 64 * (c + 1);
+          keep[c][m] = i < K ? z[i] : 0.f;
+        }
+    }
+    const float lse = softmax_row(z, K, j);
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+      ce[m] = 0.f;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int i = j + 4 * m + 64 * c;
+        if (i >= K) break;
+        const float ti = in ? t[i] : 0.f;
+        ce[m] += ti * (lse - (c == 0 ? zk[m] : keep[c > 0 ? c - 1 : 0][m]));
+        b3[doc * ldk + i] = in ? to_bf16((z[i] - ti) * inv_b) : (uint16_t)0;
+      }
+    }
+    for (int i = K + j; i < Kp; i += 4) b3[doc * ldk + i] = 0;
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1)
+#pragma unroll
+      for (int m = 0; m < d; ++m) ce[m] += ce[m + d];
+    float s = ce[0];
+    s += __shfl_xor(s, 2, 64);
+    s += __shfl_xor(s, 1, 64);
+    if (in && j == 0) row_loss[row0 + doc] = s;
+  }
+  __syncthreads();
+  auto back = [&](const uint16_t* w, int ks, const uint16_t* in, int ld_in, uint16_t* out,
+                  const float (&g)[PP][8]) {
+#pragma unroll
+    for (int pp = 0; pp < PP; ++pp) {
+      const int tp = wave + pp * kWaves;
+      if (tp >= Hp / 32) break;
+      floatx4 acc[2][1];
+      layer<1>(w, tp, ks, in, ld_in, lane, acc);
+      float d[8];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d[4 * t + r] = acc[t][0][r] * g[pp][4 * t + r];
+      store_act(out, lda, tp, l16, q, d);
+    }
+  };
+  back(f.t3, Kp / 32, b3, ldk, bx, g2);
+  store_transposed(b3, ldk, K, o.d3, o.ld, col0);
+  __syncthreads();
+  back(f.t2, Hp / 32, bx, lda, b2, g1);
+  store_transposed(bx, lda, H, o.d2, o.ld, col0);
+  __syncthreads();
+  store_transposed(b2, lda, H, o.d1, o.ld, col0);
+}
+
+// Gradient partials.  The first blocks take one 64 x 64 tile of dW1, dW2 or
+// dW3 over one chunk of rows (a wave 32 x 32 of it; both operands are 16-byte
+// pieces of the transposed tiles, straight from the caches); the others take
+// 256 bias entries over 64 rows, four interleaved row sums combined at the
+// end.  ws_w: [chunk][weights in parameter order without the biases], ws_b:
+// [64-row chunk][b1, b2, b3].
+struct GradPlan {
+  int t1, t2, t3;        // 64 x 64 tiles of each weight matrix
+  int splits;            // row chunks
+  int bias_blocks;       // column blocks of the bias entries
+  int bias_chunks;
+};
+
+__global__ void __launch_bounds__(256) k_grads(int n, int D, int H, int K, TrainTiles o, GradPlan g,
+                                               float* __restrict__ ws_w, float* __restrict__ ws_b) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l16 = lane & 15, l4 = lane >> 4;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int m0 = blockIdx.y * kTileM, n0 = blockIdx.x * kTileN;
-  const float* Af = static_cast<const float*>(Av);
-  const uint16_t* Ab = static_cast<const uint16_t*>(Av);
+  const int l16 = lane & 15, q = lane >> 4;
+  const int tiles = g.t1 + g.t2 + g.t3;
+  int b = blockIdx.x;
+  if (b >= tiles * g.splits) {
+    b -= tiles * g.splits;
+    const int chunk = b / g.bias_blocks, e = b % g.bias_blocks * 256 + tid;
+    if (e >= 2 * H + K) return;
+    const uint16_t* m = e < H ? o.d1 + (size_t)e * o.ld
+                              : e < 2 * H ? o.d2 + (size_t)(e - H) * o.ld
+                                          : o.d3 + (size_t)(e - 2 * H) * o.ld;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    const int r0 = chunk * 64, r1 = min(n, r0 + 64);
+    int z = r0 / o.chunk, c = r0 - z * o.chunk;
+    for (int r = r0; r < r1; r += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (r + u < r1) {
+          s[u] += from_bf16(m[(size_t)z * o.chunk_pad + c]);
+          if (++c == o.chunk) {
+            c = 0;
+            ++z;
+          }
+        }
+    }
+    ws_b[(size_t)chunk * (2 * H + K) + e] = (s[0] + s[1]) + (s[2] + s[3]);
+    return;
+  }
+  const int z = b / tiles;
+  int t = b % tiles;
+  const uint16_t *A, *B;
+  int M, N;
+  size_t off = (size_t)z * ((size_t)D * H + (size_t)H * H + (size_t)H * K);
+  if (t < g.t1) {
+    A = o.x, B = o.d1, M = D, N = H;
+  } else if (t < g.t1 + g.t2) {
+    t -= g.t1;
+    A = o.h1, B = o.d2, M = H, N = H;
+    off += (size_t)D * H;
+  } else {
+    t -= g.t1 + g.t2;
+    A = o.h2, B = o.d3, M = H, N = K;
+    off += (size_t)D * H + (size_t)H * H;
+  }
+  const int nt = (N + 63) / 64;
+  const int m0 = t / nt * 64 + (wave >> 1) * 32, n0 = t % nt * 64 + (wave & 1) * 32;
+  const size_t col = (size_t)z * o.chunk_pad + 8 * q;
+  const uint16_t* ap = A + (size_t)(m0 + l16) * o.ld + col;
+  const uint16_t* bp = B + (size_t)(n0 + l16) * o.ld + col;
   floatx4 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  const int kbeg = blockIdx.z * k_chunk;
-  Kd = min(Kd, kbeg + k_chunk);              // this block's end of the reduction index
-  if (EPI == kEpiStore) Cf += blockIdx.z * c_stride_z;
-  for (int k0 = kbeg; k0 < Kd; k0 += kTileK) {
-    __syncthreads();
-    // ---- A tile: As[m][k] = op(A)[m0 + m][k0 + k] ----
-    if (!TA) {
-      const int m = tid >> 2, kc = (tid & 3) * 8;
-      const int gm = m0 + m;
+#pragma unroll 4
+  for (int k0 = 0; k0 < o.chunk_pad; k0 += 32) {
+    u32x4 a[2], bb[2];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gk = k0 + kc + i;
-        uint16_t v = 0;
-        if (gm < M && gk < Kd)
-          v = AF32 ? to_bf16(Af[(size_t)gm * lda + gk]) : Ab[(size_t)gm * lda + gk];
-        As[m * kLdsK + kc + i] = v;
-      }
-    } else {
-      const int kk = tid >> 3, mc = (tid & 7) * 8;
-      const int gk = k0 + kk;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gm = m0 + mc + i;
-        uint16_t v = 0;
-        if (gm < M && gk < Kd)
-          v = AF32 ? to_bf16(Af[(size_t)gk * lda + gm]) : Ab[(size_t)gk * lda + gm];
-        As[(mc + i) * kLdsK + kk] = v;
-      }
+    for (int i = 0; i < 2; ++i) {
+      a[i] = *reinterpret_cast<const u32x4*>(ap + i * 16 * o.ld + k0);
+      bb[i] = *reinterpret_cast<const u32x4*>(bp + i * 16 * o.ld + k0);
     }
-    // ---- B tile: Bs[n][k] = op(B)[k0 + k][n0 + n] ----
-    if (TB) {
-      const int n = tid >> 2, kc = (tid & 3) * 8;
-      const int gn = n0 + n;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gk = k0 + kc + i;
-        Bs[n * kLdsK + kc + i] = (gn < N && gk < Kd) ? B[(size_t)gn * ldb + gk] : (uint16_t)0;
-      }
-    } else {
-      const int kk = tid >> 3, nc = (tid & 7) * 8;
-      const int gk = k0 + kk;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int gn = n0 + nc + i;
-        Bs[(nc + i) * kLdsK + kk] = (gn < N && gk < Kd) ? B[(size_t)gk * ldb + gn] : (uint16_t)0;
-      }
-    }
-    __syncthreads();
-    u32x4 af[2], bfr[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-      af[i] = *reinterpret_cast<const u32x4*>(As + (wm * 32 + i * 16 + l16) * kLdsK + 8 * l4);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      bfr[j] = *reinterpret_cast<const u32x4*>(Bs + (wn * 32 + j * 16 + l16) * kLdsK + 8 * l4);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[i]),
-                                                            __builtin_bit_cast(bf16x8, bfr[j]),
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]),
+                                                            __builtin_bit_cast(bf16x8, bb[j]),
                                                             acc[i][j], 0, 0, 0);
   }
-  // ---- epilogue: lane holds rows 4 l4 + r, column l16 of each 16 x 16 tile ----
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn * 32 + j * 16 + l16;
-      if (n >= N) continue;
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm * 32 + i * 16 + 4 * l4 + r;
-        if (m >= M) continue;
-        const size_t o = (size_t)m * ldc + n;
-        const float a = acc[i][j][r];
-        if (EPI == kEpiBiasGelu) {
-          const float z = a + bias[n];
-          if (Cf) Cf[o] = z;
-          Cb[o] = to_bf16(gelu(z));
-        } else if (EPI == kEpiBias) {
-          Cf[o] = a + bias[n];
-        } else if (EPI == kEpiStore) {
-          Cf[o] = a;
-        } else {
-          Cb[o] = to_bf16(a * gelu_grad(Zaux[o]));
-        }
+        const int gm = m0 + i * 16 + 4 * q + r, gn = n0 + j * 16 + l16;
+        if (gm < M && gn < N) ws_w[off + (size_t)gm * N + gn] = acc[i][j][r];
       }
-    }
 }
 
-// Row-wise softmax of the logits (one wave per row, K <= 256): P to `theta`
-// when given; with targets T, also the row's cross-entropy -sum t log p and
-// dZ3 = (P - T) * inv_b in BF16.
-__global__ void __launch_bounds__(kThreads) k_softmax(const float* __restrict__ Z, int n, int K,
-                                                      float* __restrict__ theta,
-                                                      const float* __restrict__ T, float inv_b,
-                                                      uint16_t* __restrict__ dZ,
-                                                      float* __restrict__ row_loss) {
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n) return;
-  const float* z = Z + (size_t)row * K;
-  float v[4];
-  float mx = -INFINITY;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = lane + 64 * q;
-    v[q] = k < K ? z[k] : -INFINITY;
-    mx = fmaxf(mx, v[q]);
-  }
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  float sum = 0.f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = lane + 64 * q;
-    v[q] = k < K ? expf(v[q] - mx) : 0.f;
-    sum += v[q];
-  }
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  const float inv = 1.0f / sum;
-  const float lse = mx + logf(sum);
-  float ce = 0.f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = lane + 64 * q;
-    if (k >= K) continue;
-    const float p = v[q] * inv;
-    if (theta) theta[(size_t)row * K + k] = p;
-    if (T) {
-      const float t = T[(size_t)row * K + k];
-      ce += t * (lse - z[k]);   // -t log p with log p = z - logsumexp
-      dZ[(size_t)row * K + k] = to_bf16((p - t) * inv_b);
-    }
-  }
-  if (T) {
-    for (int off = 32; off > 0; off >>= 1) ce += __shfl_xor(ce, off, 64);
-    if (lane == 0) row_loss[row] = ce;
-  }
-}
-
-// part[y][c] = sum over rows r of chunk y (rows y rchunk ..) of M[r][c] (BF16
-// input, FP32 sum in a fixed order): block (x, y) takes 64 columns of row
-// chunk y, 4 row phases per column combined in LDS; k_sum_slices then adds
-// the chunks in order (the bias gradients: column sums of dZ).
-__global__ void __launch_bounds__(kThreads) k_colsum(const uint16_t* __restrict__ Mx, int rows,
-                                                     int cols, int rchunk,
-                                                     float* __restrict__ part) {
-  __shared__ float red[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
-  const int r0 = blockIdx.y * rchunk, r1 = min(rows, r0 + rchunk);
+// Gradient of parameter e from its partials, added in chunk order.
+__device__ inline float sum_partials(const float* __restrict__ ws, int n, size_t stride) {
+  constexpr int kU = 8;
   float s = 0.f;
-  if (c < cols)
-    for (int r = r0 + ph; r < r1; r += 4) s += from_bf16(Mx[(size_t)r * cols + c]);
-  red[ph][threadIdx.x & 63] = s;
-  __syncthreads();
-  if (ph == 0 && c < cols)
-    part[(size_t)blockIdx.y * cols + c] = (red[0][threadIdx.x] + red[1][threadIdx.x]) +
-                                          (red[2][threadIdx.x] + red[3][threadIdx.x]);
+  for (int z = 0; z < n; z += kU) {
+    float v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = ws[(size_t)min(z + u, n - 1) * stride];
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (z + u < n) s += v[u];
+  }
+  return s;
 }
 
-// out[e] = sum_z ws[z][e] for z = 0 .. nz - 1 in order (e < n)
-__global__ void k_sum_slices(const float* __restrict__ ws, int nz, size_t n,
-                             float* __restrict__ out) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
+// loss = sum of the row losses / n (fixed order, one block of 256)
+__device__ inline void mean_loss(const float* __restrict__ row_loss, int n, float* out) {
+  __shared__ float red[256];
   float s = 0.f;
-  for (int z = 0; z < nz; ++z) s += ws[(size_t)z * n + e];
-  out[e] = s;
-}
-
-// loss = sum of the row losses / n (fixed order, one block)
-__global__ void __launch_bounds__(kThreads) k_loss(const float* __restrict__ row_loss, int n,
-                                                   float* __restrict__ out) {
-  __shared__ float red[kThreads];
-  float s = 0.f;
-  for (int i = threadIdx.x; i < n; i += kThreads) s += row_loss[i];
+  for (int i = threadIdx.x; i < n; i += 256) s += row_loss[i];
   red[threadIdx.x] = s;
   __syncthreads();
-  for (int w = kThreads / 2; w > 0; w >>= 1) {
+  for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
   if (threadIdx.x == 0) *out = red[0] / (float)n;
 }
 
-// Adam (Kingma & Ba, Algorithm 1) on every parameter; c1 = 1 - beta1^t and
-// c2 = 1 - beta2^t are the bias corrections.  The BF16 copies of the weight
-// matrices follow.
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, size_t n, float lr, float beta1, float beta2,
-                       float eps, float c1, float c2, uint16_t* __restrict__ wb) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = beta1 * m[i] + (1.0f - beta1) * gi;
-  const float vi = beta2 * v[i] + (1.0f - beta2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  p[i] = pi;
-  wb[i] = to_bf16(pi);
+struct AdamArgs {
+  float *p, *m, *v;
+  float lr, beta1, beta2, eps, c1, c2;   // c1 = 1 - beta1^t, c2 = 1 - beta2^t
+};
+
+// Every parameter's gradient from the partials; then either the gradient
+// itself (ADAM false, grads may be NULL) or one Adam step (Kingma & Ba,
+// Algorithm 1), with the BF16 and padded copies following.  The last block
+// takes the loss.
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_update(int n, int D, int H, int K, GradPlan g,
+                                                const float* __restrict__ ws_w,
+                                                const float* __restrict__ ws_b,
+                                                const float* __restrict__ row_loss,
+                                                float* __restrict__ loss, float* __restrict__ grads,
+                                                AdamArgs a, Frags f) {
+  if (blockIdx.x == gridDim.x - 1) {
+    if (loss != nullptr) mean_loss(row_loss, n, loss);
+    return;
+  }
+  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const size_t n1 = (size_t)D * H, n2 = n1 + H, n3 = n2 + (size_t)H * H, n4 = n3 + H,
+               n5 = n4 + (size_t)H * K, n6 = n5 + K;
+  if (e >= n6) return;
+  // a weight's place among the weights, a bias's among the biases
+  size_t w = e, bias = 0;
+  bool is_bias = false;
+  if (e >= n5) is_bias = true, bias = 2 * (size_t)H + (e - n5);
+  else if (e >= n4) w = e - 2 * (size_t)H;
+  else if (e >= n3) is_bias = true, bias = H + (e - n3);
+  else if (e >= n2) w = e - H;
+  else if (e >= n1) is_bias = true, bias = e - n1;
+  const float gi = is_bias ? sum_partials(ws_b + bias, g.bias_chunks, 2 * (size_t)H + K)
+                           : sum_partials(ws_w + w, g.splits, n6 - 2 * (size_t)H - K);
+  if (!ADAM) {
+    grads[e] = gi;
+    return;
+  }
+  const float mi = a.beta1 * a.m[e] + (1.0f - a.beta1) * gi;
+  const float vi = a.beta2 * a.v[e] + (1.0f - a.beta2) * gi * gi;
+  a.m[e] = mi;
+  a.v[e] = vi;
+  const float pi = a.p[e] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+  a.p[e] = pi;
+  put_param(f, D, H, K, e, pi);
 }
 
-__global__ void k_to_bf16(const float* __restrict__ p, size_t n, uint16_t* __restrict__ wb) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) wb[i] = to_bf16(p[i]);
-}
-
-template <bool TA, bool TB, bool AF32, int EPI>
-hipError_t gemm(int M, int N, int Kd, const void* A, int lda, const uint16_t* B, int ldb,
-                const float* bias, float* Cf, uint16_t* Cb, int ldc, const float* Zaux,
-                hipStream_t s) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  const dim3 grid((N + kTileN - 1) / kTileN, (M + kTileM - 1) / kTileM);
-  hipLaunchKernelGGL((k_gemm<TA, TB, AF32, EPI>), grid, dim3(kThreads), 0, s, M, N, Kd, A, lda, B,
-                     ldb, bias, Cf, Cb, ldc, Zaux, Kd, (size_t)0);
-  return hipGetLastError();
-}
-
-// Weight gradient C (M x N, FP32, ldc = N) = op(A) B over Kd rows, the rows
-// split into chunks of at least kGradChunk so that the grid has up to
-// kGradSplits times the output tiles; the chunk partials (in the encoder's
-// workspace) are added in chunk order.
+// Rows are split into chunks of at least kGradChunk (at most kGradSplits), each
+// with its own partial of every weight gradient.
 constexpr int kGradChunk = 128, kGradSplits = 32;
-template <bool AF32>
-hipError_t grad_gemm(tlda_mlp& m, int M, int N, int Kd, const void* A, int lda, const uint16_t* B,
-                     int ldb, float* C) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  int splits = std::min(kGradSplits, std::max(1, Kd / kGradChunk));
-  const int chunk = (Kd + splits - 1) / splits;
-  splits = (Kd + chunk - 1) / chunk;
-  const size_t mn = (size_t)M * N;
-  float* out = splits > 1 ? m.ws : C;
-  const dim3 grid((N + kTileN - 1) / kTileN, (M + kTileM - 1) / kTileM, splits);
-  hipLaunchKernelGGL((k_gemm<true, false, AF32, kEpiStore>), grid, dim3(kThreads), 0, m.stream, M,
-                     N, Kd, A, lda, B, ldb, nullptr, out, nullptr, N, nullptr, chunk, mn);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || splits == 1) return e;
-  hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0, m.stream,
-                     m.ws, splits, mn, C);
-  return hipGetLastError();
+struct Chunks {
+  int splits, chunk, chunk_pad;
+};
+Chunks chunks_of(int n) {
+  Chunks c;
+  const int s = std::min(kGradSplits, std::max(1, n / kGradChunk));
+  c.chunk = (n + s - 1) / s;
+  c.splits = (n + c.chunk - 1) / c.chunk;
+  c.chunk_pad = pad32(c.chunk);
+  return c;
 }
+// columns of the transposed tiles for up to max_batch rows: a chunk's padding
+// adds at most 31
+size_t tile_cols(int max_batch) {
+  return ((size_t)max_batch + kGradSplits * 32 + 63) / 32 * 32;
+}
+int pad64(int n) { return (n + 63) / 64 * 64; }
 
-// Bias gradient out[c] = sum over the n rows of dZ[r][c]: row chunks of 64
-// in parallel, then their sums in chunk order.
-hipError_t bias_grad(tlda_mlp& m, const uint16_t* dZ, int n, int cols, float* out) {
-  const int rchunk = 64;
-  const int nch = (n + rchunk - 1) / rchunk;
-  hipLaunchKernelGGL(k_colsum, dim3((cols + 63) / 64, nch), dim3(kThreads), 0, m.stream, dZ, n,
-                     cols, rchunk, m.ws);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sum_slices, dim3((cols + 255) / 256), dim3(256), 0, m.stream, m.ws, nch,
-                     (size_t)cols, out);
-  return hipGetLastError();
+// Dynamic LDS past the default 64 KB (of the compute unit's 160) is asked for.
+hipError_t allow_lds(const void* kernel, size_t bytes) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 }  // namespace
-
-size_t mlp_workspace_floats(int d_in, int hidden, int k_out, int max_batch) {
-  const size_t mn = std::max({(size_t)d_in * hidden, (size_t)hidden * hidden,
-                              (size_t)hidden * k_out});
-  const size_t chunks = ((size_t)max_batch + 63) / 64;
-  return std::max((size_t)kGradSplits * mn, chunks * (size_t)std::max(hidden, k_out));
-}
 
 size_t mlp_param_count(int d_in, int hidden, int k_out) {
   return (size_t)d_in * hidden + hidden + (size_t)hidden * hidden + hidden +
          (size_t)hidden * k_out + k_out;
 }
 
-void mlp_offsets(int d_in, int hidden, int k_out, size_t off[6]) {
-  off[0] = 0;                                     // W1 [d_in][hidden]
-  off[1] = off[0] + (size_t)d_in * hidden;        // b1 [hidden]
-  off[2] = off[1] + hidden;                       // W2 [hidden][hidden]
-  off[3] = off[2] + (size_t)hidden * hidden;      // b2
-  off[4] = off[3] + hidden;                       // W3 [hidden][k_out]
-  off[5] = off[4] + (size_t)hidden * k_out;       // b3 [k_out]
+size_t mlp_frag_halves(int d_in, int hidden, int k_out) { return frag_halves(d_in, hidden, k_out); }
+size_t mlp_bias_floats(int hidden, int k_out) { return bias_floats(hidden, k_out); }
+
+size_t mlp_workspace_floats(int d_in, int hidden, int k_out, int max_batch) {
+  const size_t weights = (size_t)d_in * hidden + (size_t)hidden * hidden + (size_t)hidden * k_out;
+  return kGradSplits * weights + ((size_t)max_batch + 63) / 64 * (2 * (size_t)hidden + k_out);
 }
 
-hipError_t mlp_forward(tlda_mlp& m, const float* X, int n, float* theta, bool train) {
-  size_t o[6];
-  mlp_offsets(m.d_in, m.hidden, m.k_out, o);
-  const int H = m.hidden, K = m.k_out;
-  hipError_t e = gemm<false, false, true, kEpiBiasGelu>(n, H, m.d_in, X, m.d_in, m.wb + o[0], H,
-                                                         m.params + o[1], train ? m.Z1 : nullptr,
-                                                         m.H1, H, nullptr, m.stream);
-  if (e != hipSuccess) return e;
-  e = gemm<false, false, false, kEpiBiasGelu>(n, H, H, m.H1, H, m.wb + o[2], H, m.params + o[3],
-                                               train ? m.Z2 : nullptr, m.H2, H, nullptr, m.stream);
-  if (e != hipSuccess) return e;
-  e = gemm<false, false, false, kEpiBias>(n, K, H, m.H2, H, m.wb + o[4], K, m.params + o[5],
-                                          m.logits, nullptr, K, nullptr, m.stream);
-  if (e != hipSuccess) return e;
-  if (theta != nullptr) {
-    hipLaunchKernelGGL(k_softmax, dim3((n + 3) / 4), dim3(kThreads), 0, m.stream, m.logits, n, K,
-                       theta, nullptr, 0.f, nullptr, nullptr);
-    e = hipGetLastError();
-  }
-  return e;
+size_t mlp_tile_halves(int d_in, int hidden, int k_out, int max_batch) {
+  return (pad64(d_in) + 4 * (size_t)pad64(hidden) + pad64(k_out)) * tile_cols(max_batch);
 }
 
-hipError_t mlp_backward(tlda_mlp& m, const float* X, const float* T, int n, float* loss_out) {
-  size_t o[6];
-  mlp_offsets(m.d_in, m.hidden, m.k_out, o);
-  const int H = m.hidden, K = m.k_out, Din = m.d_in;
-  float* g = m.grads;
-  hipLaunchKernelGGL(k_softmax, dim3((n + 3) / 4), dim3(kThreads), 0, m.stream, m.logits, n, K,
-                     nullptr, T, 1.0f / (float)n, m.dZ3, m.row_loss);
-  hipError_t e = hipGetLastError();
+hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta) {
+  if (n <= 0) return hipSuccess;
+  const int D = m.d_in, H = m.hidden, K = m.k_out;
+  const int lda = std::max({pad32(D), pad32(H), 2 * pad32(K)}) + 8;
+  const Frags f = frags_of(m);
+  // 64 documents a block while the grid still fills the 256 compute units
+  // twice over and two blocks' LDS fits on one; 32 or 16 below that, or for
+  // wide layers
+  auto bytes = [&](int docs) { return (size_t)2 * docs * lda * sizeof(uint16_t); };
+  int nt = 1;
+  if (bytes(64) <= 80 * 1024 && n >= 64 * 512) nt = 4;
+  else if (bytes(32) <= 80 * 1024 && n >= 32 * 512) nt = 2;
+  auto kernel = nt == 4 ? k_forward<4> : nt == 2 ? k_forward<2> : k_forward<1>;
+  const size_t lds = bytes(16 * nt);
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
   if (e != hipSuccess) return e;
-  if (loss_out != nullptr) {
-    hipLaunchKernelGGL(k_loss, dim3(1), dim3(kThreads), 0, m.stream, m.row_loss, n, loss_out);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  // layer 3
-  if ((e = grad_gemm<false>(m, H, K, n, m.H2, H, m.dZ3, K, g + o[4])) != hipSuccess) return e;
-  if ((e = bias_grad(m, m.dZ3, n, K, g + o[5])) != hipSuccess) return e;
-  if ((e = gemm<false, true, false, kEpiDGelu>(n, H, K, m.dZ3, K, m.wb + o[4], K, nullptr, nullptr,
-                                               m.dZa, H, m.Z2, m.stream)) != hipSuccess)
-    return e;
-  // layer 2
-  if ((e = grad_gemm<false>(m, H, H, n, m.H1, H, m.dZa, H, g + o[2])) != hipSuccess) return e;
-  if ((e = bias_grad(m, m.dZa, n, H, g + o[3])) != hipSuccess) return e;
-  if ((e = gemm<false, true, false, kEpiDGelu>(n, H, H, m.dZa, H, m.wb + o[2], H, nullptr, nullptr,
-                                               m.dZb, H, m.Z1, m.stream)) != hipSuccess)
-    return e;
-  // layer 1
-  if ((e = grad_gemm<true>(m, Din, H, n, X, Din, m.dZb, H, g + o[0])) != hipSuccess) return e;
-  return bias_grad(m, m.dZb, n, H, g + o[1]);
-}
-
-hipError_t mlp_adam(tlda_mlp& m, float lr, float beta1, float beta2, float eps) {
-  m.adam_t += 1;
-  const float c1 = 1.0f - (float)std::pow((double)beta1, (double)m.adam_t);
-  const float c2 = 1.0f - (float)std::pow((double)beta2, (double)m.adam_t);
-  const size_t n = m.n_params;
-  hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m.stream, m.params,
-                     m.grads, m.adam_m, m.adam_v, n, lr, beta1, beta2, eps, c1, c2, m.wb);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 16 * nt - 1) / (16 * nt))), dim3(kThreads), lds,
+                     m.stream, X, n, D, H, K, lda, f, theta);
   return hipGetLastError();
 }
 
-hipError_t mlp_refresh_bf16(tlda_mlp& m) {
+// Forward, backward and the gradient partials of n <= max_batch rows.
+static hipError_t train_partials(tlda_mlp& m, const float* X, const float* T, int n, GradPlan& g) {
+  const int D = m.d_in, H = m.hidden, K = m.k_out;
+  const Chunks c = chunks_of(n);
+  TrainTiles o;
+  o.ld = tile_cols(m.max_batch);
+  o.chunk = c.chunk;
+  o.chunk_pad = c.chunk_pad;
+  o.x = m.tiles;
+  o.h1 = o.x + (size_t)pad64(D) * o.ld;
+  o.h2 = o.h1 + (size_t)pad64(H) * o.ld;
+  o.d1 = o.h2 + (size_t)pad64(H) * o.ld;
+  o.d2 = o.d1 + (size_t)pad64(H) * o.ld;
+  o.d3 = o.d2 + (size_t)pad64(H) * o.ld;
+  const int Kp = pad32(K), lda = std::max(pad32(D), pad32(H)) + 8;
+  const size_t lds = (size_t)16 * (3 * lda + Kp + 8) * sizeof(uint16_t) + 16 * (Kp + 4) * sizeof(float);
+  const dim3 grid(c.chunk_pad / 16, c.splits);
+  const Frags f = frags_of(m);
+  const float inv_b = 1.0f / (float)n;
+  auto kernel = H <= 32 * kWaves ? k_train<1> : H <= 64 * kWaves ? k_train<2> : k_train<4>;
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, m.stream, X, T, n, D, H, K, lda, f, o, inv_b,
+                     m.row_loss);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  g.t1 = pad64(D) / 64 * (pad64(H) / 64);
+  g.t2 = pad64(H) / 64 * (pad64(H) / 64);
+  g.t3 = pad64(H) / 64 * (pad64(K) / 64);
+  g.splits = c.splits;
+  g.bias_blocks = (2 * H + K + 255) / 256;
+  g.bias_chunks = (n + 63) / 64;
+  const size_t weights = (size_t)D * H + (size_t)H * H + (size_t)H * K;
+  hipLaunchKernelGGL(k_grads, dim3((g.t1 + g.t2 + g.t3) * g.splits + g.bias_blocks * g.bias_chunks),
+                     dim3(256), 0, m.stream, n, D, H, K, o, g, m.ws, m.ws + kGradSplits * weights);
+  return hipGetLastError();
+}
+
+hipError_t mlp_gradients(tlda_mlp& m, const float* X, const float* T, int n, float* grads,
+                         float* loss) {
+  GradPlan g;
+  hipError_t e = train_partials(m, X, T, n, g);
+  if (e != hipSuccess || (grads == nullptr && loss == nullptr)) return e;
+  const int D = m.d_in, H = m.hidden, K = m.k_out;
+  const size_t weights = (size_t)D * H + (size_t)H * H + (size_t)H * K;
+  const unsigned blocks = grads != nullptr ? (unsigned)((m.n_params + 255) / 256) : 0u;
+  hipLaunchKernelGGL(k_update<false>, dim3(blocks + 1), dim3(256), 0, m.stream, n, D, H, K, g, m.ws,
+                     m.ws + kGradSplits * weights, m.row_loss, loss, grads, AdamArgs{}, Frags{});
+  return hipGetLastError();
+}
+
+hipError_t mlp_train_step(tlda_mlp& m, const float* X, const float* T, int n, float lr, float beta1,
+                          float beta2, float eps, float* loss) {
+  GradPlan g;
+  hipError_t e = train_partials(m, X, T, n, g);
+  if (e != hipSuccess) return e;
+  m.adam_t += 1;
+  AdamArgs a{m.params, m.adam_m, m.adam_v, lr, beta1, beta2, eps, 0.f, 0.f};
+  a.c1 = 1.0f - (float)std::pow((double)beta1, (double)m.adam_t);
+  a.c2 = 1.0f - (float)std::pow((double)beta2, (double)m.adam_t);
+  const int D = m.d_in, H = m.hidden, K = m.k_out;
+  const size_t weights = (size_t)D * H + (size_t)H * H + (size_t)H * K;
+  hipLaunchKernelGGL(k_update<true>, dim3((unsigned)((m.n_params + 255) / 256) + 1), dim3(256), 0,
+                     m.stream, n, D, H, K, g, m.ws, m.ws + kGradSplits * weights, m.row_loss, loss,
+                     nullptr, a, frags_of(m));
+  return hipGetLastError();
+}
+
+hipError_t mlp_refresh(tlda_mlp& m) {
   const size_t n = m.n_params;
-  hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m.stream,
-                     m.params, n, m.wb);
+  hipLaunchKernelGGL(k_refresh, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m.stream, m.params,
+                     m.d_in, m.hidden, m.k_out, n, frags_of(m));
   return hipGetLastError();
 }
 

@@ -1100,9 +1100,8 @@ namespace {
 void mlp_free(tlda_mlp* m) {
   if (!m) return;
   if (m->stream) (void)hipStreamSynchronize(m->stream);
-  dfree(m->params); dfree(m->wb); dfree(m->grads); dfree(m->adam_m); dfree(m->adam_v);
-  dfree(m->Z1); dfree(m->Z2); dfree(m->H1); dfree(m->H2); dfree(m->logits); dfree(m->dZ3);
-  dfree(m->dZa); dfree(m->dZb); dfree(m->row_loss); dfree(m->ws);
+  dfree(m->params); dfree(m->wfrag); dfree(m->bpad); dfree(m->adam_m); dfree(m->adam_v);
+  dfree(m->tiles); dfree(m->row_loss); dfree(m->ws);
   delete m;
 }
 
@@ -1145,14 +1144,14 @@ tlda_status tlda_mlp_create(int32_t d_in, int32_t hidden, int32_t k_out, int32_t
   m->max_batch = max_batch;
   m->n_params = tlda::mlp_param_count(d_in, hidden, k_out);
   m->stream = static_cast<hipStream_t>(hip_stream);
-  const size_t P = m->n_params, B = (size_t)max_batch, H = hidden, K = k_out;
-  bool ok = dalloc(&m->params, P) == hipSuccess && dalloc(&m->wb, P) == hipSuccess &&
-            dalloc(&m->grads, P) == hipSuccess && dalloc(&m->adam_m, P) == hipSuccess &&
-            dalloc(&m->adam_v, P) == hipSuccess && dalloc(&m->Z1, B * H) == hipSuccess &&
-            dalloc(&m->Z2, B * H) == hipSuccess && dalloc(&m->H1, B * H) == hipSuccess &&
-            dalloc(&m->H2, B * H) == hipSuccess && dalloc(&m->logits, B * K) == hipSuccess &&
-            dalloc(&m->dZ3, B * K) == hipSuccess && dalloc(&m->dZa, B * H) == hipSuccess &&
-            dalloc(&m->dZb, B * H) == hipSuccess && dalloc(&m->row_loss, B) == hipSuccess &&
+  const size_t P = m->n_params;
+  const size_t F = tlda::mlp_frag_halves(d_in, hidden, k_out);
+  const size_t Bp = tlda::mlp_bias_floats(hidden, k_out);
+  const size_t Tn = tlda::mlp_tile_halves(d_in, hidden, k_out, max_batch);
+  bool ok = dalloc(&m->params, P) == hipSuccess && dalloc(&m->wfrag, F) == hipSuccess &&
+            dalloc(&m->bpad, Bp) == hipSuccess && dalloc(&m->adam_m, P) == hipSuccess &&
+            dalloc(&m->adam_v, P) == hipSuccess && dalloc(&m->tiles, Tn) == hipSuccess &&
+            dalloc(&m->row_loss, (size_t)max_batch) == hipSuccess &&
             dalloc(&m->ws, tlda::mlp_workspace_floats(d_in, hidden, k_out, max_batch)) ==
                 hipSuccess;
   if (!ok) {
@@ -1160,9 +1159,11 @@ tlda_status tlda_mlp_create(int32_t d_in, int32_t hidden, int32_t k_out, int32_t
     return TLDA_ERR_OOM;
   }
   if (launch_zero(m->params, P * sizeof(float), m->stream) != hipSuccess ||
-      launch_zero(m->wb, P * sizeof(uint16_t), m->stream) != hipSuccess ||
+      launch_zero(m->wfrag, F * sizeof(uint16_t), m->stream) != hipSuccess ||
+      launch_zero(m->bpad, Bp * sizeof(float), m->stream) != hipSuccess ||
       launch_zero(m->adam_m, P * sizeof(float), m->stream) != hipSuccess ||
       launch_zero(m->adam_v, P * sizeof(float), m->stream) != hipSuccess ||
+      launch_zero(m->tiles, Tn * sizeof(uint16_t), m->stream) != hipSuccess ||
       hipStreamSynchronize(m->stream) != hipSuccess) {
     mlp_free(m);
     return TLDA_ERR_DEVICE;
@@ -1182,7 +1183,7 @@ tlda_status tlda_mlp_set_params(tlda_mlp* m, const float* host_params) {
     MLP_CHECK(m, std::isfinite(host_params[i]), TLDA_ERR_ARG, "a parameter is not finite");
   MLP_OK(m, hipMemcpyAsync(m->params, host_params, m->n_params * sizeof(float),
                            hipMemcpyHostToDevice, m->stream));
-  MLP_OK(m, tlda::mlp_refresh_bf16(*m));
+  MLP_OK(m, tlda::mlp_refresh(*m));
   MLP_OK(m, launch_zero(m->adam_m, m->n_params * sizeof(float), m->stream));
   MLP_OK(m, launch_zero(m->adam_v, m->n_params * sizeof(float), m->stream));
   MLP_OK(m, hipStreamSynchronize(m->stream));
@@ -1203,24 +1204,23 @@ tlda_status tlda_mlp_forward(tlda_mlp* m, const float* X, int64_t n_rows, float*
   if (!m) return TLDA_ERR_ARG;
   MLP_CHECK(m, n_rows >= 0, TLDA_ERR_SHAPE, "negative n_rows");
   MLP_CHECK(m, (X && theta_out) || n_rows == 0, TLDA_ERR_ARG, "X or theta is NULL");
-  for (int64_t r0 = 0; r0 < n_rows; r0 += m->max_batch) {
-    const int n = (int)std::min<int64_t>(m->max_batch, n_rows - r0);
-    MLP_OK(m, tlda::mlp_forward(*m, X + r0 * m->d_in, n, theta_out + r0 * m->k_out, false));
-  }
+  MLP_OK(m, tlda::mlp_forward(*m, X, n_rows, theta_out));
+  return TLDA_OK;
+}
+
+static tlda_status check_training(tlda_mlp* m, const float* X, const float* T, int32_t n_rows) {
+  MLP_CHECK(m, n_rows >= 1 && n_rows <= m->max_batch, TLDA_ERR_SHAPE,
+            "n_rows must be in 1 .. max_batch");
+  MLP_CHECK(m, X && T, TLDA_ERR_ARG, "X or T is NULL");
   return TLDA_OK;
 }
 
 tlda_status tlda_mlp_gradients(tlda_mlp* m, const float* X, const float* T, int32_t n_rows,
                                float* grads_out, float* loss_out) {
   if (!m) return TLDA_ERR_ARG;
-  MLP_CHECK(m, n_rows >= 1 && n_rows <= m->max_batch, TLDA_ERR_SHAPE,
-            "n_rows must be in 1 .. max_batch");
-  MLP_CHECK(m, X && T, TLDA_ERR_ARG, "X or T is NULL");
-  MLP_OK(m, tlda::mlp_forward(*m, X, n_rows, nullptr, true));
-  MLP_OK(m, tlda::mlp_backward(*m, X, T, n_rows, loss_out));
-  if (grads_out)
-    MLP_OK(m, hipMemcpyAsync(grads_out, m->grads, m->n_params * sizeof(float),
-                             hipMemcpyDeviceToDevice, m->stream));
+  tlda_status st = check_training(m, X, T, n_rows);
+  if (st != TLDA_OK) return st;
+  MLP_OK(m, tlda::mlp_gradients(*m, X, T, n_rows, grads_out, loss_out));
   return TLDA_OK;
 }
 
@@ -1228,9 +1228,9 @@ tlda_status tlda_mlp_train_step(tlda_mlp* m, const float* X, const float* T, int
                                 float lr, float* loss_out) {
   if (!m) return TLDA_ERR_ARG;
   MLP_CHECK(m, std::isfinite(lr) && lr > 0.f, TLDA_ERR_ARG, "lr must be finite and > 0");
-  tlda_status st = tlda_mlp_gradients(m, X, T, n_rows, nullptr, loss_out);
+  tlda_status st = check_training(m, X, T, n_rows);
   if (st != TLDA_OK) return st;
-  MLP_OK(m, tlda::mlp_adam(*m, lr, 0.9f, 0.999f, 1e-8f));
+  MLP_OK(m, tlda::mlp_train_step(*m, X, T, n_rows, lr, 0.9f, 0.999f, 1e-8f, loss_out));
   return TLDA_OK;
 }
 

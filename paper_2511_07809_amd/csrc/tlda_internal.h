@@ -173,21 +173,14 @@ struct tlda_mlp {
   size_t n_params = 0;
   hipStream_t stream = nullptr;
   float* params = nullptr;     // [n_params] FP32 master, packed W1 b1 W2 b2 W3 b3
-  uint16_t* wb = nullptr;      // BF16 copies of W1, W2, W3 (same offsets as in params)
-  float* grads = nullptr;      // [n_params]
+  uint16_t* wfrag = nullptr;   // BF16 copies of the weights in matrix-core fragment order
+  float* bpad = nullptr;       // the biases, padded to multiples of 32
   float* adam_m = nullptr;     // [n_params]
   float* adam_v = nullptr;     // [n_params]
   long long adam_t = 0;
-  float* Z1 = nullptr;         // [max_batch][hidden] FP32 pre-activations
-  float* Z2 = nullptr;
-  uint16_t* H1 = nullptr;      // [max_batch][hidden] BF16 activations
-  uint16_t* H2 = nullptr;
-  float* logits = nullptr;     // [max_batch][k_out]
-  uint16_t* dZ3 = nullptr;     // [max_batch][k_out] BF16
-  uint16_t* dZa = nullptr;     // [max_batch][hidden] BF16 (dZ2, then dZ1)
-  uint16_t* dZb = nullptr;
+  uint16_t* tiles = nullptr;   // X, H1, H2, dZ1, dZ2, dZ3 of a training batch, transposed
   float* row_loss = nullptr;   // [max_batch]
-  float* ws = nullptr;         // split partials of the weight and bias gradients
+  float* ws = nullptr;         // partials of the weight and bias gradients
   std::string last_error;
 };
 
@@ -406,18 +399,22 @@ hipError_t launch_classic_cp(const tlda_csr_batch& b, const float* W32, int Dp, 
                              hipStream_t s);
 // document-topic encoder (MLP)
 size_t mlp_param_count(int d_in, int hidden, int k_out);
-// floats of the encoder's gradient workspace (split partials)
+size_t mlp_frag_halves(int d_in, int hidden, int k_out);
+size_t mlp_bias_floats(int hidden, int k_out);
+// floats of the gradient partials, and halves of the transposed tiles, of a training batch
 size_t mlp_workspace_floats(int d_in, int hidden, int k_out, int max_batch);
-// offsets of W1, b1, W2, b2, W3, b3 in the packed parameter vector
-void mlp_offsets(int d_in, int hidden, int k_out, size_t off[6]);
-// forward pass of n <= max_batch rows: theta = softmax(...) (FP32 [n][k_out]);
-// with train, also keeps the intermediates for mlp_backward
-hipError_t mlp_forward(tlda_mlp& m, const float* X, int n, float* theta, bool train);
-// loss and gradients of the mean cross-entropy against targets T [n][k_out]
-// (needs a preceding mlp_forward(train) of the same rows); loss_out: device float or NULL
-hipError_t mlp_backward(tlda_mlp& m, const float* X, const float* T, int n, float* loss_out);
-hipError_t mlp_adam(tlda_mlp& m, float lr, float beta1, float beta2, float eps);
-hipError_t mlp_refresh_bf16(tlda_mlp& m);
+size_t mlp_tile_halves(int d_in, int hidden, int k_out, int max_batch);
+// forward pass of n rows: theta = softmax(...) (FP32 [n][k_out])
+hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta);
+// gradients and loss of the mean cross-entropy of n <= max_batch rows against
+// targets T [n][k_out]; grads, loss: device float or NULL
+hipError_t mlp_gradients(tlda_mlp& m, const float* X, const float* T, int n, float* grads,
+                         float* loss);
+// one Adam step on them
+hipError_t mlp_train_step(tlda_mlp& m, const float* X, const float* T, int n, float lr, float beta1,
+                          float beta2, float eps, float* loss);
+// the fragment and padded copies from the master parameters
+hipError_t mlp_refresh(tlda_mlp& m);
 // post-processing
 hipError_t launch_unwhiten(const float* Phi, const double* U, const double* eig, const double* m,
                            int V, int D, int K, double theta, uint32_t flags, double* mu,
