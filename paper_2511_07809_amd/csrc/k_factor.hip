@@ -58,6 +58,16 @@ __device__ __forceinline__ doublex4 tile_mfma(doublex4 a, doublex4 b, doublex4 a
   return acc;
 }
 
+// 1 / sqrt(d) for d > 0: the hardware estimate (about 2^-23 relative) and one
+// third-order step, to within an ulp or two, in a sixth of the dependent
+// instructions of a division by a square root; a chain of p of these is what
+// the factorisation waits for.
+__device__ __forceinline__ double inv_sqrt(double d) {
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-d * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
 // One wave: the Cholesky factor of the 16 x 16 tile `a` (row-major in LDS)
 // and the inverse of its transpose.  Lanes 0-15 (and 32-47) hold a column of
 // the tile, lanes 16-31 a column of the identity, and both take the same
@@ -75,10 +85,17 @@ __device__ inline bool factor_tile(const double* a, int lane, double* r_out, dou
     const double d = lane_value(v[j], j);
     const bool pos = d > 0.0;
     ok = ok && pos;
-    v[j] *= pos ? 1.0 / sqrt(d) : 1.0;
-    if (!pos && lane == j) v[j] = 1.0;
+    const double rs = inv_sqrt(d);
+    v[j] *= pos ? rs : 1.0;
+    v[j] = !pos && lane == j ? 1.0 : v[j];
+    // Every later row is updated here and now: left to itself the compiler
+    // puts row i's updates off to pivot i, where they are a chain, and holds
+    // all the multipliers in (spilled) scalar registers until then.
 #pragma unroll
-    for (int i = j + 1; i < kTile; ++i) v[i] = fma(-lane_value(v[j], i), v[j], v[i]);
+    for (int i = j + 1; i < kTile; ++i) {
+      v[i] = fma(-lane_value(v[j], i), v[j], v[i]);
+      asm volatile("" : "+v"(v[i]));
+    }
   }
   wave_sync();
   if (lane < 16) {
@@ -93,17 +110,18 @@ __device__ inline bool factor_tile(const double* a, int lane, double* r_out, dou
 
 // Entry (gi, gj) of the symmetric matrix padded to whole tiles by the
 // identity, read from the upper triangle.
-__device__ __forceinline__ double padded(const double* G, int p, int gi, int gj, double shift) {
+__device__ __forceinline__ double padded(const double* G, int p, int gi, int gj) {
   const int a = min(gi, gj), b = max(gi, gj);
-  if (b >= p) return a == b ? 1.0 : 0.0;
-  return G[(size_t)a * p + b] + (a == b ? shift : 0.0);
+  return b < p ? G[(size_t)a * p + b] : a == b ? 1.0 : 0.0;
 }
 
 // One wave: block column i of L^-1 = R^-T from the tiles of R and of the
 // diagonal inverses, written to Binv = R^-1 (row-major, p x p; the part below
-// the diagonal is left alone).  y: this column's own tiles (nb of them).
+// the diagonal is left alone).  y: this column's own tiles, in LDS.  The tiles
+// of R are loaded four at a time, ahead of the products that take them.
 __device__ inline void inverse_column(const double* tiles, const double* dinv, int nb, int i, int p,
                                       double* y, double* Binv, int lane) {
+  constexpr int kU = 4;
   const int row = lane >> 4, col = lane & 15;
   for (int j = i; j < nb; ++j) {
     doublex4 v;
@@ -111,23 +129,22 @@ __device__ inline void inverse_column(const double* tiles, const double* dinv, i
 #pragma unroll
       for (int r = 0; r < 4; ++r) v[r] = dinv[i * kTileE + col * kTile + 4 * r + row];
     } else {
-      // two accumulators: consecutive products do not wait for one another
-      doublex4 s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
-      int k = i;
-      for (; k + 1 < j; k += 2) {
-        s0 = tile_mfma(load_tile(tiles + (size_t)tile_at(k, j) * kTileE, lane),
-                       load_tile(y + k * kTileE, lane), s0);
-        s1 = tile_mfma(load_tile(tiles + (size_t)tile_at(k + 1, j) * kTileE, lane),
-                       load_tile(y + (k + 1) * kTileE, lane), s1);
+      const doublex4 d = load_tile(dinv + j * kTileE, lane);
+      doublex4 s[kU], a[kU];   // an accumulator each: consecutive products do not wait
+#pragma unroll
+      for (int u = 0; u < kU; ++u) s[u] = doublex4{0.0, 0.0, 0.0, 0.0};
+      for (int k = i; k < j; k += kU) {
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+          a[u] = load_tile(tiles + (size_t)tile_at(min(k + u, j - 1), j) * kTileE, lane);
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+          if (k + u < j) s[u] = tile_mfma(a[u], load_tile(y + (k + u) * kTileE, lane), s[u]);
       }
-      if (k < j)
-        s0 = tile_mfma(load_tile(tiles + (size_t)tile_at(k, j) * kTileE, lane),
-                       load_tile(y + k * kTileE, lane), s0);
-      s0 = -(s0 + s1);
-      v = tile_mfma(load_tile(dinv + j * kTileE, lane), s0, doublex4{0.0, 0.0, 0.0, 0.0});
+      v = tile_mfma(d, -((s[0] + s[1]) + (s[2] + s[3])), doublex4{0.0, 0.0, 0.0, 0.0});
     }
     store_tile(y + j * kTileE, lane, v);
-    __threadfence_block();   // the next rows of this column read it back
+    wave_sync();
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int gr = i * kTile + col, gc = j * kTile + 4 * r + row;
@@ -143,18 +160,106 @@ constexpr int panel_tiles(int n) {
   return nb;
 }
 
-// One block of NW waves; tile t = tile_at(i, j) belongs to wave t % NW.
-// SLOTS > 0: a wave's tiles stay in registers (NW SLOTS >= the tile count;
-// at most two waves per SIMD, so that a tile being factored fits beside
-// them); SLOTS == 0: they live in `tiles`, each touched by its own wave alone.
-// INV: the block goes on to the inverse (few tiles: a second launch would
-// cost more than the columns of the other compute units save).
+// The factor, tiles in registers: one block of NW waves, tile t = tile_at(i, j)
+// in slot t / NW of wave t % NW (NW SLOTS >= the tile count; at most two waves
+// per SIMD, so that a tile being factored fits beside them).  Nothing is
+// written to memory before the last step, since every barrier would wait for
+// it.  INV: the block goes on to the inverse, its tiles in LDS (few tiles: a
+// second launch would cost more than other compute units would save).
 template <int NW, int SLOTS, bool INV>
 __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, int p,
-                                               double shift_rel, double* tiles, double* dinv,
-                                               double* ytiles, double* Binv,
-                                               int* __restrict__ info) {
-  __shared__ double panel[(SLOTS == 0 ? kMaxNb : panel_tiles(NW * SLOTS)) * kTileE];
+                                                  double shift_rel, double* __restrict__ tiles,
+                                                  double* __restrict__ dinv,
+                                                  double* __restrict__ Binv,
+                                                  int* __restrict__ info) {
+  constexpr int NB = panel_tiles(NW * SLOTS);
+  // row k of R while it is applied (INV: every tile of R, kept)
+  __shared__ double panel[(INV ? NB * (NB + 1) / 2 : NB) * kTileE];
+  __shared__ double dcols[NB * kTileE], diag[kTileE];
+  __shared__ double ybuf[INV ? NB * NB * kTileE : 1];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (p + kTile - 1) / kTile, nt = nb * (nb + 1) / 2;
+  const int row = lane >> 4, col = lane & 15;
+  doublex4 acc[SLOTS];
+  int ti[SLOTS], tj[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) {
+    const int t = wave + NW * s;
+    ti[s] = tj[s] = -1;
+    if (t < nt) {
+      int j = 0;
+      while ((j + 1) * (j + 2) / 2 <= t) ++j;
+      tj[s] = j;
+      ti[s] = t - j * (j + 1) / 2;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        acc[s][r] = padded(G, p, ti[s] * kTile + 4 * r + row, j * kTile + col);
+    }
+  }
+  double mx = 0.0;
+  for (int i = lane; i < p; i += 64) mx = fmax(mx, G[(size_t)i * p + i]);
+  for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+  const double shift = shift_rel * mx;
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s)
+    if (ti[s] >= 0 && ti[s] == tj[s]) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * r + row == col && ti[s] * kTile + col < p) acc[s][r] += shift;
+    }
+  bool ok = true;
+  const doublex4 zero = {0.0, 0.0, 0.0, 0.0};
+  for (int k = 0; k < nb; ++k) {
+    if (tile_at(k, k) % NW == wave) {   // its owner factors the diagonal tile
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s)
+        if (ti[s] == k && tj[s] == k) store_tile(diag, lane, acc[s]);
+      wave_sync();
+      ok = factor_tile(diag, lane, diag, dcols + k * kTileE) && ok;
+      wave_sync();
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s)
+        if (ti[s] == k && tj[s] == k) acc[s] = load_tile(diag, lane);
+    }
+    __syncthreads();
+    // row k of R: R_kj = R_kk^-T A_kj
+    const doublex4 da = load_tile(dcols + k * kTileE, lane);
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (ti[s] == k && tj[s] > k) {
+        acc[s] = tile_mfma(da, acc[s], zero);
+        store_tile(panel + (INV ? wave + NW * s : tj[s]) * kTileE, lane, acc[s]);
+      }
+    __syncthreads();
+    // trailing tiles: A_ij -= R_ki^T R_kj
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (ti[s] > k)
+        acc[s] = tile_mfma(-load_tile(panel + (INV ? tile_at(k, ti[s]) : ti[s]) * kTileE, lane),
+                           load_tile(panel + (INV ? tile_at(k, tj[s]) : tj[s]) * kTileE, lane),
+                           acc[s]);
+  }
+  if (!ok && lane == 0) atomicOr(info, 1);
+  if (INV) {
+    for (int i = wave; i < nb; i += NW)
+      inverse_column(panel, dcols, nb, i, p, ybuf + i * NB * kTileE, Binv, lane);
+  } else {
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (ti[s] >= 0) store_tile(tiles + (size_t)(wave + NW * s) * kTileE, lane, acc[s]);
+    for (int k = wave; k < nb; k += NW)
+      store_tile(dinv + k * kTileE, lane, load_tile(dcols + k * kTileE, lane));
+  }
+}
+
+// The same for more tiles than fit in registers: they live in `tiles`, each
+// touched by wave t % 16 alone.
+__global__ void __launch_bounds__(1024) k_chol_mem(const double* __restrict__ G, int p,
+                                                   double shift_rel, double* tiles, double* dinv,
+                                                   int* __restrict__ info) {
+  constexpr int NW = 16;
+  __shared__ double panel[kMaxNb * kTileE];
   __shared__ double diag[kTileE], dcols[kTileE];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -164,47 +269,24 @@ __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, 
   for (int i = lane; i < p; i += 64) mx = fmax(mx, G[(size_t)i * p + i]);
   for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
   const double shift = shift_rel * mx;
-
-  constexpr int R = SLOTS > 0 ? SLOTS : 1;
-  doublex4 acc[R];
-  int ti[R], tj[R];
-  auto first_load = [&](int t, int& i, int& j, doublex4& v) {
-    j = 0;
+  for (int t = wave; t < nt; t += NW) {
+    int j = 0;
     while ((j + 1) * (j + 2) / 2 <= t) ++j;
-    i = t - j * (j + 1) / 2;
+    const int i = t - j * (j + 1) / 2;
+    doublex4 v;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      v[r] = padded(G, p, i * kTile + 4 * r + row, j * kTile + col, shift);
-  };
-  if (SLOTS > 0) {
-#pragma unroll
-    for (int s = 0; s < R; ++s) {
-      const int t = wave + NW * s;
-      if (t < nt) first_load(t, ti[s], tj[s], acc[s]);
-      else ti[s] = tj[s] = -1;
+    for (int r = 0; r < 4; ++r) {
+      const int gi = i * kTile + 4 * r + row, gj = j * kTile + col;
+      v[r] = padded(G, p, gi, gj) + (gi == gj && gi < p ? shift : 0.0);
     }
-  } else {
-    for (int t = wave; t < nt; t += NW) {
-      int i, j;
-      doublex4 v;
-      first_load(t, i, j, v);
-      store_tile(tiles + (size_t)t * kTileE, lane, v);
-    }
-    __threadfence_block();
+    store_tile(tiles + (size_t)t * kTileE, lane, v);
   }
-
+  __threadfence_block();
+  const doublex4 zero = {0.0, 0.0, 0.0, 0.0};
   for (int k = 0; k < nb; ++k) {
     const int tk = tile_at(k, k);
-    if (tk % NW == wave) {   // its owner factors the diagonal tile
-      doublex4 d = {0.0, 0.0, 0.0, 0.0};
-      if (SLOTS > 0) {
-#pragma unroll
-        for (int s = 0; s < R; ++s)
-          if (wave + NW * s == tk) d = acc[s];
-      } else {
-        d = load_tile(tiles + (size_t)tk * kTileE, lane);
-      }
-      store_tile(diag, lane, d);
+    if (tk % NW == wave) {
+      store_tile(diag, lane, load_tile(tiles + (size_t)tk * kTileE, lane));
       wave_sync();
       const bool ok = factor_tile(diag, lane, tiles + (size_t)tk * kTileE, dcols);
       if (!ok && lane == 0) atomicOr(info, 1);
@@ -212,60 +294,33 @@ __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, 
       store_tile(dinv + k * kTileE, lane, load_tile(dcols, lane));
     }
     __syncthreads();
-    // row k of R: R_kj = R_kk^-T A_kj
     const doublex4 da = load_tile(dcols, lane);
-    const doublex4 zero = {0.0, 0.0, 0.0, 0.0};
-    if (SLOTS > 0) {
-#pragma unroll
-      for (int s = 0; s < R; ++s)
-        if (ti[s] == k && tj[s] > k) {
-          const doublex4 v = tile_mfma(da, acc[s], zero);
-          store_tile(panel + tj[s] * kTileE, lane, v);
-          store_tile(tiles + (size_t)(wave + NW * s) * kTileE, lane, v);
-        }
-    } else {
-      for (int j = k + 1; j < nb; ++j) {
-        const int t = tile_at(k, j);
+    for (int j = k + 1; j < nb; ++j) {
+      const int t = tile_at(k, j);
+      if (t % NW != wave) continue;
+      const doublex4 v = tile_mfma(da, load_tile(tiles + (size_t)t * kTileE, lane), zero);
+      store_tile(panel + j * kTileE, lane, v);
+      store_tile(tiles + (size_t)t * kTileE, lane, v);
+    }
+    __syncthreads();
+    for (int j = k + 1; j < nb; ++j)
+      for (int i = k + 1; i <= j; ++i) {
+        const int t = tile_at(i, j);
         if (t % NW != wave) continue;
-        const doublex4 v = tile_mfma(da, load_tile(tiles + (size_t)t * kTileE, lane), zero);
-        store_tile(panel + j * kTileE, lane, v);
-        store_tile(tiles + (size_t)t * kTileE, lane, v);
+        double* tp = tiles + (size_t)t * kTileE;
+        store_tile(tp, lane, tile_mfma(-load_tile(panel + i * kTileE, lane),
+                                       load_tile(panel + j * kTileE, lane), load_tile(tp, lane)));
       }
-    }
-    __syncthreads();
-    // trailing tiles: A_ij -= R_ki^T R_kj
-    if (SLOTS > 0) {
-#pragma unroll
-      for (int s = 0; s < R; ++s)
-        if (ti[s] > k)
-          acc[s] = tile_mfma(-load_tile(panel + ti[s] * kTileE, lane),
-                             load_tile(panel + tj[s] * kTileE, lane), acc[s]);
-    } else {
-      for (int j = k + 1; j < nb; ++j)
-        for (int i = k + 1; i <= j; ++i) {
-          const int t = tile_at(i, j);
-          if (t % NW != wave) continue;
-          double* tp = tiles + (size_t)t * kTileE;
-          store_tile(tp, lane, tile_mfma(-load_tile(panel + i * kTileE, lane),
-                                         load_tile(panel + j * kTileE, lane),
-                                         load_tile(tp, lane)));
-        }
-    }
-  }
-  if (INV) {
-    __threadfence_block();
-    __syncthreads();
-    for (int i = wave; i < nb; i += NW)
-      inverse_column(tiles, dinv, nb, i, p, ytiles + (size_t)i * nb * kTileE, Binv, lane);
   }
 }
 
 // One wave per block column of the inverse.
 __global__ void __launch_bounds__(64) k_tri_inverse(const double* __restrict__ tiles,
                                                     const double* __restrict__ dinv, int p,
-                                                    double* ytiles, double* __restrict__ Binv) {
-  const int nb = (p + kTile - 1) / kTile, i = blockIdx.x;
-  inverse_column(tiles, dinv, nb, i, p, ytiles + (size_t)i * nb * kTileE, Binv, threadIdx.x);
+                                                    double* __restrict__ Binv) {
+  __shared__ double y[kMaxNb * kTileE];
+  const int nb = (p + kTile - 1) / kTile;
+  inverse_column(tiles, dinv, nb, blockIdx.x, p, y, Binv, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -415,7 +470,7 @@ __global__ void __launch_bounds__(256) k_gram_sum(const double* __restrict__ par
 
 size_t chol_scratch_doubles(int p) {
   const size_t nb = (p + kTile - 1) / kTile;
-  return (nb * (nb + 1) / 2 + nb + nb * nb) * kTileE;
+  return (nb * (nb + 1) / 2 + nb) * kTileE;
 }
 
 // Binv (p x p; its part below the diagonal must hold zeros, which stay)
@@ -427,21 +482,21 @@ hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double*
   if (p < 1 || nb > kMaxNb) return hipErrorInvalidValue;
   double* tiles = scratch;
   double* dinv = tiles + (size_t)nb * (nb + 1) / 2 * kTileE;
-  double* ytiles = dinv + (size_t)nb * kTileE;
 #define TLDA_CHOL(nw, slots, inv)                                                             \
   hipLaunchKernelGGL((k_chol<nw, slots, inv>), dim3(1), dim3(64 * nw), 0, s, G, p, shift_rel, \
-                     tiles, dinv, ytiles, Binv, info)
+                     tiles, dinv, Binv, info)
   if (nb <= 5) {
     TLDA_CHOL(4, 4, true);
     return hipGetLastError();
   }
   if (nb <= 9) TLDA_CHOL(8, 6, false);
   else if (nb <= 13) TLDA_CHOL(8, 12, false);
-  else TLDA_CHOL(16, 0, false);
+  else
+    hipLaunchKernelGGL(k_chol_mem, dim3(1), dim3(1024), 0, s, G, p, shift_rel, tiles, dinv, info);
 #undef TLDA_CHOL
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_tri_inverse, dim3(nb), dim3(64), 0, s, tiles, dinv, p, ytiles, Binv);
+  hipLaunchKernelGGL(k_tri_inverse, dim3(nb), dim3(64), 0, s, tiles, dinv, p, Binv);
   return hipGetLastError();
 }
 
