@@ -324,73 +324,72 @@ __global__ void __launch_bounds__(64) k_tri_inverse(const double* __restrict__ t
 }
 
 // ---------------------------------------------------------------------------
-// G = A^T B for tall row-major blocks A, B (V x p).  Lane l of a step over
-// four rows v needs A[v + l / 16][16 i + l % 16] and B[v + l / 16][16 j +
-// l % 16]: 128-byte row segments straight from memory, no staging.  A block
-// takes one unit of at most kGramN tiles of one tile row (one A operand feeds
-// them all) and one chunk of the rows, its four waves every fourth group of
-// four rows; the waves' tiles are added in LDS, the chunks' in chunk order by
-// k_gram_sum, so the sum's order is fixed.  SYM (B = A, or A^T B symmetric by
-// construction): only tiles i <= j are formed, and mirrored.
+// G (pa x pb) = A^T (B - m 1^T) for tall row-major blocks A (V x pa), B (V x
+// pb); m [V] or NULL.  Lane l of a step over four rows v needs A[v + l / 16]
+// [16 i + l % 16] and B[v + l / 16][16 j + l % 16]: 128-byte row segments
+// straight from memory, no staging.  A block takes one unit of at most kGramN
+// tiles of one tile row (one A operand feeds them all) and one chunk of the
+// rows, its four waves every fourth group of four rows; the waves' tiles are
+// added in LDS, the chunks' in chunk order by k_gram_sum, so the sum's order
+// is fixed.  sym (B = A, or A^T B symmetric by construction): only tiles i <=
+// j are formed, and mirrored.
 // Bound: the matrix cores, 2 V p (p + 16) / 2 flops when symmetric; a wider
 // unit would spill, a narrower one reads more operand bytes per product.
 // ---------------------------------------------------------------------------
 constexpr int kGramN = 7, kGramWaves = 4;
 
-// Unit u of nb tile columns: tile row i, first column j0, n tiles.
-__host__ __device__ inline int gram_units(int nb, bool sym) {
-  int u = 0;
-  for (int i = 0; i < nb; ++i) u += ((sym ? nb - i : nb) + kGramN - 1) / kGramN;
-  return u;
-}
-__device__ inline void gram_unit(int u, int nb, bool sym, int& i, int& j0, int& n) {
-  for (i = 0;; ++i) {
-    const int len = sym ? nb - i : nb, parts = (len + kGramN - 1) / kGramN;
-    if (u < parts) {
-      const int a = u * len / parts, b = (u + 1) * len / parts;
-      j0 = (sym ? i : 0) + a;
-      n = b - a;
-      return;
-    }
-    u -= parts;
+struct GramShape {
+  int pa, pb;
+  bool sym;
+  __host__ __device__ int na() const { return (pa + kTile - 1) / kTile; }
+  __host__ __device__ int nb() const { return (pb + kTile - 1) / kTile; }
+  // tiles of tile row i, and the units they are dealt out in
+  __host__ __device__ int len(int i) const { return sym ? nb() - i : nb(); }
+  __host__ __device__ int parts(int i) const { return (len(i) + kGramN - 1) / kGramN; }
+  __host__ __device__ int units() const {
+    int u = 0;
+    for (int i = 0; i < na(); ++i) u += parts(i);
+    return u;
   }
-}
-// tiles of the (upper) result, numbered by unit order within a tile row
-__host__ __device__ inline int gram_tile(int i, int j, int nb, bool sym) {
-  return sym ? i * nb - i * (i - 1) / 2 + (j - i) : i * nb + j;
-}
-inline int gram_tiles(int nb, bool sym) { return sym ? nb * (nb + 1) / 2 : nb * nb; }
+  __host__ __device__ int tiles() const { return sym ? nb() * (nb() + 1) / 2 : na() * nb(); }
+  // number of the first tile of tile row i
+  __host__ __device__ int tile0(int i) const { return sym ? i * nb() - i * (i - 1) / 2 : i * nb(); }
+};
 
 __global__ void __launch_bounds__(64 * kGramWaves) k_gram(const double* __restrict__ A,
-                                                          const double* __restrict__ B, int V,
-                                                          int p, int chunk, bool sym,
+                                                          const double* __restrict__ B,
+                                                          const double* __restrict__ m, int V,
+                                                          GramShape g, int chunk,
                                                           double* __restrict__ part) {
   __shared__ double red[kGramWaves - 1][kGramN * kTileE];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nb = (p + kTile - 1) / kTile;
-  int i, j0, n;
-  gram_unit(blockIdx.x, nb, sym, i, j0, n);
+  int i = 0, u = blockIdx.x;   // unit u of the tile rows: j0 .. j0 + n - 1 of row i
+  while (u >= g.parts(i)) u -= g.parts(i++);
+  const int first = u * g.len(i) / g.parts(i);
+  const int n = (u + 1) * g.len(i) / g.parts(i) - first;
+  const int j0 = (g.sym ? i : 0) + first;
   const int v0 = blockIdx.y * chunk, v1 = min(V, v0 + chunk);
   const int row = lane >> 4, col = lane & 15;
-  const int ca = min(i * kTile + col, p - 1);
+  const int ca = min(i * kTile + col, g.pa - 1);
   doublex4 acc[kGramN];
 #pragma unroll
   for (int q = 0; q < kGramN; ++q) acc[q] = doublex4{0.0, 0.0, 0.0, 0.0};
   // Operands of the next four rows are loaded while the current ones are
-  // multiplied, all from clamped addresses: columns past p only reach entries
-  // that are not stored, and rows past the chunk are taken out by a zero A
-  // operand when it is used (a select at the load would wait for it).
-  double a, b[kGramN];
+  // multiplied, all from clamped addresses: columns past the last only reach
+  // entries that are not stored, and rows past the chunk are taken out by a
+  // zero A operand when it is used (a select at the load would wait for it).
+  double a, b[kGramN], mr = 0.0;
   bool in;
   auto load = [&](int v) {
     const int r = v + row;
     in = r < v1;
-    const size_t o = (size_t)min(r, V - 1) * p;
-    a = A[o + ca];
+    const size_t rc = (size_t)min(r, V - 1);
+    a = A[rc * g.pa + ca];
+    if (m != nullptr) mr = m[rc];
 #pragma unroll
     for (int q = 0; q < kGramN; ++q)
-      b[q] = B[o + min((j0 + min(q, n - 1)) * kTile + col, p - 1)];
+      b[q] = B[rc * g.pb + min((j0 + min(q, n - 1)) * kTile + col, g.pb - 1)];
   };
   int v = v0 + 4 * wave;
   if (v < v1) load(v);
@@ -398,7 +397,7 @@ __global__ void __launch_bounds__(64 * kGramWaves) k_gram(const double* __restri
     const double ac = in ? a : 0.0;
     double bc[kGramN];
 #pragma unroll
-    for (int q = 0; q < kGramN; ++q) bc[q] = b[q];
+    for (int q = 0; q < kGramN; ++q) bc[q] = b[q] - mr;
     if (v + 4 * kGramWaves < v1) load(v + 4 * kGramWaves);
 #pragma unroll
     for (int q = 0; q < kGramN; ++q)
@@ -411,31 +410,31 @@ __global__ void __launch_bounds__(64 * kGramWaves) k_gram(const double* __restri
   }
   __syncthreads();
   if (wave == 0) {
-    double* out = part + (size_t)blockIdx.y * (sym ? nb * (nb + 1) / 2 : nb * nb) * kTileE;
+    double* out = part + ((size_t)blockIdx.y * g.tiles() + g.tile0(i) + first) * kTileE;
 #pragma unroll
     for (int q = 0; q < kGramN; ++q)
       if (q < n) {
         doublex4 s = acc[q];
 #pragma unroll
         for (int w = 0; w < kGramWaves - 1; ++w) s += load_tile(red[w] + q * kTileE, lane);
-        store_tile(out + (size_t)gram_tile(i, j0 + q, nb, sym) * kTileE, lane, s);
+        store_tile(out + q * kTileE, lane, s);
       }
   }
 }
 
-// G (p x p) from nz chunks of tiles: four lanes per entry, lane c adding the
+// G (pa x pb) from nz chunks of tiles: four lanes per entry, lane c adding the
 // c-th quarter of the chunks in chunk order, the quarters combined as
 // (q0 + q1) + (q2 + q3).  A lane issues the loads of 8 chunks before adding
 // them; the last batch loads from chunk indexes clamped into its quarter and
-// adds only the chunks that exist.
-__global__ void __launch_bounds__(256) k_gram_sum(const double* __restrict__ part, int nz, int nt,
-                                                  int p, bool sym, double* __restrict__ G) {
+// adds only the chunks that exist.  G32: an FP32 copy, or NULL.
+__global__ void __launch_bounds__(256) k_gram_sum(const double* __restrict__ part, int nz,
+                                                  GramShape g, double* __restrict__ G,
+                                                  float* __restrict__ G32) {
   constexpr int kU = 8;
-  const int nb = (p + kTile - 1) / kTile;
   const int e = blockIdx.x * 64 + (threadIdx.x >> 2);   // 64 entries per block: within one tile
   const int c = threadIdx.x & 3;
   const int t = e / kTileE;
-  const size_t stride = (size_t)nt * kTileE;
+  const size_t stride = (size_t)g.tiles() * kTileE;
   const int per = (nz + 3) / 4;
   const int z0 = min(c * per, nz), z1 = min(z0 + per, nz);
   double s = 0.0;
@@ -449,21 +448,122 @@ __global__ void __launch_bounds__(256) k_gram_sum(const double* __restrict__ par
   }
   s += __shfl_xor(s, 1, 64);
   s += __shfl_xor(s, 2, 64);
-  int i = 0, j;
-  if (sym) {
-    int k = t;
-    while (k >= nb - i) k -= nb - i++;
-    j = i + k;
-  } else {
-    i = t / nb;
-    j = t % nb;
-  }
+  int i = 0;
+  while (t >= g.tile0(i + 1)) ++i;
+  const int j = (g.sym ? i : 0) + t - g.tile0(i);
   const int w = e % kTileE;
   const int gi = i * kTile + w / kTile, gj = j * kTile + w % kTile;
-  if (c == 0 && gi < p && gj < p) {
-    G[(size_t)gi * p + gj] = s;
-    if (sym && i != j) G[(size_t)gj * p + gi] = s;
+  if (c == 0 && gi < g.pa && gj < g.pb) {
+    G[(size_t)gi * g.pb + gj] = s;
+    if (G32 != nullptr) G32[(size_t)gi * g.pb + gj] = (float)s;
+    if (g.sym && i != j) G[(size_t)gj * g.pb + gi] = s;
   }
+}
+
+// ---------------------------------------------------------------------------
+// The largest eigenvalue of a symmetric positive semidefinite n x n matrix,
+// n <= 128, by repeated squaring: B <- B^2 / tr(B^2) from G / tr(G) tends to
+// the projector on the top eigenspace, and tr(G B) / tr(B) is the mean of the
+// eigenvalues weighted by their 2^k-th powers.  After k squarings it is short
+// of the largest by less than n / (2 e 2^k) relative whatever the gaps are
+// (x e^(-2^(k+1) x), summed), so 40 bound it by 5e-11, far below the FP32 step
+// size it is for; usually B is a projector (tr(B^2) = 1 to rounding) after 8
+// to 15, and that ends it.  One block; the tiles stay in LDS, and as B is
+// symmetric its tiles serve as both operands as they are stored.
+// Writes step = 1 / lambda (0 when there is no positive eigenvalue).
+// ---------------------------------------------------------------------------
+constexpr int kTopNb = 8, kTopWaves = 8;
+
+template <int SLOTS>
+__global__ void __launch_bounds__(64 * kTopWaves) k_top_eig(const double* __restrict__ G, int n,
+                                                            float* __restrict__ step) {
+  constexpr int NBM = SLOTS <= 2 ? 4 : kTopNb;
+  __shared__ double B[NBM * NBM * kTileE];
+  __shared__ double red[kTopWaves];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = lane >> 4, col = lane & 15;
+  const int nb = (n + kTile - 1) / kTile, nt = nb * (nb + 1) / 2;
+  doublex4 g[SLOTS], v[SLOTS];
+  int ti[SLOTS], tj[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) {
+    const int t = wave + kTopWaves * s;
+    ti[s] = tj[s] = -1;
+    g[s] = doublex4{0.0, 0.0, 0.0, 0.0};
+    if (t < nt) {
+      int j = 0;
+      while ((j + 1) * (j + 2) / 2 <= t) ++j;
+      tj[s] = j;
+      ti[s] = t - j * (j + 1) / 2;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int gi = ti[s] * kTile + 4 * r + row, gj = j * kTile + col;
+        if (gi < n && gj < n) g[s][r] = G[(size_t)gi * n + gj];
+      }
+    }
+    v[s] = g[s];
+  }
+  // sum over the block of f(slot), in wave order
+  auto total = [&](auto f) {
+    double x = 0.0;
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (ti[s] >= 0) x += f(s);
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    __syncthreads();
+    if (lane == 0) red[wave] = x;
+    __syncthreads();
+    double all = 0.0;
+#pragma unroll
+    for (int w = 0; w < kTopWaves; ++w) all += red[w];
+    return all;
+  };
+  auto trace_part = [&](int s) {
+    double x = 0.0;
+    if (ti[s] == tj[s]) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * r + row == col) x += v[s][r];
+    }
+    return x;
+  };
+  double tr = total(trace_part);
+  double mx = 0.0;
+  if (tr > 0.0) {
+    for (int k = 0; k < 40; ++k) {
+      const double sc = 1.0 / tr;
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s)
+        if (ti[s] >= 0) {
+          v[s] *= sc;
+          store_tile(B + (ti[s] * nb + tj[s]) * kTileE, lane, v[s]);
+          if (ti[s] != tj[s]) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              B[(tj[s] * nb + ti[s]) * kTileE + col * kTile + 4 * r + row] = v[s][r];
+          }
+        }
+      __syncthreads();
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s)
+        if (ti[s] >= 0) {
+          v[s] = doublex4{0.0, 0.0, 0.0, 0.0};
+          for (int m = 0; m < nb; ++m)
+            v[s] = tile_mfma(load_tile(B + (m * nb + ti[s]) * kTileE, lane),
+                             load_tile(B + (m * nb + tj[s]) * kTileE, lane), v[s]);
+        }
+      tr = total(trace_part);
+      if (!(tr < 1.0 - 1e-14)) break;
+    }
+    mx = total([&](int s) {
+      double x = 0.0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x += g[s][r] * v[s][r];
+      return ti[s] == tj[s] ? x : 2.0 * x;
+    }) / tr;
+  }
+  if (threadIdx.x == 0) *step = mx > 0.0 ? (float)(1.0 / mx) : 0.0f;
 }
 
 }  // namespace
@@ -500,30 +600,54 @@ hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double*
   return hipGetLastError();
 }
 
-// Row chunks of the Gram product: enough blocks for four waves per SIMD of the
-// 256 compute units (1024), chunks of at least 64 rows.
-static int gram_chunks(int V, int nb, bool sym) {
-  const int want = 1024 / gram_units(nb, sym), most = (V + 63) / 64;
+// Row chunks of the Gram product: enough blocks for `blocks` in all, chunks of
+// at least 64 rows.
+static int gram_chunks(int V, const GramShape& g, int blocks) {
+  const int want = blocks / g.units(), most = (V + 63) / 64;
   return want < 1 ? 1 : want < most ? want : most;
 }
+// 1024 blocks are four waves per SIMD of the 256 compute units; half of them
+// for the one product of an inference, whose scratch every context keeps.
+constexpr int kGramBlocks = 1024, kProjectBlocks = 512;
 
-size_t gram_scratch_doubles(int V, int p, bool sym) {
-  const int nb = (p + kTile - 1) / kTile;
-  return (size_t)gram_chunks(V, nb, sym) * gram_tiles(nb, sym) * kTileE;
-}
-
-hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
-                       double* part, hipStream_t s) {
-  const int nb = (p + kTile - 1) / kTile, nt = gram_tiles(nb, sym);
-  int nz = gram_chunks(V, nb, sym);
+static hipError_t launch_gram_shape(const double* A, const double* B, const double* m, int V,
+                                    const GramShape& g, int blocks, double* part, double* G,
+                                    float* G32, hipStream_t s) {
+  int nz = gram_chunks(V, g, blocks);
   const int step = 4 * kGramWaves;
   const int chunk = ((V + nz - 1) / nz + step - 1) / step * step;
   nz = (V + chunk - 1) / chunk;
-  hipLaunchKernelGGL(k_gram, dim3(gram_units(nb, sym), nz), dim3(64 * kGramWaves), 0, s, A, B, V, p,
-                     chunk, sym, part);
+  hipLaunchKernelGGL(k_gram, dim3(g.units(), nz), dim3(64 * kGramWaves), 0, s, A, B, m, V, g, chunk,
+                     part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_gram_sum, dim3(nt * (kTileE / 64)), dim3(256), 0, s, part, nz, nt, p, sym, G);
+  hipLaunchKernelGGL(k_gram_sum, dim3(g.tiles() * (kTileE / 64)), dim3(256), 0, s, part, nz, g, G,
+                     G32);
+  return hipGetLastError();
+}
+
+size_t gram_scratch_doubles(int V, int p, bool sym) {
+  const GramShape g{p, p, sym};
+  return (size_t)gram_chunks(V, g, kGramBlocks) * g.tiles() * kTileE;
+}
+hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
+                       double* part, hipStream_t s) {
+  return launch_gram_shape(A, B, nullptr, V, GramShape{p, p, sym}, kGramBlocks, part, G, nullptr, s);
+}
+
+size_t project_scratch_doubles(int V, int D, int K) {
+  const GramShape g{D, K, false};
+  return (size_t)gram_chunks(V, g, kProjectBlocks) * g.tiles() * kTileE;
+}
+hipError_t launch_project(const double* W, const double* m, const double* mu, int V, int D, int K,
+                          double* part, double* A, float* A32, hipStream_t s) {
+  return launch_gram_shape(W, mu, m, V, GramShape{D, K, false}, kProjectBlocks, part, A, A32, s);
+}
+
+hipError_t launch_top_eig(const double* G, int n, float* step, hipStream_t s) {
+  if (n < 1 || n > kTile * kTopNb) return hipErrorInvalidValue;
+  if (n <= 64) hipLaunchKernelGGL(k_top_eig<2>, dim3(1), dim3(64 * kTopWaves), 0, s, G, n, step);
+  else hipLaunchKernelGGL(k_top_eig<5>, dim3(1), dim3(64 * kTopWaves), 0, s, G, n, step);
   return hipGetLastError();
 }
 

@@ -14,7 +14,10 @@ namespace tlda {
 namespace {
 
 // Per topic: scale[k] = (1+theta)^(1/3) a_k^(-1/3), alpha[k] = a_k / sum a,
-// lambda[k] = (1+theta) |phi_k|^3.  One block; K <= 256.
+// lambda[k] = (1+theta) |phi_k|^3.  One block; K <= 256.  With u = a^(1/3) the
+// weight's equation is f(u) = u^3 + r u - 1 = 0, f convex and increasing, so
+// Newton's method comes down to the root from any start above it (min(1, 1 /
+// r) is) and squares its error: 200 bisections with a cube root each took 25 us.
 __global__ void __launch_bounds__(256) k_frame_weights(const float* __restrict__ Phi, int D, int K,
                                                        double theta, double* __restrict__ scale,
                                                        double* __restrict__ alpha,
@@ -30,14 +33,15 @@ __global__ void __launch_bounds__(256) k_frame_weights(const float* __restrict__
     }
     const double c = cbrt(1.0 + theta);
     const double r = c * c * n2;   // |w_k|^2
-    double lo = 0.0, hi = 1.0;
-    for (int it = 0; it < 200; ++it) {
-      const double mid = 0.5 * (lo + hi);
-      if (cbrt(mid) * r + mid < 1.0) lo = mid;
-      else hi = mid;
+    // (a norm past the range, or NaN, is an infinite one: the weight vanishes)
+    double u = !(r < INFINITY) ? 0x1p-67 : r > 1.0 ? 1.0 / r : 1.0;
+    for (int it = 0; it < 60 && r < INFINITY; ++it) {
+      const double d = (u * (u * u + r) - 1.0) / (3.0 * u * u + r);
+      u -= d;
+      if (!(fabs(d) > 1e-16 * u)) break;
     }
-    a = 0.5 * (lo + hi);
-    scale[k] = c / cbrt(a);
+    a = u * u * u;
+    scale[k] = c / u;
     if (lambda != nullptr) lambda[k] = (1.0 + theta) * n2 * sqrt(n2);
   }
   a_sh[k] = a;
@@ -97,75 +101,111 @@ __global__ void __launch_bounds__(256) k_rebase(const double* __restrict__ C,
   }
 }
 
-// mu[i][k] = sum_d U[i][d] sqrt(eig[d]) phi[d][k] scale[k] + m[i] (m may be NULL)
-__global__ void k_mu(const float* __restrict__ Phi, const double* __restrict__ U,
-                     const double* __restrict__ eig, const double* __restrict__ m,
-                     const double* __restrict__ scale, int V, int D, int K,
-                     double* __restrict__ mu) {
-  const size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (size_t)V * K) return;
-  const int i = (int)(e / K), k = (int)(e % K);
-  double s = 0.0;
-  for (int d = 0; d < D; ++d) s += U[(size_t)i * D + d] * sqrt(eig[d]) * (double)Phi[d * K + k];
-  mu[e] = s * scale[k] + (m != nullptr ? m[i] : 0.0);
-}
-
-// Clip negative entries and renormalise every column to sum one (a column
-// with no positive entry is left at zero).  One block per column.
-__global__ void __launch_bounds__(256) k_simplex_columns(double* __restrict__ mu, int V, int K) {
-  __shared__ double red[256];
-  const int k = blockIdx.x, tid = threadIdx.x;
-  double s = 0.0;
-  for (int i = tid; i < V; i += blockDim.x) s += fmax(mu[(size_t)i * K + k], 0.0);
-  red[tid] = s;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
+// mu[i][k] = sum_d U[i][d] sqrt(eig[d]) phi[d][k] scale[k] + m[i] (m may be
+// NULL).  A block takes a run of rows and 64 columns, one lane per column:
+// sqrt(eig) phi scale is formed once per block in LDS, a row of U is read by
+// all lanes at once, and the row of mu is one 512-byte write.  sums (or NULL):
+// [block row][K] sums of the clipped entries, added in row order by
+// k_simplex_scale.  Bound: 2 V D K flops and the writes of mu.
+constexpr int kMuRows = 64;   // rows per block, 16 per wave
+__global__ void __launch_bounds__(256) k_mu(const float* __restrict__ Phi,
+                                            const double* __restrict__ U,
+                                            const double* __restrict__ eig,
+                                            const double* __restrict__ m,
+                                            const double* __restrict__ scale, int V, int D, int K,
+                                            double* __restrict__ mu, double* __restrict__ sums) {
+  constexpr int kD = 64;   // rows of Phi at a time
+  __shared__ double P[kD * 64];
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k = blockIdx.y * 64 + lane;
+  const int r0 = blockIdx.x * kMuRows + wave * 16;
+  const double sk = k < K ? scale[k] : 0.0;
+  double s[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s[i] = 0.0;
+  for (int d0 = 0; d0 < D; d0 += kD) {
+    const int nd = min(kD, D - d0);
     __syncthreads();
+    for (int d = wave; d < nd; d += 4)
+      P[d * 64 + lane] = k < K ? sqrt(eig[d0 + d]) * (double)Phi[(d0 + d) * K + k] : 0.0;
+    __syncthreads();
+    for (int d = 0; d < nd; ++d) {
+      const double p = P[d * 64 + lane];
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        s[i] = fma(U[(size_t)min(r0 + i, V - 1) * D + d0 + d], p, s[i]);
+    }
   }
-  const double tot = red[0] > 0.0 ? red[0] : 1.0;
-  for (int i = tid; i < V; i += blockDim.x) {
-    const double v = fmax(mu[(size_t)i * K + k], 0.0);
-    mu[(size_t)i * K + k] = v / tot;
+  double pos = 0.0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int r = r0 + i;
+    if (r < V && k < K) {
+      const double v = s[i] * sk + (m != nullptr ? m[r] : 0.0);
+      mu[(size_t)r * K + k] = v;
+      pos += fmax(v, 0.0);
+    }
+  }
+  if (sums == nullptr) return;
+  red[wave][lane] = pos;
+  __syncthreads();
+  if (wave == 0 && k < K)
+    sums[(size_t)blockIdx.x * K + k] =
+        (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+}
+
+// tot[k] = sum over the nb blocks' column sums, in a fixed order (16 phases
+// combined in LDS); a column with no positive entry gets 1.
+__global__ void __launch_bounds__(1024) k_simplex_total(const double* __restrict__ sums, int nb,
+                                                        int K, double* __restrict__ tot) {
+  __shared__ double red[16][64];
+  const int lane = threadIdx.x & 63, ph = threadIdx.x >> 6;
+  const int k = blockIdx.x * 64 + lane;
+  double s = 0.0;
+  if (k < K)
+    for (int b = ph; b < nb; b += 16) s += sums[(size_t)b * K + k];
+  red[ph][lane] = s;
+  __syncthreads();
+  if (ph == 0 && k < K) {
+    for (int i = 1; i < 16; ++i) s += red[i][lane];
+    tot[k] = s > 0.0 ? s : 1.0;
   }
 }
 
-// A[d][k] = sum_i W[i][d] (mu[i][k] - m[i])
-__global__ void k_infer_A(const double* __restrict__ W, const double* __restrict__ m,
-                          const double* __restrict__ mu, int V, int D, int K,
-                          double* __restrict__ A, float* __restrict__ A32) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= D * K) return;
-  const int d = e / K, k = e % K;
-  double s = 0.0;
-  for (int i = 0; i < V; ++i) s += W[(size_t)i * D + d] * (mu[(size_t)i * K + k] - m[i]);
-  A[e] = s;
-  A32[e] = (float)s;
+// Clips negative entries and divides every column by its total.
+__global__ void __launch_bounds__(256) k_simplex_scale(double* __restrict__ mu, size_t n, int K,
+                                                       const double* __restrict__ tot) {
+  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (e < n) mu[e] = fmax(mu[e], 0.0) / tot[e % K];
 }
 
-// G = A^T A (K x K) into the Jacobi work matrix Gw, plus an FP32 copy.
-__global__ void k_infer_G(const double* __restrict__ A, int D, int K, double* __restrict__ Gw,
-                          float* __restrict__ G32) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= K * K) return;
-  const int j = e / K, k = e % K;
-  double s = 0.0;
-  for (int d = 0; d < D; ++d) s += A[d * K + j] * A[d * K + k];
-  Gw[e] = s;
-  G32[e] = (float)s;
+// G32 = A^T A (K x K, FP64 sums rounded to FP32), and into Gw the smaller of
+// A^T A and A A^T, whose largest eigenvalue is the same.  One thread per entry.
+__global__ void __launch_bounds__(256) k_infer_G(const double* __restrict__ A, int D, int K,
+                                                 double* __restrict__ Gw,
+                                                 float* __restrict__ G32) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e < K * K) {
+    const int j = e / K, k = e % K;
+    double s = 0.0;
+    for (int d = 0; d < D; ++d) s += A[d * K + j] * A[d * K + k];
+    if (K <= D) Gw[e] = s;
+    G32[e] = (float)s;
+  }
+  if (D < K && e < D * D) {
+    const int i = e / D, j = e % D;
+    double s = 0.0;
+    for (int k = 0; k < K; ++k) s += A[i * K + k] * A[j * K + k];
+    Gw[e] = s;
+  }
 }
 
 // Orders this wave's LDS stores before its later LDS loads by other lanes.
 __device__ inline void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
-}
-
-__global__ void k_infer_step(const double* __restrict__ ev, int K, float* __restrict__ step) {
-  if (threadIdx.x != 0) return;
-  double mx = 0.0;
-  for (int k = 0; k < K; ++k) mx = fmax(mx, ev[k]);
-  step[0] = mx > 0.0 ? (float)(1.0 / mx) : 0.0f;
 }
 
 // One wave per document; lane l owns topics l, l + 64, ... (TPL per lane).
@@ -289,6 +329,29 @@ __global__ void __launch_bounds__(256) k_infer(const float* __restrict__ X, int 
 
 }  // namespace
 
+size_t unwhiten_scratch_doubles(int V, int K) {
+  return (size_t)((V + kMuRows - 1) / kMuRows + 2) * K;   // column sums, totals, scales
+}
+
+// mu from the scales in scratch[0 .. K), clipped and renormalised when asked.
+static hipError_t launch_mu(const float* Phi, const double* U, const double* eig, const double* m,
+                            int V, int D, int K, uint32_t flags, double* mu, double* scratch,
+                            hipStream_t s) {
+  const bool simplex = (flags & TLDA_PROJECT_SIMPLEX) != 0;
+  const int nb = (V + kMuRows - 1) / kMuRows, kb = (K + 63) / 64;
+  double *tot = scratch + K, *sums = tot + K;
+  hipLaunchKernelGGL(k_mu, dim3(nb, kb), dim3(256), 0, s, Phi, U, eig, m, scratch, V, D, K, mu,
+                     simplex ? sums : nullptr);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !simplex) return e;
+  hipLaunchKernelGGL(k_simplex_total, dim3(kb), dim3(1024), 0, s, sums, nb, K, tot);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const size_t n = (size_t)V * K;
+  hipLaunchKernelGGL(k_simplex_scale, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, mu, n, K,
+                     tot);
+  return hipGetLastError();
+}
+
 hipError_t launch_unwhiten(const float* Phi, const double* U, const double* eig, const double* m,
                            int V, int D, int K, double theta, uint32_t flags, double* mu,
                            double* alpha, double* lambda, double* scratch, hipStream_t s) {
@@ -296,16 +359,7 @@ hipError_t launch_unwhiten(const float* Phi, const double* U, const double* eig,
                      lambda);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t n = (size_t)V * K;
-  hipLaunchKernelGGL(k_mu, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, Phi, U, eig, m,
-                     scratch, V, D, K, mu);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (flags & TLDA_PROJECT_SIMPLEX) {
-    hipLaunchKernelGGL(k_simplex_columns, dim3(K), dim3(256), 0, s, mu, V, K);
-    e = hipGetLastError();
-  }
-  return e;
+  return launch_mu(Phi, U, eig, m, V, D, K, flags, mu, scratch, s);
 }
 
 hipError_t launch_rebase(const double* C, const double* eig, const double* eig_prev, int D, int K,
@@ -321,33 +375,18 @@ hipError_t launch_unwhiten_classic(const float* Phi, const double* U, const doub
                      alpha, lambda);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const size_t n = (size_t)V * K;
-  hipLaunchKernelGGL(k_mu, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, Phi, U, eig,
-                     static_cast<const double*>(nullptr), scratch, V, D, K, mu);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (flags & TLDA_PROJECT_SIMPLEX) {
-    hipLaunchKernelGGL(k_simplex_columns, dim3(K), dim3(256), 0, s, mu, V, K);
-    e = hipGetLastError();
-  }
-  return e;
+  return launch_mu(Phi, U, eig, nullptr, V, D, K, flags, mu, scratch, s);
 }
 
 hipError_t launch_inference_setup(const double* W, const double* m, const double* mu, int V,
-                                  int D, int K, double* A, double* G, double* Z, double* ev,
-                                  float* A32, float* G32, float* step32, int* info,
-                                  hipStream_t s) {
-  hipLaunchKernelGGL(k_infer_A, dim3((D * K + 255) / 256), dim3(256), 0, s, W, m, mu, V, D, K, A,
-                     A32);
-  hipError_t e = hipGetLastError();
+                                  int D, int K, double* part, double* A, double* G, float* A32,
+                                  float* G32, float* step32, hipStream_t s) {
+  hipError_t e = launch_project(W, m, mu, V, D, K, part, A, A32, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_infer_G, dim3((K * K + 255) / 256), dim3(256), 0, s, A, D, K, G, G32);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = launch_jacobi(G, Z, ev, K, info, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_infer_step, dim3(1), dim3(64), 0, s, ev, K, step32);
-  return hipGetLastError();
+  const int n = K > D ? K : D;
+  hipLaunchKernelGGL(k_infer_G, dim3((n * n + 255) / 256), dim3(256), 0, s, A, D, K, G, G32);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  return launch_top_eig(G, K < D ? K : D, step32, s);
 }
 
 template <bool GIVEN, bool GAP_RULE>

@@ -570,7 +570,7 @@ void destroy_all(tlda_ctx* c) {
   dfree(c->cp.partial); dfree(c->cp.R1); dfree(c->cp.phi0); dfree(c->cp.grad); dfree(c->cp.X);
   dfree(c->cp.gsq);
   dfree(c->cp.Z); dfree(c->cp.rz); dfree(c->cp.Z16);
-  dfree(c->post); dfree(c->postA); dfree(c->postG); dfree(c->postZ); dfree(c->postEv);
+  dfree(c->post); dfree(c->postA); dfree(c->postG); dfree(c->postP);
   dfree(c->A32); dfree(c->G32); dfree(c->step32); dfree(c->dev_flags); dfree(c->block_counts);
   for (auto& s : c->slots) {
     if (s.free_) (void)hipEventSynchronize(s.free_);
@@ -673,9 +673,10 @@ tlda_status tlda_create(const tlda_config* cfg, void* hip_stream, tlda_ctx** out
             dalloc(&ctx->wh.mw32, (size_t)ctx->Dp) == hipSuccess &&
             dalloc(&ctx->cp.R1, D * K) == hipSuccess && dalloc(&ctx->cp.phi0, D * K) == hipSuccess &&
             dalloc(&ctx->cp.gsq, (size_t)K * K) == hipSuccess &&
-            dalloc(&ctx->cp.grad, D * K) == hipSuccess && dalloc(&ctx->post, K) == hipSuccess &&
+            dalloc(&ctx->cp.grad, D * K) == hipSuccess &&
+            dalloc(&ctx->post, tlda::unwhiten_scratch_doubles(c.V, c.K)) == hipSuccess &&
+            dalloc(&ctx->postP, tlda::project_scratch_doubles(c.V, c.D, c.K)) == hipSuccess &&
             dalloc(&ctx->postA, D * K) == hipSuccess && dalloc(&ctx->postG, K * K) == hipSuccess &&
-            dalloc(&ctx->postZ, K * K) == hipSuccess && dalloc(&ctx->postEv, K) == hipSuccess &&
             dalloc(&ctx->A32, D * K) == hipSuccess && dalloc(&ctx->G32, K * K) == hipSuccess &&
             dalloc(&ctx->step32, 1) == hipSuccess && dalloc(&ctx->dev_flags, 4) == hipSuccess &&
             dalloc(&ctx->block_counts, 2 * tlda::kWhitenBlockCounts) == hipSuccess;
@@ -905,9 +906,8 @@ tlda_status tlda_infer_doc_topics_whitened(tlda_ctx* c, const float* X, int32_t 
   if (n_rows == 0) return TLDA_OK;
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
   HIP_OK(c, launch_zero(c->dev_flags, 4 * sizeof(int), c->stream));
-  HIP_OK(c, tlda::launch_inference_setup(c->wh.W, c->wh.m, mu, V, D, K, c->postA, c->postG,
-                                         c->postZ, c->postEv, c->A32, c->G32, c->step32,
-                                         c->dev_flags + 1, c->stream));
+  HIP_OK(c, tlda::launch_inference_setup(c->wh.W, c->wh.m, mu, V, D, K, c->postP, c->postA,
+                                         c->postG, c->A32, c->G32, c->step32, c->stream));
   HIP_OK(c, tlda::launch_infer(X, n_rows, c->A32, c->G32, c->step32, D, K, max_iter, tol,
                                theta_out, c->stream));
   return TLDA_OK;
@@ -1257,9 +1257,8 @@ tlda_status tlda_infer_doc_topics_mlp(tlda_ctx* c, tlda_mlp* m, const float* X, 
   if (n_rows == 0) return TLDA_OK;
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
   HIP_OK(c, launch_zero(c->dev_flags + 1, sizeof(int), c->stream));
-  HIP_OK(c, tlda::launch_inference_setup(c->wh.W, c->wh.m, mu, V, D, K, c->postA, c->postG,
-                                         c->postZ, c->postEv, c->A32, c->G32, c->step32,
-                                         c->dev_flags + 1, c->stream));
+  HIP_OK(c, tlda::launch_inference_setup(c->wh.W, c->wh.m, mu, V, D, K, c->postP, c->postA,
+                                         c->postG, c->A32, c->G32, c->step32, c->stream));
   if (m != nullptr) {
     tlda_status st = tlda_mlp_forward(m, X, n_rows, theta_out);
     if (st != TLDA_OK) {

@@ -144,11 +144,10 @@ struct tlda_ctx {
   tlda::CpScratch cp;
   tlda::Tuning tune;
   tlda::StageSlot slots[2];
-  double* post = nullptr;     // [K] scratch for unwhiten
+  double* post = nullptr;     // scratch for unwhiten (unwhiten_scratch_doubles)
+  double* postP = nullptr;    // row-chunk partials of the inference matrix
   double* postA = nullptr;    // [D][K] inference matrix
   double* postG = nullptr;    // [K][K]
-  double* postZ = nullptr;    // [K][K]
-  double* postEv = nullptr;   // [K]
   float* A32 = nullptr;       // [D][K]
   float* G32 = nullptr;       // [K][K]
   float* step32 = nullptr;    // [1]
@@ -415,7 +414,8 @@ hipError_t mlp_train_step(tlda_mlp& m, const float* X, const float* T, int n, fl
                           float beta2, float eps, float* loss);
 // the fragment and padded copies from the master parameters
 hipError_t mlp_refresh(tlda_mlp& m);
-// post-processing
+// post-processing (scratch: unwhiten_scratch_doubles)
+size_t unwhiten_scratch_doubles(int V, int K);
 hipError_t launch_unwhiten(const float* Phi, const double* U, const double* eig, const double* m,
                            int V, int D, int K, double theta, uint32_t flags, double* mu,
                            double* alpha, double* lambda, double* scratch, hipStream_t s);
@@ -427,10 +427,16 @@ hipError_t launch_unwhiten_classic(const float* Phi, const double* U, const doub
 // Phi[:, k] <- diag(eig)^(-1/2) C diag(eig_prev)^(1/2) Phi[:, k] (FP64 sums)
 hipError_t launch_rebase(const double* C, const double* eig, const double* eig_prev, int D, int K,
                          float* Phi, hipStream_t s);
+// A = W^T (mu - m 1^T) (FP64 and FP32), G32 = A^T A and step32 = 1 / lambda_max(A^T A);
+// part: project_scratch_doubles(V, D, K)
 hipError_t launch_inference_setup(const double* W, const double* m, const double* mu, int V,
-                                  int D, int K, double* A, double* G, double* Z, double* ev,
-                                  float* A32, float* G32, float* step32, int* info,
-                                  hipStream_t s);
+                                  int D, int K, double* part, double* A, double* G, float* A32,
+                                  float* G32, float* step32, hipStream_t s);
+size_t project_scratch_doubles(int V, int D, int K);
+hipError_t launch_project(const double* W, const double* m, const double* mu, int V, int D, int K,
+                          double* part, double* A, float* A32, hipStream_t s);
+// step = 1 / (largest eigenvalue of the n x n positive semidefinite G), n <= 128
+hipError_t launch_top_eig(const double* G, int n, float* step, hipStream_t s);
 hipError_t launch_infer(const float* X, int n_rows, const float* A32, const float* G32,
                         const float* step32, int D, int K, int max_iter, float tol,
                         float* theta, hipStream_t s);
