@@ -181,18 +181,24 @@ __global__ void __launch_bounds__(256) k_simplex_scale(double* __restrict__ mu, 
   if (e < n) mu[e] = fmax(mu[e], 0.0) / tot[e % K];
 }
 
-// G32 = A^T A (K x K, FP64 sums rounded to FP32), and into Gw the smaller of
-// A^T A and A A^T, whose largest eigenvalue is the same.  One thread per entry.
+// G = A^T A (FP64 sums rounded to FP32) in the fragment order of k_infer, and
+// into Gw the smaller of A^T A and A A^T, whose largest eigenvalue is the same.
+// One thread per entry; entries of topics past K are zeros.
 __global__ void __launch_bounds__(256) k_infer_G(const double* __restrict__ A, int D, int K,
                                                  double* __restrict__ Gw,
-                                                 float* __restrict__ G32) {
+                                                 float* __restrict__ Gf) {
   const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e < K * K) {
-    const int j = e / K, k = e % K;
+  const int Kp = (K + 15) / 16 * 16;
+  if (e < Kp * Kp) {
+    const int j = e / Kp, k = e % Kp;
     double s = 0.0;
-    for (int d = 0; d < D; ++d) s += A[d * K + j] * A[d * K + k];
-    if (K <= D) Gw[e] = s;
-    G32[e] = (float)s;
+    if (j < K && k < K) {
+      for (int d = 0; d < D; ++d) s += A[d * K + j] * A[d * K + k];
+      if (K <= D) Gw[j * K + k] = s;
+    }
+    // row j = 16 mo + m of the product, column k = 16 mt + 4 q + r of its step (mt, r)
+    const int lane = (k >> 2 & 3) * 16 + (j & 15);
+    Gf[((j >> 4) * (Kp / 4) + (k >> 4) * 4 + (k & 3)) * 64 + lane] = (float)s;
   }
   if (D < K && e < D * D) {
     const int i = e / D, j = e % D;
@@ -202,129 +208,225 @@ __global__ void __launch_bounds__(256) k_infer_G(const double* __restrict__ A, i
   }
 }
 
-// Orders this wave's LDS stores before its later LDS loads by other lanes.
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// One wave per document; lane l owns topics l, l + 64, ... (TPL per lane).
-// The simplex projection finds, for each topic, its rank in decreasing order
-// (ties by index) and the sum of all values ranked at or above it; the
-// largest rank r whose value exceeds (prefix_r - 1) / r sets the threshold.
+// The projected-gradient solve: 16 documents per wave, one per column of the
+// FP32 matrix core's tiles (v_mfma_f32_16x16x4_f32).  Lane (l16, q) holds, for
+// document l16, topics 16 mt + 4 q + r (mt < TM, r < 4) of every vector: what
+// a product leaves in its accumulators, and what step (mt, r) of the next
+// product takes as its B operand, if G's columns are taken in that order.  So
+// t, b and the iterate never leave their registers; sums over a document's
+// topics are 4 TM values in the lane and two exchanges between lane groups.
 //
-// GIVEN: the start point is read from `out` (e.g. an encoder's output on the
+// The simplex projection max(y - tau, 0) solves sum max(y - tau, 0) = 1 by
+// Newton's method on that convex, decreasing, piecewise linear function of
+// tau: tau <- (sum of the entries above tau - 1) / (their number), started from
+// the previous iterate's tau (whose support is mostly the same: two or three
+// passes), until the number above stays.  From any start the sets are nested
+// from then on, so an unchanged number is an unchanged set, and the last tau is
+// the exact threshold of it.
+//
+// Documents finish at different iterations: a wave takes new ones from the
+// queue when kRefill columns are free (the b = A^T x of new documents costs
+// about an iteration for the whole wave).
+//
+// Bound: the vector ALUs (the projection) and the FP32 matrix cores (4 TM
+// steps of TM tiles an iteration) about alike; two waves or more per SIMD
+// overlap them.  G's fragments stay in registers up to 64 topics.
+//
+// given: the start point is read from `out` (e.g. an encoder's output on the
 // simplex) instead of the uniform 1/K.
-// GAP_RULE: instead of stopping when the L1 change of an iterate falls below
+// gap_rule: instead of stopping when the L1 change of an iterate falls below
 // tol, stop at the first iterate after min_steps steps whose duality gap for
 // h(t) = |x - A t|^2 / 2, g.t - min_k g_k with g = A^T (A t - x) = G t - b, is
 // at most gap_tol (it bounds h(t) - min h); rows that need more than
 // min_steps steps are counted in *n_stepped.
-template <int TPL, bool GIVEN, bool GAP_RULE>
-__global__ void __launch_bounds__(256) k_infer(const float* __restrict__ X, int n_rows,
-                                               const float* __restrict__ A32,
-                                               const float* __restrict__ G32,
-                                               const float* __restrict__ step32, int D, int K,
-                                               int max_iter, float tol, float* __restrict__ out,
-                                               float gap_tol, int min_steps,
-                                               int* __restrict__ n_stepped) {
-  __shared__ float xs[4][TLDA_MAX_D];
-  __shared__ float ys[4][64 * TPL];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = blockIdx.x * 4 + wave;
-  if (row >= n_rows) return;
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+constexpr int kRefill = 4;
+
+__device__ __forceinline__ float group_sum(float v) {   // over the document's four lanes
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+__device__ __forceinline__ int group_sum(int v) {
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+__device__ __forceinline__ float group_min(float v) {
+  v = fminf(v, __shfl_xor(v, 16, 64));
+  return fminf(v, __shfl_xor(v, 32, 64));
+}
+
+template <int TM>
+__global__ void __launch_bounds__(64, TM <= 4 ? 2 : 1) k_infer(
+    const float* __restrict__ X, int n_rows, const float* __restrict__ A32,
+    const float* __restrict__ Gf, const float* __restrict__ step32, int D, int K, int max_iter,
+    float tol, float* __restrict__ out, bool given, bool gap_rule, float gap_tol, int min_steps,
+    int* __restrict__ n_stepped, unsigned* __restrict__ queue) {
+  constexpr bool kRegs = TM <= 4;   // G's fragments in registers
+  const int lane = threadIdx.x, l16 = lane & 15, q = lane >> 4;
+  const int nt = (K + 15) / 16;                        // tiles of topics (<= TM)
+  const int last = min(4, K - 16 * (nt - 1));          // steps of the last tile with topics < K
   const float step = step32[0];
-  for (int d = lane; d < D; d += 64) xs[wave][d] = X[(size_t)row * D + d];
-  wave_sync();
-  float b[TPL], t[TPL];
+  float gf[kRegs ? TM * TM * 4 : 1];
+  if (kRegs) {
 #pragma unroll
-  for (int q = 0; q < TPL; ++q) {
-    const int k = lane + 64 * q;
-    float s = 0.f;
-    if (k < K)
-      for (int d = 0; d < D; ++d) s = fmaf(A32[d * K + k], xs[wave][d], s);
-    b[q] = s;
-    if (GIVEN)
-      t[q] = k < K ? out[(size_t)row * K + k] : 0.f;
-    else
-      t[q] = k < K ? 1.0f / (float)K : 0.f;
+    for (int i = 0; i < TM * TM * 4; ++i) {
+      const int mo = i / (4 * TM), ks = i % (4 * TM);
+      gf[i] = mo < nt && ks < 4 * nt ? Gf[(mo * 4 * nt + ks) * 64 + lane] : 0.f;
+    }
   }
-  for (int it = 0; it < max_iter; ++it) {
+  float t[TM][4], b[TM][4];
 #pragma unroll
-    for (int q = 0; q < TPL; ++q) ys[wave][lane + 64 * q] = t[q];
-    wave_sync();
-    float y[TPL];
-    float gt = 0.f, gmin = INFINITY;
+  for (int m = 0; m < TM; ++m)
 #pragma unroll
-    for (int q = 0; q < TPL; ++q) {
-      const int k = lane + 64 * q;
-      float g = 0.f;
-      if (k < K) {
-        for (int j = 0; j < K; ++j) g = fmaf(G32[k * K + j], ys[wave][j], g);
-        g -= b[q];
-        gt = fmaf(g, t[q], gt);
-        gmin = fminf(gmin, g);
+    for (int r = 0; r < 4; ++r) t[m][r] = b[m][r] = 0.f;
+  int row = -1, it = 0, stepped = 0;
+  float tau = 0.f;
+  bool drained = false;
+  auto topic = [&](int m, int r) { return 16 * m + 4 * q + r; };
+
+  while (true) {
+    const unsigned free = (unsigned)(__ballot(row < 0) & 0xffffull);
+    const int nfree = __popc(free);
+    if (nfree == 16 && drained) break;
+    if (!drained && nfree >= kRefill) {
+      // (unsigned: every wave's last request goes past n_rows)
+      unsigned base = 0;
+      if (lane == 0) base = atomicAdd(queue, (unsigned)nfree);
+      base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+      drained = base + nfree >= (unsigned)n_rows;
+      const unsigned mine = base + __popc(free & ((1u << l16) - 1u));
+      const bool fresh = row < 0 && mine < (unsigned)n_rows;
+      if (fresh) {
+        row = (int)mine;
+        it = 0;
+        tau = -INFINITY;
       }
-      y[q] = t[q] - step * g;
-    }
-    if (GAP_RULE) {
-      for (int off = 32; off > 0; off >>= 1) {
-        gt += __shfl_xor(gt, off, 64);
-        gmin = fminf(gmin, __shfl_xor(gmin, off, 64));
-      }
-      if (it >= min_steps && gt - gmin <= gap_tol) break;   // within gap_tol of the minimum
-      if (it == min_steps && lane == 0) atomicAdd(n_stepped, 1);
-    }
-    wave_sync();
+      if (__ballot(fresh) != 0) {
+        floatx4 acc[TM];
 #pragma unroll
-    for (int q = 0; q < TPL; ++q) ys[wave][lane + 64 * q] = y[q];
-    wave_sync();
-    int best_rank = 0;
-    float best_tau = 0.f;
+        for (int m = 0; m < TM; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        const float* x = X + (size_t)(fresh ? row : 0) * D;
+        for (int d0 = 0; d0 < D; d0 += 4) {
+          const int d = d0 + q, dc = min(d, D - 1);
+          const float xv = x[dc], xb = fresh && d < D ? xv : 0.f;
 #pragma unroll
-    for (int q = 0; q < TPL; ++q) {
-      const int k = lane + 64 * q;
-      if (k >= K) continue;
-      int rank = 0;
-      float pref = 0.f;
-      for (int j = 0; j < K; ++j) {
-        const float v = ys[wave][j];
-        if (v > y[q] || (v == y[q] && j <= k)) {
-          ++rank;
-          pref += v;
+          for (int m = 0; m < TM; ++m)
+            if (m < nt) {
+              const float a = A32[dc * K + min(16 * m + l16, K - 1)];
+              acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, xb, acc[m], 0, 0, 0);
+            }
+        }
+        if (fresh) {
+#pragma unroll
+          for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const bool in = topic(m, r) < K;
+              b[m][r] = in ? acc[m][r] : 0.f;
+              t[m][r] = !in ? 0.f : given ? out[(size_t)row * K + topic(m, r)] : 1.0f / (float)K;
+            }
         }
       }
-      const float tau = (pref - 1.0f) / (float)rank;
-      if (y[q] - tau > 0.f && rank > best_rank) {
-        best_rank = rank;
-        best_tau = tau;
+    }
+    bool done = row >= 0 && it >= max_iter;   // (at once when max_iter is 0)
+    if (max_iter > 0) {
+      // g = G t - b
+      floatx4 acc[TM];
+#pragma unroll
+      for (int m = 0; m < TM; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int mt = 0; mt < TM; ++mt) {
+        if (mt >= nt) break;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (mt == nt - 1 && r >= last) break;
+#pragma unroll
+          for (int mo = 0; mo < TM; ++mo) {
+            if (!kRegs && mo >= nt) break;
+            const float a = kRegs ? gf[mo * 4 * TM + mt * 4 + r]
+                                  : Gf[(mo * 4 * nt + mt * 4 + r) * 64 + lane];
+            acc[mo] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, t[mt][r], acc[mo], 0, 0, 0);
+          }
+        }
+      }
+      float y[TM][4];
+      float gt = 0.f, gmin = INFINITY;
+#pragma unroll
+      for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float g = acc[m][r] - b[m][r];
+          const bool in = topic(m, r) < K;
+          if (gap_rule) {
+            gt = fmaf(g, t[m][r], gt);
+            gmin = fminf(gmin, in ? g : INFINITY);
+          }
+          y[m][r] = in ? t[m][r] - step * g : -INFINITY;
+        }
+      if (gap_rule) {
+        const bool close = group_sum(gt) - group_min(gmin) <= gap_tol;
+        done = done || (row >= 0 && it >= min_steps && close);
+        stepped += __popcll(__ballot(row >= 0 && it == min_steps && !done) & 0xffffull);
+      }
+      bool settled = row < 0 || done;
+      int above = -1;
+      for (int pass = 0; pass < K + 8; ++pass) {
+        float s = 0.f;
+        int c = 0;
+#pragma unroll
+        for (int m = 0; m < TM; ++m)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const bool a = y[m][r] > tau;
+            s += a ? y[m][r] : 0.f;
+            c += a ? 1 : 0;
+          }
+        s = group_sum(s);
+        c = group_sum(c);
+        settled = settled || c == above;
+        above = c;
+        if (__ballot(c == 0) != 0) {
+          // nothing above an old tau: restart below the largest entry
+          float mx = -INFINITY;
+#pragma unroll
+          for (int m = 0; m < TM; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, y[m][r]);
+          mx = -group_min(-mx);
+          // (no finite entry at all: the document's numbers are not finite)
+          tau = c != 0 ? (s - 1.0f) / (float)c : mx > -INFINITY ? mx - 1.0f : 0.f;
+        } else {
+          tau = (s - 1.0f) / (float)c;
+        }
+        if (__ballot(!settled) == 0) break;
+      }
+      float change = 0.f;
+      const bool move = row >= 0 && !done;
+#pragma unroll
+      for (int m = 0; m < TM; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float tn = fmaxf(y[m][r] - tau, 0.f);
+          change += fabsf(tn - t[m][r]);
+          t[m][r] = move ? tn : t[m][r];
+        }
+      if (move) ++it;
+      done = done || (row >= 0 && it >= max_iter);
+      if (!gap_rule && tol > 0.f) {
+        const bool still = group_sum(change) < tol;
+        done = done || (row >= 0 && still);
       }
     }
-    for (int off = 32; off > 0; off >>= 1) {
-      const int orank = __shfl_xor(best_rank, off, 64);
-      const float otau = __shfl_xor(best_tau, off, 64);
-      if (orank > best_rank) {
-        best_rank = orank;
-        best_tau = otau;
-      }
-    }
-    float change = 0.f;
+    if (done) {
 #pragma unroll
-    for (int q = 0; q < TPL; ++q) {
-      const int k = lane + 64 * q;
-      const float tn = k < K ? fmaxf(y[q] - best_tau, 0.f) : 0.f;
-      change += fabsf(tn - t[q]);
-      t[q] = tn;
-    }
-    for (int off = 32; off > 0; off >>= 1) change += __shfl_xor(change, off, 64);
-    wave_sync();
-    if (!GAP_RULE && change < tol) break;
-  }
+      for (int m = 0; m < TM; ++m)
 #pragma unroll
-  for (int q = 0; q < TPL; ++q) {
-    const int k = lane + 64 * q;
-    if (k < K) out[(size_t)row * K + k] = t[q];
+        for (int r = 0; r < 4; ++r)
+          if (topic(m, r) < K) out[(size_t)row * K + topic(m, r)] = t[m][r];
+      row = -1;
+    }
   }
+  if (stepped > 0 && lane == 0) atomicAdd(n_stepped, stepped);
 }
 
 }  // namespace
@@ -380,52 +482,49 @@ hipError_t launch_unwhiten_classic(const float* Phi, const double* U, const doub
 
 hipError_t launch_inference_setup(const double* W, const double* m, const double* mu, int V,
                                   int D, int K, double* part, double* A, double* G, float* A32,
-                                  float* G32, float* step32, hipStream_t s) {
+                                  float* Gf, float* step32, hipStream_t s) {
   hipError_t e = launch_project(W, m, mu, V, D, K, part, A, A32, s);
   if (e != hipSuccess) return e;
-  const int n = K > D ? K : D;
-  hipLaunchKernelGGL(k_infer_G, dim3((n * n + 255) / 256), dim3(256), 0, s, A, D, K, G, G32);
+  const int n = K > D ? (K + 15) / 16 * 16 : (D + 15) / 16 * 16;
+  hipLaunchKernelGGL(k_infer_G, dim3((n * n + 255) / 256), dim3(256), 0, s, A, D, K, G, Gf);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_top_eig(G, K < D ? K : D, step32, s);
 }
 
-template <bool GIVEN, bool GAP_RULE>
-hipError_t launch_infer_t(const float* X, int n_rows, const float* A32, const float* G32,
-                          const float* step32, int D, int K, int max_iter, float tol, float* theta,
-                          float gap_tol, int min_steps, int* n_stepped, hipStream_t s) {
+// *queue must be zero.  As many waves as the 256 compute units hold: three per
+// SIMD with G in registers up to 64 topics, one past that.
+static hipError_t launch_infer_k(const float* X, int n_rows, const float* A32, const float* Gf,
+                                 const float* step32, int D, int K, int max_iter, float tol,
+                                 float* theta, bool given, bool gap_rule, float gap_tol,
+                                 int min_steps, int* n_stepped, int* queue, hipStream_t s) {
   if (n_rows == 0) return hipSuccess;
-  const dim3 grid((n_rows + 3) / 4);
-  if (K <= 64)
-    hipLaunchKernelGGL((k_infer<1, GIVEN, GAP_RULE>), grid, dim3(256), 0, s, X, n_rows, A32, G32,
-                       step32, D, K, max_iter, tol, theta, gap_tol, min_steps,
-                       n_stepped);
-  else if (K <= 128)
-    hipLaunchKernelGGL((k_infer<2, GIVEN, GAP_RULE>), grid, dim3(256), 0, s, X, n_rows, A32, G32,
-                       step32, D, K, max_iter, tol, theta, gap_tol, min_steps,
-                       n_stepped);
-  else
-    hipLaunchKernelGGL((k_infer<4, GIVEN, GAP_RULE>), grid, dim3(256), 0, s, X, n_rows, A32, G32,
-                       step32, D, K, max_iter, tol, theta, gap_tol, min_steps,
-                       n_stepped);
+  const int waves = (n_rows + 15) / 16, most = K <= 64 ? 3072 : 1024;
+  const dim3 grid(waves < most ? waves : most);
+#define TLDA_INFER(tm)                                                                           \
+  hipLaunchKernelGGL(k_infer<tm>, grid, dim3(64), 0, s, X, n_rows, A32, Gf, step32, D, K,        \
+                     max_iter, tol, theta, given, gap_rule, gap_tol, min_steps, n_stepped, reinterpret_cast<unsigned*>(queue))
+  if (K <= 16) TLDA_INFER(1);
+  else if (K <= 32) TLDA_INFER(2);
+  else if (K <= 64) TLDA_INFER(4);
+  else if (K <= 128) TLDA_INFER(8);
+  else TLDA_INFER(16);
+#undef TLDA_INFER
   return hipGetLastError();
 }
 
-hipError_t launch_infer(const float* X, int n_rows, const float* A32, const float* G32,
+hipError_t launch_infer(const float* X, int n_rows, const float* A32, const float* Gf,
                         const float* step32, int D, int K, int max_iter, float tol,
-                        float* theta, hipStream_t s) {
-  return launch_infer_t<false, false>(X, n_rows, A32, G32, step32, D, K, max_iter, tol, theta,
-                                      0.f, 0, nullptr, s);
+                        float* theta, int* queue, hipStream_t s) {
+  return launch_infer_k(X, n_rows, A32, Gf, step32, D, K, max_iter, tol, theta, false, false, 0.f,
+                        0, nullptr, queue, s);
 }
 
-hipError_t launch_infer_gap(const float* X, int n_rows, const float* A32, const float* G32,
+hipError_t launch_infer_gap(const float* X, int n_rows, const float* A32, const float* Gf,
                             const float* step32, int D, int K, bool given_start, float gap_tol,
-                            int min_steps, int max_iter, float* theta, int* n_stepped,
+                            int min_steps, int max_iter, float* theta, int* n_stepped, int* queue,
                             hipStream_t s) {
-  return given_start
-             ? launch_infer_t<true, true>(X, n_rows, A32, G32, step32, D, K, max_iter, 0.f, theta,
-                                          gap_tol, min_steps, n_stepped, s)
-             : launch_infer_t<false, true>(X, n_rows, A32, G32, step32, D, K, max_iter, 0.f,
-                                           theta, gap_tol, min_steps, n_stepped, s);
+  return launch_infer_k(X, n_rows, A32, Gf, step32, D, K, max_iter, 0.f, theta, given_start, true,
+                        gap_tol, min_steps, n_stepped, queue, s);
 }
 
 }  // namespace tlda

@@ -149,9 +149,10 @@ struct tlda_ctx {
   double* postA = nullptr;    // [D][K] inference matrix
   double* postG = nullptr;    // [K][K]
   float* A32 = nullptr;       // [D][K]
-  float* G32 = nullptr;       // [K][K]
+  float* Gf = nullptr;        // A^T A in fragment order, K padded to 16
   float* step32 = nullptr;    // [1]
-  int* dev_flags = nullptr;   // [4] CSR validation and inference status words
+  int* dev_flags = nullptr;   // [4] CSR validation and inference words: 0, 1 validation, 1
+                              // the solve's queue, 2 kept rows, 3 stepped rows
   int* block_counts = nullptr;  // [2 * kWhitenBlockCounts] per-block document counts
   // timing hook: event pairs recorded around the main kernel of each hot-path call
   hipEvent_t* t_start = nullptr;
@@ -427,27 +428,28 @@ hipError_t launch_unwhiten_classic(const float* Phi, const double* U, const doub
 // Phi[:, k] <- diag(eig)^(-1/2) C diag(eig_prev)^(1/2) Phi[:, k] (FP64 sums)
 hipError_t launch_rebase(const double* C, const double* eig, const double* eig_prev, int D, int K,
                          float* Phi, hipStream_t s);
-// A = W^T (mu - m 1^T) (FP64 and FP32), G32 = A^T A and step32 = 1 / lambda_max(A^T A);
-// part: project_scratch_doubles(V, D, K)
+// A = W^T (mu - m 1^T) (FP64 and FP32), Gf = A^T A (FP32, in the solve's fragment order, K
+// padded to 16) and step32 = 1 / lambda_max(A^T A); part: project_scratch_doubles(V, D, K)
 hipError_t launch_inference_setup(const double* W, const double* m, const double* mu, int V,
                                   int D, int K, double* part, double* A, double* G, float* A32,
-                                  float* G32, float* step32, hipStream_t s);
+                                  float* Gf, float* step32, hipStream_t s);
 size_t project_scratch_doubles(int V, int D, int K);
 hipError_t launch_project(const double* W, const double* m, const double* mu, int V, int D, int K,
                           double* part, double* A, float* A32, hipStream_t s);
 // step = 1 / (largest eigenvalue of the n x n positive semidefinite G), n <= 128
 hipError_t launch_top_eig(const double* G, int n, float* step, hipStream_t s);
-hipError_t launch_infer(const float* X, int n_rows, const float* A32, const float* G32,
+// queue: a zeroed device counter, which the solve's waves take rows from
+hipError_t launch_infer(const float* X, int n_rows, const float* A32, const float* Gf,
                         const float* step32, int D, int K, int max_iter, float tol,
-                        float* theta, hipStream_t s);
+                        float* theta, int* queue, hipStream_t s);
 // Projected gradient with a duality-gap stopping rule: from the start point
 // held in theta (given_start) or from 1/K, at least min_steps steps, then
 // until the gap of the iterate is at most gap_tol or max_iter steps; rows
 // that need more than min_steps steps are counted in *n_stepped (which the
 // caller zeroes).
-hipError_t launch_infer_gap(const float* X, int n_rows, const float* A32, const float* G32,
+hipError_t launch_infer_gap(const float* X, int n_rows, const float* A32, const float* Gf,
                             const float* step32, int D, int K, bool given_start, float gap_tol,
-                            int min_steps, int max_iter, float* theta, int* n_stepped,
+                            int min_steps, int max_iter, float* theta, int* n_stepped, int* queue,
                             hipStream_t s);
 
 }  // namespace tlda
