@@ -5,130 +5,17 @@
 // The data term R1 = X^T (X Phi)^2 is the only part that touches the batch;
 // the D x D x D tensor is never formed.
 //
-// k_cp_reduce: each block walks a fixed set of row tiles (tile b, b + nblk,
-// ...).  Per tile, Phi (D x K, resident in LDS for the whole block) and the
-// X tile give S = X_t Phi with 4 x 4 register blocking, S is squared in LDS,
-// and R1 += X_t^T S^2 accumulates in registers (each thread owns up to four
-// 4 x 4 blocks of R1).  Each block writes its R1 partial; the row partition
-// depends only on n_rows, so the reduction order is fixed.
+// The reductions (k_cp_reduce_mfma up to D, K of 128, k_cp_reduce_wide past
+// that): each block walks a fixed set of row tiles (tile b, b + nblk, ...),
+// forms S = X_t Phi and adds X_t^T S^2 to its own R1, and writes that partial;
+// the row partition depends only on n_rows, so the reduction order is fixed.
 #include "tlda_internal.h"
 
 namespace tlda {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kMaxRBlocks = 4;   // (D/4)*(K/4) <= 1024 for D*K <= 16384
-
-__global__ void __launch_bounds__(kThreads) k_cp_reduce(const float* __restrict__ X, int n_rows,
-                                                        const float* __restrict__ Phi, int D,
-                                                        int K, int T, int nblk,
-                                                        float* __restrict__ partial,
-                                                        float* __restrict__ phi_copy) {
-  extern __shared__ float smem[];
-  const int Dq = (D + 3) & ~3, Kq = (K + 3) & ~3;
-  float* Ps = smem;                 // [Dq][Kq]
-  float* Xs = Ps + Dq * Kq;         // [T][Dq]
-  float* Ss = Xs + T * Dq;          // [T][Kq]
-  const int tid = threadIdx.x;
-  for (int e = blockIdx.x * kThreads + tid; e < D * K; e += nblk * kThreads) phi_copy[e] = Phi[e];
-  for (int e = tid; e < Dq * Kq; e += kThreads) {
-    const int d = e / Kq, k = e % Kq;
-    Ps[e] = (d < D && k < K) ? Phi[d * K + k] : 0.f;
-  }
-  const int nkb = Kq / 4, ndb = Dq / 4;
-  const int nSb = (T / 4) * nkb;     // 4x4 blocks of S
-  const int nRb = ndb * nkb;         // 4x4 blocks of R1
-  float acc[kMaxRBlocks][4][4];
-#pragma unroll
-  for (int q = 0; q < kMaxRBlocks; ++q)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[q][i][j] = 0.f;
-
-  const int ntiles = (n_rows + T - 1) / T;
-  for (int tile = blockIdx.x; tile < ntiles; tile += nblk) {
-    __syncthreads();
-    const int r0 = tile * T;
-    for (int e = tid; e < T * Dq; e += kThreads) {
-      const int r = e / Dq, d = e % Dq;
-      const int gr = r0 + r;
-      Xs[e] = (gr < n_rows && d < D) ? X[(size_t)gr * D + d] : 0.f;
-    }
-    __syncthreads();
-    // S = X_t Phi, squared
-    for (int bidx = tid; bidx < nSb; bidx += kThreads) {
-      const int rb = bidx / nkb, kb = bidx % nkb;
-      float s[4][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) s[i][j] = 0.f;
-      const float* x0 = Xs + (rb * 4) * Dq;
-      for (int d = 0; d < Dq; ++d) {
-        const float4 p = *reinterpret_cast<const float4*>(Ps + d * Kq + kb * 4);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float xv = x0[i * Dq + d];
-          s[i][0] = fmaf(xv, p.x, s[i][0]);
-          s[i][1] = fmaf(xv, p.y, s[i][1]);
-          s[i][2] = fmaf(xv, p.z, s[i][2]);
-          s[i][3] = fmaf(xv, p.w, s[i][3]);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float4 o;
-        o.x = s[i][0] * s[i][0];
-        o.y = s[i][1] * s[i][1];
-        o.z = s[i][2] * s[i][2];
-        o.w = s[i][3] * s[i][3];
-        *reinterpret_cast<float4*>(Ss + (rb * 4 + i) * Kq + kb * 4) = o;
-      }
-    }
-    __syncthreads();
-    // R1 += X_t^T S^2
-#pragma unroll
-    for (int q = 0; q < kMaxRBlocks; ++q) {
-      const int bidx = tid + q * kThreads;
-      if (bidx >= nRb) break;
-      const int db = bidx / nkb, kb = bidx % nkb;
-      for (int r = 0; r < T; ++r) {
-        const float4 xv = *reinterpret_cast<const float4*>(Xs + r * Dq + db * 4);
-        const float4 sv = *reinterpret_cast<const float4*>(Ss + r * Kq + kb * 4);
-        const float xa[4] = {xv.x, xv.y, xv.z, xv.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[q][i][0] = fmaf(xa[i], sv.x, acc[q][i][0]);
-          acc[q][i][1] = fmaf(xa[i], sv.y, acc[q][i][1]);
-          acc[q][i][2] = fmaf(xa[i], sv.z, acc[q][i][2]);
-          acc[q][i][3] = fmaf(xa[i], sv.w, acc[q][i][3]);
-        }
-      }
-    }
-  }
-  float* out = partial + (size_t)blockIdx.x * D * K;
-#pragma unroll
-  for (int q = 0; q < kMaxRBlocks; ++q) {
-    const int bidx = tid + q * kThreads;
-    if (bidx >= nRb) break;
-    const int db = bidx / nkb, kb = bidx % nkb;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int d = db * 4 + i;
-      if (d >= D) continue;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int k = kb * 4 + j;
-        if (k < K) out[d * K + k] = acc[q][i][j];
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// FP32 matrix-core variant of the reduction (D, K <= 128 after padding to
-// 16).  Per row tile (T rows of X staged in LDS):
+// FP32 matrix-core reduction (D, K <= 128 after padding to 16).  Per row tile (T rows of X staged in LDS):
 //   S = X_t Phi      with v_mfma_f32_16x16x4_f32; each wave owns S column
 //                    tiles ct = wave, wave + 4, ... and keeps the Phi
 //                    fragments of those columns in registers for the whole
@@ -271,6 +158,133 @@ __global__ void __launch_bounds__(64 * cp_waves(DQ, KQ)) k_cp_reduce_mfma(const 
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int d = (t / NCT) * 16 + 4 * l4 + r;
+        if (d < D && k < K) out[d * K + k] = acc[q][r];
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same for D or K past 128 (D K <= 16384): 16 waves, row tiles of 64, the
+// shape at run time.  Phi stays in LDS (past 128 its fragments would not fit
+// in registers), the wave takes S tiles t = wave, wave + 16, .. and keeps R1
+// tiles t = wave, .. (at most kWideR of them: 72 tiles at 130 x 116) in
+// registers.  Bound: the FP32 matrix cores; on the vector ALUs with 4-row
+// tiles at the largest shapes it took 58 us for 40 001 rows of 150 x 37.
+// gsq (or NULL): the blocks also form the squared Gram entries, as k_gram_sq
+// does, 16 entries per wave.
+// ---------------------------------------------------------------------------
+constexpr int kWideT = 64, kWideR = 5, kWideThreads = 1024;
+
+size_t cp_wide_lds_floats(int D, int K) {
+  const size_t dq = (D + 15) & ~15, kq = (K + 15) & ~15;
+  return kWideT * (dq + 4 + kq + 4) + dq * (kq + 4);
+}
+
+__global__ void __launch_bounds__(kWideThreads) k_cp_reduce_wide(
+    const float* __restrict__ X, int n_rows, const float* __restrict__ Phi, int D, int K, int nblk,
+    float* __restrict__ partial, float* __restrict__ phi_copy, double* __restrict__ gsq) {
+  extern __shared__ float smem[];
+  const int DQ = (D + 15) & ~15, KQ = (K + 15) & ~15;
+  const int LDX = DQ + 4, LDS = KQ + 4;
+  float* Xs = smem;                    // [64][LDX]
+  float* Ss = Xs + kWideT * LDX;       // [64][LDS]
+  float* Ps = Ss + kWideT * LDS;       // [DQ][LDS]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int nct = KQ / 16, nrt = DQ / 16 * nct;
+  for (int e = blockIdx.x * kWideThreads + tid; e < D * K; e += nblk * kWideThreads)
+    phi_copy[e] = Phi[e];
+  for (int e = tid; e < kWideT * LDX; e += kWideThreads) Xs[e] = 0.f;   // padding stays zero
+  for (int e = tid; e < DQ * LDS; e += kWideThreads) {
+    const int d = e / LDS, k = e - d * LDS;
+    Ps[e] = d < D && k < K ? Phi[d * K + k] : 0.f;
+  }
+  floatx4 acc[kWideR];
+#pragma unroll
+  for (int q = 0; q < kWideR; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // wave w stages rows w, w + 16, .. of a tile, lane l columns l, l + 64, ..;
+  // rows past the batch load a clamped address and are zeroed when stored
+  float pre[4][4];
+  auto fetch = [&](int tile) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* x = X + (size_t)min(tile * kWideT + wave + 16 * i, n_rows - 1) * D;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (64 * j < D) pre[i][j] = x[min(lane + 64 * j, D - 1)];
+    }
+  };
+  const int ntiles = (n_rows + kWideT - 1) / kWideT;
+  if (blockIdx.x < ntiles) fetch(blockIdx.x);
+  __syncthreads();
+  if (gsq != nullptr) {
+    const int c = lane & 3, M = D / 4;
+    for (int e0 = (wave * nblk + blockIdx.x) * 16; e0 < K * K; e0 += 16 * nblk * 16) {
+      const int e = e0 + (lane >> 2);
+      const bool in = e < K * K;
+      const int j = in ? e / K : 0, k = in ? e % K : 0;
+      double a = 0.0;
+      for (int m = 0; m < M; ++m) {
+        const float* p = Ps + (4 * m + c) * LDS;
+        a += (double)p[j] * (double)p[k];
+      }
+      if (c == 0)
+        for (int i = 4 * M; i < D; ++i) a += (double)Ps[i * LDS + j] * (double)Ps[i * LDS + k];
+      a += __shfl_xor(a, 1, 64);                  // (c0 + c1), (c2 + c3)
+      a += __shfl_xor(a, 2, 64);
+      if (in && c == 0) gsq[e] = a * a;
+    }
+  }
+  for (int tile = blockIdx.x; tile < ntiles; tile += nblk) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = wave + 16 * i;
+      const bool in = tile * kWideT + r < n_rows;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (lane + 64 * j < D) Xs[r * LDX + lane + 64 * j] = in ? pre[i][j] : 0.f;
+    }
+    __syncthreads();
+    if (tile + nblk < ntiles) fetch(tile + nblk);
+    for (int t = wave; t < 4 * nct; t += 16) {
+      const int rt = t & 3, ct = t >> 2;
+      floatx4 sacc = {0.f, 0.f, 0.f, 0.f};
+      const float* xa = Xs + (rt * 16 + l16) * LDX + l4;
+      const float* pb = Ps + l4 * LDS + ct * 16 + l16;
+      for (int d0 = 0; d0 < DQ; d0 += 16)   // (columns of X past D are zeros)
+#pragma unroll
+        for (int d = 0; d < 16; d += 4)
+          sacc = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[d0 + d], pb[(d0 + d) * LDS], sacc, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        Ss[(rt * 16 + 4 * l4 + r) * LDS + ct * 16 + l16] = sacc[r] * sacc[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kWideR; ++q) {
+      const int t = wave + 16 * q;
+      if (t < nrt) {
+        const float* xa = Xs + l4 * LDX + t / nct * 16 + l16;
+        const float* sb = Ss + l4 * LDS + t % nct * 16 + l16;
+#pragma unroll
+        for (int rs = 0; rs < kWideT / 4; ++rs)
+          acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[4 * rs * LDX], sb[4 * rs * LDS], acc[q],
+                                                        0, 0, 0);
+      }
+    }
+  }
+  float* out = partial + (size_t)blockIdx.x * D * K;
+#pragma unroll
+  for (int q = 0; q < kWideR; ++q) {
+    const int t = wave + 16 * q;
+    if (t < nrt) {
+      const int k = t % nct * 16 + l16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int d = t / nct * 16 + 4 * l4 + r;
         if (d < D && k < K) out[d * K + k] = acc[q][r];
       }
     }
@@ -573,18 +587,13 @@ __global__ void __launch_bounds__(kFinThreads, 8) k_cp_finish_multi(const SliceS
 
 }  // namespace
 
-// LDS bytes of the reduction kernel for a row tile of T rows: Phi and the X
-// and S tiles.
-size_t cp_lds_bytes(int D, int K, int T) {
-  const int Dq = (D + 3) & ~3, Kq = (K + 3) & ~3;
-  return sizeof(float) * ((size_t)Dq * Kq + (size_t)T * (Dq + Kq));
-}
-
-// Row-tile height for the reduction: the largest of 64, 32, 16, 8, 4 whose
-// LDS footprint stays within 64 KiB.
+// The FP32 shapes a context takes: Phi and a row tile of 64, 32, 16, 8 or 4
+// rows of X and S (padded to 4) within 64 KiB; returns the largest such tile,
+// 0 when the shape is not taken.
 int cp_tile_rows(int D, int K) {
+  const size_t dq = (D + 3) & ~3, kq = (K + 3) & ~3;
   for (int T = 64; T >= 4; T >>= 1)
-    if (cp_lds_bytes(D, K, T) <= 65536) return T;
+    if (sizeof(float) * (dq * kq + T * (dq + kq)) <= 65536) return T;
   return 0;
 }
 
@@ -627,8 +636,7 @@ int cp_resident_blocks(int D, int K, int num_cu) {
 #undef TLDA_OCC_ROW
 #undef TLDA_OCC
   } else {
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cp_reduce, kThreads,
-                                                      cp_lds_bytes(D, K, cp_tile_rows(D, K)));
+    per_cu = 1;   // 16 waves of up to 128 registers
   }
   if (e != hipSuccess || per_cu < 1) per_cu = 1;
   return per_cu * num_cu;
@@ -637,13 +645,17 @@ int cp_resident_blocks(int D, int K, int num_cu) {
 int cp_num_blocks(int n_rows, int D, int K, int max_blocks) {
   if (max_blocks <= 0) max_blocks = 1024;
   const int Tm = cp_mfma_tile_rows(D, K);
-  const int T = Tm > 0 ? Tm : cp_tile_rows(D, K);
+  const int T = Tm > 0 ? Tm : kWideT;
   const int ntiles = (n_rows + T - 1) / T;
   return ntiles < max_blocks ? (ntiles < 1 ? 1 : ntiles) : max_blocks;
 }
 
+bool cp_reduce_forms_gram(int D, int K) {
+  return cp_mfma_tile_rows(D, K) == 0 && D * K >= kGramOnceDK;
+}
+
 hipError_t launch_cp_reduce(const float* X, int n_rows, const float* Phi, int D, int K, int nblk,
-                            float* partial, float* phi_copy, hipStream_t s) {
+                            float* partial, float* phi_copy, double* gsq, hipStream_t s) {
   const int Tm = cp_mfma_tile_rows(D, K);
   if (Tm > 0) {
     const int dq = mfma_bucket(D), kq = mfma_bucket(K);
@@ -662,9 +674,15 @@ hipError_t launch_cp_reduce(const float* X, int n_rows, const float* Phi, int D,
 #undef TLDA_MFMA_ROW
 #undef TLDA_MFMA
   } else {
-    const int T = cp_tile_rows(D, K);
-    launch_main(k_cp_reduce, dim3(nblk), dim3(kThreads), (unsigned)cp_lds_bytes(D, K, T), s, X,
-                n_rows, Phi, D, K, T, nblk, partial, phi_copy);
+    const size_t lds = cp_wide_lds_floats(D, K) * sizeof(float);
+    if (lds > 65536) {
+      const hipError_t e =
+          hipFuncSetAttribute(reinterpret_cast<const void*>(k_cp_reduce_wide),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    launch_main(k_cp_reduce_wide, dim3(nblk), dim3(kWideThreads), (unsigned)lds, s, X, n_rows, Phi,
+                D, K, nblk, partial, phi_copy, gsq);
   }
   return hipGetLastError();
 }

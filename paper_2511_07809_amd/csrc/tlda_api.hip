@@ -796,16 +796,17 @@ tlda_status tlda_cp_step(tlda_ctx* c, const float* X, int32_t n_rows, const int3
   tlda_status st = ensure_partial(c, (size_t)nblk * D * K);
   if (st != TLDA_OK) return st;
   float* g = grad ? grad : c->cp.grad;
+  const bool gram = !is_bf16(c) && tlda::cp_reduce_forms_gram(D, K);
   HIP_OK(c, timing_start(c));
   if (is_bf16(c))
     HIP_OK(c, tlda::launch_cp_reduce_bf16(X, n_rows, Phi, D, K, nblk, c->cp.partial, c->cp.phi0,
                                           c->stream));
   else
     HIP_OK(c, tlda::launch_cp_reduce(X, n_rows, Phi, D, K, nblk, c->cp.partial, c->cp.phi0,
-                                     c->stream));
+                                     gram ? c->cp.gsq : nullptr, c->stream));
   HIP_OK(c, timing_stop(c));
   return finish_step(c, c->cp.partial, nblk, n_kept, n_kept ? 1 : 0, n_rows, beta, Phi, g,
-                     nullptr);
+                     nullptr, gram);
 }
 
 tlda_status tlda_whiten_cp_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float* Phi,
