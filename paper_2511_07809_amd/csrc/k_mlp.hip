@@ -457,16 +457,30 @@ __global__ void __launch_bounds__(256) k_grads(int n, int D, int H, int K, Train
     float s[4] = {0.f, 0.f, 0.f, 0.f};
     const int r0 = chunk * 64, r1 = min(n, r0 + 64);
     int z = r0 / o.chunk, c = r0 - z * o.chunk;
-    for (int r = r0; r < r1; r += 4) {
+    if (c + 64 <= o.chunk && r1 - r0 == 64 && c % 8 == 0) {
+      // 64 rows in a piece (16-byte aligned: chunks are padded to 32)
+      const u32x4* p = reinterpret_cast<const u32x4*>(m + (size_t)z * o.chunk_pad + c);
+      u32x4 v[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (r + u < r1) {
-          s[u] += from_bf16(m[(size_t)z * o.chunk_pad + c]);
-          if (++c == o.chunk) {
-            c = 0;
-            ++z;
+      for (int i = 0; i < 8; ++i) v[i] = p[i];
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        const uint32_t w = v[i >> 2][i & 3];
+        s[2 * (i & 1)] += __uint_as_float(w << 16);
+        s[2 * (i & 1) + 1] += __uint_as_float(w & 0xffff0000u);
+      }
+    } else {
+      for (int r = r0; r < r1; r += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (r + u < r1) {
+            s[u] += from_bf16(m[(size_t)z * o.chunk_pad + c]);
+            if (++c == o.chunk) {
+              c = 0;
+              ++z;
+            }
           }
-        }
+      }
     }
     ws_b[(size_t)chunk * (2 * H + K) + e] = (s[0] + s[1]) + (s[2] + s[3]);
     return;
@@ -497,14 +511,7 @@ __global__ void __launch_bounds__(256) k_grads(int n, int D, int H, int K, Train
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-  for (int k0 = 0; k0 < o.chunk_pad; k0 += 32) {
-    u32x4 a[2], bb[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      a[i] = *reinterpret_cast<const u32x4*>(ap + i * 16 * o.ld + k0);
-      bb[i] = *reinterpret_cast<const u32x4*>(bp + i * 16 * o.ld + k0);
-    }
+  auto products = [&](const u32x4 (&a)[2], const u32x4 (&bb)[2]) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -512,6 +519,31 @@ __global__ void __launch_bounds__(256) k_grads(int n, int D, int H, int K, Train
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]),
                                                             __builtin_bit_cast(bf16x8, bb[j]),
                                                             acc[i][j], 0, 0, 0);
+  };
+  // 128 rows (the usual chunk) at a time, every operand loaded before the
+  // first product: one round trip to the caches
+  int k0 = 0;
+  for (; k0 + 128 <= o.chunk_pad; k0 += 128) {
+    u32x4 a[4][2], bb[4][2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[u][i] = *reinterpret_cast<const u32x4*>(ap + i * 16 * o.ld + k0 + 32 * u);
+        bb[u][i] = *reinterpret_cast<const u32x4*>(bp + i * 16 * o.ld + k0 + 32 * u);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) products(a[u], bb[u]);
+  }
+  for (; k0 < o.chunk_pad; k0 += 32) {
+    u32x4 a[2], bb[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      a[i] = *reinterpret_cast<const u32x4*>(ap + i * 16 * o.ld + k0);
+      bb[i] = *reinterpret_cast<const u32x4*>(bp + i * 16 * o.ld + k0);
+    }
+    products(a, bb);
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
