@@ -21,9 +21,15 @@ namespace {
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_gemm64(int M, int N, int Kd, const double* __restrict__ A,
                                                 int lda, const double* __restrict__ B, int ldb,
-                                                double* __restrict__ C, int ldc) {
+                                                double* __restrict__ C, int ldc,
+                                                const int* __restrict__ pick,
+                                                const double* __restrict__ B_set) {
   __shared__ double As[16][64 + 2];
   __shared__ double Bs[16][64 + 2];
+  if (pick != nullptr && *pick) {
+    if (B_set == nullptr) return;
+    B = B_set;
+  }
   const int tid = threadIdx.x;
   const int tx = tid & 15, ty = tid >> 4;
   const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
@@ -98,6 +104,8 @@ __global__ void __launch_bounds__(256) k_gemm64(int M, int N, int Kd, const doub
 // equal runs, so that every compute unit ends together whatever M is.  A run
 // that covers a tile writes C; the pieces of a divided tile go to ws, piece
 // (block + tile), and k_dgemm_sum adds them in order.
+// pick (or NULL): with B_set, *pick chooses the right operand (B_set where it
+// is set); without it, nothing is done where it is set.
 // ---------------------------------------------------------------------------
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int kDgBM = 128, kDgBK = 16, kDgThreads = 512, kDgMaxNT = 13;
@@ -141,12 +149,16 @@ template <int NT, bool SYM>
 __global__ void __launch_bounds__(kDgThreads, NT <= 7 ? 4 : 2) k_dgemm_mfma(
     int M, int N, int K, int gx, int slabs, long long total, const double* __restrict__ A, int lda,
     const double* __restrict__ B, int ldb, double* __restrict__ C, int ldc,
-    double* __restrict__ ws) {
+    double* __restrict__ ws, const int* __restrict__ pick, const double* __restrict__ B_set) {
   constexpr int BNC = 16 * NT, LDB_S = 16 * (NT | 1);
   constexpr int A_PER = kDgBM * kDgBK / kDgThreads;
   constexpr int B_PER = (kDgBK * BNC + kDgThreads - 1) / kDgThreads;
   __shared__ double As[2][kDgBK * kDgLdA];
   __shared__ double Bs[2][kDgBK * LDB_S];
+  if (pick != nullptr && *pick) {
+    if (B_set == nullptr) return;
+    B = B_set;
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   long long s0 = blockIdx.x * total / gridDim.x;
@@ -237,8 +249,10 @@ __global__ void __launch_bounds__(kDgThreads, NT <= 7 ? 4 : 2) k_dgemm_mfma(
 // in block order, 8 loads in flight.
 __global__ void __launch_bounds__(256) k_dgemm_sum(const double* __restrict__ ws, int M, int N,
                                                    int bnc, int gx, int slabs, int blocks,
-                                                   double* __restrict__ C, int ldc) {
+                                                   double* __restrict__ C, int ldc,
+                                                   const int* __restrict__ skip) {
   constexpr int kU = 8;
+  if (skip != nullptr && *skip) return;
   const int tile = blockIdx.y;
   const long long total = (long long)gridDim.y * slabs, s = (long long)tile * slabs;
   // the block of slab s starts at or before it: b total / blocks < s + 1
@@ -263,14 +277,15 @@ __global__ void __launch_bounds__(256) k_dgemm_sum(const double* __restrict__ ws
 
 template <bool SYM>
 hipError_t dgemm_mfma(int M, int N, int K, const double* A, int lda, const double* B, int ldb,
-                      double* C, int ldc, hipStream_t s) {
+                      double* C, int ldc, const int* pick, const double* B_set, hipStream_t s) {
   DgPlan d = dgemm_plan(M, N, K, g_eig_env.num_cu);
   if (d.ws() > g_eig_env.ws_doubles) d.blocks = d.gx * d.gy;
   switch (d.nt) {
 #define TLDA_DG(n)                                                                                \
   case n:                                                                                         \
     hipLaunchKernelGGL((k_dgemm_mfma<n, SYM>), dim3(d.blocks), dim3(kDgThreads), 0, s, M, N, K,   \
-                       d.gx, d.slabs, d.total(), A, lda, B, ldb, C, ldc, g_eig_env.ws);           \
+                       d.gx, d.slabs, d.total(), A, lda, B, ldb, C, ldc, g_eig_env.ws, pick,      \
+                       B_set);                                                                    \
     break;
     TLDA_DG(1) TLDA_DG(2) TLDA_DG(3) TLDA_DG(4) TLDA_DG(5) TLDA_DG(6) TLDA_DG(7) TLDA_DG(8)
     TLDA_DG(9) TLDA_DG(10) TLDA_DG(11) TLDA_DG(12) TLDA_DG(13)
@@ -280,19 +295,20 @@ hipError_t dgemm_mfma(int M, int N, int K, const double* A, int lda, const doubl
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || d.blocks == d.gx * d.gy) return e;
   hipLaunchKernelGGL(k_dgemm_sum, dim3(kDgBM * 16 * d.nt / 256, d.gx * d.gy), dim3(256), 0, s,
-                     g_eig_env.ws, M, N, 16 * d.nt, d.gx, d.slabs, d.blocks, C, ldc);
+                     g_eig_env.ws, M, N, 16 * d.nt, d.gx, d.slabs, d.blocks, C, ldc,
+                     B_set == nullptr ? pick : nullptr);
   return hipGetLastError();
 }
 
 // C (M x N) = A (M x Kd) B: the matrix cores, or the vector-ALU tile kernel.
-// sym: A is symmetric.
+// sym: A is symmetric.  pick, B_set: as for k_dgemm_mfma.
 hipError_t gemm(int M, int N, int Kd, const double* A, int lda, const double* B, int ldb, double* C,
-                int ldc, bool sym, hipStream_t s) {
+                int ldc, bool sym, const int* pick, const double* B_set, hipStream_t s) {
   if (g_eig_env.route == 0)
-    return sym ? dgemm_mfma<true>(M, N, Kd, A, lda, B, ldb, C, ldc, s)
-               : dgemm_mfma<false>(M, N, Kd, A, lda, B, ldb, C, ldc, s);
+    return sym ? dgemm_mfma<true>(M, N, Kd, A, lda, B, ldb, C, ldc, pick, B_set, s)
+               : dgemm_mfma<false>(M, N, Kd, A, lda, B, ldb, C, ldc, pick, B_set, s);
   hipLaunchKernelGGL(k_gemm64, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, s, M, N, Kd, A,
-                     lda, B, ldb, C, ldc);
+                     lda, B, ldb, C, ldc, pick, B_set);
   return hipGetLastError();
 }
 
@@ -709,8 +725,8 @@ hipError_t launch_random_block(double* Q, int V, int p, uint64_t seed, hipStream
 }
 
 hipError_t launch_m2_apply(const double* M2, const double* Q, double* Y, int V, int p,
-                           hipStream_t s) {
-  return gemm(V, p, V, M2, V, Q, p, Y, p, true, s);
+                           const int* pick, const double* Q_set, hipStream_t s) {
+  return gemm(V, p, V, M2, V, Q, p, Y, p, true, pick, Q_set, s);
 }
 
 hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s) {
@@ -730,8 +746,8 @@ hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hip
 }
 
 hipError_t launch_block_product(const double* Q, const double* Z, double* Out, int V, int p,
-                                hipStream_t s) {
-  return gemm(V, p, p, Q, p, Z, p, Out, p, false, s);
+                                const int* skip, hipStream_t s) {
+  return gemm(V, p, p, Q, p, Z, p, Out, p, false, skip, nullptr, s);
 }
 
 hipError_t launch_ritz_vectors(const double* Q, const double* Z, const double* ev, int V, int p,
@@ -741,7 +757,7 @@ hipError_t launch_ritz_vectors(const double* Q, const double* Z, const double* e
   hipLaunchKernelGGL(k_select_top, dim3(1), dim3(256), 0, s, Z, ev, p, D, Zs, eigD);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = gemm(V, D, p, Q, p, Zs, D, U, D, false, s);
+  e = gemm(V, D, p, Q, p, Zs, D, U, D, false, nullptr, nullptr, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_sign_fix, dim3(D), dim3(256), 0, s, U, V, D);
   return hipGetLastError();

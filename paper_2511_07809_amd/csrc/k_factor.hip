@@ -160,19 +160,27 @@ constexpr int panel_tiles(int n) {
   return nb;
 }
 
+// Where the diagonal of R spans less than this, the block's columns come out of
+// one Cholesky-QR pass orthonormal to about 1e-16 / kWell^2 = 1e-8.
+constexpr double kWell = 1e-4;
+
 // The factor, tiles in registers: one block of NW waves, tile t = tile_at(i, j)
 // in slot t / NW of wave t % NW (NW SLOTS >= the tile count; at most two waves
 // per SIMD, so that a tile being factored fits beside them).  Nothing is
 // written to memory before the last step, since every barrier would wait for
-// it.  INV: the block goes on to the inverse, its tiles in LDS (few tiles: a
+// it.  skip (or NULL): nothing to do when it is set.  well (or NULL) receives 1
+// when the smallest diagonal entry of R is at least kWell of the largest.  INV: the block goes on to the inverse, its tiles in LDS (few tiles: a
 // second launch would cost more than other compute units would save).
 template <int NW, int SLOTS, bool INV>
 __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, int p,
                                                   double shift_rel, double* __restrict__ tiles,
                                                   double* __restrict__ dinv,
                                                   double* __restrict__ Binv,
-                                                  int* __restrict__ info) {
+                                                  int* __restrict__ info,
+                                                  const int* __restrict__ skip,
+                                                  int* __restrict__ well) {
   constexpr int NB = panel_tiles(NW * SLOTS);
+  if (skip != nullptr && *skip) return;
   // row k of R while it is applied (INV: every tile of R, kept)
   __shared__ double panel[(INV ? NB * (NB + 1) / 2 : NB) * kTileE];
   __shared__ double dcols[NB * kTileE], diag[kTileE];
@@ -241,6 +249,36 @@ __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, 
                            acc[s]);
   }
   if (!ok && lane == 0) atomicOr(info, 1);
+  if (well != nullptr) {
+    // diag is free now: the waves' smallest and largest diagonal entries
+    double lo = INFINITY, hi = 0.0;
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s)
+      if (ti[s] >= 0 && ti[s] == tj[s]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (4 * r + row == col && ti[s] * kTile + col < p) {
+            lo = fmin(lo, acc[s][r]);
+            hi = fmax(hi, acc[s][r]);
+          }
+      }
+    for (int off = 32; off > 0; off >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, off, 64));
+      hi = fmax(hi, __shfl_xor(hi, off, 64));
+    }
+    if (lane == 0) {
+      diag[2 * wave] = lo;
+      diag[2 * wave + 1] = hi;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < NW; ++w) {
+        lo = fmin(lo, diag[2 * w]);
+        hi = fmax(hi, diag[2 * w + 1]);
+      }
+      *well = lo >= kWell * hi ? 1 : 0;
+    }
+  }
   if (INV) {
     for (int i = wave; i < nb; i += NW)
       inverse_column(panel, dcols, nb, i, p, ybuf + i * NB * kTileE, Binv, lane);
@@ -257,8 +295,11 @@ __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, 
 // touched by wave t % 16 alone.
 __global__ void __launch_bounds__(1024) k_chol_mem(const double* __restrict__ G, int p,
                                                    double shift_rel, double* tiles, double* dinv,
-                                                   int* __restrict__ info) {
+                                                   int* __restrict__ info,
+                                                   const int* __restrict__ skip,
+                                                   int* __restrict__ well) {
   constexpr int NW = 16;
+  if (skip != nullptr && *skip) return;
   __shared__ double panel[kMaxNb * kTileE];
   __shared__ double diag[kTileE], dcols[kTileE];
   const int lane = threadIdx.x & 63;
@@ -312,13 +353,31 @@ __global__ void __launch_bounds__(1024) k_chol_mem(const double* __restrict__ G,
                                        load_tile(panel + j * kTileE, lane), load_tile(tp, lane)));
       }
   }
+  if (well == nullptr) return;
+  __threadfence_block();
+  __syncthreads();
+  if (wave == 0) {
+    double lo = INFINITY, hi = 0.0;
+    for (int j = lane; j < p; j += 64) {
+      const double d = tiles[(size_t)tile_at(j / kTile, j / kTile) * kTileE + j % kTile * (kTile + 1)];
+      lo = fmin(lo, d);
+      hi = fmax(hi, d);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, off, 64));
+      hi = fmax(hi, __shfl_xor(hi, off, 64));
+    }
+    if (lane == 0) *well = lo >= kWell * hi ? 1 : 0;
+  }
 }
 
 // One wave per block column of the inverse.
 __global__ void __launch_bounds__(64) k_tri_inverse(const double* __restrict__ tiles,
                                                     const double* __restrict__ dinv, int p,
-                                                    double* __restrict__ Binv) {
+                                                    double* __restrict__ Binv,
+                                                    const int* __restrict__ skip) {
   __shared__ double y[kMaxNb * kTileE];
+  if (skip != nullptr && *skip) return;
   const int nb = (p + kTile - 1) / kTile;
   inverse_column(tiles, dinv, nb, blockIdx.x, p, y, Binv, threadIdx.x);
 }
@@ -360,8 +419,10 @@ __global__ void __launch_bounds__(64 * kGramWaves) k_gram(const double* __restri
                                                           const double* __restrict__ B,
                                                           const double* __restrict__ m, int V,
                                                           GramShape g, int chunk,
-                                                          double* __restrict__ part) {
+                                                          double* __restrict__ part,
+                                                          const int* __restrict__ skip) {
   __shared__ double red[kGramWaves - 1][kGramN * kTileE];
+  if (skip != nullptr && *skip) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int i = 0, u = blockIdx.x;   // unit u of the tile rows: j0 .. j0 + n - 1 of row i
@@ -429,8 +490,10 @@ __global__ void __launch_bounds__(64 * kGramWaves) k_gram(const double* __restri
 // adds only the chunks that exist.  G32: an FP32 copy, or NULL.
 __global__ void __launch_bounds__(256) k_gram_sum(const double* __restrict__ part, int nz,
                                                   GramShape g, double* __restrict__ G,
-                                                  float* __restrict__ G32) {
+                                                  float* __restrict__ G32,
+                                                  const int* __restrict__ skip) {
   constexpr int kU = 8;
+  if (skip != nullptr && *skip) return;
   const int e = blockIdx.x * 64 + (threadIdx.x >> 2);   // 64 entries per block: within one tile
   const int c = threadIdx.x & 3;
   const int t = e / kTileE;
@@ -577,14 +640,15 @@ size_t chol_scratch_doubles(int p) {
 // becomes R^-1 of G + shift_rel max diag(G) I = R^T R; *info |= 1 on a pivot
 // that is not positive.  scratch: chol_scratch_doubles(p).
 hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
-                               double* Binv, int* info, hipStream_t s) {
+                               double* Binv, int* info, const int* skip, int* well,
+                               hipStream_t s) {
   const int nb = (p + kTile - 1) / kTile;
   if (p < 1 || nb > kMaxNb) return hipErrorInvalidValue;
   double* tiles = scratch;
   double* dinv = tiles + (size_t)nb * (nb + 1) / 2 * kTileE;
 #define TLDA_CHOL(nw, slots, inv)                                                             \
   hipLaunchKernelGGL((k_chol<nw, slots, inv>), dim3(1), dim3(64 * nw), 0, s, G, p, shift_rel, \
-                     tiles, dinv, Binv, info)
+                     tiles, dinv, Binv, info, skip, well)
   if (nb <= 5) {
     TLDA_CHOL(4, 4, true);
     return hipGetLastError();
@@ -592,11 +656,12 @@ hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double*
   if (nb <= 9) TLDA_CHOL(8, 6, false);
   else if (nb <= 13) TLDA_CHOL(8, 12, false);
   else
-    hipLaunchKernelGGL(k_chol_mem, dim3(1), dim3(1024), 0, s, G, p, shift_rel, tiles, dinv, info);
+    hipLaunchKernelGGL(k_chol_mem, dim3(1), dim3(1024), 0, s, G, p, shift_rel, tiles, dinv, info,
+                       skip, well);
 #undef TLDA_CHOL
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_tri_inverse, dim3(nb), dim3(64), 0, s, tiles, dinv, p, Binv);
+  hipLaunchKernelGGL(k_tri_inverse, dim3(nb), dim3(64), 0, s, tiles, dinv, p, Binv, skip);
   return hipGetLastError();
 }
 
@@ -612,17 +677,17 @@ constexpr int kGramBlocks = 1024, kProjectBlocks = 512;
 
 static hipError_t launch_gram_shape(const double* A, const double* B, const double* m, int V,
                                     const GramShape& g, int blocks, double* part, double* G,
-                                    float* G32, hipStream_t s) {
+                                    float* G32, const int* skip, hipStream_t s) {
   int nz = gram_chunks(V, g, blocks);
   const int step = 4 * kGramWaves;
   const int chunk = ((V + nz - 1) / nz + step - 1) / step * step;
   nz = (V + chunk - 1) / chunk;
   hipLaunchKernelGGL(k_gram, dim3(g.units(), nz), dim3(64 * kGramWaves), 0, s, A, B, m, V, g, chunk,
-                     part);
+                     part, skip);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_gram_sum, dim3(g.tiles() * (kTileE / 64)), dim3(256), 0, s, part, nz, g, G,
-                     G32);
+                     G32, skip);
   return hipGetLastError();
 }
 
@@ -631,8 +696,9 @@ size_t gram_scratch_doubles(int V, int p, bool sym) {
   return (size_t)gram_chunks(V, g, kGramBlocks) * g.tiles() * kTileE;
 }
 hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
-                       double* part, hipStream_t s) {
-  return launch_gram_shape(A, B, nullptr, V, GramShape{p, p, sym}, kGramBlocks, part, G, nullptr, s);
+                       double* part, const int* skip, hipStream_t s) {
+  return launch_gram_shape(A, B, nullptr, V, GramShape{p, p, sym}, kGramBlocks, part, G, nullptr,
+                           skip, s);
 }
 
 size_t project_scratch_doubles(int V, int D, int K) {
@@ -641,7 +707,8 @@ size_t project_scratch_doubles(int V, int D, int K) {
 }
 hipError_t launch_project(const double* W, const double* m, const double* mu, int V, int D, int K,
                           double* part, double* A, float* A32, hipStream_t s) {
-  return launch_gram_shape(W, mu, m, V, GramShape{D, K, false}, kProjectBlocks, part, A, A32, s);
+  return launch_gram_shape(W, mu, m, V, GramShape{D, K, false}, kProjectBlocks, part, A, A32,
+                           nullptr, s);
 }
 
 hipError_t launch_top_eig(const double* G, int n, float* step, hipStream_t s) {

@@ -256,7 +256,7 @@ tlda_status ensure_acc(tlda_ctx* c) {
 tlda_status ensure_eig(tlda_ctx* c, int p) {
   tlda::EigScratch& e = c->eig;
   if (e.p == p && e.Q) return TLDA_OK;
-  dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
+  dfree(e.Q); dfree(e.Y); dfree(e.T); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
   dfree(e.fac);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   e.p = 0;
@@ -265,6 +265,7 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
   const size_t V = c->cfg.V, D = c->cfg.D;
   HIP_OK(c, dalloc(&e.Q, V * p));
   HIP_OK(c, dalloc(&e.Y, V * p));
+  HIP_OK(c, dalloc(&e.T, V * p));
   HIP_OK(c, dalloc(&e.G, (size_t)p * p));
   HIP_OK(c, dalloc(&e.Z, (size_t)p * p));
   HIP_OK(c, dalloc(&e.Binv, (size_t)p * p));
@@ -288,16 +289,23 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
 }
 
 // Two Cholesky-QR passes (the first with a small diagonal shift so that a
-// rank-deficient block still factors): in -> out, using tmp as scratch.
-tlda_status orthonormalise(tlda_ctx* c, const double* in, double* tmp, double* out) {
+// rank-deficient block still factors): in -> T -> out.  Between iterations
+// (may_skip) only the span matters, so the second pass is left out, on the
+// device, where the factor of the first shows the block to be well conditioned:
+// info[1] is then set and the block is in T.
+tlda_status orthonormalise(tlda_ctx* c, const double* in, double* out, bool may_skip) {
   tlda::EigScratch& e = c->eig;
   const int V = c->cfg.V, p = e.p;
-  HIP_OK(c, tlda::launch_gram(in, in, e.G, V, p, true, e.part, c->stream));
-  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 1e-12, e.fac, e.Binv, e.info, c->stream));
-  HIP_OK(c, tlda::launch_block_product(in, e.Binv, tmp, V, p, c->stream));
-  HIP_OK(c, tlda::launch_gram(tmp, tmp, e.G, V, p, true, e.part, c->stream));
-  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 0.0, e.fac, e.Binv, e.info, c->stream));
-  HIP_OK(c, tlda::launch_block_product(tmp, e.Binv, out, V, p, c->stream));
+  int* well = e.info + 1;
+  const int* skip = may_skip ? well : nullptr;
+  HIP_OK(c, tlda::launch_gram(in, in, e.G, V, p, true, e.part, nullptr, c->stream));
+  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 1e-12, e.fac, e.Binv, e.info, nullptr,
+                                      may_skip ? well : nullptr, c->stream));
+  HIP_OK(c, tlda::launch_block_product(in, e.Binv, e.T, V, p, nullptr, c->stream));
+  HIP_OK(c, tlda::launch_gram(e.T, e.T, e.G, V, p, true, e.part, skip, c->stream));
+  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 0.0, e.fac, e.Binv, e.info, skip, nullptr,
+                                      c->stream));
+  HIP_OK(c, tlda::launch_block_product(e.T, e.Binv, out, V, p, skip, c->stream));
   return TLDA_OK;
 }
 
@@ -355,29 +363,30 @@ tlda_status refresh(tlda_ctx* c, bool warm) {
   const double a1 = c->cfg.alpha0 + 1.0;
   HIP_OK(c, tlda::launch_fx_symmetric(c->mom.acc, e.mcand, V, a1 / N,
                                       is_classic(c) ? c->cfg.alpha0 : a1, c->mom.M2, c->stream));
-  double* q = e.Q;
-  double* y = e.Y;
+  double* q = e.Q;   // the block
+  double* y = e.Y;   // M2~ times it
   if (warm) {
     // start block: the orthonormal block of the previous refresh
     if (e.warm != q) std::swap(q, y);
   }
-  e.warm = nullptr;   // both buffers are overwritten below; set again on success
+  e.warm = nullptr;   // the buffers are overwritten below; set again on success
   if (!warm) {
-    // start block: seeded uniform entries, orthonormalised (y -> tmp q -> y)
+    // start block: seeded uniform entries, orthonormalised
     HIP_OK(c, tlda::launch_random_block(y, V, p, c->cfg.eig_seed, c->stream));
-    st = orthonormalise(c, y, q, y);
+    st = orthonormalise(c, y, q, false);
     if (st != TLDA_OK) return st;
-    std::swap(q, y);   // q: orthonormal block
   }
+  bool may_skip = false;
   for (int it = 0; it < iters; ++it) {
-    HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, c->stream));
-    st = orthonormalise(c, y, q, y);   // y -> tmp q -> y
+    HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, may_skip ? e.info + 1 : nullptr, e.T,
+                                    c->stream));
+    may_skip = it + 1 < iters;   // the Rayleigh-Ritz step takes an orthonormal block
+    st = orthonormalise(c, y, q, may_skip);
     if (st != TLDA_OK) return st;
-    std::swap(q, y);
   }
   // Rayleigh-Ritz: H = Q^T M2~ Q, eigenpairs by Jacobi, U = Q Z_top
-  HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, c->stream));
-  HIP_OK(c, tlda::launch_gram(q, y, e.G, V, p, true, e.part, c->stream));
+  HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, nullptr, nullptr, c->stream));
+  HIP_OK(c, tlda::launch_gram(q, y, e.G, V, p, true, e.part, nullptr, c->stream));
   HIP_OK(c, tlda::launch_jacobi(e.G, e.Z, e.ev, p, e.info, c->stream));
   HIP_OK(c, tlda::launch_ritz_vectors(q, e.Z, e.ev, V, p, D, y, e.sel, c->stream));
   int info[4] = {0, 0, 0, 0};
@@ -397,7 +406,7 @@ tlda_status refresh(tlda_ctx* c, bool warm) {
   HIP_OK(c, hipMemcpyAsync(c->wh.U, y, sizeof(double) * (size_t)V * D, hipMemcpyDeviceToDevice, c->stream));
   // the next warm start: the full Ritz basis Q Z (p columns), so that the
   // projected matrix of the next refresh starts close to diagonal
-  HIP_OK(c, tlda::launch_block_product(q, e.Z, y, V, p, c->stream));
+  HIP_OK(c, tlda::launch_block_product(q, e.Z, y, V, p, nullptr, c->stream));
   e.warm = y;
   HIP_OK(c, hipMemcpyAsync(c->wh.eig, e.sel, sizeof(double) * D, hipMemcpyDeviceToDevice, c->stream));
   HIP_OK(c, hipMemcpyAsync(c->wh.m, e.mcand, sizeof(double) * V, hipMemcpyDeviceToDevice, c->stream));
@@ -564,7 +573,7 @@ void destroy_all(tlda_ctx* c) {
   delete[] c->t_start;
   delete[] c->t_stop;
   tlda::EigScratch& e = c->eig;
-  dfree(e.Q); dfree(e.Y); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
+  dfree(e.Q); dfree(e.Y); dfree(e.T); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
   dfree(e.fac);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   dfree(c->cp.partial); dfree(c->cp.R1); dfree(c->cp.phi0); dfree(c->cp.grad); dfree(c->cp.X);
@@ -1060,7 +1069,8 @@ tlda_status tlda_rebase_phi(tlda_ctx* c, float* Phi) {
   CHECK_ARG(c, c->wh.ready && c->wh.prev_ready, TLDA_ERR_STATE,
             "no previous whitening to rebase from");
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
-  HIP_OK(c, tlda::launch_gram(c->wh.U, c->wh.Uprev, c->wh.C, V, D, false, c->wh.part, c->stream));
+  HIP_OK(c, tlda::launch_gram(c->wh.U, c->wh.Uprev, c->wh.C, V, D, false, c->wh.part, nullptr,
+                              c->stream));
   HIP_OK(c, tlda::launch_rebase(c->wh.C, c->wh.eig, c->wh.eigprev, D, K, Phi, c->stream));
   return TLDA_OK;
 }

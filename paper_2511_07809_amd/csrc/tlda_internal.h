@@ -78,6 +78,7 @@ struct EigScratch {
   int p = 0;
   double* Q = nullptr;     // [V][p]
   double* Y = nullptr;     // [V][p]
+  double* T = nullptr;     // [V][p]  block after the first Cholesky-QR pass
   double* G = nullptr;     // [p][p]  Gram / projected matrix
   double* Z = nullptr;     // [p][p]  eigenvectors of the projected matrix
   double* ev = nullptr;    // [p]
@@ -85,7 +86,8 @@ struct EigScratch {
   double* fac = nullptr;   // tiles of the factorisation (chol_scratch_doubles)
   double* sel = nullptr;   // [D + p*D] selected Ritz values and vectors
   double* mcand = nullptr; // [V]     M1 of the refresh in progress
-  int* info = nullptr;     // [4]     device status words
+  int* info = nullptr;     // [4]     device status words: 0 failures, 1 the last block needs
+                           //         no second Cholesky-QR pass (it is in T)
   double* warm = nullptr;  // Q or Y: the orthonormal block the last refresh converged to
   double* part = nullptr;  // row-chunk partials of the Gram products (gram_scratch_doubles)
   double* ws = nullptr;    // pieces of the product with M2 (dgemm_ws_doubles)
@@ -272,22 +274,26 @@ hipError_t launch_mean(const unsigned long long* fsum, const unsigned long long*
                        hipStream_t s);
 // eigen-solver building blocks (FP64)
 hipError_t launch_random_block(double* Q, int V, int p, uint64_t seed, hipStream_t s);
+// Y = M2 Q, or M2 Q_set where *pick is set (pick may be NULL)
 hipError_t launch_m2_apply(const double* M2, const double* Q, double* Y, int V, int p,
-                           hipStream_t s);
+                           const int* pick, const double* Q_set, hipStream_t s);
 // G (p x p) = A^T B for V x p blocks; sym: A^T B is symmetric, only its upper
-// tiles are formed.  part: gram_scratch_doubles(V, p, sym) doubles
+// tiles are formed.  part: gram_scratch_doubles(V, p, sym) doubles.  Here and
+// below: nothing is done where *skip is set (skip may be NULL)
 size_t gram_scratch_doubles(int V, int p, bool sym);
 hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
-                       double* part, hipStream_t s);
+                       double* part, const int* skip, hipStream_t s);
 // Binv <- R^-1 with G + shift_rel max diag(G) I = R^T R (R upper; p <= 512);
-// *info |= 1 on a pivot that is not positive
+// *info |= 1 on a pivot that is not positive; *well (or NULL) tells whether
+// one Cholesky-QR pass with it leaves the block's columns orthonormal to 1e-8
 size_t chol_scratch_doubles(int p);
 hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
-                               double* Binv, int* info, hipStream_t s);
+                               double* Binv, int* info, const int* skip, int* well,
+                               hipStream_t s);
 hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s);
 // Out (V x p) = Q (V x p) Z (p x p)
 hipError_t launch_block_product(const double* Q, const double* Z, double* Out, int V, int p,
-                                hipStream_t s);
+                                const int* skip, hipStream_t s);
 hipError_t launch_ritz_vectors(const double* Q, const double* Z, const double* ev, int V, int p,
                                int D, double* U, double* eigD, hipStream_t s);
 hipError_t launch_form_whitening(const double* U, const double* eig, const double* m, int V, int D,
