@@ -441,168 +441,224 @@ __global__ void __launch_bounds__(1024) k_jacobi(double* __restrict__ A, double*
   for (int i = tid; i < p; i += nt) ev[i] = A[(size_t)i * p + i];
 }
 
-// The same iteration with the p x p matrix in LDS (p <= kLdsP).  ZL: the
-// rotation accumulator Z is in LDS as well (p <= kLdsPZ, the two matrices
-// fill the 160 KB), and Z's array doubles as the reduction scratch before Z
-// is formed and after it is written out; otherwise Z stays in global memory.
-constexpr int kLdsP = 128, kLdsPZ = 100;
-template <bool ZL>
-__global__ void __launch_bounds__(1024) k_jacobi_lds(double* __restrict__ Ag, double* __restrict__ Zg,
-                                                 double* __restrict__ ev, int p,
-                                                 int* __restrict__ info) {
-  constexpr int PA = ZL ? kLdsPZ : kLdsP;
-  __shared__ double A[PA * PA];
-  __shared__ double Zl[ZL ? PA * PA : 1];
-  __shared__ double sh[3 * (PA / 2) + (ZL ? 0 : 2 * 1024)];   // c, s, pair indices (, scratch)
-  __shared__ int sh_rot;
-  __shared__ double sh_norm;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int m = (p + 1) & ~1;
-  const int half = m / 2;
-  double* cs = sh;
-  double* sn = sh + half;
-  int* pi = reinterpret_cast<int*>(sh + 2 * half);
-  int* pj = pi + half;
-  double* red = ZL ? Zl : sh + 3 * half;     // 2 * nt doubles
-  double* Z = ZL ? Zl : Zg;
-  for (int idx = tid; idx < p * p; idx += nt) {
-    A[idx] = Ag[idx];
-    if (!ZL) Z[idx] = (idx / p == idx % p) ? 1.0 : 0.0;
+// The same iteration for p <= kRotP: the packed lower triangle of A stays in
+// LDS (160.8 KB at p = 200) and every rotation is written out, for
+// k_jacobi_vectors to apply to Z afterwards, one row of Z per wave on its own
+// compute unit; kept in one block, Z is as many LDS or L2 bytes a round again.
+// Bound: LDS, half (half - 1) / 2 rotated 2 x 2 blocks a round, then the chain
+// of a rotation's angle and two barriers a round.  (i, j) entry of A, i >= j,
+// at i (i + 1) / 2 + j.  A thread owns the 2 x 2 blocks at the rows of pair a
+// and the columns of pair b > a of the same (a, b) in every round, at most MAXB.
+// rot: [sweeps][m - 1][half] rotations (c, s); *n_sweeps: sweeps that rotated.
+constexpr int kRotP = 200, kRotThreads = 1024, kMaxSweeps = 60;
+
+__device__ __forceinline__ int tri(int i, int j) {
+  const int hi = max(i, j), lo = min(i, j);
+  return hi * (hi + 1) / 2 + lo;
+}
+
+// Pair k of round r of the circle method over m players.
+__device__ __forceinline__ int2 circle_pair(int r, int k, int m) {
+  int i, j;
+  if (k == 0) {
+    i = 0;
+    j = 1 + r;
+  } else {
+    i = r + k;
+    if (i >= m - 1) i -= m - 1;
+    j = r - k;
+    if (j < 0) j += m - 1;
+    ++i;
+    ++j;
   }
-  __syncthreads();
+  return i < j ? make_int2(i, j) : make_int2(j, i);
+}
+
+// 1 / sqrt(x), x > 0: the hardware estimate and one third-order step
+__device__ __forceinline__ double inv_sqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// Barrier for LDS data alone: __syncthreads would also wait for the rotations
+// on their way to memory, twice a round.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int MAXB>
+__global__ void __launch_bounds__(kRotThreads) k_jacobi_rot(const double* __restrict__ Ag, int p,
+                                                            double* __restrict__ ev,
+                                                            double2* __restrict__ rot,
+                                                            int* __restrict__ n_sweeps,
+                                                            int* __restrict__ info) {
+  extern __shared__ double A[];           // [p (p + 1) / 2]
+  __shared__ double2 cs[kRotP / 2];
+  __shared__ int2 pr[kRotP / 2];
+  __shared__ double red[kRotThreads / 64];
+  __shared__ int sh_rot;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m = (p + 1) & ~1, half = m / 2;
+  auto block_sum = [&](double v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    __syncthreads();
+    if (lane == 0) red[wave] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int w = 0; w < kRotThreads / 64; ++w) t += red[w];
+    return t;
+  };
   // Frobenius norm (invariant under the rotations)
   double tot = 0.0;
-  for (int idx = tid; idx < p * p; idx += nt) tot += A[idx] * A[idx];
-  red[tid] = tot;
-  __syncthreads();
-  for (int w = nt / 2; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
+  for (int idx = tid; idx < p * p; idx += kRotThreads) {
+    const int i = idx / p, j = idx - i * p;
+    if (j <= i) {
+      const double v = Ag[idx];
+      A[tri(i, j)] = v;
+      tot += (i == j ? 1.0 : 2.0) * v * v;
+    }
   }
-  if (tid == 0) sh_norm = sqrt(red[0]);
-  __threadfence_block();
-  __syncthreads();
-  const double tiny = 1e-20 * sh_norm;
-  if (ZL) {
-    for (int idx = tid; idx < p * p; idx += nt) Z[idx] = (idx / p == idx % p) ? 1.0 : 0.0;
-    __syncthreads();
+  const double norm = sqrt(block_sum(tot));
+  const double tiny = 1e-20 * norm;
+  // this thread's blocks (a, b), a < b, of the half (half - 1) / 2
+  int ba[MAXB], bb[MAXB];
+#pragma unroll
+  for (int u = 0; u < MAXB; ++u) {
+    int t = tid + u * kRotThreads;
+    ba[u] = -1;
+    bb[u] = 0;
+    if (t < half * (half - 1) / 2) {
+      int b = 1;
+      while (b * (b + 1) / 2 <= t) ++b;
+      bb[u] = b;
+      ba[u] = t - b * (b - 1) / 2;
+    }
   }
-  for (int sweep = 0; sweep < 60; ++sweep) {
+  int sweep = 0;
+  for (; sweep < kMaxSweeps; ++sweep) {
     if (tid == 0) sh_rot = 0;
     __syncthreads();
     for (int r = 0; r < m - 1; ++r) {
-      for (int k = tid; k < half; k += nt) {
-        int i, j;
-        if (k == 0) { i = 0; j = 1 + r; }
-        else {
-          i = 1 + (r + k) % (m - 1);
-          j = 1 + (r - k + (m - 1)) % (m - 1);
-        }
-        if (i > j) { const int t = i; i = j; j = t; }
+      if (tid < half) {
+        const int2 ij = circle_pair(r, tid, m);
         double c = 1.0, s = 0.0;
-        if (j < p) {
-          const double aij = A[(size_t)i * p + j];
-          const double aii = A[(size_t)i * p + i], ajj = A[(size_t)j * p + j];
-          if (fabs(aij) > tiny && fabs(aij) > 1e-15 * sqrt(fabs(aii * ajj))) {
-            const double tau = (ajj - aii) / (2.0 * aij);
-            const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + t * t);
-            s = t * c;
+        if (ij.y < p) {
+          const int xii = tri(ij.x, ij.x), xjj = tri(ij.y, ij.y), xij = tri(ij.y, ij.x);
+          const double aij = A[xij], aii = A[xii], ajj = A[xjj];
+          if (fabs(aij) > tiny && aij * aij > 1e-30 * fabs(aii * ajj)) {
+            // cos 2phi = |d| / h, h = sqrt(d^2 + o^2); c = cos phi, s of o's and d's signs
+            const double d = ajj - aii, o = 2.0 * aij;
+            const double ih = inv_sqrt(fma(d, d, o * o));
+            const double c2 = fma(0.5 * fabs(d), ih, 0.5);
+            const double rc = inv_sqrt(c2);
+            const double hs = (d >= 0.0 ? 0.5 : -0.5) * o * ih;
+            c = c2 * rc;
+            s = hs * rc;
+            const double t = s * rc;
+            A[xii] = fma(-t, aij, aii);
+            A[xjj] = fma(t, aij, ajj);
+            A[xij] = 0.0;
             sh_rot = 1;
           }
         }
-        pi[k] = i;
-        pj[k] = j;
-        cs[k] = c;
-        sn[k] = s;
+        pr[tid] = ij;
+        cs[tid] = make_double2(c, s);
+        rot[((size_t)sweep * (m - 1) + r) * half + tid] = make_double2(c, s);
       }
-      __syncthreads();
-      // A <- J^T A J in one pass: a thread owns the 2 x 2 block of A at the
-      // rows of pair a and the columns of pair b, rotated by b's columns and
-      // then by a's rows (the same operations, in the same order, as a column
-      // pass followed by a row pass).  Entries at the padding index p do not
-      // exist.
-      // Lane l of every wave owns column pair b = l (half <= 64), the waves
-      // take the row pairs a in turn.
-      const int lb = tid & 63, nw = nt >> 6;
-      const bool own = lb < half;
-      const double sb = own ? sn[lb] : 0.0, cb = own ? cs[lb] : 1.0;
-      const int ib = own ? pi[lb] : 0, jb = own ? pj[lb] : p;
-      const bool rb = jb < p;
-      for (int a = own ? (tid >> 6) : half; a < half; a += nw) {
-        const double sa = sn[a];
-        if (sa == 0.0 && sb == 0.0) continue;
-        const int ia = pi[a], ja = pj[a];
-        const bool ra = ja < p;
-        const double ca = cs[a];
-        double x00 = A[(size_t)ia * p + ib];
-        double x01 = rb ? A[(size_t)ia * p + jb] : 0.0;
-        double x10 = ra ? A[(size_t)ja * p + ib] : 0.0;
-        double x11 = ra && rb ? A[(size_t)ja * p + jb] : 0.0;
-        if (sb != 0.0) {
-          const double y00 = cb * x00 - sb * x01, y01 = sb * x00 + cb * x01;
-          const double y10 = cb * x10 - sb * x11, y11 = sb * x10 + cb * x11;
-          x00 = y00; x01 = y01; x10 = y10; x11 = y11;
-        }
-        if (sa != 0.0) {
-          const double y00 = ca * x00 - sa * x10, y10 = sa * x00 + ca * x10;
-          const double y01 = ca * x01 - sa * x11, y11 = sa * x01 + ca * x11;
-          x00 = y00; x01 = y01; x10 = y10; x11 = y11;
-        }
-        A[(size_t)ia * p + ib] = x00;
-        if (rb) A[(size_t)ia * p + jb] = x01;
-        if (ra) A[(size_t)ja * p + ib] = x10;
-        if (ra && rb) A[(size_t)ja * p + jb] = x11;
-      }
-      // Z <- Z J: the same lane owns the same pair b in every row, the waves
-      // take the rows in turn, and each thread issues kZ rows' loads before
-      // its stores
-      constexpr int kZ = 8;
-      if (rb && sb != 0.0) {
-        for (int r0 = tid >> 6; r0 < p; r0 += kZ * nw) {
-          double zi[kZ], zj[kZ];
+      lds_barrier();
+      // A <- J^T A J on the block (a, b): b's columns, then a's rows.  Entries
+      // at the padding index p do not exist.
 #pragma unroll
-          for (int u = 0; u < kZ; ++u) {
-            const int row = r0 + u * nw;
-            zi[u] = zj[u] = 0.0;
-            if (row < p) {
-              zi[u] = Z[(size_t)row * p + ib];
-              zj[u] = Z[(size_t)row * p + jb];
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < kZ; ++u) {
-            const int row = r0 + u * nw;
-            if (row < p) {
-              Z[(size_t)row * p + ib] = cb * zi[u] - sb * zj[u];
-              Z[(size_t)row * p + jb] = sb * zi[u] + cb * zj[u];
-            }
-          }
-        }
+      for (int u = 0; u < MAXB; ++u) {
+        if (ba[u] < 0) continue;
+        const double2 ra = cs[ba[u]], rb = cs[bb[u]];
+        if (ra.y == 0.0 && rb.y == 0.0) continue;
+        const int2 ia = pr[ba[u]], ib = pr[bb[u]];
+        const bool ha = ia.y < p, hb = ib.y < p;
+        const int t00 = tri(ia.x, ib.x), t01 = tri(ia.x, ib.y), t10 = tri(ia.y, ib.x),
+                  t11 = tri(ia.y, ib.y);
+        const double x00 = A[t00];
+        const double x01 = hb ? A[t01] : 0.0, x10 = ha ? A[t10] : 0.0;
+        const double x11 = ha && hb ? A[t11] : 0.0;
+        const double y00 = rb.x * x00 - rb.y * x01, y01 = rb.y * x00 + rb.x * x01;
+        const double y10 = rb.x * x10 - rb.y * x11, y11 = rb.y * x10 + rb.x * x11;
+        A[t00] = ra.x * y00 - ra.y * y10;
+        if (hb) A[t01] = ra.x * y01 - ra.y * y11;
+        if (ha) A[t10] = ra.y * y00 + ra.x * y10;
+        if (ha && hb) A[t11] = ra.y * y01 + ra.x * y11;
       }
-      __threadfence_block();
-      __syncthreads();
+      lds_barrier();
     }
     if (sh_rot == 0) break;
     __syncthreads();
   }
-  if (ZL) {
-    for (int idx = tid; idx < p * p; idx += nt) Zg[idx] = Z[idx];
-    __syncthreads();
-  }
   // final check of the remaining off-diagonal mass
   double off = 0.0;
-  for (int idx = tid; idx < p * p; idx += nt)
-    if (idx / p != idx % p) off += A[idx] * A[idx];
-  red[tid] = off;
-  __syncthreads();
-  for (int w = nt / 2; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
+  for (int idx = tid; idx < p * p; idx += kRotThreads) {
+    const int i = idx / p, j = idx - i * p;
+    if (j < i) off += 2.0 * A[tri(i, j)] * A[tri(i, j)];
   }
-  if (tid == 0 && sqrt(red[0]) > 1e-10 * sh_norm) atomicOr(info, 2);
-  for (int i = tid; i < p; i += nt) ev[i] = A[(size_t)i * p + i];
-  for (int idx = tid; idx < p * p; idx += nt) Ag[idx] = A[idx];
+  off = block_sum(off);
+  if (tid == 0) {
+    if (sqrt(off) > 1e-10 * norm) atomicOr(info, 2);
+    *n_sweeps = sweep;
+  }
+  for (int i = tid; i < p; i += kRotThreads) ev[i] = A[tri(i, i)];
+}
+
+// Z = the product of k_jacobi_rot's rotations: one wave per row of Z, the row
+// in LDS, lane l taking pairs l and l + 64 of every round; the next round's
+// rotations are on their way while this one's are applied.
+__global__ void __launch_bounds__(64) k_jacobi_vectors(const double2* __restrict__ rot,
+                                                       const int* __restrict__ n_sweeps, int p,
+                                                       double* __restrict__ Z) {
+  __shared__ double z[kRotP + 2];
+  const int lane = threadIdx.x, row = blockIdx.x;
+  const int m = (p + 1) & ~1, half = m / 2;
+  for (int i = lane; i < m; i += 64) z[i] = i == row ? 1.0 : 0.0;
+  const int rounds = *n_sweeps * (m - 1);
+  const int k0 = min(lane, half - 1), k1 = min(lane + 64, half - 1);
+  constexpr int kU = 4;   // rounds of rotations in flight
+  double2 q0[kU], q1[kU];
+#pragma unroll
+  for (int u = 0; u < kU; ++u) {
+    const size_t o = (size_t)min(u, max(rounds - 1, 0)) * half;
+    q0[u] = rot[o + k0];
+    q1[u] = rot[o + k1];
+  }
+  int r = 0;
+  for (int t = 0; t < rounds; t += kU) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const double2 c0 = q0[u], c1 = q1[u];
+      const size_t o = (size_t)min(t + u + kU, rounds - 1) * half;
+      q0[u] = rot[o + k0];
+      q1[u] = rot[o + k1];
+      if (t + u < rounds) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (lane < half && c0.y != 0.0) {
+          const int2 ij = circle_pair(r, lane, m);
+          const double a = z[ij.x], b = z[ij.y];
+          z[ij.x] = c0.x * a - c0.y * b;
+          z[ij.y] = c0.y * a + c0.x * b;
+        }
+        if (lane + 64 < half && c1.y != 0.0) {
+          const int2 ij = circle_pair(r, lane + 64, m);
+          const double a = z[ij.x], b = z[ij.y];
+          z[ij.x] = c1.x * a - c1.y * b;
+          z[ij.y] = c1.y * a + c1.x * b;
+        }
+        if (++r == m - 1) r = 0;
+      }
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (int i = lane; i < p; i += 64) Z[(size_t)row * p + i] = z[i];
 }
 
 // Sorts the Ritz values in decreasing order (ties: lower index first), keeps
@@ -729,13 +785,28 @@ hipError_t launch_m2_apply(const double* M2, const double* Q, double* Y, int V, 
   return gemm(V, p, V, M2, V, Q, p, Y, p, true, pick, Q_set, s);
 }
 
-hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s) {
-  if (p <= kLdsPZ) {
-    hipLaunchKernelGGL(k_jacobi_lds<true>, dim3(1), dim3(1024), 0, s, A, Z, ev, p, info);
-    return hipGetLastError();
-  }
-  if (p <= kLdsP) {
-    hipLaunchKernelGGL(k_jacobi_lds<false>, dim3(1), dim3(1024), 0, s, A, Z, ev, p, info);
+size_t jacobi_scratch_doubles(int p) {
+  if (p > kRotP) return 0;
+  const size_t m = (p + 1) & ~1;
+  return 2 * (size_t)kMaxSweeps * (m - 1) * (m / 2);
+}
+
+hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, double* scratch, int* info,
+                         hipStream_t s) {
+  if (p <= kRotP) {
+    const size_t lds = sizeof(double) * p * (p + 1) / 2;
+    auto kernel = p <= 128 ? k_jacobi_rot<2> : k_jacobi_rot<5>;
+    if (lds > 60 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    double2* rot = reinterpret_cast<double2*>(scratch);
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(kRotThreads), lds, s, A, p, ev, rot, info + 2, info);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_jacobi_vectors, dim3(p), dim3(64), 0, s, rot, info + 2, p, Z);
     return hipGetLastError();
   }
   const int m = (p + 1) & ~1;

@@ -257,7 +257,7 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
   tlda::EigScratch& e = c->eig;
   if (e.p == p && e.Q) return TLDA_OK;
   dfree(e.Q); dfree(e.Y); dfree(e.T); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
-  dfree(e.fac);
+  dfree(e.fac); dfree(e.rot);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   e.p = 0;
   e.ws_doubles = 0;
@@ -271,6 +271,8 @@ tlda_status ensure_eig(tlda_ctx* c, int p) {
   HIP_OK(c, dalloc(&e.Binv, (size_t)p * p));
   HIP_OK(c, launch_zero(e.Binv, sizeof(double) * p * p, c->stream));
   HIP_OK(c, dalloc(&e.fac, tlda::chol_scratch_doubles(p)));
+  if (tlda::jacobi_scratch_doubles(p) > 0)
+    HIP_OK(c, dalloc(&e.rot, tlda::jacobi_scratch_doubles(p)));
   HIP_OK(c, dalloc(&e.ev, (size_t)p));
   HIP_OK(c, dalloc(&e.sel, D + (size_t)p * D));
   HIP_OK(c, dalloc(&e.mcand, V));
@@ -387,7 +389,7 @@ tlda_status refresh(tlda_ctx* c, bool warm) {
   // Rayleigh-Ritz: H = Q^T M2~ Q, eigenpairs by Jacobi, U = Q Z_top
   HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, nullptr, nullptr, c->stream));
   HIP_OK(c, tlda::launch_gram(q, y, e.G, V, p, true, e.part, nullptr, c->stream));
-  HIP_OK(c, tlda::launch_jacobi(e.G, e.Z, e.ev, p, e.info, c->stream));
+  HIP_OK(c, tlda::launch_jacobi(e.G, e.Z, e.ev, p, e.rot, e.info, c->stream));
   HIP_OK(c, tlda::launch_ritz_vectors(q, e.Z, e.ev, V, p, D, y, e.sel, c->stream));
   int info[4] = {0, 0, 0, 0};
   std::vector<double> eigD(D);
@@ -574,7 +576,7 @@ void destroy_all(tlda_ctx* c) {
   delete[] c->t_stop;
   tlda::EigScratch& e = c->eig;
   dfree(e.Q); dfree(e.Y); dfree(e.T); dfree(e.G); dfree(e.Z); dfree(e.ev); dfree(e.Binv);
-  dfree(e.fac);
+  dfree(e.fac); dfree(e.rot);
   dfree(e.sel); dfree(e.mcand); dfree(e.info); dfree(e.part); dfree(e.ws);
   dfree(c->cp.partial); dfree(c->cp.R1); dfree(c->cp.phi0); dfree(c->cp.grad); dfree(c->cp.X);
   dfree(c->cp.gsq);

@@ -84,10 +84,11 @@ struct EigScratch {
   double* ev = nullptr;    // [p]
   double* Binv = nullptr;  // [p][p]  inverse of the upper Cholesky factor (zeros below)
   double* fac = nullptr;   // tiles of the factorisation (chol_scratch_doubles)
+  double* rot = nullptr;   // rotations of the eigensolver (jacobi_scratch_doubles)
   double* sel = nullptr;   // [D + p*D] selected Ritz values and vectors
   double* mcand = nullptr; // [V]     M1 of the refresh in progress
   int* info = nullptr;     // [4]     device status words: 0 failures, 1 the last block needs
-                           //         no second Cholesky-QR pass (it is in T)
+                           //         no second Cholesky-QR pass (it is in T), 2 Jacobi sweeps
   double* warm = nullptr;  // Q or Y: the orthonormal block the last refresh converged to
   double* part = nullptr;  // row-chunk partials of the Gram products (gram_scratch_doubles)
   double* ws = nullptr;    // pieces of the product with M2 (dgemm_ws_doubles)
@@ -290,7 +291,12 @@ size_t chol_scratch_doubles(int p);
 hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
                                double* Binv, int* info, const int* skip, int* well,
                                hipStream_t s);
-hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, int* info, hipStream_t s);
+// Eigenpairs of the symmetric A (destroyed): values ev, vectors the columns of Z;
+// info[0] |= 2 when it does not converge, info[2] is written.  scratch:
+// jacobi_scratch_doubles(p)
+size_t jacobi_scratch_doubles(int p);
+hipError_t launch_jacobi(double* A, double* Z, double* ev, int p, double* scratch, int* info,
+                         hipStream_t s);
 // Out (V x p) = Q (V x p) Z (p x p)
 hipError_t launch_block_product(const double* Q, const double* Z, double* Out, int V, int p,
                                 const int* skip, hipStream_t s);
