@@ -30,6 +30,11 @@ constexpr int kTile = 16, kTileE = kTile * kTile, kMaxNb = 32;   // p <= 512
 
 __device__ __forceinline__ int tile_at(int i, int j) { return j * (j + 1) / 2 + i; }   // i <= j
 
+// the same tile in the order k_gram numbers them (by tile rows)
+__device__ __forceinline__ int part_tile(int i, int j, int nb) {
+  return i * nb - i * (i - 1) / 2 + (j - i);
+}
+
 __device__ __forceinline__ double lane_value(double v, int lane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
   const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
@@ -169,7 +174,9 @@ constexpr double kWell = 1e-4;
 // per SIMD, so that a tile being factored fits beside them).  Nothing is
 // written to memory before the last step, since every barrier would wait for
 // it.  skip (or NULL): nothing to do when it is set.  well (or NULL) receives 1
-// when the smallest diagonal entry of R is at least kWell of the largest.  INV: the block goes on to the inverse, its tiles in LDS (few tiles: a
+// when the smallest diagonal entry of R is at least kWell of the largest.
+// nz > 0: G holds the nz chunks of a Gram product's tiles (k_gram), which are
+// added here in chunk order: a launch less where there are few.  INV: the block goes on to the inverse, its tiles in LDS (few tiles: a
 // second launch would cost more than other compute units would save).
 template <int NW, int SLOTS, bool INV>
 __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, int p,
@@ -178,7 +185,7 @@ __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, 
                                                   double* __restrict__ Binv,
                                                   int* __restrict__ info,
                                                   const int* __restrict__ skip,
-                                                  int* __restrict__ well) {
+                                                  int* __restrict__ well, int nz) {
   constexpr int NB = panel_tiles(NW * SLOTS);
   if (skip != nullptr && *skip) return;
   // row k of R while it is applied (INV: every tile of R, kept)
@@ -200,13 +207,48 @@ __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, 
       while ((j + 1) * (j + 2) / 2 <= t) ++j;
       tj[s] = j;
       ti[s] = t - j * (j + 1) / 2;
+      if (nz > 0) {
+        const double* g = G + (size_t)part_tile(ti[s], j, nb) * kTileE;
+        acc[s] = doublex4{0.0, 0.0, 0.0, 0.0};
+        for (int z = 0; z < nz; z += 8) {   // 8 chunks' loads in flight
+          doublex4 c[8];
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        acc[s][r] = padded(G, p, ti[s] * kTile + 4 * r + row, j * kTile + col);
+          for (int u = 0; u < 8; ++u)
+            c[u] = load_tile(g + (size_t)min(z + u, nz - 1) * nt * kTileE, lane);
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (z + u < nz) acc[s] += c[u];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int gi = ti[s] * kTile + 4 * r + row, gj = j * kTile + col;
+          if (max(gi, gj) >= p) acc[s][r] = gi == gj ? 1.0 : 0.0;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          acc[s][r] = padded(G, p, ti[s] * kTile + 4 * r + row, j * kTile + col);
+      }
     }
   }
   double mx = 0.0;
-  for (int i = lane; i < p; i += 64) mx = fmax(mx, G[(size_t)i * p + i]);
+  for (int i = lane; i < p; i += 64) {
+    double g = 0.0;
+    if (nz > 0) {
+      const double* d = G + (size_t)part_tile(i / kTile, i / kTile, nb) * kTileE + i % kTile * (kTile + 1);
+      for (int z = 0; z < nz; z += 8) {
+        double c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = d[(size_t)min(z + u, nz - 1) * nt * kTileE];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (z + u < nz) g += c[u];
+      }
+    } else {
+      g = G[(size_t)i * p + i];
+    }
+    mx = fmax(mx, g);
+  }
   for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
   const double shift = shift_rel * mx;
 #pragma unroll
@@ -638,17 +680,18 @@ size_t chol_scratch_doubles(int p) {
 
 // Binv (p x p; its part below the diagonal must hold zeros, which stay)
 // becomes R^-1 of G + shift_rel max diag(G) I = R^T R; *info |= 1 on a pivot
-// that is not positive.  scratch: chol_scratch_doubles(p).
-hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
-                               double* Binv, int* info, const int* skip, int* well,
-                               hipStream_t s) {
+// that is not positive.  scratch: chol_scratch_doubles(p).  nz > 0: G is the
+// chunks of k_gram (nb <= 5).
+static hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
+                                      double* Binv, int* info, const int* skip, int* well, int nz,
+                                      hipStream_t s) {
   const int nb = (p + kTile - 1) / kTile;
   if (p < 1 || nb > kMaxNb) return hipErrorInvalidValue;
   double* tiles = scratch;
   double* dinv = tiles + (size_t)nb * (nb + 1) / 2 * kTileE;
 #define TLDA_CHOL(nw, slots, inv)                                                             \
   hipLaunchKernelGGL((k_chol<nw, slots, inv>), dim3(1), dim3(64 * nw), 0, s, G, p, shift_rel, \
-                     tiles, dinv, Binv, info, skip, well)
+                     tiles, dinv, Binv, info, skip, well, nz)
   if (nb <= 5) {
     TLDA_CHOL(4, 4, true);
     return hipGetLastError();
@@ -675,17 +718,21 @@ static int gram_chunks(int V, const GramShape& g, int blocks) {
 // for the one product of an inference, whose scratch every context keeps.
 constexpr int kGramBlocks = 1024, kProjectBlocks = 512;
 
-static hipError_t launch_gram_shape(const double* A, const double* B, const double* m, int V,
-                                    const GramShape& g, int blocks, double* part, double* G,
-                                    float* G32, const int* skip, hipStream_t s) {
-  int nz = gram_chunks(V, g, blocks);
+// The chunks alone; their number to nz.
+static hipError_t launch_gram_chunks(const double* A, const double* B, const double* m, int V,
+                                     const GramShape& g, int blocks, double* part, int& nz,
+                                     const int* skip, hipStream_t s) {
+  nz = gram_chunks(V, g, blocks);
   const int step = 4 * kGramWaves;
   const int chunk = ((V + nz - 1) / nz + step - 1) / step * step;
   nz = (V + chunk - 1) / chunk;
   hipLaunchKernelGGL(k_gram, dim3(g.units(), nz), dim3(64 * kGramWaves), 0, s, A, B, m, V, g, chunk,
                      part, skip);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  return hipGetLastError();
+}
+
+static hipError_t launch_gram_sum(const double* part, int nz, const GramShape& g, double* G,
+                                  float* G32, const int* skip, hipStream_t s) {
   hipLaunchKernelGGL(k_gram_sum, dim3(g.tiles() * (kTileE / 64)), dim3(256), 0, s, part, nz, g, G,
                      G32, skip);
   return hipGetLastError();
@@ -696,9 +743,26 @@ size_t gram_scratch_doubles(int V, int p, bool sym) {
   return (size_t)gram_chunks(V, g, kGramBlocks) * g.tiles() * kTileE;
 }
 hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
-                       double* part, const int* skip, hipStream_t s) {
-  return launch_gram_shape(A, B, nullptr, V, GramShape{p, p, sym}, kGramBlocks, part, G, nullptr,
-                           skip, s);
+                       double* part, hipStream_t s) {
+  const GramShape g{p, p, sym};
+  int nz = 0;
+  const hipError_t e = launch_gram_chunks(A, B, nullptr, V, g, kGramBlocks, part, nz, nullptr, s);
+  return e != hipSuccess ? e : launch_gram_sum(part, nz, g, G, nullptr, nullptr, s);
+}
+
+hipError_t launch_gram_chol(const double* A, double* G, int V, int p, double* part,
+                            double shift_rel, double* scratch, double* Binv, int* info,
+                            const int* skip, int* well, hipStream_t s) {
+  const GramShape g{p, p, true};
+  int nz = 0;
+  hipError_t e = launch_gram_chunks(A, A, nullptr, V, g, kGramBlocks, part, nz, skip, s);
+  if (e != hipSuccess) return e;
+  // up to 16 chunks (V <= 1024) of at most 15 tiles the factorisation adds itself
+  if (nz <= 16 && g.nb() <= 5)
+    return launch_chol_inverse(part, p, shift_rel, scratch, Binv, info, skip, well, nz, s);
+  e = launch_gram_sum(part, nz, g, G, nullptr, skip, s);
+  if (e != hipSuccess) return e;
+  return launch_chol_inverse(G, p, shift_rel, scratch, Binv, info, skip, well, 0, s);
 }
 
 size_t project_scratch_doubles(int V, int D, int K) {
@@ -707,8 +771,10 @@ size_t project_scratch_doubles(int V, int D, int K) {
 }
 hipError_t launch_project(const double* W, const double* m, const double* mu, int V, int D, int K,
                           double* part, double* A, float* A32, hipStream_t s) {
-  return launch_gram_shape(W, mu, m, V, GramShape{D, K, false}, kProjectBlocks, part, A, A32,
-                           nullptr, s);
+  const GramShape g{D, K, false};
+  int nz = 0;
+  const hipError_t e = launch_gram_chunks(W, mu, m, V, g, kProjectBlocks, part, nz, nullptr, s);
+  return e != hipSuccess ? e : launch_gram_sum(part, nz, g, A, A32, nullptr, s);
 }
 
 hipError_t launch_top_eig(const double* G, int n, float* step, hipStream_t s) {

@@ -300,13 +300,11 @@ tlda_status orthonormalise(tlda_ctx* c, const double* in, double* out, bool may_
   const int V = c->cfg.V, p = e.p;
   int* well = e.info + 1;
   const int* skip = may_skip ? well : nullptr;
-  HIP_OK(c, tlda::launch_gram(in, in, e.G, V, p, true, e.part, nullptr, c->stream));
-  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 1e-12, e.fac, e.Binv, e.info, nullptr,
-                                      may_skip ? well : nullptr, c->stream));
+  HIP_OK(c, tlda::launch_gram_chol(in, e.G, V, p, e.part, 1e-12, e.fac, e.Binv, e.info, nullptr,
+                                   may_skip ? well : nullptr, c->stream));
   HIP_OK(c, tlda::launch_block_product(in, e.Binv, e.T, V, p, nullptr, c->stream));
-  HIP_OK(c, tlda::launch_gram(e.T, e.T, e.G, V, p, true, e.part, skip, c->stream));
-  HIP_OK(c, tlda::launch_chol_inverse(e.G, p, 0.0, e.fac, e.Binv, e.info, skip, nullptr,
-                                      c->stream));
+  HIP_OK(c, tlda::launch_gram_chol(e.T, e.G, V, p, e.part, 0.0, e.fac, e.Binv, e.info, skip,
+                                   nullptr, c->stream));
   HIP_OK(c, tlda::launch_block_product(e.T, e.Binv, out, V, p, skip, c->stream));
   return TLDA_OK;
 }
@@ -388,7 +386,7 @@ tlda_status refresh(tlda_ctx* c, bool warm) {
   }
   // Rayleigh-Ritz: H = Q^T M2~ Q, eigenpairs by Jacobi, U = Q Z_top
   HIP_OK(c, tlda::launch_m2_apply(c->mom.M2, q, y, V, p, nullptr, nullptr, c->stream));
-  HIP_OK(c, tlda::launch_gram(q, y, e.G, V, p, true, e.part, nullptr, c->stream));
+  HIP_OK(c, tlda::launch_gram(q, y, e.G, V, p, true, e.part, c->stream));
   HIP_OK(c, tlda::launch_jacobi(e.G, e.Z, e.ev, p, e.rot, e.info, c->stream));
   HIP_OK(c, tlda::launch_ritz_vectors(q, e.Z, e.ev, V, p, D, y, e.sel, c->stream));
   int info[4] = {0, 0, 0, 0};
@@ -1071,8 +1069,7 @@ tlda_status tlda_rebase_phi(tlda_ctx* c, float* Phi) {
   CHECK_ARG(c, c->wh.ready && c->wh.prev_ready, TLDA_ERR_STATE,
             "no previous whitening to rebase from");
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
-  HIP_OK(c, tlda::launch_gram(c->wh.U, c->wh.Uprev, c->wh.C, V, D, false, c->wh.part, nullptr,
-                              c->stream));
+  HIP_OK(c, tlda::launch_gram(c->wh.U, c->wh.Uprev, c->wh.C, V, D, false, c->wh.part, c->stream));
   HIP_OK(c, tlda::launch_rebase(c->wh.C, c->wh.eig, c->wh.eigprev, D, K, Phi, c->stream));
   return TLDA_OK;
 }

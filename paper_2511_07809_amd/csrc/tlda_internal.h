@@ -279,18 +279,18 @@ hipError_t launch_random_block(double* Q, int V, int p, uint64_t seed, hipStream
 hipError_t launch_m2_apply(const double* M2, const double* Q, double* Y, int V, int p,
                            const int* pick, const double* Q_set, hipStream_t s);
 // G (p x p) = A^T B for V x p blocks; sym: A^T B is symmetric, only its upper
-// tiles are formed.  part: gram_scratch_doubles(V, p, sym) doubles.  Here and
-// below: nothing is done where *skip is set (skip may be NULL)
+// tiles are formed.  part: gram_scratch_doubles(V, p, sym) doubles
 size_t gram_scratch_doubles(int V, int p, bool sym);
 hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p, bool sym,
-                       double* part, const int* skip, hipStream_t s);
-// Binv <- R^-1 with G + shift_rel max diag(G) I = R^T R (R upper; p <= 512);
-// *info |= 1 on a pivot that is not positive; *well (or NULL) tells whether
-// one Cholesky-QR pass with it leaves the block's columns orthonormal to 1e-8
+                       double* part, hipStream_t s);
+// Binv <- R^-1 with A^T A + shift_rel max diag(A^T A) I = R^T R (R upper; p <=
+// 512); *info |= 1 on a pivot that is not positive; *well (or NULL) tells
+// whether one Cholesky-QR pass with it leaves the block's columns orthonormal
+// to 1e-8.  Here and below: nothing is done where *skip is set (skip may be NULL)
 size_t chol_scratch_doubles(int p);
-hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, double* scratch,
-                               double* Binv, int* info, const int* skip, int* well,
-                               hipStream_t s);
+hipError_t launch_gram_chol(const double* A, double* G, int V, int p, double* part,
+                            double shift_rel, double* scratch, double* Binv, int* info,
+                            const int* skip, int* well, hipStream_t s);
 // Eigenpairs of the symmetric A (destroyed): values ev, vectors the columns of Z;
 // info[0] |= 2 when it does not converge, info[2] is written.  scratch:
 // jacobi_scratch_doubles(p)
