@@ -36,7 +36,11 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int fused_waves(int DQ, int KQ) { return (DQ > 64 || KQ > 64) ? 8 : 4; }
 constexpr int fused_min_waves(int DQ, int KQ) { return (DQ > 64 || KQ > 64) ? 4 : 3; }
 
-template <int DQ, int KQ, int T, int G>
+// P > 1 (small batches): P lane groups share a document, group g taking
+// nonzeros g NB .. g NB + NB - 1 of every P NB, each lane fetching its own
+// group's entries (the G lanes of a group read one address), and their sums
+// are combined by a butterfly.
+template <int DQ, int KQ, int T, int G, int P = 1>
 __global__ void __launch_bounds__(64 * fused_waves(DQ, KQ), fused_min_waves(DQ, KQ)) k_whiten_cp(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     const float* __restrict__ val, int n_rows, const float* __restrict__ W32,
@@ -55,7 +59,8 @@ __global__ void __launch_bounds__(64 * fused_waves(DQ, KQ), fused_min_waves(DQ, 
   // live through the gathers and spilled); otherwise tiles w, w + NW, ...
   constexpr bool kColOwner = NW > 4 && 2 * NCT > NW;
   constexpr int RT = kColOwner ? NDT : (NRT + NW - 1) / NW;
-  constexpr int RPW = 64 / G;              // documents per wave per whitening pass
+  constexpr int GP = G * P;                // lanes per document
+  constexpr int RPW = 64 / GP;             // documents per wave per whitening pass
   constexpr int RPB = NW * RPW;            // documents per block per pass
   constexpr int NB = NW > 4 ? 4 : 8;       // nonzeros per gather step (wide instances: 4,
                                            // so that their 128 registers hold the rest)
@@ -97,7 +102,7 @@ __global__ void __launch_bounds__(64 * fused_waves(DQ, KQ), fused_min_waves(DQ, 
     // ---- 1. whitening of the tile into LDS ----
 #pragma unroll 1
     for (int pass = 0; pass < PASSES; ++pass) {
-      const int lr = pass * RPB + wave * RPW + lane / G;   // row within the tile
+      const int lr = pass * RPB + wave * RPW + lane / GP;   // row within the tile
       const int row = tile * T + lr;
       const bool valid = lr < T && row < n_rows;
       int b = 0, e = 0;
@@ -107,6 +112,41 @@ __global__ void __launch_bounds__(64 * fused_waves(DQ, KQ), fused_min_waves(DQ, 
       }
       float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
       float Lp = 0.f;
+      if constexpr (P > 1) {
+        for (int jb = b + lane % GP / G * NB; jb < e; jb += P * NB) {
+          int c[NB];
+          float v[NB];
+          float4 w[NB];
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            const int j = min(jb + t, e - 1);
+            c[t] = col_idx[j];
+            v[t] = val[j];
+          }
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            if (jb + t >= e) v[t] = 0.f;
+            w[t] = *reinterpret_cast<const float4*>(W32 + (uint32_t)c[t] * (uint32_t)Dp +
+                                                    (uint32_t)c4);
+          }
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            Lp += v[t];
+            a.x = fmaf(v[t], w[t].x, a.x);
+            a.y = fmaf(v[t], w[t].y, a.y);
+            a.z = fmaf(v[t], w[t].z, a.z);
+            a.w = fmaf(v[t], w[t].w, a.w);
+          }
+        }
+#pragma unroll
+        for (int off = G; off < GP; off <<= 1) {
+          Lp += __shfl_xor(Lp, off, GP);
+          a.x += __shfl_xor(a.x, off, GP);
+          a.y += __shfl_xor(a.y, off, GP);
+          a.z += __shfl_xor(a.z, off, GP);
+          a.w += __shfl_xor(a.w, off, GP);
+        }
+      } else
       for (int jb = b; jb < e; jb += NB) {
         int cidx[SLOTS];
         float cval[SLOTS];
@@ -137,8 +177,11 @@ __global__ void __launch_bounds__(64 * fused_waves(DQ, KQ), fused_min_waves(DQ, 
         }
       }
       float L = Lp;
+      if constexpr (P == 1) {   // (with P > 1 the lanes of a group hold the same counts)
 #pragma unroll
-      for (int off = 1; off < G; off <<= 1) L += __shfl_xor(L, off, G);
+        for (int off = 1; off < G; off <<= 1) L += __shfl_xor(L, off, G);
+      }
+      const bool first = P == 1 || lane % GP < G;   // the group that stores
       const int kept = (valid && L >= 3.f) ? 1 : 0;
       float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
       if (kept && active) {
@@ -148,15 +191,15 @@ __global__ void __launch_bounds__(64 * fused_waves(DQ, KQ), fused_min_waves(DQ, 
         x.z = fmaf(a.z, invL, -mw.z);
         x.w = fmaf(a.w, invL, -mw.w);
       }
-      if (in_lds && lr < T) *reinterpret_cast<float4*>(Xs + lr * LDX + c4) = x;
-      if (Xout != nullptr && valid && active) {
+      if (in_lds && lr < T && first) *reinterpret_cast<float4*>(Xs + lr * LDX + c4) = x;
+      if (Xout != nullptr && valid && active && first) {
         float* out = Xout + (size_t)row * D;
         if (c4 + 0 < D) out[c4 + 0] = x.x;
         if (c4 + 1 < D) out[c4 + 1] = x.y;
         if (c4 + 2 < D) out[c4 + 2] = x.z;
         if (c4 + 3 < D) out[c4 + 3] = x.w;
       }
-      kept_total += __popcll(__ballot(kept && gl == 0));
+      kept_total += __popcll(__ballot(kept && gl == 0 && first));
     }
     __syncthreads();
     // ---- 2. S = X_t Phi, squared into LDS ----
@@ -900,6 +943,37 @@ hipError_t launch_wide(const tlda_csr_batch& b, const float* W32, const float* m
   return hipGetLastError();
 }
 
+// Small batches of narrow shapes: 16 lanes per document whatever G is, and
+// 16-row tiles.  With G lanes (2 at D = 5) a document's nonzeros go 8 at a
+// time, two round trips each, and 1000 documents are 16 blocks: latency is all
+// there is (11.3 us for 1000 documents of 33 words); 16 lanes take 64 of them at
+// once, on 63 blocks.  Steps at D = K = 5, 51 tokens: 15.0 -> 9.3 us for 1000
+// documents, 16.0 -> 12.6 for 16 000; at 30 000 both take 17.3 and at 60 000
+// this takes 25.0 against 21.9 (the lanes' redundant reads then count; at D = 20
+// the two cross between 30 000 and 60 000 as well).
+constexpr int kSmallRows = 16384, kSmallTile = 16;
+bool fused_small(int D, int K, int n_rows) {
+  return mfma_bucket(D) <= 32 && mfma_bucket(K) <= 64 && D > 0 && n_rows <= kSmallRows;
+}
+
+template <int DQ, int KQ>
+hipError_t launch_fused_small(int G, const tlda_csr_batch& b, const float* W32, const float* mw32,
+                              int D, int Dp, const float* Phi, int K, int nblk, float* partial,
+                              int* block_counts, float* Xout, float* phi_copy, hipStream_t s) {
+  auto go = [&](auto kernel) {
+    launch_main(kernel, dim3(nblk), dim3(64 * fused_waves(DQ, KQ)), 0, s, b.row_ptr, b.col_idx,
+                b.val, b.n_rows, W32, mw32, D, Dp, Phi, K, nblk, partial, block_counts, Xout,
+                phi_copy);
+    return hipGetLastError();
+  };
+  switch (G) {
+    case 1: return go(k_whiten_cp<DQ, KQ, kSmallTile, 1, 16>);
+    case 2: return go(k_whiten_cp<DQ, KQ, kSmallTile, 2, 8>);
+    case 4: return go(k_whiten_cp<DQ, KQ, kSmallTile, 4, 4>);
+    default: return go(k_whiten_cp<DQ, KQ, kSmallTile, 8, 2>);
+  }
+}
+
 template <int DQ, int KQ, int T, int G>
 hipError_t launch_fused_t(const tlda_csr_batch& b, const float* W32, const float* mw32, int D,
                           int Dp, const float* Phi, int K, int nblk, float* partial,
@@ -945,7 +1019,8 @@ namespace {
 bool fused_wide(int D, int K) { return mfma_bucket(D) > 64 || mfma_bucket(K) > 64; }
 }  // namespace
 
-int fused_tile_rows(int D, int K) {
+int fused_tile_rows(int D, int K, int n_rows) {
+  if (fused_small(D, K, n_rows)) return kSmallTile;
   if (mfma_bucket(D) >= 64 && mfma_bucket(K) >= 64) return 48;   // the hybrid kernel
   return fused_wide(D, K) ? 32 : cp_mfma_tile_rows(D, K);        // 8-wave : 4-wave
 }
@@ -996,10 +1071,19 @@ hipError_t launch_whiten_cp(const tlda_csr_batch& b, const float* W32, const flo
     return launch_hyb<64, 64, 16, 16>(b, W32, mw32, D, Dp, Dt, tail_base, Phi, K, nblk, partial,
                                       block_counts, Xout, phi_copy, gsq, s);
   }
-  const int T = fused_tile_rows(D, K);
+  const int T = fused_tile_rows(D, K, b.n_rows);
   int G = Dp / 4;   // lanes per document: Dp is 4, 8, 16, 32 or 64 here
   if (G < 1) G = 1;
   if (G > 16) G = 16;
+  if (partial != nullptr && fused_small(D, K, b.n_rows)) {
+#define TLDA_SMALL(DQ_, KQ_)                                                                     \
+  if (dq == DQ_ && kq == KQ_)                                                                    \
+    return launch_fused_small<DQ_, KQ_>(G, b, W32, mw32, D, Dp, Phi, K, nblk, partial,           \
+                                        block_counts, Xout, phi_copy, s);
+    TLDA_SMALL(16, 16) TLDA_SMALL(16, 32) TLDA_SMALL(16, 64)
+    TLDA_SMALL(32, 16) TLDA_SMALL(32, 32) TLDA_SMALL(32, 64)
+#undef TLDA_SMALL
+  }
 #define TLDA_FUSED(DQ_, KQ_)                                                                   \
   if (dq == DQ_ && kq == KQ_)                                                                  \
     return T == 64 ? launch_fused_g<DQ_, KQ_, 64>(G, b, W32, mw32, D, Dp, Phi, K, nblk, partial, \

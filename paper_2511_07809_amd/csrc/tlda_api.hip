@@ -435,7 +435,7 @@ tlda_status fused_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float* 
   if (is_bf16(c)) {
     nblk = bf16_grid(c, 0, b->n_rows);
   } else {
-    const int T = tlda::fused_tile_rows(D, K);
+    const int T = tlda::fused_tile_rows(D, K, b->n_rows);
     const int ntiles = (b->n_rows + T - 1) / T;
     if (c->tune.fused_blocks <= 0) {
       int per_cu = 0;
@@ -461,7 +461,7 @@ tlda_status fused_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float* 
   // kGramOnceDK entries)
   const bool gram_in_kernel =
       is_bf16(c) || (tlda::fused_forms_gram(D, K) &&
-                     (D * K >= tlda::kGramOnceDK || tlda::fused_tile_rows(D, K) == 48));
+                     (D * K >= tlda::kGramOnceDK || tlda::fused_tile_rows(D, K, b->n_rows) == 48));
   st = begin_use(c, b);
   if (st != TLDA_OK) return st;
   HIP_OK(c, timing_start(c));

@@ -337,7 +337,7 @@ int mfma_bucket(int n);
 int cp_mfma_tile_rows(int D, int K);
 // fused whitening + CP reduction
 bool fused_supported(int D, int K, int Dp);
-int fused_tile_rows(int D, int K);        // row tile of the fused kernel for this shape
+int fused_tile_rows(int D, int K, int n_rows);   // row tile of the fused kernel for this batch
 // With partial == nullptr, launch_whiten_cp only stores in *block_counts how
 // many blocks of the kernel it would launch can be resident on one CU.
 // Dt > 0: W32 also holds, from element tail_base on, a [V][Dt] copy of the
