@@ -16,13 +16,11 @@
 // g_d = 2 l3 and e = -(c2/c3) l2 (s^2 - q) + (alpha0^2/c3) r^2 (zero for
 // dropped documents).
 //
-// k_classic_z forms Z (FP32, V x Kp) and r once per step.  k_classic_cp runs
-// over tiles of 16 documents: phase 1 (a wave per document) gathers the Z rows
-// of the document's words for s, q and the coefficients; phase 2 stages the
-// tile's nonzero rows (W rows with their scaled Z rows) in LDS, kRows at a
-// time and double-buffered, and accumulates the D x K outer products on FP32
-// matrix cores.  Each block writes its partial sum and its kept-document
-// count; the shared finish kernel adds them in block order, forms the
+// k_classic_z forms Z (FP32, V x Kp) and r once per step.  k_classic_cp gathers
+// the Z rows of a document's words for s, q and the coefficients, turns them
+// into reduction rows, and accumulates the D x K outer products with the W rows
+// on FP32 matrix cores.  Each block writes its partial sum and its
+// kept-document count; the shared finish kernel adds them in block order, forms the
 // gradient with the penalty term and updates Phi.
 #include "tlda_internal.h"
 
@@ -30,9 +28,21 @@ namespace tlda {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kDocs = 16;    // documents per tile
-constexpr int kRows = 16;    // reduction rows per staged chunk (two buffers)
+constexpr int kDocs = 16;    // documents per tile of the BF16 kernel
+constexpr int kRing = 48;    // reduction rows that a wave of the FP32 kernel keeps in LDS
+// Waves per block of the FP32 kernel (one block per CU): three per SIMD where
+// the 4 NDT NCT registers of a wave's sums leave 168 for all (131 at 16 tiles),
+// else two (256).
+constexpr int classic_waves(int ndt, int nct) { return ndt * nct <= 16 ? 12 : 8; }
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// The lanes of a wave exchange data through LDS: what was written before is
+// visible to the others after it (a wave's LDS operations complete in order,
+// so this only holds the compiler's order).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // Z[w][k] = sum_d W32[w][d] Phi[d][k] (zero for K <= k < Kp); block 0 also
 // writes r[k] = sum_d mw32[d] Phi[d][k] and the copy of Phi that the finish
@@ -69,206 +79,309 @@ __global__ void __launch_bounds__(kThreads) k_classic_z(const float* __restrict_
   }
 }
 
-template <int DQ, int KQ>
-__global__ void __launch_bounds__(kThreads, 2) k_classic_cp(
+// A wave works alone on a run of consecutive documents; no wave waits for
+// another before the block's sums are added at the end.  For each document
+//   phase 1: lane k takes column k.  The Z rows of the document's words, 32 at
+//     a time, come straight into registers and give s, q, L and the
+//     coefficients a, b, g;
+//   the reduction rows c (a + b z + g z^2) are formed from the same registers
+//     and put into the wave's ring of kRing rows in LDS (documents of more than
+//     32 words gather their Z rows a second time for it);
+//   the Z rows of the next document are asked for, and
+//   phase 2: as long as the ring holds 16 rows they go through the matrix
+//     cores, four at a time: B from the ring, A (the W rows) straight from
+//     memory into the operand registers, 16 rows ahead of their use.  The rows
+//     of a run are consecutive nonzeros, so this side needs no document.
+// Each wave keeps all NDT x NCT tiles of the D x K sum.  K > 64 is split over
+// gridDim.y: the columns do not depend on each other.
+//
+// What bounds it: issue slots and the latency of the gathers.  131072 documents
+// of 20 words at D = K = 50, V = 20000 (2.52 million nonzeros, 1.35 GB through
+// L2) take 293 us: the matrix cores are busy for 140 of them, the vector ALU
+// for about 75 (per nonzero row two offsets, two readlanes, four operations for
+// L, s and q, three for the reduction row).  Tiles of 16 documents per block of
+// four waves, with Z gathered twice, staged in LDS and a barrier per 16 rows,
+// took 475 us.  Z rows kept in LDS between the phases took 350 us: 20 KB a wave
+// leave two waves per SIMD, where a ring of 12 KB leaves three.  A 64-bit
+// multiply for each row's address costs 8 us, scalar multiplies 25 us.  The W
+// rows of a batch are asked for while the batch before is multiplied; holding
+// its products back until all of them are asked for costs 7 us.  The wait at
+// the top of the loop, where nothing is in flight that was not asked for before
+// the last products, lets the next products start without waiting for the Z
+// rows that are asked for just ahead of them: 40 us less.
+//
+// (V <= 131072: words take 24 bits, and 32 reach all of W and Z.)
+template <int NDT, int NCT>
+__global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     const float* __restrict__ val, int n_rows, const float* __restrict__ W32, int Dp,
     const float* __restrict__ Z, int Kp, const float* __restrict__ mw32,
-    const float* __restrict__ r_g, int D, int K, float c2r, float a0r, int nblk,
+    const float* __restrict__ r_g, int D, int K, float c2r, float a0r,
     float* __restrict__ partial, int* __restrict__ block_counts) {
-  constexpr int LDA = DQ + 4, LDB = KQ + 4;
-  constexpr int NCT = KQ / 16, NDT = DQ / 16, NRT = NDT * NCT;
-  constexpr int RT = (NRT + 3) / 4;
-  constexpr int NK = (KQ + 63) / 64;                        // phase-1 columns per lane
-  constexpr int GA = DQ / 4, GB = KQ / 4;                   // float4 groups per staged row
-  constexpr int TPR = kThreads / kRows;                     // threads per staged row
-  constexpr int UA = (GA + TPR - 1) / TPR, UB = (GB + TPR - 1) / TPR;
-  constexpr int NB = 8;                                     // nonzeros per gather step
-  static_assert(kThreads % kRows == 0, "staging maps whole rows to threads");
-  __shared__ __attribute__((aligned(16))) float As[2][kRows * LDA];
-  __shared__ __attribute__((aligned(16))) float Bs[2][kRows * LDB];
-  __shared__ __attribute__((aligned(16))) float Al[kDocs * LDB];
-  __shared__ __attribute__((aligned(16))) float Be[kDocs * LDB];
-  __shared__ float gam[kDocs];
-  __shared__ int rps[kDocs + 1];
-  __shared__ float rsh[KQ];
-  __shared__ float dsh[4][KQ];
-  __shared__ int wave_kept[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NW = classic_waves(NDT, NCT);
+  extern __shared__ __attribute__((aligned(16))) char ring_lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, l4 = lane >> 4;
-  const int srow = tid / TPR, ssub = tid % TPR;   // staged row and column-group lane
+  const int k0 = blockIdx.y * 64;
+  char* ring = ring_lds + wave * (kRing * 256);
+  // columns past Kp repeat the last one (they reach no output)
+  const int kc = k0 + lane < Kp ? k0 + lane : Kp - 1;
+  const unsigned zoff = 4u * (unsigned)kc;
+  const char* Zb = reinterpret_cast<const char*>(Z);
+  const float rk = r_g[kc];
+  const char* Wb = reinterpret_cast<const char*>(W32);
+  const unsigned woff = 4u * (unsigned)(l16 < Dp ? l16 : Dp - 1);
+  const unsigned wstride = 4u * (unsigned)Dp, zstride = 4u * (unsigned)Kp;
 
-  for (int k = tid; k < KQ; k += kThreads) rsh[k] = k < K ? r_g[k] : 0.f;
-  float dl[NK];
+  floatx4 acc[NDT][NCT];
 #pragma unroll
-  for (int u = 0; u < NK; ++u) dl[u] = 0.f;
-  floatx4 acc[RT];
+  for (int i = 0; i < NDT; ++i)
 #pragma unroll
-  for (int q = 0; q < RT; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-  int kept_total = 0;
-  int buf = 0;
+    for (int j = 0; j < NCT; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float es = 0.f;
+  int kept = 0;
 
-  const int ntiles = (n_rows + kDocs - 1) / kDocs;
-  for (int tile = blockIdx.x; tile < ntiles; tile += nblk) {
-    const int t0 = tile * kDocs;
-    const int nd = n_rows - t0 < kDocs ? n_rows - t0 : kDocs;
-    __syncthreads();   // the previous tile's LDS reads are done
-    if (tid <= kDocs) rps[tid] = row_ptr[t0 + (tid < nd ? tid : nd)];
-    __syncthreads();
-    // ---- phase 1: per-document s, q, L and coefficients (a wave per document) ----
-    for (int ld = wave; ld < kDocs; ld += 4) {
-      float s[NK], q[NK];
+  const int run = blockIdx.x * NW + wave, runs = gridDim.x * NW;
+  const int d0 = (int)((long long)n_rows * run / runs);
+  const int d1 = (int)((long long)n_rows * (run + 1) / runs);
+  const int nz0 = __builtin_amdgcn_readfirstlane(row_ptr[d0]);
+  const int nz1 = __builtin_amdgcn_readfirstlane(row_ptr[d1]);
+
+  // ---- A side: the W rows of the next 16 nonzeros, their words 16 further ----
+  float an[4][NDT];
+  int ac = 0;                 // the word of nonzero l16 of them
+  int anext = nz0 + l16;      // the first nonzero whose word is not asked for yet
+  auto load_cols = [&]() {
+    ac = col_idx[anext < nz1 ? anext : nz1 - 1];
+    anext += 16;
+  };
+  auto load_a = [&]() {
 #pragma unroll
-      for (int u = 0; u < NK; ++u) s[u] = q[u] = 0.f;
-      float L = 0.f;
-      if (ld < nd) {
-        const int b = rps[ld], e = rps[ld + 1];
-        for (int jb = b; jb < e; jb += NB) {
-          int mc = 0;
-          float mv = 0.f;
-          if (lane < NB && jb + lane < e) {
-            mc = col_idx[jb + lane];
-            mv = val[jb + lane];
-          }
-          float zv[NB][NK];
+    for (int i = 0; i < 4; ++i) {
+      const unsigned c = (unsigned)__shfl(ac, 4 * i + l4, 64);
+      unsigned o = __umul24(c, wstride) + woff;
+      asm("" : "+v"(o));
+      const float* w = reinterpret_cast<const float*>(Wb + o);
 #pragma unroll
-          for (int t = 0; t < NB; ++t) {
-            const int c = __shfl(mc, t, 64);   // 0 (a valid row) past the document's end
+      for (int t = 0; t < NDT; ++t) an[i][t] = w[16 * t];
+    }
+  };
+  int head = 0;     // the ring's first row not yet multiplied, a multiple of 16
+  int fill = 0;     // rows from there on
+  auto multiply = [&]() {   // 16 rows
+    float a[4][NDT];
 #pragma unroll
-            for (int u = 0; u < NK; ++u) {
-              const int k = lane + 64 * u;
-              zv[t][u] = k < Kp ? Z[(size_t)c * Kp + k] : 0.f;
-            }
-          }
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int t = 0; t < NB; ++t) {
-            const float v = __shfl(mv, t, 64);   // 0 past the document's end
+      for (int t = 0; t < NDT; ++t) a[i][t] = an[i][t];
+    load_a();
+    load_cols();
+    const char* rows = ring + head * 256 + l4 * 256 + 4 * l16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float bb[NCT];
+#pragma unroll
+      for (int c = 0; c < NCT; ++c)
+        bb[c] = *reinterpret_cast<const float*>(rows + 1024 * i + 64 * c);
+#pragma unroll
+      for (int t = 0; t < NDT; ++t)
+#pragma unroll
+        for (int c = 0; c < NCT; ++c)
+          acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][t], bb[c], acc[t][c], 0, 0, 0);
+    }
+    fill -= 16;
+    head = head + 16 == kRing ? 0 : head + 16;
+  };
+
+  // ---- B side: segments of at most 32 entries of one document ----
+  int rp = 0;               // row_ptr[dbase + lane]
+  int dbase = d0;
+  auto load_rp = [&](int d) {
+    dbase = d;
+    rp = row_ptr[d + lane < d1 ? d + lane : d1];
+  };
+  // a segment: the document, its first entry and entries, the segment's first
+  // entry; documents of more than 32 entries are passed over twice
+  struct Seg {
+    int d, b, n, j, pass;
+    __device__ int count() const { return n - j < 32 ? n - j : 32; }
+    __device__ bool last() const { return j + 32 >= n; }
+    __device__ bool puts() const { return n <= 32 || pass == 1; }
+  };
+  auto next = [&](const Seg& x) {
+    Seg y = x;
+    y.j = x.j + 32;
+    if (x.last()) {
+      y.j = 0;
+      y.pass = 1;
+      if (x.puts()) {
+        y.pass = 0;
+        y.d = x.d + 1;
+        y.n = 0;
+        if (y.d < d1) {
+          if (y.d + 1 - dbase > 63) load_rp(y.d);
+          y.b = __builtin_amdgcn_readlane(rp, y.d - dbase);
+          y.n = __builtin_amdgcn_readlane(rp, y.d + 1 - dbase) - y.b;
+        }
+      }
+    }
+    return y;
+  };
+  // word and count of entry `lane`
+  auto load_entries = [&](const Seg& x, int& c, float& v) {
+    const int count = x.count();
+    c = 0;
+    v = 0.f;
+    if (count > 0) {
+      c = col_idx[x.b + x.j + (lane < count ? lane : count - 1)];
+      if (lane < count) v = val[x.b + x.j + lane];
+    }
+  };
+  // the offsets of this segment's Z rows, the words of the next one and the one after
+  int c0 = 0, c1 = 0, c2 = 0;
+  float v0 = 0.f, v1 = 0.f, v2 = 0.f;
+  // the Z rows at offsets c0, four at a time (those that fill the last four have
+  // no count)
+  float z[32];
+  auto load_z = [&](int count) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (4 * c < count) {
+#pragma unroll
+        for (int t = 4 * c; t < 4 * c + 4; ++t) {
+          unsigned o = (unsigned)__builtin_amdgcn_readlane(c0, t) + zoff;
+          asm("" : "+v"(o));   // the base stays in scalar registers
+          z[t] = *reinterpret_cast<const float*>(Zb + o);
+        }
+      }
+  };
+  Seg s0{d0, nz0, 0, 0, 0}, s1, s2;
+  if (nz1 > nz0) {
+    load_cols();
+    load_a();
+    load_cols();
+  }
+  if (d0 < d1) {
+    load_rp(d0);
+    s0.n = __builtin_amdgcn_readlane(rp, 1) - nz0;
+  }
+  load_entries(s0, c0, v0);
+  s1 = next(s0);
+  load_entries(s1, c2, v2);
+  c0 = (int)__umul24((unsigned)c0, zstride);
+  load_z(s0.count());
+  float s = 0.f, q = 0.f, L = 0.f, al = 0.f, be = 0.f, g = 0.f;
+  while (s0.d < d1 || fill > 0) {
+    // everything asked for has arrived: the Z rows were asked for before the
+    // products below, the W rows at their start, the entries before that
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    c1 = c2;
+    v1 = v2;
+    s2 = next(s1);
+    load_entries(s2, c2, v2);
+    const int cnt = s0.count();
+    if (s0.pass == 0 && s0.d < d1) {
+      if (s0.j == 0) s = q = L = 0.f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (4 * c < cnt) {
+#pragma unroll
+          for (int t = 4 * c; t < 4 * c + 4; ++t) {
+            const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v0), t));
             L += v;
-#pragma unroll
-            for (int u = 0; u < NK; ++u) {
-              s[u] = fmaf(v, zv[t][u], s[u]);
-              q[u] = fmaf(v * zv[t][u], zv[t][u], q[u]);
-            }
+            s = fmaf(v, z[t], s);
+            q = fmaf(v * z[t], z[t], q);
           }
         }
+      if (s0.last()) {
+        const bool keep = L >= 3.f;   // L is the same on every lane
+        const float l2 = keep ? 1.0f / (L * (L - 1.0f)) : 0.f;
+        const float l3 = keep ? l2 / (L - 2.0f) : 0.f;
+        const float d2 = s * s - q;
+        al = l3 * d2 - 2.0f * c2r * l2 * rk * s;
+        be = -2.0f * l3 * s + 2.0f * c2r * l2 * rk;
+        g = 2.0f * l3;
+        if (keep) es += -c2r * l2 * d2 + a0r * rk * rk;
+        kept += __builtin_amdgcn_readfirstlane(keep ? 1 : 0);
       }
-      const bool keep = ld < nd && L >= 3.f;   // L is the same on every lane
-      const float l2 = keep ? 1.0f / (L * (L - 1.0f)) : 0.f;
-      const float l3 = keep ? l2 / (L - 2.0f) : 0.f;
-#pragma unroll
-      for (int u = 0; u < NK; ++u) {
-        const int k = lane + 64 * u;
-        if (k < KQ) {
-          const float rk = rsh[k], sk = s[u], d2 = s[u] * s[u] - q[u];
-          Al[ld * LDB + k] = l3 * d2 - 2.0f * c2r * l2 * rk * sk;
-          Be[ld * LDB + k] = -2.0f * l3 * sk + 2.0f * c2r * l2 * rk;
-          if (keep) dl[u] += -c2r * l2 * d2 + a0r * rk * rk;
-        }
-      }
-      if (lane == 0) gam[ld] = 2.0f * l3;
-      kept_total += keep ? 1 : 0;
     }
-    __syncthreads();
-    // ---- phase 2: one reduction row per nonzero, staged kRows at a time
-    // (double-buffered: the gathers of chunk i+1 are in flight during the
-    // matrix-core work on chunk i) ----
-    const int nb0 = rps[0];
-    const int nnz = rps[nd] - nb0;
-    float4 wr[UA], zr[UB];
-    float pv = 0.f;
-    int pdoc = 0;
-    auto fetch = [&](int cs) {
-      const int gi = cs + srow;
-      const bool in = gi < nnz;
-      const int j = nb0 + (in ? gi : 0);
-      const int col = col_idx[j];
-      pv = in ? val[j] : 0.f;            // rows past the tile's end add zero
-      int lo = 0, hi = nd;               // rps[lo] <= j < rps[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (rps[mid] <= j) lo = mid;
-        else hi = mid;
-      }
-      pdoc = lo;
+    if (s0.puts()) {
+      const int at = head + fill;
 #pragma unroll
-      for (int u = 0; u < UA; ++u) {
-        const int g = ssub + TPR * u;
-        wr[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (g < GA && 4 * g < Dp) wr[u] = *reinterpret_cast<const float4*>(W32 + (size_t)col * Dp + 4 * g);
-      }
+      for (int c = 0; c < 8; ++c)
+        if (4 * c < cnt) {
 #pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        const int g = ssub + TPR * u;
-        zr[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (g < GB && 4 * g < Kp) zr[u] = *reinterpret_cast<const float4*>(Z + (size_t)col * Kp + 4 * g);
-      }
-    };
-    if (nnz > 0) fetch(0);
-    for (int cs = 0; cs < nnz; cs += kRows) {
-      // B row = c (a_d + b_d * z + g_d z^2); A row = W row
-      const float g = gam[pdoc];
-#pragma unroll
-      for (int u = 0; u < UA; ++u) {
-        const int gg = ssub + TPR * u;
-        if (gg < GA) *reinterpret_cast<float4*>(&As[buf][srow * LDA + 4 * gg]) = wr[u];
-      }
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        const int gg = ssub + TPR * u;
-        if (gg < GB) {
-          const float4 al = *reinterpret_cast<const float4*>(Al + pdoc * LDB + 4 * gg);
-          const float4 be = *reinterpret_cast<const float4*>(Be + pdoc * LDB + 4 * gg);
-          const float4 z = zr[u];
-          float4 o;
-          o.x = pv * fmaf(g * z.x + be.x, z.x, al.x);
-          o.y = pv * fmaf(g * z.y + be.y, z.y, al.y);
-          o.z = pv * fmaf(g * z.z + be.z, z.z, al.z);
-          o.w = pv * fmaf(g * z.w + be.w, z.w, al.w);
-          *reinterpret_cast<float4*>(&Bs[buf][srow * LDB + 4 * gg]) = o;
+          for (int t = 4 * c; t < 4 * c + 4; ++t) {
+            const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v0), t));
+            const int r = at + t >= kRing ? at + t - kRing : at + t;
+            *reinterpret_cast<float*>(ring + r * 256 + 4 * lane) =
+                v * fmaf(g * z[t] + be, z[t], al);
+          }
         }
-      }
-      __syncthreads();
-      if (cs + kRows < nnz) fetch(cs + kRows);
-      const float* Ab = As[buf];
-      const float* Bb = Bs[buf];
-#pragma unroll
-      for (int rs = 0; rs < kRows / 4; ++rs) {
-        const float* xa = Ab + (rs * 4 + l4) * LDA + l16;
-        const float* sb = Bb + (rs * 4 + l4) * LDB + l16;
-#pragma unroll
-        for (int q = 0; q < RT; ++q) {
-          const int t = wave + 4 * q;
-          if (t < NRT)
-            acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[(t / NCT) * 16], sb[(t % NCT) * 16],
-                                                          acc[q], 0, 0, 0);
-        }
-      }
-      buf ^= 1;
+      fill += cnt;
     }
+    if (s0.d >= d1) {
+      // the run's last rows: zeros up to a whole batch (no wrap: head is a
+      // multiple of 16)
+      for (int r = fill; r < 16; ++r)
+        *reinterpret_cast<float*>(ring + (head + r) * 256 + 4 * lane) = 0.f;
+      fill = 16;
+    }
+    s0 = s1;
+    s1 = s2;
+    c0 = (int)__umul24((unsigned)c1, zstride);
+    v0 = v1;
+    load_z(s0.count());
+    wave_fence();
+    // ---- phase 2: the whole batches, two at most (kRing = 48) ----
+    if (fill >= 16) {
+      multiply();
+      if (fill >= 16) multiply();
+    }
+    wave_fence();
   }
-  // ---- m_w (x) sum e, then the block's partial and kept count ----
-#pragma unroll
-  for (int u = 0; u < NK; ++u) {
-    const int k = lane + 64 * u;
-    if (k < KQ) dsh[wave][k] = dl[u];
-  }
-  if (lane == 0) wave_kept[wave] = kept_total;
+
+  // ---- the block's sum in wave order, m_w (x) sum e, and the kept count ----
+  constexpr int RD = 8;                       // tiles per round
+  __shared__ float esum[64];
+  __shared__ int wave_kept[NW];
+  float* lds = reinterpret_cast<float*>(ring_lds);
   __syncthreads();
+  lds[tid] = es;
+  if (lane == 0) wave_kept[wave] = kept;
+  __syncthreads();
+  if (tid < 64) {
+    float x = 0.f;
+    for (int w = 0; w < NW; ++w) x += lds[w * 64 + tid];
+    esum[tid] = x;
+  }
   float* out = partial + (size_t)blockIdx.x * D * K;
 #pragma unroll
-  for (int q = 0; q < RT; ++q) {
-    const int t = wave + 4 * q;
-    if (t < NRT) {
-      const int k = (t % NCT) * 16 + l16;
-      const float es = dsh[0][k] + dsh[1][k] + dsh[2][k] + dsh[3][k];
+  for (int q0 = 0; q0 < NDT * NCT; q0 += RD) {
+    __syncthreads();
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int d = (t / NCT) * 16 + 4 * l4 + r;
-        if (d < D && k < K) out[d * K + k] = fmaf(mw32[d], es, acc[q][r]);
+    for (int t = q0; t < q0 + RD; ++t)
+      if (t < NDT * NCT)
+        *reinterpret_cast<floatx4*>(lds + ((wave * RD + t - q0) * 64 + lane) * 4) =
+            acc[t / NCT][t % NCT];
+    __syncthreads();
+    for (int e = tid; e < RD * 256; e += 64 * NW) {
+      const int t = q0 + e / 256, ln = (e >> 2) & 63;
+      const int k = (t % NCT) * 16 + (ln & 15), dd = (t / NCT) * 16 + 4 * (ln >> 4) + (e & 3);
+      if (t < NDT * NCT && dd < D && k0 + k < K) {
+        float x = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) x += lds[w * RD * 256 + e];
+        out[dd * K + k0 + k] = fmaf(mw32[dd], esum[k], x);
       }
     }
   }
-  if (tid == 0) block_counts[blockIdx.x] = wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
+  if (tid == 0 && blockIdx.y == 0) {
+    int x = 0;
+    for (int w = 0; w < NW; ++w) x += wave_kept[w];
+    block_counts[blockIdx.x] = x;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -536,22 +649,21 @@ hipError_t launch_classic16_t(const tlda_csr_batch& b, const uint16_t* W16, int 
   return hipGetLastError();
 }
 
-template <int DQ, int KQ>
+template <int NDT, int NCT>
 hipError_t launch_classic_t(const tlda_csr_batch& b, const float* W32, int Dp, const float* Z,
                             int Kp, const float* mw32, const float* r, int D, int K, double alpha0,
                             int nblk, float* partial, int* block_counts, hipStream_t s) {
-  if (partial == nullptr) {   // occupancy query: resident blocks per CU in *block_counts
-    int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_classic_cp<DQ, KQ>,
-                                                                 kThreads, 0);
-    *block_counts = per_cu;
-    return e;
-  }
+  constexpr int NW = classic_waves(NDT, NCT);
+  const unsigned shmem = NW * kRing * 256;
+  auto* kern = k_classic_cp<NDT, NCT>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+  if (e != hipSuccess) return e;
   const double c2 = alpha0 * (alpha0 + 1.0) / 2.0;
   const double c3 = (alpha0 + 1.0) * (alpha0 + 2.0) / 2.0;
-  launch_main(k_classic_cp<DQ, KQ>, dim3(nblk), dim3(kThreads), 0, s, b.row_ptr, b.col_idx,
+  launch_main(kern, dim3(nblk, K > 64 ? 2 : 1), dim3(64 * NW), shmem, s, b.row_ptr, b.col_idx,
               b.val, b.n_rows, W32, Dp, Z, Kp, mw32, r, D, K, (float)(c2 / c3),
-              (float)(alpha0 * alpha0 / c3), nblk, partial, block_counts);
+              (float)(alpha0 * alpha0 / c3), partial, block_counts);
   return hipGetLastError();
 }
 
@@ -611,18 +723,26 @@ hipError_t launch_classic_cp16(const tlda_csr_batch& b, const uint16_t* W16, int
   return hipErrorInvalidValue;
 }
 
+int classic_blocks(int D, int K, int n_rows, int num_cu) {
+  const int nw = classic_waves((D + 15) / 16, K > 64 ? 4 : (K + 15) / 16);
+  const int room = K > 64 ? (num_cu + 1) / 2 : num_cu;
+  const int want = (n_rows - 1) / nw + 1;
+  return want < room ? want : room;
+}
+
 hipError_t launch_classic_cp(const tlda_csr_batch& b, const float* W32, int Dp, const float* Z,
                              int Kp, const float* mw32, const float* r, int D, int K,
                              double alpha0, int nblk, float* partial, int* block_counts,
                              hipStream_t s) {
-  const int dq = classic_bucket(D), kq = classic_bucket(K);
-#define TLDA_CLASSIC(DQ_, KQ_)                                                                \
-  if (dq == DQ_ && kq == KQ_)                                                                 \
-    return launch_classic_t<DQ_, KQ_>(b, W32, Dp, Z, Kp, mw32, r, D, K, alpha0, nblk, partial, \
-                                      block_counts, s);
-#define TLDA_CLASSIC_ROW(DQ_) \
-  TLDA_CLASSIC(DQ_, 16) TLDA_CLASSIC(DQ_, 32) TLDA_CLASSIC(DQ_, 64) TLDA_CLASSIC(DQ_, 128)
-  TLDA_CLASSIC_ROW(16) TLDA_CLASSIC_ROW(32) TLDA_CLASSIC_ROW(64) TLDA_CLASSIC_ROW(128)
+  const int ndt = (D + 15) / 16, nct = K > 64 ? 4 : (K + 15) / 16;
+#define TLDA_CLASSIC(NDT_, NCT_)                                                              \
+  if (ndt == NDT_ && nct == NCT_)                                                             \
+    return launch_classic_t<NDT_, NCT_>(b, W32, Dp, Z, Kp, mw32, r, D, K, alpha0, nblk,       \
+                                        partial, block_counts, s);
+#define TLDA_CLASSIC_ROW(NDT_) \
+  TLDA_CLASSIC(NDT_, 1) TLDA_CLASSIC(NDT_, 2) TLDA_CLASSIC(NDT_, 3) TLDA_CLASSIC(NDT_, 4)
+  TLDA_CLASSIC_ROW(1) TLDA_CLASSIC_ROW(2) TLDA_CLASSIC_ROW(3) TLDA_CLASSIC_ROW(4)
+  TLDA_CLASSIC_ROW(5) TLDA_CLASSIC_ROW(6) TLDA_CLASSIC_ROW(7) TLDA_CLASSIC_ROW(8)
 #undef TLDA_CLASSIC_ROW
 #undef TLDA_CLASSIC
   return hipErrorInvalidValue;

@@ -534,15 +534,7 @@ tlda_status classic_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float
     HIP_OK(c, dalloc(&c->cp.Z, (size_t)V * Kp));
     HIP_OK(c, dalloc(&c->cp.rz, (size_t)Kp));
   }
-  if (c->tune.classic_resident <= 0) {
-    int per_cu = 0;
-    HIP_OK(c, tlda::launch_classic_cp(*b, c->wh.W32, c->Dp, c->cp.Z, Kp, c->wh.mw32, c->cp.rz, D,
-                                      K, c->cfg.alpha0, 0, nullptr, &per_cu, c->stream));
-    c->tune.classic_resident = (per_cu > 0 ? per_cu : 1) * c->num_cu;
-  }
-  const int ntiles = (b->n_rows + 15) / 16;
-  int nblk = ntiles < c->tune.classic_resident ? ntiles : c->tune.classic_resident;
-  if (nblk > 2 * tlda::kWhitenBlockCounts) nblk = 2 * tlda::kWhitenBlockCounts;
+  const int nblk = tlda::classic_blocks(D, K, b->n_rows, c->num_cu);
   st = ensure_partial(c, (size_t)nblk * D * K);
   if (st != TLDA_OK) return st;
   float* g = grad ? grad : c->cp.grad;
