@@ -24,17 +24,41 @@
 // gradient with the penalty term and updates Phi.
 #include "tlda_internal.h"
 
+#include <type_traits>
+
 namespace tlda {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kDocs = 16;    // documents per tile of the BF16 kernel
-constexpr int kRing = 48;    // reduction rows that a wave of the FP32 kernel keeps in LDS
-// Waves per block of the FP32 kernel (one block per CU): three per SIMD where
-// the 4 NDT NCT registers of a wave's sums leave 168 for all (131 at 16 tiles),
+constexpr int kRing = 48;     // reduction rows that a wave keeps in LDS: 15 and 32 more, in batches
+constexpr int kRing16 = 52;   // BF16: rows from one column of them to the next
+constexpr int classic_ring_bytes(bool bf16) { return bf16 ? 64 * kRing16 * 2 : 64 * kRing * 4; }
+// Waves per block (one block per CU): three per SIMD where a wave's sums (4 NDT
+// NCT registers) and W rows (4 NDT, and as many on the way) leave 168 for all,
 // else two (256).
-constexpr int classic_waves(int ndt, int nct) { return ndt * nct <= 16 ? 12 : 8; }
+constexpr int classic_waves(int ndt, int nct) { return ndt * (nct + 1) <= 20 ? 12 : 8; }
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef short bf16x4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float bf_to_f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+// FP32 -> BF16 bits, round to nearest even (hardware conversion).
+__device__ __forceinline__ uint16_t f_to_bf(float f) {
+  const __bf16 h = (__bf16)f;
+  return __builtin_bit_cast(uint16_t, h);
+}
+
+// Elements of W and Z, the same as a register holds them, and their value.
+template <bool BF>
+using classic_elem = std::conditional_t<BF, uint16_t, float>;
+template <bool BF>
+using classic_elem_bits = std::conditional_t<BF, uint32_t, float>;
+template <bool BF>
+__device__ __forceinline__ float classic_value(classic_elem_bits<BF> x) {
+  if constexpr (BF)
+    return __uint_as_float(x << 16);
+  else
+    return x;
+}
 
 // The lanes of a wave exchange data through LDS: what was written before is
 // visible to the others after it (a wave's LDS operations complete in order,
@@ -84,13 +108,14 @@ __global__ void __launch_bounds__(kThreads) k_classic_z(const float* __restrict_
 //   phase 1: lane k takes column k.  The Z rows of the document's words, 32 at
 //     a time, come straight into registers and give s, q, L and the
 //     coefficients a, b, g;
-//   the reduction rows c (a + b z + g z^2) are formed from the same registers
+//   the reduction rows c (a + b z + g z^2), rounded to BF16 where W is, are formed from the same registers
 //     and put into the wave's ring of kRing rows in LDS (documents of more than
 //     32 words gather their Z rows a second time for it);
 //   the Z rows of the next document are asked for, and
 //   phase 2: as long as the ring holds 16 rows they go through the matrix
 //     cores, four at a time: B from the ring, A (the W rows) straight from
-//     memory into the operand registers, 16 rows ahead of their use.  The rows
+//     memory into the operand registers, 16 rows ahead of their use (BF16: all
+//     16 at once).  The rows
 //     of a run are consecutive nonzeros, so this side needs no document.
 // Each wave keeps all NDT x NCT tiles of the D x K sum.  K > 64 is split over
 // gridDim.y: the columns do not depend on each other.
@@ -109,30 +134,36 @@ __global__ void __launch_bounds__(kThreads) k_classic_z(const float* __restrict_
 // the top of the loop, where nothing is in flight that was not asked for before
 // the last products, lets the next products start without waiting for the Z
 // rows that are asked for just ahead of them: 40 us less.
+// BF16 (contexts created with TLDA_CLASSIC | TLDA_BF16): the copy W16 of W (with
+// its mean projection mw16), Z16 = bf16(W16 Phi), sums and coefficients in FP32.
+// It takes 150 us, with an eighth of the matrix cores' time and half the bytes;
+// staged column by column in blocks of four waves it took 330.
 //
 // (V <= 131072: words take 24 bits, and 32 reach all of W and Z.)
-template <int NDT, int NCT>
+template <int NDT, int NCT, bool BF>
 __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    const float* __restrict__ val, int n_rows, const float* __restrict__ W32, int Dp,
-    const float* __restrict__ Z, int Kp, const float* __restrict__ mw32,
+    const float* __restrict__ val, int n_rows, const classic_elem<BF>* __restrict__ W, int Dp,
+    const classic_elem<BF>* __restrict__ Z, int Kp, const float* __restrict__ mw,
     const float* __restrict__ r_g, int D, int K, float c2r, float a0r,
     float* __restrict__ partial, int* __restrict__ block_counts) {
+  using E = classic_elem<BF>;
   constexpr int NW = classic_waves(NDT, NCT);
+  constexpr int NB = 16;    // rows per batch
   extern __shared__ __attribute__((aligned(16))) char ring_lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, l4 = lane >> 4;
   const int k0 = blockIdx.y * 64;
-  char* ring = ring_lds + wave * (kRing * 256);
+  char* ring = ring_lds + wave * classic_ring_bytes(BF);
   // columns past Kp repeat the last one (they reach no output)
   const int kc = k0 + lane < Kp ? k0 + lane : Kp - 1;
-  const unsigned zoff = 4u * (unsigned)kc;
+  const unsigned zoff = (unsigned)(sizeof(E) * kc);
   const char* Zb = reinterpret_cast<const char*>(Z);
   const float rk = r_g[kc];
-  const char* Wb = reinterpret_cast<const char*>(W32);
-  const unsigned woff = 4u * (unsigned)(l16 < Dp ? l16 : Dp - 1);
-  const unsigned wstride = 4u * (unsigned)Dp, zstride = 4u * (unsigned)Kp;
+  const char* Wb = reinterpret_cast<const char*>(W);
+  const unsigned woff = (unsigned)(sizeof(E) * (l16 < Dp ? l16 : Dp - 1));
+  const unsigned wstride = (unsigned)(sizeof(E) * Dp), zstride = (unsigned)(sizeof(E) * Kp);
 
   floatx4 acc[NDT][NCT];
 #pragma unroll
@@ -148,50 +179,83 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
   const int nz0 = __builtin_amdgcn_readfirstlane(row_ptr[d0]);
   const int nz1 = __builtin_amdgcn_readfirstlane(row_ptr[d1]);
 
-  // ---- A side: the W rows of the next 16 nonzeros, their words 16 further ----
-  float an[4][NDT];
-  int ac = 0;                 // the word of nonzero l16 of them
-  int anext = nz0 + l16;      // the first nonzero whose word is not asked for yet
+  // ---- A side: the W rows of the next batch, the words of the one after it.
+  // Four rows are one FP32 operand or, packed, four of a BF16 operand's
+  // sixteen.  (The bits are kept as they come: a conversion next to a load
+  // would wait for it.)
+  classic_elem_bits<BF> an[4][NDT];
+  int ac = 0;                 // the word of row lane % NB
+  int anext = nz0 + lane % NB;
   auto load_cols = [&]() {
     ac = col_idx[anext < nz1 ? anext : nz1 - 1];
-    anext += 16;
+    anext += NB;
   };
   auto load_a = [&]() {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const unsigned c = (unsigned)__shfl(ac, 4 * i + l4, 64);
+      const unsigned c = (unsigned)__shfl(ac, BF ? 4 * l4 + i : 4 * i + l4, 64);
       unsigned o = __umul24(c, wstride) + woff;
       asm("" : "+v"(o));
-      const float* w = reinterpret_cast<const float*>(Wb + o);
+      const E* w = reinterpret_cast<const E*>(Wb + o);
 #pragma unroll
       for (int t = 0; t < NDT; ++t) an[i][t] = w[16 * t];
     }
   };
-  int head = 0;     // the ring's first row not yet multiplied, a multiple of 16
+  int head = 0;     // the ring's first row not yet multiplied, a multiple of NB
   int fill = 0;     // rows from there on
-  auto multiply = [&]() {   // 16 rows
-    float a[4][NDT];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int t = 0; t < NDT; ++t) a[i][t] = an[i][t];
-    load_a();
-    load_cols();
-    const char* rows = ring + head * 256 + l4 * 256 + 4 * l16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float bb[NCT];
-#pragma unroll
-      for (int c = 0; c < NCT; ++c)
-        bb[c] = *reinterpret_cast<const float*>(rows + 1024 * i + 64 * c);
+  // FP32: rows of 64 columns; BF16: columns of kRing rows, two words further
+  // apart (a lane's operand is four rows of a column)
+  auto place = [&](int r) -> char* {
+    r = r >= kRing ? r - kRing : r;
+    return BF ? ring + (lane * kRing16 + r) * 2 : ring + r * 256 + 4 * lane;
+  };
+  auto put = [&](int r, float x) {
+    if constexpr (BF)
+      *reinterpret_cast<uint16_t*>(place(r)) = f_to_bf(x);
+    else
+      *reinterpret_cast<float*>(place(r)) = x;
+  };
+  auto multiply = [&]() {   // a batch
+    if constexpr (BF) {
+      uint2 a[NDT];
 #pragma unroll
       for (int t = 0; t < NDT; ++t)
+        a[t] = make_uint2(an[0][t] | an[1][t] << 16, an[2][t] | an[3][t] << 16);
+      load_a();
+      load_cols();
+#pragma unroll
+      for (int c = 0; c < NCT; ++c) {
+        const bf16x4_t bb = *reinterpret_cast<const bf16x4_t*>(
+            ring + ((16 * c + l16) * kRing16 + head + 4 * l4) * 2);
+#pragma unroll
+        for (int t = 0; t < NDT; ++t)
+          acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+              __builtin_bit_cast(bf16x4_t, a[t]), bb, acc[t][c], 0, 0, 0);
+      }
+    } else {
+      float a[4][NDT];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < NDT; ++t) a[i][t] = an[i][t];
+      load_a();
+      load_cols();
+      const char* rows = ring + head * 256 + l4 * 256 + 4 * l16;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float bb[NCT];
 #pragma unroll
         for (int c = 0; c < NCT; ++c)
-          acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][t], bb[c], acc[t][c], 0, 0, 0);
+          bb[c] = *reinterpret_cast<const float*>(rows + 1024 * i + 64 * c);
+#pragma unroll
+        for (int t = 0; t < NDT; ++t)
+#pragma unroll
+          for (int c = 0; c < NCT; ++c)
+            acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][t], bb[c], acc[t][c], 0, 0, 0);
+      }
     }
-    fill -= 16;
-    head = head + 16 == kRing ? 0 : head + 16;
+    fill -= NB;
+    head = head + NB == kRing ? 0 : head + NB;
   };
 
   // ---- B side: segments of at most 32 entries of one document ----
@@ -243,7 +307,7 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
   float v0 = 0.f, v1 = 0.f, v2 = 0.f;
   // the Z rows at offsets c0, four at a time (those that fill the last four have
   // no count)
-  float z[32];
+  classic_elem_bits<BF> z[32];
   auto load_z = [&](int count) {
 #pragma unroll
     for (int c = 0; c < 8; ++c)
@@ -252,7 +316,7 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
         for (int t = 4 * c; t < 4 * c + 4; ++t) {
           unsigned o = (unsigned)__builtin_amdgcn_readlane(c0, t) + zoff;
           asm("" : "+v"(o));   // the base stays in scalar registers
-          z[t] = *reinterpret_cast<const float*>(Zb + o);
+          z[t] = *reinterpret_cast<const E*>(Zb + o);
         }
       }
   };
@@ -289,9 +353,10 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
 #pragma unroll
           for (int t = 4 * c; t < 4 * c + 4; ++t) {
             const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v0), t));
+            const float zt = classic_value<BF>(z[t]);
             L += v;
-            s = fmaf(v, z[t], s);
-            q = fmaf(v * z[t], z[t], q);
+            s = fmaf(v, zt, s);
+            q = fmaf(v * zt, zt, q);
           }
         }
       if (s0.last()) {
@@ -314,19 +379,17 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
 #pragma unroll
           for (int t = 4 * c; t < 4 * c + 4; ++t) {
             const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v0), t));
-            const int r = at + t >= kRing ? at + t - kRing : at + t;
-            *reinterpret_cast<float*>(ring + r * 256 + 4 * lane) =
-                v * fmaf(g * z[t] + be, z[t], al);
+            const float zt = classic_value<BF>(z[t]);
+            put(at + t, v * fmaf(g * zt + be, zt, al));
           }
         }
       fill += cnt;
     }
     if (s0.d >= d1) {
       // the run's last rows: zeros up to a whole batch (no wrap: head is a
-      // multiple of 16)
-      for (int r = fill; r < 16; ++r)
-        *reinterpret_cast<float*>(ring + (head + r) * 256 + 4 * lane) = 0.f;
-      fill = 16;
+      // multiple of NB)
+      for (int r = fill; r < NB; ++r) put(head + r, 0.f);
+      fill = NB;
     }
     s0 = s1;
     s1 = s2;
@@ -335,9 +398,9 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
     load_z(s0.count());
     wave_fence();
     // ---- phase 2: the whole batches, two at most (kRing = 48) ----
-    if (fill >= 16) {
+    if (fill >= NB) {
       multiply();
-      if (fill >= 16) multiply();
+      if (fill >= NB) multiply();
     }
     wave_fence();
   }
@@ -373,7 +436,7 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
         float x = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) x += lds[w * RD * 256 + e];
-        out[dd * K + k0 + k] = fmaf(mw32[dd], esum[k], x);
+        out[dd * K + k0 + k] = fmaf(mw[dd], esum[k], x);
       }
     }
   }
@@ -382,25 +445,6 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
     for (int w = 0; w < NW; ++w) x += wave_kept[w];
     block_counts[blockIdx.x] = x;
   }
-}
-
-// ---------------------------------------------------------------------------
-// BF16 variant (contexts created with TLDA_CLASSIC | TLDA_BF16): the BF16
-// whitening copy W16 (with its mean projection mw16) in place of W, Z16 =
-// bf16(W16 Phi) in place of Z, and the reduction rows rounded to BF16 for
-// v_mfma_f32_16x16x32_bf16 with FP32 accumulation; the per-document sums s,
-// q and the coefficients stay FP32.  Phase 1 gathers 2 bytes per column of a
-// Z16 row; phase 2 stages each chunk of 32 rows column-major in LDS (a lane's
-// MFMA operand is 8 consecutive rows of one column).
-// ---------------------------------------------------------------------------
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float bf_to_f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-// FP32 -> BF16 bits, round to nearest even (hardware conversion).
-__device__ __forceinline__ uint16_t f_to_bf(float f) {
-  const __bf16 h = (__bf16)f;
-  return __builtin_bit_cast(uint16_t, h);
 }
 
 // Z16[w][k] = bf16(sum_d W16[w][d] Phi[d][k]) (zero for K <= k < Kh); block 0
@@ -437,248 +481,49 @@ __global__ void __launch_bounds__(kThreads) k_classic_z16(const uint16_t* __rest
   }
 }
 
-template <int DQ, int KQ>
-__global__ void __launch_bounds__(kThreads, 2) k_classic_cp16(
-    const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-    const float* __restrict__ val, int n_rows, const uint16_t* __restrict__ W16, int Dh,
-    const uint16_t* __restrict__ Z16, int Kh, const float* __restrict__ mw16,
-    const float* __restrict__ r_g, int D, int K, float c2r, float a0r, int nblk,
-    float* __restrict__ partial, int* __restrict__ block_counts) {
-  constexpr int R = 32;                                     // rows per chunk (one MFMA k-step)
-  constexpr int LDR = R + 8;                                // column stride of the staged tiles
-  constexpr int LDB = KQ + 4;
-  constexpr int NCT = KQ / 16, NDT = DQ / 16, NRT = NDT * NCT;
-  constexpr int RT = (NRT + 3) / 4;
-  constexpr int NK = (KQ + 63) / 64;
-  constexpr int GA = DQ / 8, GB = KQ / 8;                   // 8-column groups per staged row
-  constexpr int TPR = kThreads / R;                         // threads per staged row (8)
-  constexpr int UA = (GA + TPR - 1) / TPR, UB = (GB + TPR - 1) / TPR;
-  constexpr int NB = 8;
-  __shared__ __attribute__((aligned(16))) uint16_t WsT[DQ * LDR];
-  __shared__ __attribute__((aligned(16))) uint16_t BsT[KQ * LDR];
-  __shared__ __attribute__((aligned(16))) float Al[kDocs * LDB];
-  __shared__ __attribute__((aligned(16))) float Be[kDocs * LDB];
-  __shared__ float gam[kDocs];
-  __shared__ int rps[kDocs + 1];
-  __shared__ float rsh[KQ];
-  __shared__ float dsh[4][KQ];
-  __shared__ int wave_kept[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l16 = lane & 15, l4 = lane >> 4;
-  const int srow = tid / TPR, ssub = tid % TPR;
-  const unsigned char* W16b = reinterpret_cast<const unsigned char*>(W16);
-  const unsigned char* Z16b = reinterpret_cast<const unsigned char*>(Z16);
-
-  for (int k = tid; k < KQ; k += kThreads) rsh[k] = k < K ? r_g[k] : 0.f;
-  float dl[NK];
-#pragma unroll
-  for (int u = 0; u < NK; ++u) dl[u] = 0.f;
-  floatx4 acc[RT];
-#pragma unroll
-  for (int q = 0; q < RT; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-  int kept_total = 0;
-
-  const int ntiles = (n_rows + kDocs - 1) / kDocs;
-  for (int tile = blockIdx.x; tile < ntiles; tile += nblk) {
-    const int t0 = tile * kDocs;
-    const int nd = n_rows - t0 < kDocs ? n_rows - t0 : kDocs;
-    __syncthreads();
-    if (tid <= kDocs) rps[tid] = row_ptr[t0 + (tid < nd ? tid : nd)];
-    __syncthreads();
-    // ---- phase 1: s, q, L and the coefficients (a wave per document) ----
-    for (int ld = wave; ld < kDocs; ld += 4) {
-      float s[NK], q[NK];
-#pragma unroll
-      for (int u = 0; u < NK; ++u) s[u] = q[u] = 0.f;
-      float L = 0.f;
-      if (ld < nd) {
-        const int b = rps[ld], e = rps[ld + 1];
-        for (int jb = b; jb < e; jb += NB) {
-          int mc = 0;
-          float mv = 0.f;
-          if (lane < NB && jb + lane < e) {
-            mc = col_idx[jb + lane];
-            mv = val[jb + lane];
-          }
-          float zv[NB][NK];
-#pragma unroll
-          for (int t = 0; t < NB; ++t) {
-            const int c = __shfl(mc, t, 64);
-#pragma unroll
-            for (int u = 0; u < NK; ++u) {
-              const int k = lane + 64 * u;
-              zv[t][u] = k < Kh ? bf_to_f(Z16[(size_t)c * Kh + k]) : 0.f;
-            }
-          }
-#pragma unroll
-          for (int t = 0; t < NB; ++t) {
-            const float v = __shfl(mv, t, 64);
-            L += v;
-#pragma unroll
-            for (int u = 0; u < NK; ++u) {
-              s[u] = fmaf(v, zv[t][u], s[u]);
-              q[u] = fmaf(v * zv[t][u], zv[t][u], q[u]);
-            }
-          }
-        }
-      }
-      const bool keep = ld < nd && L >= 3.f;
-      const float l2 = keep ? 1.0f / (L * (L - 1.0f)) : 0.f;
-      const float l3 = keep ? l2 / (L - 2.0f) : 0.f;
-#pragma unroll
-      for (int u = 0; u < NK; ++u) {
-        const int k = lane + 64 * u;
-        if (k < KQ) {
-          const float rk = rsh[k], sk = s[u], d2 = s[u] * s[u] - q[u];
-          Al[ld * LDB + k] = l3 * d2 - 2.0f * c2r * l2 * rk * sk;
-          Be[ld * LDB + k] = -2.0f * l3 * sk + 2.0f * c2r * l2 * rk;
-          if (keep) dl[u] += -c2r * l2 * d2 + a0r * rk * rk;
-        }
-      }
-      if (lane == 0) gam[ld] = 2.0f * l3;
-      kept_total += keep ? 1 : 0;
-    }
-    __syncthreads();
-    // ---- phase 2: the tile's nonzero rows in chunks of R, column-major ----
-    const int nb0 = rps[0];
-    const int nnz = rps[nd] - nb0;
-    for (int cs = 0; cs < nnz; cs += R) {
-      const int gi = cs + srow;
-      const bool in = gi < nnz;
-      const int j = nb0 + (in ? gi : 0);
-      const int col = col_idx[j];
-      const float v = in ? val[j] : 0.f;    // rows past the tile's end add zero
-      int lo = 0, hi = nd;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (rps[mid] <= j) lo = mid;
-        else hi = mid;
-      }
-      const float g = gam[lo];
-#pragma unroll
-      for (int u = 0; u < UA; ++u) {
-        const int gg = ssub + TPR * u;
-        if (gg < GA) {
-          u32x4_t w = u32x4_t{0u, 0u, 0u, 0u};
-          if (8 * gg < Dh)
-            w = *reinterpret_cast<const u32x4_t*>(W16b + ((size_t)col * Dh + 8 * gg) * 2u);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const uint32_t wi = w[i];
-            WsT[(8 * gg + 2 * i) * LDR + srow] = (uint16_t)(wi & 0xffffu);
-            WsT[(8 * gg + 2 * i + 1) * LDR + srow] = (uint16_t)(wi >> 16);
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < UB; ++u) {
-        const int gg = ssub + TPR * u;
-        if (gg < GB) {
-          u32x4_t z = u32x4_t{0u, 0u, 0u, 0u};
-          if (8 * gg < Kh)
-            z = *reinterpret_cast<const u32x4_t*>(Z16b + ((size_t)col * Kh + 8 * gg) * 2u);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const uint32_t zi = z[i];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const int kk = 8 * gg + 2 * i + h;
-              const float zf = __uint_as_float(h == 0 ? (zi << 16) : (zi & 0xffff0000u));
-              const float o = v * fmaf(g * zf + Be[lo * LDB + kk], zf, Al[lo * LDB + kk]);
-              BsT[kk * LDR + srow] = f_to_bf(o);
-            }
-          }
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < RT; ++q) {
-        const int t = wave + 4 * q;
-        if (t < NRT) {
-          const u32x4_t a = *reinterpret_cast<const u32x4_t*>(WsT + ((t / NCT) * 16 + l16) * LDR + 8 * l4);
-          const u32x4_t b = *reinterpret_cast<const u32x4_t*>(BsT + ((t % NCT) * 16 + l16) * LDR + 8 * l4);
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                          __builtin_bit_cast(bf16x8_t, b), acc[q],
-                                                          0, 0, 0);
-        }
-      }
-      __syncthreads();
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < NK; ++u) {
-    const int k = lane + 64 * u;
-    if (k < KQ) dsh[wave][k] = dl[u];
-  }
-  if (lane == 0) wave_kept[wave] = kept_total;
-  __syncthreads();
-  float* out = partial + (size_t)blockIdx.x * D * K;
-#pragma unroll
-  for (int q = 0; q < RT; ++q) {
-    const int t = wave + 4 * q;
-    if (t < NRT) {
-      const int k = (t % NCT) * 16 + l16;
-      const float es = dsh[0][k] + dsh[1][k] + dsh[2][k] + dsh[3][k];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int d = (t / NCT) * 16 + 4 * l4 + r;
-        if (d < D && k < K) out[d * K + k] = fmaf(mw16[d], es, acc[q][r]);
-      }
-    }
-  }
-  if (tid == 0) block_counts[blockIdx.x] = wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
-}
-
-template <int DQ, int KQ>
-hipError_t launch_classic16_t(const tlda_csr_batch& b, const uint16_t* W16, int Dh,
-                              const uint16_t* Z16, int Kh, const float* mw16, const float* r, int D,
-                              int K, double alpha0, int nblk, float* partial, int* block_counts,
-                              hipStream_t s) {
-  if (partial == nullptr) {
-    int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_classic_cp16<DQ, KQ>,
-                                                                 kThreads, 0);
-    *block_counts = per_cu;
-    return e;
-  }
-  const double c2 = alpha0 * (alpha0 + 1.0) / 2.0;
-  const double c3 = (alpha0 + 1.0) * (alpha0 + 2.0) / 2.0;
-  launch_main(k_classic_cp16<DQ, KQ>, dim3(nblk), dim3(kThreads), 0, s, b.row_ptr, b.col_idx,
-              b.val, b.n_rows, W16, Dh, Z16, Kh, mw16, r, D, K, (float)(c2 / c3),
-              (float)(alpha0 * alpha0 / c3), nblk, partial, block_counts);
-  return hipGetLastError();
-}
-
-template <int NDT, int NCT>
-hipError_t launch_classic_t(const tlda_csr_batch& b, const float* W32, int Dp, const float* Z,
-                            int Kp, const float* mw32, const float* r, int D, int K, double alpha0,
-                            int nblk, float* partial, int* block_counts, hipStream_t s) {
+template <int NDT, int NCT, bool BF>
+hipError_t launch_classic_t(const tlda_csr_batch& b, const classic_elem<BF>* W, int Dp,
+                            const classic_elem<BF>* Z, int Kp, const float* mw, const float* r,
+                            int D, int K, double alpha0, int nblk, float* partial,
+                            int* block_counts, hipStream_t s) {
   constexpr int NW = classic_waves(NDT, NCT);
-  const unsigned shmem = NW * kRing * 256;
-  auto* kern = k_classic_cp<NDT, NCT>;
+  constexpr unsigned sums = NW * 8 * 1024;   // the block's sum: eight tiles at a time
+  constexpr unsigned rings = NW * classic_ring_bytes(BF);
+  const unsigned shmem = rings > sums ? rings : sums;
+  auto* kern = k_classic_cp<NDT, NCT, BF>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
   const double c2 = alpha0 * (alpha0 + 1.0) / 2.0;
   const double c3 = (alpha0 + 1.0) * (alpha0 + 2.0) / 2.0;
   launch_main(kern, dim3(nblk, K > 64 ? 2 : 1), dim3(64 * NW), shmem, s, b.row_ptr, b.col_idx,
-              b.val, b.n_rows, W32, Dp, Z, Kp, mw32, r, D, K, (float)(c2 / c3),
+              b.val, b.n_rows, W, Dp, Z, Kp, mw, r, D, K, (float)(c2 / c3),
               (float)(alpha0 * alpha0 / c3), partial, block_counts);
   return hipGetLastError();
 }
 
-// Padded size of a D or K dimension: 16, 32, 64 or 128 (0 above 128).
-int classic_bucket(int n) {
-  if (n <= 16) return 16;
-  if (n <= 32) return 32;
-  if (n <= 64) return 64;
-  if (n <= 128) return 128;
-  return 0;
+template <bool BF>
+hipError_t launch_classic(const tlda_csr_batch& b, const classic_elem<BF>* W, int Dp,
+                          const classic_elem<BF>* Z, int Kp, const float* mw, const float* r, int D,
+                          int K, double alpha0, int nblk, float* partial, int* block_counts,
+                          hipStream_t s) {
+  const int ndt = (D + 15) / 16, nct = K > 64 ? 4 : (K + 15) / 16;
+#define TLDA_CLASSIC(NDT_, NCT_)                                                              \
+  if (ndt == NDT_ && nct == NCT_)                                                             \
+    return launch_classic_t<NDT_, NCT_, BF>(b, W, Dp, Z, Kp, mw, r, D, K, alpha0, nblk,       \
+                                            partial, block_counts, s);
+#define TLDA_CLASSIC_ROW(NDT_) \
+  TLDA_CLASSIC(NDT_, 1) TLDA_CLASSIC(NDT_, 2) TLDA_CLASSIC(NDT_, 3) TLDA_CLASSIC(NDT_, 4)
+  TLDA_CLASSIC_ROW(1) TLDA_CLASSIC_ROW(2) TLDA_CLASSIC_ROW(3) TLDA_CLASSIC_ROW(4)
+  TLDA_CLASSIC_ROW(5) TLDA_CLASSIC_ROW(6) TLDA_CLASSIC_ROW(7) TLDA_CLASSIC_ROW(8)
+#undef TLDA_CLASSIC_ROW
+#undef TLDA_CLASSIC
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-bool classic_supported(int D, int K) { return classic_bucket(D) > 0 && classic_bucket(K) > 0; }
+bool classic_supported(int D, int K) { return D >= 1 && D <= 128 && K >= 1 && K <= 128; }
 
 hipError_t launch_classic_z(const float* W32, int V, int D, int Dp, const float* Phi, int K,
                             int Kp, const float* mw32, float* Z, float* r, float* phi_copy,
@@ -710,17 +555,8 @@ hipError_t launch_classic_cp16(const tlda_csr_batch& b, const uint16_t* W16, int
                                const uint16_t* Z16, int Kh, const float* mw16, const float* r,
                                int D, int K, double alpha0, int nblk, float* partial,
                                int* block_counts, hipStream_t s) {
-  const int dq = classic_bucket(D), kq = classic_bucket(K);
-#define TLDA_CLASSIC16(DQ_, KQ_)                                                              \
-  if (dq == DQ_ && kq == KQ_)                                                                 \
-    return launch_classic16_t<DQ_, KQ_>(b, W16, Dh, Z16, Kh, mw16, r, D, K, alpha0, nblk,      \
-                                        partial, block_counts, s);
-#define TLDA_CLASSIC16_ROW(DQ_) \
-  TLDA_CLASSIC16(DQ_, 16) TLDA_CLASSIC16(DQ_, 32) TLDA_CLASSIC16(DQ_, 64) TLDA_CLASSIC16(DQ_, 128)
-  TLDA_CLASSIC16_ROW(16) TLDA_CLASSIC16_ROW(32) TLDA_CLASSIC16_ROW(64) TLDA_CLASSIC16_ROW(128)
-#undef TLDA_CLASSIC16_ROW
-#undef TLDA_CLASSIC16
-  return hipErrorInvalidValue;
+  return launch_classic<true>(b, W16, Dh, Z16, Kh, mw16, r, D, K, alpha0, nblk, partial,
+                              block_counts, s);
 }
 
 int classic_blocks(int D, int K, int n_rows, int num_cu) {
@@ -734,18 +570,8 @@ hipError_t launch_classic_cp(const tlda_csr_batch& b, const float* W32, int Dp, 
                              int Kp, const float* mw32, const float* r, int D, int K,
                              double alpha0, int nblk, float* partial, int* block_counts,
                              hipStream_t s) {
-  const int ndt = (D + 15) / 16, nct = K > 64 ? 4 : (K + 15) / 16;
-#define TLDA_CLASSIC(NDT_, NCT_)                                                              \
-  if (ndt == NDT_ && nct == NCT_)                                                             \
-    return launch_classic_t<NDT_, NCT_>(b, W32, Dp, Z, Kp, mw32, r, D, K, alpha0, nblk,       \
-                                        partial, block_counts, s);
-#define TLDA_CLASSIC_ROW(NDT_) \
-  TLDA_CLASSIC(NDT_, 1) TLDA_CLASSIC(NDT_, 2) TLDA_CLASSIC(NDT_, 3) TLDA_CLASSIC(NDT_, 4)
-  TLDA_CLASSIC_ROW(1) TLDA_CLASSIC_ROW(2) TLDA_CLASSIC_ROW(3) TLDA_CLASSIC_ROW(4)
-  TLDA_CLASSIC_ROW(5) TLDA_CLASSIC_ROW(6) TLDA_CLASSIC_ROW(7) TLDA_CLASSIC_ROW(8)
-#undef TLDA_CLASSIC_ROW
-#undef TLDA_CLASSIC
-  return hipErrorInvalidValue;
+  return launch_classic<false>(b, W32, Dp, Z, Kp, mw32, r, D, K, alpha0, nblk, partial,
+                               block_counts, s);
 }
 
 }  // namespace tlda

@@ -502,16 +502,7 @@ tlda_status classic_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float
       HIP_OK(c, dalloc(&c->cp.Z16, (size_t)V * Kh));
       if (c->cp.rz == nullptr) HIP_OK(c, dalloc(&c->cp.rz, (size_t)Kh));
     }
-    if (c->tune.classic16_resident <= 0) {
-      int per_cu = 0;
-      HIP_OK(c, tlda::launch_classic_cp16(*b, c->wh.W16, c->Dh, c->cp.Z16, Kh, c->wh.mw16,
-                                          c->cp.rz, D, K, c->cfg.alpha0, 0, nullptr, &per_cu,
-                                          c->stream));
-      c->tune.classic16_resident = (per_cu > 0 ? per_cu : 1) * c->num_cu;
-    }
-    const int ntiles = (b->n_rows + 15) / 16;
-    int nblk = ntiles < c->tune.classic16_resident ? ntiles : c->tune.classic16_resident;
-    if (nblk > 2 * tlda::kWhitenBlockCounts) nblk = 2 * tlda::kWhitenBlockCounts;
+    const int nblk = tlda::classic_blocks(D, K, b->n_rows, c->num_cu);
     st = ensure_partial(c, (size_t)nblk * D * K);
     if (st != TLDA_OK) return st;
     float* g = grad ? grad : c->cp.grad;

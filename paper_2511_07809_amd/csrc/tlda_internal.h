@@ -109,7 +109,6 @@ struct Tuning {
   int fused_blocks = 0;
   int bf16_blocks = 0;
   int bf16_resident[3] = {0, 0, 0};   // cached occupancy rounds of the BF16 kernels
-  int classic16_resident = 0;         // the same for the BF16 classic-moment kernel
   int whiten_v4 = 0;
   int whiten_chunks = 0;
   int gemm_route = 0;                 // refresh products: 0 built-in choice, 1 the vector kernel
@@ -393,10 +392,9 @@ hipError_t launch_whiten_bf16(const tlda_csr_batch& b, const uint16_t* W16, cons
 int cp_resident_blocks(int D, int K, int num_cu);
 // classic-moment CP step (FP32, D, K <= 128): Z = W Phi, r = Phi^T mw32 and
 // phi_copy = Phi, then the per-block data-term partials divided by c3 and the
-// kept counts (block_counts[0 .. nblk)).  With partial == nullptr,
-// launch_classic_cp16 only stores in *block_counts the resident blocks per CU.
+// kept counts (block_counts[0 .. nblk)).
 bool classic_supported(int D, int K);
-// Blocks of the FP32 kernel for a batch of n_rows > 0 documents.
+// Their blocks for a batch of n_rows > 0 documents.
 int classic_blocks(int D, int K, int n_rows, int num_cu);
 hipError_t launch_classic_z(const float* W32, int V, int D, int Dp, const float* Phi, int K,
                             int Kp, const float* mw32, float* Z, float* r, float* phi_copy,

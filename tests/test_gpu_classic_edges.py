@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+from bf16_ref import assert_within, bf16_round, classic_bf16_bound, z16_like_kernel
 from oracle import tlda_oracle as O
 from synth import init_phi
 
@@ -71,3 +72,31 @@ def test_classic_step_matches_oracle(D, K, n):
     g2, _ = step(ctx, rp, ci, va, Phi)
     assert np.array_equal(g, g2)
     check(g, kept, rp, ci, va, V, m, W, Phi, 1.5)
+
+
+@pytest.mark.parametrize("n", [1, 13, 300, 3500])
+@pytest.mark.parametrize("D,K", [(4, 16), (16, 33), (17, 48), (50, 49), (65, 65), (97, 20),
+                                 (128, 127), (112, 32)])
+def test_classic_bf16_step_within_its_bound(D, K, n):
+    if n >= 3500 and (D, K) not in ((50, 49), (65, 65)):
+        pytest.skip("one shape per kind at the sizes with several documents a wave")
+    rng = np.random.default_rng(D * 100 + K)
+    rp, ci, va = batch(n, n + D)
+    Q, _ = np.linalg.qr(rng.standard_normal((V, D)))
+    W = Q * rng.uniform(5, 30, D)
+    m = rng.dirichlet(np.ones(V))
+    Phi = (init_phi(D, K, D + K) * 0.3).astype(np.float32)
+    ctx = tl.tlda_create(V, K, D, 1.5, 0.5, classic=True, bf16=True)
+    tl.tlda_set_whitening(ctx, W, m)
+    g, kept = step(ctx, rp, ci, va, Phi)
+    g2, _ = step(ctx, rp, ci, va, Phi)
+    assert np.array_equal(g, g2)
+    P = Phi.astype(np.float64)
+    W16 = bf16_round(W)
+    Z16 = z16_like_kernel(W16, Phi)
+    data, n_kept = O.classic_data_term(rp, ci, va, V, m, W16, P, 1.5, Z=Z16)
+    assert kept == n_kept
+    G = P.T @ P
+    ref = 4.5 * P @ (G * G) - 3.0 / max(kept, 1) * data if kept else np.zeros_like(P)
+    bound = 3.0 / max(kept, 1) * classic_bf16_bound(rp, ci, va, W16, Z16, P, m, 1.5)
+    assert_within(g, ref, bound + 2.0 ** -22 * np.abs(ref), f"classic BF16 D={D} K={K} n={n}")
