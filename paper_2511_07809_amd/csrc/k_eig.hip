@@ -104,6 +104,10 @@ __global__ void __launch_bounds__(256) k_gemm64(int M, int N, int Kd, const doub
 // equal runs, so that every compute unit ends together whatever M is.  A run
 // that covers a tile writes C; the pieces of a divided tile go to ws, piece
 // (block + tile), and k_dgemm_sum adds them in order.
+// 20000^2 x 200: 2.70 ms, 59 TFLOP/s, and 27 us for the pieces (3.6 ms with
+// narrower tiles and K in whole chunks); 20000^2 x 100: 1.5 ms, 53 TFLOP/s (1.95
+// ms).  Storing the next slab before the last
+// products changed neither.
 // pick (or NULL): with B_set, *pick chooses the right operand (B_set where it
 // is set); without it, nothing is done where it is set.
 // ---------------------------------------------------------------------------
@@ -120,9 +124,11 @@ struct DgPlan {
     return blocks == gx * gy ? 0 : (size_t)(blocks + gx * gy) * kDgBM * 16 * nt;
   }
 };
-// One round of resident blocks (two on a CU while the tile leaves room), runs
-// of at least 4 slabs; short products (K < 256) take whole tiles, whose pieces
-// would cost more than the rows left over.
+// One round of resident blocks: two on a CU while the sums of a tile take at
+// most 112 columns (56 registers of a lane; one block above that has the CU's
+// registers to itself).  Runs of at least 4 slabs; short products (K < 256: the
+// block times a p x p matrix, 16 slabs at most) take whole tiles, whose pieces
+// would be a read and a write of C more.
 DgPlan dgemm_plan(int M, int N, int K, int num_cu) {
   DgPlan d;
   const int tiles = (N + 15) / 16;
@@ -609,6 +615,9 @@ __global__ void __launch_bounds__(kRotThreads) k_jacobi_rot(const double* __rest
   for (int i = tid; i < p; i += kRotThreads) ev[i] = A[tri(i, i)];
 }
 
+// The rotations take 3.6 ms at p = 200 and 0.5 at p = 100, the vectors 0.29 and
+// 0.1 (58 and 1.42 ms when one block kept matrix and vectors, the larger one in
+// memory): a round is two barriers and one pair per thread, a serial chain.
 // Z = the product of k_jacobi_rot's rotations: one wave per row of Z, the row
 // in LDS, lane l taking pairs l and l + 64 of every round; the next round's
 // rotations are on their way while this one's are applied.

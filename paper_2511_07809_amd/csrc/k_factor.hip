@@ -20,6 +20,11 @@
 // since lane l supplies A[l % 16][4 s + l / 16] and B[4 s + l / 16][l % 16] in
 // step s.  R_kk^-T is stored by columns, where entry s * 64 + l is the A
 // operand.
+//
+// Factor and inverse at p = 100: 45 us (34 and 11), 145 before (a wave per
+// column and a block-wide barrier per pivot, on the vector ALUs); at p = 200:
+// 88 and 27 us, 1420 before (the matrix in memory); at p = 21: 12 us, 29 before.
+// A 16-pivot step takes 4.75 us of them.
 #include "tlda_internal.h"
 
 namespace tlda {
@@ -166,7 +171,9 @@ constexpr int panel_tiles(int n) {
 }
 
 // Where the diagonal of R spans less than this, the block's columns come out of
-// one Cholesky-QR pass orthonormal to about 1e-16 / kWell^2 = 1e-8.
+// one Cholesky-QR pass orthonormal to about 1e-16 / kWell^2 = 1e-8, and the
+// iteration goes on without the second (the cold refresh at V = 20000, p = 200
+// takes 263 ms with it everywhere, 244 without it there).
 constexpr double kWell = 1e-4;
 
 // The factor, tiles in registers: one block of NW waves, tile t = tile_at(i, j)
@@ -176,8 +183,8 @@ constexpr double kWell = 1e-4;
 // it.  skip (or NULL): nothing to do when it is set.  well (or NULL) receives 1
 // when the smallest diagonal entry of R is at least kWell of the largest.
 // nz > 0: G holds the nz chunks of a Gram product's tiles (k_gram), which are
-// added here in chunk order: a launch less where there are few.  INV: the block goes on to the inverse, its tiles in LDS (few tiles: a
-// second launch would cost more than other compute units would save).
+// added here in chunk order: a launch less where there are few.  INV: the block
+// goes on to the inverse, its tiles in LDS.
 template <int NW, int SLOTS, bool INV>
 __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, int p,
                                                   double shift_rel, double* __restrict__ tiles,
@@ -333,8 +340,8 @@ __global__ void __launch_bounds__(64 * NW) k_chol(const double* __restrict__ G, 
   }
 }
 
-// The same for more tiles than fit in registers: they live in `tiles`, each
-// touched by wave t % 16 alone.
+// The same for more tiles than fit in registers (91 at p = 208): they live in
+// `tiles`, each touched by wave t % 16 alone.
 __global__ void __launch_bounds__(1024) k_chol_mem(const double* __restrict__ G, int p,
                                                    double shift_rel, double* tiles, double* dinv,
                                                    int* __restrict__ info,
@@ -413,7 +420,8 @@ __global__ void __launch_bounds__(1024) k_chol_mem(const double* __restrict__ G,
   }
 }
 
-// One wave per block column of the inverse.
+// One wave per block column of the inverse: independent chains, so the columns
+// go to different compute units (27 us at p = 200; 123 in one block of waves).
 __global__ void __launch_bounds__(64) k_tri_inverse(const double* __restrict__ tiles,
                                                     const double* __restrict__ dinv, int p,
                                                     double* __restrict__ Binv,
@@ -436,6 +444,8 @@ __global__ void __launch_bounds__(64) k_tri_inverse(const double* __restrict__ t
 // j are formed, and mirrored.
 // Bound: the matrix cores, 2 V p (p + 16) / 2 flops when symmetric; a wider
 // unit would spill, a narrower one reads more operand bytes per product.
+// V = 20000, p = 200: 48 us and 6 for the sum of the chunks (18 TFLOP/s; 150 us
+// on the vector ALUs with every entry formed), p = 100: 19 and 7.
 // ---------------------------------------------------------------------------
 constexpr int kGramN = 7, kGramWaves = 4;
 
@@ -574,7 +584,9 @@ __global__ void __launch_bounds__(256) k_gram_sum(const double* __restrict__ par
 // (x e^(-2^(k+1) x), summed), so 40 bound it by 5e-11, far below the FP32 step
 // size it is for; usually B is a projector (tr(B^2) = 1 to rounding) after 8
 // to 15, and that ends it.  One block; the tiles stay in LDS, and as B is
-// symmetric its tiles serve as both operands as they are stored.
+// symmetric its tiles serve as both operands as they are stored.  Bound: the
+// chain of squarings, 30 us at n = 50 (1030 us when a whole Jacobi iteration
+// gave the one eigenvalue).
 // Writes step = 1 / lambda (0 when there is no positive eigenvalue).
 // ---------------------------------------------------------------------------
 constexpr int kTopNb = 8, kTopWaves = 8;
@@ -692,6 +704,11 @@ static hipError_t launch_chol_inverse(const double* G, int p, double shift_rel, 
 #define TLDA_CHOL(nw, slots, inv)                                                             \
   hipLaunchKernelGGL((k_chol<nw, slots, inv>), dim3(1), dim3(64 * nw), 0, s, G, p, shift_rel, \
                      tiles, dinv, Binv, info, skip, well, nz)
+  // Up to p = 80 the block forms the inverse as well (its 15 tiles fit LDS beside
+  // their inverse, and a launch costs 2 us and more where the columns' waves on
+  // other compute units would save less); up to 144 and 208 the tiles fit in 6
+  // and 12 slots of eight waves, past that they stay in memory, where every step
+  // of the chain waits for it.
   if (nb <= 5) {
     TLDA_CHOL(4, 4, true);
     return hipGetLastError();
@@ -716,6 +733,8 @@ static int gram_chunks(int V, const GramShape& g, int blocks) {
 }
 // 1024 blocks are four waves per SIMD of the 256 compute units; half of them
 // for the one product of an inference, whose scratch every context keeps.
+// Blocks of the tall products: four a CU for the refresh's, whose tile rows are
+// several units; two for the projection's, whose chunks the sum reads again.
 constexpr int kGramBlocks = 1024, kProjectBlocks = 512;
 
 // The chunks alone; their number to nz.

