@@ -439,6 +439,29 @@ __device__ __forceinline__ void cp_bf16_block(
 }
 
 
+// The squared Gram entries (phi_j . phi_k)^2 with k_gram_sq's summation: four
+// lanes per entry, e4 = 4 entry + chain, chain c over d = 4m + c, chain 0 also
+// the tail, added as (c0 + c1) + (c2 + c3).  4 K^2 is a multiple of 4, so the
+// four lanes of an entry leave the loop together.
+__device__ __forceinline__ void gram_entries(const float* P, int D, int K, int first, int stride,
+                                             double* __restrict__ gsq) {
+  for (int e4 = first; e4 < 4 * K * K; e4 += stride) {
+    const int e = e4 >> 2, c = e4 & 3;
+    const int j = e / K, k = e % K;
+    double accg = 0.0;
+    const int M = D / 4;
+    for (int m = 0; m < M; ++m) {
+      const int i = 4 * m + c;
+      accg += (double)P[i * K + j] * (double)P[i * K + k];
+    }
+    if (c == 0)
+      for (int i = 4 * M; i < D; ++i) accg += (double)P[i * K + j] * (double)P[i * K + k];
+    accg += __shfl_xor(accg, 1, 64);
+    accg += __shfl_xor(accg, 2, 64);
+    if (c == 0) gsq[e] = accg * accg;
+  }
+}
+
 template <int DQ, int KQ, int G, int MODE>
 __global__ void __launch_bounds__(64 * (MODE == kWhitenOnly ? 4 : bf16_waves(DQ, KQ)),
                                   (DQ <= 64 && KQ <= 64) ? 3 : 4)
@@ -468,11 +491,8 @@ __global__ void __launch_bounds__(64 * (MODE == kWhitenOnly ? 4 : bf16_waves(DQ,
                                  Xin, D, Phi, K, partial, block_counts, Xout, phi_copy, Xs, XsT,
                                  SsT, wave_kept, ent);
   // The fused step also forms the finish's squared Gram entries of Phi (still
-  // Phi0 here: the finish writes Phi after this kernel), with k_gram_sq's
-  // summation (four lanes per entry, chain c over d = 4m + c, chain 0 also
-  // the tail, added as (c0 + c1) + (c2 + c3)), so no launch of its own.
-  // 4 K^2 is a multiple of 4, so the four lanes of an entry leave the loop
-  // together.  The 16-wave blocks read Phi from an LDS copy in the space of
+  // Phi0 here: the finish writes Phi after this kernel), so no launch of its
+  // own.  The 16-wave blocks read Phi from an LDS copy in the space of
   // the column-major tiles (free since the block's last barrier; 17 408
   // floats >= D K), the others from global memory.
   constexpr int kThr = 64 * NW;
@@ -485,32 +505,19 @@ __global__ void __launch_bounds__(64 * (MODE == kWhitenOnly ? 4 : bf16_waves(DQ,
       __syncthreads();
       P = Pf;
     }
-    for (int e4 = blockIdx.x * kThr + threadIdx.x; e4 < 4 * K * K; e4 += nblk * kThr) {
-      const int e = e4 >> 2, c = e4 & 3;
-      const int j = e / K, k = e % K;
-      double accg = 0.0;
-      const int M = D / 4;
-      for (int m = 0; m < M; ++m) {
-        const int i = 4 * m + c;
-        accg += (double)P[i * K + j] * (double)P[i * K + k];
-      }
-      if (c == 0)
-        for (int i = 4 * M; i < D; ++i) accg += (double)P[i * K + j] * (double)P[i * K + k];
-      accg += __shfl_xor(accg, 1, 64);
-      accg += __shfl_xor(accg, 2, 64);
-      if (c == 0) gsq[e] = accg * accg;
-    }
+    gram_entries(P, D, K, blockIdx.x * kThr + threadIdx.x, nblk * kThr, gsq);
   }
 }
 
 // Several batches (the slices of a batched run, each with its own
 // whitening, D, K and Phi) in one launch: block b serves slice blk_slice[b],
 // as block b - blk0 of that slice's nblk blocks.  One LDS allocation of the
-// largest shape (D, K <= 64) serves every slice.  Tile shape: TR documents
+// largest shape (D, K <= 64) serves every slice.  Four waves per SIMD: the Gram
+// entries at the end would take 4-wave blocks to three (263 us).  Tile shape: TR documents
 // per row tile, NW waves per block (the plan's autotuner picks among the
 // instances below).
 template <int TR, int NW>
-__global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_cp_bf16_multi(
+__global__ void __launch_bounds__(64 * NW, 4) k_cp_bf16_multi(
     const SliceStep* __restrict__ sl, const int* __restrict__ blk_slice) {
   constexpr int LDA = 64 + 8, LDT = TR + 8;
   __shared__ __attribute__((aligned(16))) uint16_t Xs[TR * LDA];
@@ -535,6 +542,10 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 4) k_cp_bf16_multi(
     default: break;
   }
 #undef TLDA_MULTI
+  // The slice's squared Gram entries, once: formed by every block of the finish
+  // for its own entries they were most of its time (24 slices, D = K = 50 at
+  // most: finish 28 -> 17 us, this kernel 241 -> 243).
+  gram_entries(d.Phi, d.D, d.K, blk * 64 * NW + threadIdx.x, d.nblk * 64 * NW, d.gsq);
 }
 
 struct Bf16Args {

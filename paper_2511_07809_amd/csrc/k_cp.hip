@@ -582,7 +582,7 @@ __global__ void __launch_bounds__(kFinThreads, 8) k_cp_finish_multi(const SliceS
   const SliceStep& d = sl[fin_slice[blockIdx.x]];
   cp_finish_block<kFinEntries>(blockIdx.x - d.fin0, d.partial, d.nblk, d.block_counts, d.nblk, 0,
                                d.phi_copy, d.D, d.K, d.alpha0, d.theta, d.beta, d.Phi, d.grad,
-                               d.R1, d.n_kept_out, ph, nullptr);
+                               d.R1, d.n_kept_out, ph, d.gsq);
 }
 
 }  // namespace

@@ -1427,6 +1427,7 @@ tlda_status tlda_multi_create(int32_t n_slices, tlda_ctx* const* ctxs,
     d.shape = tlda::multi_shape(d.D, d.K);
     d.Phi = Phis[i];
     d.phi_copy = c->cp.phi0;
+    d.gsq = c->cp.gsq;
     d.grad = c->cp.grad;
     d.R1 = c->cp.R1;
     d.n_kept_out = n_kept_out ? n_kept_out + i : nullptr;

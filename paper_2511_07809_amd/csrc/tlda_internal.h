@@ -201,6 +201,7 @@ struct SliceStep {
   int Dh, D, K, shape;
   float* Phi;            // read by the reduction (copied to phi_copy), written by the finish
   float* phi_copy;
+  double* gsq;           // [K][K] squared Gram entries of Phi, from the reduction
   float* partial;        // [nblk][D][K]
   int* block_counts;     // [nblk]
   int nblk, blk0, fin0;
