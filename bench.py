@@ -257,7 +257,7 @@ def run_classic(args) -> None:
     # roofline of the data-term kernel: one reduction row per nonzero, a D x K
     # outer product on the matrix cores; bytes = CSR + W + Z copies, once
     per = args.steps
-    kname = "k_classic_cp16" if bf16 else "k_classic_cp"
+    kname = "k_classic_cp"
     peak = BF16_MFMA_PEAK_TFLOPS if bf16 else FP32_VALU_PEAK_TFLOPS
     flops = 2.0 * (r["nnz"] / per) * D * K
     elem = 2 if bf16 else 4

@@ -6,7 +6,8 @@ the matrix tiles of 16 and the split of K at 64, and fewer documents than waves.
 Tolerance: 1e-5 of the data term's Frobenius norm, ten times what FP32 products
 and sums of a few thousand terms (6e-8 each, about 1e-6 together) lose against
 FP64.  (Not of the gradient's norm: at D = 1, n = 3500 the penalty and the data
-term cancel to a hundredth.)"""
+term cancel to a hundredth.)  BF16: the oracle on the operands that the kernel
+rounds, the rest within the entry-wise bound derived in tests/bf16_ref.py."""
 import numpy as np
 import pytest
 import torch
