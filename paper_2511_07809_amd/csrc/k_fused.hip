@@ -951,16 +951,20 @@ hipError_t launch_wide(const tlda_csr_batch& b, const float* W32, const float* m
 // documents, 16.0 -> 12.6 for 16 000; at 30 000 both take 17.3 and at 60 000
 // this takes 25.0 against 21.9 (the lanes' redundant reads then count; at D = 20
 // the two cross between 30 000 and 60 000 as well).
-constexpr int kSmallRows = 16384, kSmallTile = 16;
-bool fused_small(int D, int K, int n_rows) {
-  return mfma_bucket(D) <= 32 && mfma_bucket(K) <= 64 && D > 0 && n_rows <= kSmallRows;
-}
+constexpr int kSmallTile = 16;
 
 template <int DQ, int KQ>
 hipError_t launch_fused_small(int G, const tlda_csr_batch& b, const float* W32, const float* mw32,
                               int D, int Dp, const float* Phi, int K, int nblk, float* partial,
                               int* block_counts, float* Xout, float* phi_copy, hipStream_t s) {
   auto go = [&](auto kernel) {
+    if (partial == nullptr) {
+      int per_cu = 0;
+      const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &per_cu, kernel, 64 * fused_waves(DQ, KQ), 0);
+      *block_counts = per_cu;
+      return e;
+    }
     launch_main(kernel, dim3(nblk), dim3(64 * fused_waves(DQ, KQ)), 0, s, b.row_ptr, b.col_idx,
                 b.val, b.n_rows, W32, mw32, D, Dp, Phi, K, nblk, partial, block_counts, Xout,
                 phi_copy);
@@ -1019,6 +1023,10 @@ namespace {
 bool fused_wide(int D, int K) { return mfma_bucket(D) > 64 || mfma_bucket(K) > 64; }
 }  // namespace
 
+bool fused_small(int D, int K, int n_rows) {
+  return mfma_bucket(D) <= 32 && mfma_bucket(K) <= 64 && D > 0 && n_rows <= kFusedSmallRows;
+}
+
 int fused_tile_rows(int D, int K, int n_rows) {
   if (fused_small(D, K, n_rows)) return kSmallTile;
   if (mfma_bucket(D) >= 64 && mfma_bucket(K) >= 64) return 48;   // the hybrid kernel
@@ -1075,7 +1083,7 @@ hipError_t launch_whiten_cp(const tlda_csr_batch& b, const float* W32, const flo
   int G = Dp / 4;   // lanes per document: Dp is 4, 8, 16, 32 or 64 here
   if (G < 1) G = 1;
   if (G > 16) G = 16;
-  if (partial != nullptr && fused_small(D, K, b.n_rows)) {
+  if (fused_small(D, K, b.n_rows)) {
 #define TLDA_SMALL(DQ_, KQ_)                                                                     \
   if (dq == DQ_ && kq == KQ_)                                                                    \
     return launch_fused_small<DQ_, KQ_>(G, b, W32, mw32, D, Dp, Phi, K, nblk, partial,           \

@@ -145,6 +145,27 @@ int bf16_grid(tlda_ctx* c, int mode, int n_rows) {
   return nblk < 1 ? 1 : nblk;
 }
 
+// Blocks of the FP32 fused kernel: the tuned number, or one full round of
+// resident blocks of the instance that is launched.  Small batches take an
+// instance of their own, so each has its number: a batch is cut the same way
+// whatever the context stepped before it.
+tlda_status fused_grid(tlda_ctx* c, bool small, int* blocks) {
+  *blocks = c->tune.fused_blocks;
+  if (*blocks > 0) return TLDA_OK;
+  int& resident = c->tune.fused_resident[small ? 1 : 0];
+  if (resident <= 0) {
+    tlda_csr_batch b{};
+    b.n_rows = small ? 1 : tlda::kFusedSmallRows + 1;
+    int per_cu = 0;
+    HIP_OK(c, tlda::launch_whiten_cp(b, c->wh.W32, c->wh.mw32, c->cfg.D, c->Dp, c->Dt,
+                                     w32_tail_base(c), nullptr, c->cfg.K, 0, nullptr, &per_cu,
+                                     nullptr, nullptr, nullptr, c->stream));
+    resident = (per_cu > 0 ? per_cu : 1) * c->num_cu;
+  }
+  *blocks = resident;
+  return TLDA_OK;
+}
+
 tlda_status ensure_partial(tlda_ctx* c, size_t need) {
   if (c->cp.cap < need) {
     HIP_OK(c, hipStreamSynchronize(c->stream));
@@ -437,14 +458,9 @@ tlda_status fused_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float* 
   } else {
     const int T = tlda::fused_tile_rows(D, K, b->n_rows);
     const int ntiles = (b->n_rows + T - 1) / T;
-    if (c->tune.fused_blocks <= 0) {
-      int per_cu = 0;
-      HIP_OK(c, tlda::launch_whiten_cp(*b, c->wh.W32, c->wh.mw32, D, c->Dp, c->Dt,
-                                       w32_tail_base(c), Phi, K, 0, nullptr,
-                                       &per_cu, nullptr, nullptr, nullptr, c->stream));
-      c->tune.fused_blocks = (per_cu > 0 ? per_cu : 1) * c->num_cu;
-    }
-    nblk = ntiles < c->tune.fused_blocks ? ntiles : c->tune.fused_blocks;
+    st = fused_grid(c, tlda::fused_small(D, K, b->n_rows), &nblk);
+    if (st != TLDA_OK) return st;
+    if (ntiles < nblk) nblk = ntiles;
     if (nblk > 2 * tlda::kWhitenBlockCounts) nblk = 2 * tlda::kWhitenBlockCounts;
   }
   if (partial != nullptr) {
@@ -1636,14 +1652,13 @@ tlda_status tlda_graph_capture_steps(tlda_ctx* c, const tlda_csr_batch* batches,
   if (is_bf16(c)) {
     need = (size_t)bf16_grid(c, 0, max_rows) * D * K;
   } else {
-    if (c->tune.fused_blocks <= 0) {
-      int per_cu = 0;
-      HIP_OK(c, tlda::launch_whiten_cp(batches[0], c->wh.W32, c->wh.mw32, D, c->Dp, c->Dt,
-                                       w32_tail_base(c), Phi, K, 0,
-                                       nullptr, &per_cu, nullptr, nullptr, nullptr, c->stream));
-      c->tune.fused_blocks = (per_cu > 0 ? per_cu : 1) * c->num_cu;
-    }
-    int nblk = std::min(c->tune.fused_blocks, 2 * tlda::kWhitenBlockCounts);
+    // (room for either instance's full grid: a later step must not regrow the
+    // buffer that the graph writes)
+    int large = 0, small = 0;
+    tlda_status st = fused_grid(c, false, &large);
+    if (st == TLDA_OK && tlda::fused_small(D, K, 1)) st = fused_grid(c, true, &small);
+    if (st != TLDA_OK) return st;
+    const int nblk = std::min(std::max(large, small), 2 * tlda::kWhitenBlockCounts);
     need = (size_t)nblk * D * K;
   }
   tlda_status st = ensure_partial(c, need);

@@ -107,6 +107,8 @@ struct EigScratch {
 struct Tuning {
   int cp_max_blocks = 0;
   int fused_blocks = 0;
+  int fused_resident[2] = {0, 0};     // cached occupancy rounds of the FP32 fused kernels: the
+                                      // one of large batches, the one of small ones
   int bf16_blocks = 0;
   int bf16_resident[3] = {0, 0, 0};   // cached occupancy rounds of the BF16 kernels
   int whiten_v4 = 0;
@@ -336,9 +338,13 @@ int mfma_bucket(int n);
 int cp_mfma_tile_rows(int D, int K);
 // fused whitening + CP reduction
 bool fused_supported(int D, int K, int Dp);
+// Whether a batch takes the small-batch instance (never past kFusedSmallRows rows).
+constexpr int kFusedSmallRows = 16384;
+bool fused_small(int D, int K, int n_rows);
 int fused_tile_rows(int D, int K, int n_rows);   // row tile of the fused kernel for this batch
 // With partial == nullptr, launch_whiten_cp only stores in *block_counts how
-// many blocks of the kernel it would launch can be resident on one CU.
+// many blocks of the kernel it would launch for this batch can be resident on
+// one CU.
 // Dt > 0: W32 also holds, from element tail_base on, a [V][Dt] copy of the
 // columns past the last whole 128-byte line of each row (w32_tail_cols).
 // gsq != nullptr: the kernel also forms the K x K squared Gram entries of

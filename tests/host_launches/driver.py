@@ -1,0 +1,120 @@
+"""Drives libtlda's host layer on the runtime stand-in (fake_hip.cpp), without
+a GPU.  Usage: python driver.py STAND_IN_SO CHECK; exit status 0 when CHECK
+holds.  Run in a process of its own: the stand-in takes the real runtime's
+place, so torch (which loads that) must stay out."""
+import ctypes
+import os
+import sys
+import types
+
+ROOT = os.path.dirname(os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+sys.path.insert(0, ROOT)
+FAKE = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sys.modules["torch"] = types.ModuleType("torch")   # the binding's import
+
+import numpy as np  # noqa: E402
+
+from paper_2511_07809_amd import tlda as tl  # noqa: E402
+
+LIB = tl._LIB
+for name, res in (("fake_kernel", ctypes.c_char_p), ("fake_query", ctypes.c_char_p),
+                  ("fake_grid", ctypes.c_uint32), ("fake_block", ctypes.c_uint32),
+                  ("fake_arg", ctypes.c_uint64)):
+    getattr(FAKE, name).restype = res
+FAKE.fake_fail_malloc.argtypes = [ctypes.c_longlong]
+
+NUM_CU = 256
+
+
+def context(V, K, D, flags=0):
+    cfg = tl.tlda_config(V, K, D, flags, 1.0, 0.0, 0, 0, 0, 0)
+    h = ctypes.c_void_p()
+    # (any stream but the null one, which is never captured)
+    assert LIB.tlda_create(ctypes.byref(cfg), ctypes.c_void_p(8), ctypes.byref(h)) == 0
+    return h
+
+
+def set_whitening(h, V, D, seed=0):
+    rng = np.random.default_rng(seed)
+    W, m = rng.standard_normal((V, D)), np.full(V, 1.0 / V)
+    return LIB.tlda_set_whitening(h, W.ctypes.data, m.ctypes.data)
+
+
+def batch(n, words=4):
+    """n documents of `words` words each (arrays that outlive the call)."""
+    rp = np.arange(n + 1, dtype=np.int32) * words
+    ci = np.tile(np.arange(words, dtype=np.int32), n)
+    va = np.ones(n * words, dtype=np.float32)
+    batch.keep = getattr(batch, "keep", []) + [(rp, ci, va)]
+    return tl.tlda_csr_batch(n, n * words, rp.ctypes.data, ci.ctypes.data, va.ctypes.data, -1, 0)
+
+
+def step(h, b, D, K):
+    """The step's launches, as (kernel, grid in x)."""
+    Phi = np.zeros((D, K), dtype=np.float32)
+    FAKE.fake_clear()
+    assert LIB.tlda_whiten_cp_step(h, ctypes.byref(b), 0.0, Phi.ctypes.data, None, None, None) == 0
+    return launches()
+
+
+def launches():
+    return [(FAKE.fake_kernel(i).decode(), FAKE.fake_grid(i, 0))
+            for i in range(FAKE.fake_launches())]
+
+
+def base(kernel):
+    return kernel.replace("(anonymous namespace)::", "").split("(")[0].split("<")[0].split("::")[-1]
+
+
+def check_fused_grid_does_not_depend_on_the_batch_before():
+    """The grid of a fused FP32 step is a function of its own batch: one round
+    of the blocks of the instance that is launched, whichever batch came first."""
+    # every row-tile height its own occupancy: 16 rows (small batches), 32, 64
+    for t, n in ((16, 3), (32, 5), (64, 7)):
+        for dq in (16, 32):
+            for kq in (16, 32, 64):
+                FAKE.fake_occupancy(f"k_whiten_cp<{dq}, {kq}, {t},".encode(), n)
+    V = 400
+    for D, K in ((5, 5), (32, 10), (16, 33)):
+        seen = []
+        for order in ((1000, 200000), (200000, 1000), (16384, 16385), (16385, 16384)):
+            h = context(V, K, D)
+            assert set_whitening(h, V, D) == 0
+            grids = {}
+            for n in order:
+                b = batch(n, 1)
+                kernel, grid = step(h, b, D, K)[0]
+                assert base(kernel) == "k_whiten_cp", kernel
+                queried = [FAKE.fake_query(i).decode() for i in range(FAKE.fake_queries())]
+                assert all(q == kernel for q in queried), (queried, kernel)
+                grids[n] = grid
+            seen.append(grids)
+            LIB.tlda_destroy(h)
+        assert seen[0] == seen[1] and seen[2] == seen[3], (D, K, seen)
+        assert seen[0][200000] in (5 * NUM_CU, 7 * NUM_CU), seen   # the round is full
+
+
+def check_captured_steps_never_regrow_their_partials():
+    """A graph of steps keeps the address of the context's partials: neither
+    instance's later step may need more than the capture reserved."""
+    for t, n in ((16, 8), (32, 1), (64, 1)):
+        FAKE.fake_occupancy(f", {t},".encode(), n)
+    FAKE.fake_keep_args(b"k_whiten_cp", 13)
+    V, D, K = 400, 5, 5
+    Phi = np.zeros((D, K), dtype=np.float32)
+    h = context(V, K, D)
+    assert set_whitening(h, V, D) == 0
+    FAKE.fake_clear()
+    arr = (tl.tlda_csr_batch * 1)(batch(200000, 1))
+    g = ctypes.c_void_p()
+    assert LIB.tlda_graph_capture_steps(h, arr, 1, 0.0, Phi.ctypes.data, ctypes.byref(g)) == 0
+    partial = FAKE.fake_arg(0, 11)
+    for n in (16384, 1000, 500000):
+        step(h, batch(n, 1), D, K)
+        assert FAKE.fake_arg(0, 11) == partial, n
+    LIB.tlda_graph_destroy(g)
+    LIB.tlda_destroy(h)
+
+
+if __name__ == "__main__":
+    globals()["check_" + sys.argv[2]]()
