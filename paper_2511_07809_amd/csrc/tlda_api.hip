@@ -44,7 +44,10 @@ template <typename T>
 hipError_t dalloc(T** p, size_t count) {
   *p = nullptr;
   if (count == 0) count = 1;
-  return hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+  const hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
+  // reported here: left behind, it would be taken for the next launch's error
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
 }
 
 template <typename T>
@@ -334,12 +337,12 @@ tlda_status orthonormalise(tlda_ctx* c, const double* in, double* out, bool may_
 tlda_status save_prev(tlda_ctx* c) {
   if (!c->wh.ready) return TLDA_OK;
   const size_t V = c->cfg.V, D = c->cfg.D;
-  if (c->wh.Uprev == nullptr) {
-    HIP_OK(c, dalloc(&c->wh.Uprev, V * D));
-    HIP_OK(c, dalloc(&c->wh.eigprev, D));
-    HIP_OK(c, dalloc(&c->wh.C, D * D));
+  // (each on its own: an earlier call may have run out of memory part of the way)
+  if (c->wh.Uprev == nullptr) HIP_OK(c, dalloc(&c->wh.Uprev, V * D));
+  if (c->wh.eigprev == nullptr) HIP_OK(c, dalloc(&c->wh.eigprev, D));
+  if (c->wh.C == nullptr) HIP_OK(c, dalloc(&c->wh.C, D * D));
+  if (c->wh.part == nullptr)
     HIP_OK(c, dalloc(&c->wh.part, tlda::gram_scratch_doubles((int)V, (int)D, false)));
-  }
   HIP_OK(c, hipMemcpyAsync(c->wh.Uprev, c->wh.U, sizeof(double) * V * D, hipMemcpyDeviceToDevice,
                            c->stream));
   HIP_OK(c, hipMemcpyAsync(c->wh.eigprev, c->wh.eig, sizeof(double) * D, hipMemcpyDeviceToDevice,

@@ -99,7 +99,7 @@ def check_captured_steps_never_regrow_their_partials():
     instance's later step may need more than the capture reserved."""
     for t, n in ((16, 8), (32, 1), (64, 1)):
         FAKE.fake_occupancy(f", {t},".encode(), n)
-    FAKE.fake_keep_args(b"k_whiten_cp", 13)
+    FAKE.fake_keep_args(b"k_whiten_cp<", 13)
     V, D, K = 400, 5, 5
     Phi = np.zeros((D, K), dtype=np.float32)
     h = context(V, K, D)
@@ -114,6 +114,37 @@ def check_captured_steps_never_regrow_their_partials():
         assert FAKE.fake_arg(0, 11) == partial, n
     LIB.tlda_graph_destroy(g)
     LIB.tlda_destroy(h)
+
+
+def check_rebase_after_a_failed_allocation():
+    """Out of memory anywhere in keeping the previous whitening leaves a context
+    whose next whitening and rebase work: no kernel gets a null buffer."""
+    FAKE.fake_keep_args(b"k_gram(", 8)
+    FAKE.fake_keep_args(b"k_gram_sum(", 6)
+    FAKE.fake_keep_args(b"k_rebase(", 6)
+    V, D, K = 300, 6, 5
+    Phi = np.zeros((D, K), dtype=np.float32)
+    failures = 0
+    for after in range(6):
+        h = context(V, K, D)
+        assert set_whitening(h, V, D, 1) == 0
+        FAKE.fake_fail_malloc(after)
+        st = set_whitening(h, V, D, 2)
+        FAKE.fake_fail_malloc(-1)
+        assert st in (0, 6), st   # TLDA_ERR_OOM
+        failures += st == 6
+        assert set_whitening(h, V, D, 3) == 0
+        FAKE.fake_clear()
+        assert LIB.tlda_rebase_phi(h, Phi.ctypes.data) == 0
+        seen = set()
+        for i, (kernel, _) in enumerate(launches()):
+            pointers = {"k_gram": (0, 1, 6), "k_gram_sum": (0, 3), "k_rebase": (0, 1, 2, 5)}
+            seen.add(base(kernel))
+            for a in pointers[base(kernel)]:
+                assert FAKE.fake_arg(i, a) != 0, (after, kernel, a)
+        assert seen == {"k_gram", "k_gram_sum", "k_rebase"}
+        LIB.tlda_destroy(h)
+    assert failures == 4
 
 
 if __name__ == "__main__":
