@@ -517,10 +517,8 @@ tlda_status classic_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
   if (is_bf16(c)) {
     const int Kh = tlda::bf16_cols(K);
-    if (c->cp.Z16 == nullptr) {
-      HIP_OK(c, dalloc(&c->cp.Z16, (size_t)V * Kh));
-      if (c->cp.rz == nullptr) HIP_OK(c, dalloc(&c->cp.rz, (size_t)Kh));
-    }
+    if (c->cp.Z16 == nullptr) HIP_OK(c, dalloc(&c->cp.Z16, (size_t)V * Kh));
+    if (c->cp.rz == nullptr) HIP_OK(c, dalloc(&c->cp.rz, (size_t)Kh));
     const int nblk = tlda::classic_blocks(D, K, b->n_rows, c->num_cu);
     st = ensure_partial(c, (size_t)nblk * D * K);
     if (st != TLDA_OK) return st;
@@ -540,10 +538,8 @@ tlda_status classic_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float
                      n_kept_out);
   }
   const int Kp = tlda::padded_d(K);
-  if (c->cp.Z == nullptr) {
-    HIP_OK(c, dalloc(&c->cp.Z, (size_t)V * Kp));
-    HIP_OK(c, dalloc(&c->cp.rz, (size_t)Kp));
-  }
+  if (c->cp.Z == nullptr) HIP_OK(c, dalloc(&c->cp.Z, (size_t)V * Kp));
+  if (c->cp.rz == nullptr) HIP_OK(c, dalloc(&c->cp.rz, (size_t)Kp));
   const int nblk = tlda::classic_blocks(D, K, b->n_rows, c->num_cu);
   st = ensure_partial(c, (size_t)nblk * D * K);
   if (st != TLDA_OK) return st;

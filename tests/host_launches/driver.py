@@ -147,5 +147,29 @@ def check_rebase_after_a_failed_allocation():
     assert failures == 4
 
 
+def check_classic_step_after_a_failed_allocation():
+    """Out of memory in a classic context's first step: the next one works."""
+    FAKE.fake_keep_args(b"k_classic_z", 10)
+    FAKE.fake_keep_args(b"k_classic_cp<", 15)
+    V, D, K = 300, 6, 5
+    for flags in (tl.TLDA_CLASSIC, tl.TLDA_CLASSIC | tl.TLDA_BF16):
+        failures = 0
+        for after in range(4):
+            h = context(V, K, D, flags)
+            assert set_whitening(h, V, D, 1) == 0
+            Phi, b = np.zeros((D, K), dtype=np.float32), batch(100)
+            FAKE.fake_fail_malloc(after)
+            st = LIB.tlda_whiten_cp_step(h, ctypes.byref(b), 0.0, Phi.ctypes.data, None, None, None)
+            FAKE.fake_fail_malloc(-1)
+            assert st in (0, 6), st
+            failures += st == 6
+            seen = [base(k) for k, _ in step(h, b, D, K)]
+            assert seen[1] == "k_classic_cp", seen
+            for i, args in ((0, (0, 4, 7, 8, 9)), (1, (4, 6, 8, 9, 14))):
+                assert all(FAKE.fake_arg(i, a) != 0 for a in args), (flags, after, i)
+            LIB.tlda_destroy(h)
+        assert failures == 3
+
+
 if __name__ == "__main__":
     globals()["check_" + sys.argv[2]]()

@@ -28,6 +28,7 @@ def stand_in(tmp_path_factory):
     "fused_grid_does_not_depend_on_the_batch_before",
     "captured_steps_never_regrow_their_partials",
     "rebase_after_a_failed_allocation",
+    "classic_step_after_a_failed_allocation",
 ])
 def test_host_launches(stand_in, check):
     r = subprocess.run([sys.executable, os.path.join(HERE, "driver.py"), stand_in, check],
