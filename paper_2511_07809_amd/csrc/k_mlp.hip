@@ -697,9 +697,15 @@ hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta) {
   const size_t lds = bytes(16 * nt);
   hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 16 * nt - 1) / (16 * nt))), dim3(kThreads), lds,
-                     m.stream, X, n, D, H, K, lda, f, theta);
-  return hipGetLastError();
+  // a launch takes fewer than 2^32 work items
+  const int64_t docs = 16 * nt, most = ((int64_t(1) << 32) / kThreads - 1) * docs;
+  for (int64_t r = 0; r < n; r += most) {
+    const int64_t rows = std::min(most, n - r);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + docs - 1) / docs)), dim3(kThreads), lds,
+                       m.stream, X + r * D, rows, D, H, K, lda, f, theta + r * K);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Forward, backward and the gradient partials of n <= max_batch rows.

@@ -171,5 +171,30 @@ def check_classic_step_after_a_failed_allocation():
         assert failures == 3
 
 
+def check_encoder_forward_takes_any_number_of_rows():
+    """Every launch stays within the 2^32 work items of a grid, and together they
+    take every row once, from the right place of X and theta."""
+    FAKE.fake_keep_args(b"k_forward<", 8)
+    for d_in, hidden, k_out in ((50, 256, 50), (5, 16, 5), (1, 1024, 2), (1024, 64, 16)):
+        m = ctypes.c_void_p()
+        assert LIB.tlda_mlp_create(d_in, hidden, k_out, 64, None, ctypes.byref(m)) == 0
+        for n in (1, 17, 1 << 20, (1 << 27) - 16, (1 << 27) + 1, (1 << 29) + 5, (1 << 33) + 7):
+            FAKE.fake_clear()
+            X, theta = 1 << 20, 1 << 50   # never read
+            assert LIB.tlda_mlp_forward(m, X, n, theta) == 0, (hidden, n)
+            row = 0
+            for i, (kernel, grid) in enumerate(launches()):
+                assert base(kernel) == "k_forward"
+                docs = 16 * int(kernel.split("k_forward<")[1].split(">")[0])
+                assert FAKE.fake_arg(i, 0) == X + 4 * d_in * row
+                assert FAKE.fake_arg(i, 7) == theta + 4 * k_out * row, (i, kernel)
+                rows = FAKE.fake_arg(i, 1)
+                assert (grid - 1) * docs < rows <= grid * docs
+                assert grid * FAKE.fake_block(i, 0) < 1 << 32
+                row += rows
+            assert row == n
+        LIB.tlda_mlp_destroy(m)
+
+
 if __name__ == "__main__":
     globals()["check_" + sys.argv[2]]()
