@@ -37,6 +37,23 @@ constexpr int classic_ring_bytes(bool bf16) { return bf16 ? 64 * kRing16 * 2 : 6
 // NCT registers) and W rows (4 NDT, and as many on the way) leave 168 for all,
 // else two (256).
 constexpr int classic_waves(int ndt, int nct) { return ndt * (nct + 1) <= 20 ? 12 : 8; }
+// What a document costs besides its nonzeros, in nonzeros: less where each of
+// these is many products (131072 documents of 0 to 40 words in order of length:
+// FP32 at D = K = 50 340 us with 4 and 358 with 8, BF16 246 and 220, FP32 at
+// D = K = 5 216 and 177).
+constexpr int classic_doc_cost(int ndt, int nct, bool bf16) {
+  return bf16 || ndt * nct < 4 ? 8 : 4;
+}
+// Runs are cut by work, not by documents, from this many nonzeros a run on and
+// where a run has more than one document.  Documents in order of length, as
+// bucketed corpora have them, leave the last waves twice the mean otherwise
+// (131072 documents of 0 to 40 words, D = K = 50: 564 us by documents, 340 by
+// work; shuffled 337 and 309).  Finding the boundaries takes 2 to 3 us, which
+// smaller batches do not get back: 16000 documents of 8 words at D = K = 20 take
+// 29.9 us by work and 27.9 by documents, of 20 words 42.2 and 46.5; and with a
+// document a run (2000 of 300 words) the cut by work gives some waves two, 137
+// against 108.
+constexpr int kWorkPerRun = 96;
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef short bf16x4_t __attribute__((ext_vector_type(4)));
 
@@ -66,6 +83,40 @@ __device__ __forceinline__ float classic_value(classic_elem_bits<BF> x) {
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+
+// Where the run boundaries `first` and `last` of `runs` fall, for runs of equal
+// work: a document costs its nonzeros and kDocCost nonzeros more.  Boundary r is the first
+// document with at least r / runs of all work before it, so neighbouring runs
+// agree on it and the boundaries depend on the batch alone.  The wave asks 64
+// places at a time: three rounds of loads up to 2^18 documents.
+template <int kDocCost>
+__device__ __forceinline__ void run_bounds(const int32_t* __restrict__ row_ptr, int n, int first,
+                                           int last, int runs, int lane, int& d0, int& d1) {
+  const int base = row_ptr[0];
+  const long long total = row_ptr[n] - base + (long long)kDocCost * n;
+  const long long t[2] = {total * first / runs, total * last / runs};
+  int lo[2] = {0, 0}, hi[2] = {n, n};   // the boundary is in lo .. hi
+  while (lo[0] < hi[0] || lo[1] < hi[1]) {
+    int p[2], v[2], step[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      step[i] = (int)(((long long)hi[i] - lo[i] + 63) / 64);
+      p[i] = (int)min((long long)lo[i] + (long long)lane * step[i], (long long)hi[i]);
+      v[i] = row_ptr[p[i]];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const unsigned long long at =
+          __ballot((long long)(v[i] - base) + (long long)kDocCost * p[i] >= t[i]);
+      const int k = at != 0 ? __builtin_ctzll(at) : 64;   // the first place past the boundary
+      const long long l = lo[i], h = hi[i], s = step[i];
+      if (k < 64) hi[i] = (int)min(h, l + k * s);
+      if (k > 0) lo[i] = (int)min((long long)hi[i], l + (k - 1) * s + 1);
+    }
+  }
+  d0 = lo[0];
+  d1 = lo[1];
 }
 
 // Z[w][k] = sum_d W32[w][d] Phi[d][k] (zero for K <= k < Kp); block 0 also
@@ -103,20 +154,22 @@ __global__ void __launch_bounds__(kThreads) k_classic_z(const float* __restrict_
   }
 }
 
-// A wave works alone on a run of consecutive documents; no wave waits for
-// another before the block's sums are added at the end.  For each document
+// A wave works alone on a run of consecutive documents (by_work: runs of equal
+// work, else of equal documents); no wave waits for another before the block's
+// sums are added at the end.  For each document
 //   phase 1: lane k takes column k.  The Z rows of the document's words, 32 at
 //     a time, come straight into registers and give s, q, L and the
 //     coefficients a, b, g;
-//   the reduction rows c (a + b z + g z^2), rounded to BF16 where W is, are formed from the same registers
-//     and put into the wave's ring of kRing rows in LDS (documents of more than
-//     32 words gather their Z rows a second time for it);
+//   the reduction rows c (a + b z + g z^2), rounded to BF16 where W is, are
+//     formed from the same registers and put into the wave's ring of kRing rows
+//     in LDS (documents of more than 32 words gather their Z rows a second time
+//     for it);
 //   the Z rows of the next document are asked for, and
 //   phase 2: as long as the ring holds 16 rows they go through the matrix
 //     cores, four at a time: B from the ring, A (the W rows) straight from
 //     memory into the operand registers, 16 rows ahead of their use (BF16: all
-//     16 at once).  The rows
-//     of a run are consecutive nonzeros, so this side needs no document.
+//     16 at once).  The rows of a run are consecutive nonzeros, so this side
+//     needs no document.
 // Each wave keeps all NDT x NCT tiles of the D x K sum.  K > 64 is split over
 // gridDim.y: the columns do not depend on each other.
 //
@@ -145,7 +198,7 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
     const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
     const float* __restrict__ val, int n_rows, const classic_elem<BF>* __restrict__ W, int Dp,
     const classic_elem<BF>* __restrict__ Z, int Kp, const float* __restrict__ mw,
-    const float* __restrict__ r_g, int D, int K, float c2r, float a0r,
+    const float* __restrict__ r_g, int D, int K, float c2r, float a0r, int by_work,
     float* __restrict__ partial, int* __restrict__ block_counts) {
   using E = classic_elem<BF>;
   constexpr int NW = classic_waves(NDT, NCT);
@@ -174,8 +227,10 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
   int kept = 0;
 
   const int run = blockIdx.x * NW + wave, runs = gridDim.x * NW;
-  const int d0 = (int)((long long)n_rows * run / runs);
-  const int d1 = (int)((long long)n_rows * (run + 1) / runs);
+  int d0 = (int)((long long)n_rows * run / runs);
+  int d1 = (int)((long long)n_rows * (run + 1) / runs);
+  if (by_work)
+    run_bounds<classic_doc_cost(NDT, NCT, BF)>(row_ptr, n_rows, run, run + 1, runs, lane, d0, d1);
   const int nz0 = __builtin_amdgcn_readfirstlane(row_ptr[d0]);
   const int nz1 = __builtin_amdgcn_readfirstlane(row_ptr[d1]);
 
@@ -494,11 +549,13 @@ hipError_t launch_classic_t(const tlda_csr_batch& b, const classic_elem<BF>* W, 
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
+  const long long runs = (long long)nblk * NW;
+  const int by_work = b.n_rows > runs && b.nnz >= kWorkPerRun * runs;
   const double c2 = alpha0 * (alpha0 + 1.0) / 2.0;
   const double c3 = (alpha0 + 1.0) * (alpha0 + 2.0) / 2.0;
   launch_main(kern, dim3(nblk, K > 64 ? 2 : 1), dim3(64 * NW), shmem, s, b.row_ptr, b.col_idx,
               b.val, b.n_rows, W, Dp, Z, Kp, mw, r, D, K, (float)(c2 / c3),
-              (float)(alpha0 * alpha0 / c3), partial, block_counts);
+              (float)(alpha0 * alpha0 / c3), by_work, partial, block_counts);
   return hipGetLastError();
 }
 
