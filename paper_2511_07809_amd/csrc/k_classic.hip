@@ -203,7 +203,9 @@ __global__ void __launch_bounds__(64 * classic_waves(NDT, NCT)) k_classic_cp(
   using E = classic_elem<BF>;
   constexpr int NW = classic_waves(NDT, NCT);
   constexpr int NB = 16;    // rows per batch
-  extern __shared__ __attribute__((aligned(16))) char ring_lds[];
+  constexpr int kSums = NW * 8 * 1024;   // the block's sum at the end: eight tiles at a time
+  constexpr int kRings = NW * classic_ring_bytes(BF);
+  __shared__ __attribute__((aligned(16))) char ring_lds[kRings > kSums ? kRings : kSums];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, l4 = lane >> 4;
@@ -542,19 +544,12 @@ hipError_t launch_classic_t(const tlda_csr_batch& b, const classic_elem<BF>* W, 
                             int D, int K, double alpha0, int nblk, float* partial,
                             int* block_counts, hipStream_t s) {
   constexpr int NW = classic_waves(NDT, NCT);
-  constexpr unsigned sums = NW * 8 * 1024;   // the block's sum: eight tiles at a time
-  constexpr unsigned rings = NW * classic_ring_bytes(BF);
-  const unsigned shmem = rings > sums ? rings : sums;
-  auto* kern = k_classic_cp<NDT, NCT, BF>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-  if (e != hipSuccess) return e;
   const long long runs = (long long)nblk * NW;
   const int by_work = b.n_rows > runs && b.nnz >= kWorkPerRun * runs;
   const double c2 = alpha0 * (alpha0 + 1.0) / 2.0;
   const double c3 = (alpha0 + 1.0) * (alpha0 + 2.0) / 2.0;
-  launch_main(kern, dim3(nblk, K > 64 ? 2 : 1), dim3(64 * NW), shmem, s, b.row_ptr, b.col_idx,
-              b.val, b.n_rows, W, Dp, Z, Kp, mw, r, D, K, (float)(c2 / c3),
+  launch_main(k_classic_cp<NDT, NCT, BF>, dim3(nblk, K > 64 ? 2 : 1), dim3(64 * NW), 0, s,
+              b.row_ptr, b.col_idx, b.val, b.n_rows, W, Dp, Z, Kp, mw, r, D, K, (float)(c2 / c3),
               (float)(alpha0 * alpha0 / c3), by_work, partial, block_counts);
   return hipGetLastError();
 }

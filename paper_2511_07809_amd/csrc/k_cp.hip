@@ -175,16 +175,20 @@ __global__ void __launch_bounds__(64 * cp_waves(DQ, KQ)) k_cp_reduce_mfma(const 
 // does, 16 entries per wave.
 // ---------------------------------------------------------------------------
 constexpr int kWideT = 64, kWideR = 5, kWideThreads = 1024;
+// Floats of LDS: the most that a shape within cp_tile_rows takes, for every
+// shape (a block fills its compute unit's registers anyway, and LDS that is not
+// asked for at the launch needs no permission for more than 64 KB).
+constexpr int kWideLds = 38784;
 
-size_t cp_wide_lds_floats(int D, int K) {
-  const size_t dq = (D + 15) & ~15, kq = (K + 15) & ~15;
+int cp_wide_lds_floats(int D, int K) {
+  const int dq = (D + 15) & ~15, kq = (K + 15) & ~15;
   return kWideT * (dq + 4 + kq + 4) + dq * (kq + 4);
 }
 
 __global__ void __launch_bounds__(kWideThreads) k_cp_reduce_wide(
     const float* __restrict__ X, int n_rows, const float* __restrict__ Phi, int D, int K, int nblk,
     float* __restrict__ partial, float* __restrict__ phi_copy, double* __restrict__ gsq) {
-  extern __shared__ float smem[];
+  __shared__ float smem[kWideLds];
   const int DQ = (D + 15) & ~15, KQ = (K + 15) & ~15;
   const int LDX = DQ + 4, LDS = KQ + 4;
   float* Xs = smem;                    // [64][LDX]
@@ -674,15 +678,9 @@ hipError_t launch_cp_reduce(const float* X, int n_rows, const float* Phi, int D,
 #undef TLDA_MFMA_ROW
 #undef TLDA_MFMA
   } else {
-    const size_t lds = cp_wide_lds_floats(D, K) * sizeof(float);
-    if (lds > 65536) {
-      const hipError_t e =
-          hipFuncSetAttribute(reinterpret_cast<const void*>(k_cp_reduce_wide),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
-    launch_main(k_cp_reduce_wide, dim3(nblk), dim3(kWideThreads), (unsigned)lds, s, X, n_rows, Phi,
-                D, K, nblk, partial, phi_copy, gsq);
+    if (cp_wide_lds_floats(D, K) > kWideLds) return hipErrorInvalidValue;
+    launch_main(k_cp_reduce_wide, dim3(nblk), dim3(kWideThreads), 0, s, X, n_rows, Phi, D, K, nblk,
+                partial, phi_copy, gsq);
   }
   return hipGetLastError();
 }

@@ -656,13 +656,22 @@ size_t tile_cols(int max_batch) {
 }
 int pad64(int n) { return (n + 63) / 64 * 64; }
 
-// Dynamic LDS past the default 64 KB (of the compute unit's 160) is asked for.
-hipError_t allow_lds(const void* kernel, size_t bytes) {
-  if (bytes <= 64 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
 }  // namespace
+
+// Dynamic LDS past the default 64 KB (of the compute unit's 160) has to be
+// allowed; once, when an encoder is made, and for any encoder's widths.
+hipError_t mlp_allow_lds() {
+  const void* kernels[] = {
+      reinterpret_cast<const void*>(k_forward<1>), reinterpret_cast<const void*>(k_forward<2>),
+      reinterpret_cast<const void*>(k_forward<4>), reinterpret_cast<const void*>(k_train<1>),
+      reinterpret_cast<const void*>(k_train<2>),   reinterpret_cast<const void*>(k_train<4>)};
+  for (const void* k : kernels) {
+    const hipError_t e =
+        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 size_t mlp_param_count(int d_in, int hidden, int k_out) {
   return (size_t)d_in * hidden + hidden + (size_t)hidden * hidden + hidden +
@@ -695,15 +704,14 @@ hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta) {
   else if (bytes(32) <= 80 * 1024 && n >= 32 * 512) nt = 2;
   auto kernel = nt == 4 ? k_forward<4> : nt == 2 ? k_forward<2> : k_forward<1>;
   const size_t lds = bytes(16 * nt);
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
-  if (e != hipSuccess) return e;
   // a launch takes fewer than 2^32 work items
   const int64_t docs = 16 * nt, most = ((int64_t(1) << 32) / kThreads - 1) * docs;
   for (int64_t r = 0; r < n; r += most) {
     const int64_t rows = std::min(most, n - r);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + docs - 1) / docs)), dim3(kThreads), lds,
                        m.stream, X + r * D, rows, D, H, K, lda, f, theta + r * K);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -728,11 +736,10 @@ static hipError_t train_partials(tlda_mlp& m, const float* X, const float* T, in
   const Frags f = frags_of(m);
   const float inv_b = 1.0f / (float)n;
   auto kernel = H <= 32 * kWaves ? k_train<1> : H <= 64 * kWaves ? k_train<2> : k_train<4>;
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), lds);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, m.stream, X, T, n, D, H, K, lda, f, o, inv_b,
                      m.row_loss);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   g.t1 = pad64(D) / 64 * (pad64(H) / 64);
   g.t2 = pad64(H) / 64 * (pad64(H) / 64);
   g.t3 = pad64(H) / 64 * (pad64(K) / 64);

@@ -196,5 +196,31 @@ def check_encoder_forward_takes_any_number_of_rows():
         LIB.tlda_mlp_destroy(m)
 
 
+def check_steps_only_launch():
+    """A step on a warm context makes no runtime call beyond its launches that
+    would cost host time on every one of them: no function attributes."""
+    V = 400
+    for D, K, flags in ((5, 5, 0), (100, 100, 0), (50, 50, tl.TLDA_BF16), (50, 49, tl.TLDA_CLASSIC),
+                        (128, 128, tl.TLDA_CLASSIC), (50, 50, tl.TLDA_CLASSIC | tl.TLDA_BF16),
+                        (150, 37, 0), (56, 256, 0), (1, 256, 0)):
+        h = context(V, K, D, flags)
+        assert set_whitening(h, V, D) == 0
+        for n in (100, 50000):
+            for _ in range(2):
+                assert len(step(h, batch(n), D, K)) >= 2
+            assert FAKE.fake_set_attribute() == 0, (D, K, flags)
+        LIB.tlda_destroy(h)
+    for d_in, hidden, k_out in ((50, 256, 50), (1024, 1024, 256)):
+        m = ctypes.c_void_p()
+        assert LIB.tlda_mlp_create(d_in, hidden, k_out, 5000, None, ctypes.byref(m)) == 0
+        FAKE.fake_clear()
+        X, T, theta = 1 << 20, 1 << 30, 1 << 40
+        for n in (1, 5000):
+            assert LIB.tlda_mlp_forward(m, X, 40 * n, theta) == 0
+            assert LIB.tlda_mlp_train_step(m, X, T, n, 1e-3, None) == 0
+        assert FAKE.fake_set_attribute() == 0, hidden
+        LIB.tlda_mlp_destroy(m)
+
+
 if __name__ == "__main__":
     globals()["check_" + sys.argv[2]]()
