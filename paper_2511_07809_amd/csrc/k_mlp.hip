@@ -175,6 +175,36 @@ __device__ inline void load_rows(const float* __restrict__ X, int rows, int docs
     act[r * lda + d] = r < rows && d < D ? to_bf16(X[(size_t)r * D + d]) : (uint16_t)0;
   }
 }
+// The same for wide inputs (rows > 0): a wave takes every kWaves-th document, with
+// eight loads of a lane on their way at once, where the loop above has one.  A
+// narrow network over a wide input is bound by them: 262144 rows of 1024 - 64 -
+// 16 take 452 us (2.4 TB/s of X) and took 821; up to 128 inputs the loop above
+// is as fast (50 - 256 - 50, 131072 rows) or faster (5 - 16 - 5 by 10%).
+constexpr int kWideInput = 128;
+template <int DOCS>
+__device__ inline void load_wide_rows(const float* __restrict__ X, int rows, int D, int Dp,
+                                      uint16_t* act, int lda) {
+  constexpr int R = DOCS / kWaves, S = 8 / R;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int d0 = 0; d0 < Dp; d0 += 64 * S) {
+    float v[S][R];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int r = min(wave + kWaves * i, rows - 1), d = min(d0 + 64 * s + lane, D - 1);
+        v[s][i] = X[(size_t)r * D + d];
+      }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int r = wave + kWaves * i, d = d0 + 64 * s + lane;
+        if (d < Dp) act[r * lda + d] = r < rows && d < D ? to_bf16(v[s][i]) : (uint16_t)0;
+      }
+  }
+}
 
 // Softmax of the logits of one document over four lanes (j = 0 .. 3, lane j
 // holding entries j, j + 4, ...): p[i] replaces z[i].  Entries l, l + 64, ..
@@ -208,12 +238,13 @@ __device__ inline float softmax_row(float* z, int K, int j) {
 }
 
 // theta = softmax(...) for a tile of 16 NT documents.  LDS: two activation
-// buffers of 16 NT documents, lda halves each (lda >= every padded width and
-// 2 (K padded) + 8, for the logits in FP32).
+// buffers of 16 NT documents, each as wide as what it holds: lda halves for the
+// rows of X and the second hidden layer, ldb for the first and the logits in
+// FP32.
 template <int NT>
 __global__ void __launch_bounds__(kThreads) k_forward(const float* __restrict__ X, int64_t n_rows,
-                                                      int D, int H, int K, int lda, Frags f,
-                                                      float* __restrict__ theta) {
+                                                      int D, int H, int K, int lda, int ldb,
+                                                      Frags f, float* __restrict__ theta) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   constexpr int docs = 16 * NT;
   uint16_t* buf[2] = {lds, lds + docs * lda};
@@ -222,7 +253,10 @@ __global__ void __launch_bounds__(kThreads) k_forward(const float* __restrict__ 
   const int Dp = pad32(D), Hp = pad32(H), Kp = pad32(K);
   const int64_t row0 = (int64_t)blockIdx.x * docs;
   const int rows = (int)min((int64_t)docs, n_rows - row0);
-  load_rows(X + row0 * D, rows, docs, D, Dp, buf[0], lda);
+  if (D > kWideInput)
+    load_wide_rows<docs>(X + row0 * D, rows, D, Dp, buf[0], lda);
+  else
+    load_rows(X + row0 * D, rows, docs, D, Dp, buf[0], lda);
   __syncthreads();
 #pragma unroll
   for (int l = 0; l < 2; ++l) {   // hidden layers
@@ -230,7 +264,7 @@ __global__ void __launch_bounds__(kThreads) k_forward(const float* __restrict__ 
     const float* bias = l == 0 ? f.b1 : f.b2;
     for (int tp = wave; tp < Hp / 32; tp += kWaves) {
       floatx4 acc[2][NT];
-      layer<NT>(w, tp, (l == 0 ? Dp : Hp) / 32, buf[l], lda, lane, acc);
+      layer<NT>(w, tp, (l == 0 ? Dp : Hp) / 32, buf[l], l == 0 ? lda : ldb, lane, acc);
       const float* bp = bias + tp * 32 + 8 * q;
 #pragma unroll
       for (int n = 0; n < NT; ++n) {
@@ -242,13 +276,13 @@ __global__ void __launch_bounds__(kThreads) k_forward(const float* __restrict__ 
             const float z = acc[t][n][r] + bp[4 * t + r];
             h[4 * t + r] = 0.5f * z * phi_cdf2(z);
           }
-        store_act(buf[1 - l], lda, tp, n * 16 + l16, q, h);
+        store_act(buf[1 - l], l == 0 ? ldb : lda, tp, n * 16 + l16, q, h);
       }
     }
     __syncthreads();
   }
   float* logits = reinterpret_cast<float*>(buf[1]);
-  const int ldl = lda / 2;
+  const int ldl = ldb / 2;
   for (int tp = wave; tp < Kp / 32; tp += kWaves) {
     floatx4 acc[2][NT];
     layer<NT>(f.w3, tp, Hp / 32, buf[0], lda, lane, acc);
@@ -693,12 +727,13 @@ size_t mlp_tile_halves(int d_in, int hidden, int k_out, int max_batch) {
 hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta) {
   if (n <= 0) return hipSuccess;
   const int D = m.d_in, H = m.hidden, K = m.k_out;
-  const int lda = std::max({pad32(D), pad32(H), 2 * pad32(K)}) + 8;
+  const int lda = std::max(pad32(D), pad32(H)) + 8;
+  const int ldb = std::max(pad32(H), 2 * pad32(K)) + 8;
   const Frags f = frags_of(m);
   // 64 documents a block while the grid still fills the 256 compute units
   // twice over and two blocks' LDS fits on one; 32 or 16 below that, or for
   // wide layers
-  auto bytes = [&](int docs) { return (size_t)2 * docs * lda * sizeof(uint16_t); };
+  auto bytes = [&](int docs) { return (size_t)docs * (lda + ldb) * sizeof(uint16_t); };
   int nt = 1;
   if (bytes(64) <= 80 * 1024 && n >= 64 * 512) nt = 4;
   else if (bytes(32) <= 80 * 1024 && n >= 32 * 512) nt = 2;
@@ -709,7 +744,7 @@ hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta) {
   for (int64_t r = 0; r < n; r += most) {
     const int64_t rows = std::min(most, n - r);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + docs - 1) / docs)), dim3(kThreads), lds,
-                       m.stream, X + r * D, rows, D, H, K, lda, f, theta + r * K);
+                       m.stream, X + r * D, rows, D, H, K, lda, ldb, f, theta + r * K);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -174,7 +174,7 @@ def check_classic_step_after_a_failed_allocation():
 def check_encoder_forward_takes_any_number_of_rows():
     """Every launch stays within the 2^32 work items of a grid, and together they
     take every row once, from the right place of X and theta."""
-    FAKE.fake_keep_args(b"k_forward<", 8)
+    FAKE.fake_keep_args(b"k_forward<", 9)
     for d_in, hidden, k_out in ((50, 256, 50), (5, 16, 5), (1, 1024, 2), (1024, 64, 16)):
         m = ctypes.c_void_p()
         assert LIB.tlda_mlp_create(d_in, hidden, k_out, 64, None, ctypes.byref(m)) == 0
@@ -187,12 +187,25 @@ def check_encoder_forward_takes_any_number_of_rows():
                 assert base(kernel) == "k_forward"
                 docs = 16 * int(kernel.split("k_forward<")[1].split(">")[0])
                 assert FAKE.fake_arg(i, 0) == X + 4 * d_in * row
-                assert FAKE.fake_arg(i, 7) == theta + 4 * k_out * row, (i, kernel)
+                assert FAKE.fake_arg(i, 8) == theta + 4 * k_out * row, (i, kernel)
                 rows = FAKE.fake_arg(i, 1)
                 assert (grid - 1) * docs < rows <= grid * docs
                 assert grid * FAKE.fake_block(i, 0) < 1 << 32
                 row += rows
             assert row == n
+        LIB.tlda_mlp_destroy(m)
+
+
+def check_encoder_tiles_fit_what_they_hold():
+    """LDS is sized by what each buffer holds, so that a wide input beside narrow
+    layers, or a wide output, does not shrink the tile of documents."""
+    for d_in, hidden, k_out, docs in ((50, 256, 50, 64), (1024, 64, 16, 32), (16, 16, 256, 64),
+                                      (1024, 1024, 256, 16)):
+        m = ctypes.c_void_p()
+        assert LIB.tlda_mlp_create(d_in, hidden, k_out, 64, None, ctypes.byref(m)) == 0
+        FAKE.fake_clear()
+        assert LIB.tlda_mlp_forward(m, 1 << 20, 262144, 1 << 40) == 0
+        assert [g for _, g in launches()] == [262144 // docs], (d_in, launches())
         LIB.tlda_mlp_destroy(m)
 
 

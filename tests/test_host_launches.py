@@ -30,6 +30,7 @@ def stand_in(tmp_path_factory):
     "rebase_after_a_failed_allocation",
     "classic_step_after_a_failed_allocation",
     "encoder_forward_takes_any_number_of_rows",
+    "encoder_tiles_fit_what_they_hold",
     "steps_only_launch",
 ])
 def test_host_launches(stand_in, check):
