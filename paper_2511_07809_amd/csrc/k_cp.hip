@@ -174,6 +174,14 @@ __global__ void __launch_bounds__(64 * cp_waves(DQ, KQ)) k_cp_reduce_mfma(const 
 // gsq (or NULL): the blocks also form the squared Gram entries, as k_gram_sq
 // does, 16 entries per wave.
 // ---------------------------------------------------------------------------
+// A block's share of the Gram entries, at about D + 128 an entry, up to which
+// that is cheaper than a launch of k_gram_sq (5 to 7 us): step times with the
+// entries in this kernel and apart, at a share of 150 000 (4000 rows) 18.1 and
+// 18.9 us for 16 x 256, 35.5 and 38.1 for 256 x 56 (500 rows); at 200 000 and
+// more 34.8 and 35.1 for 130 x 110 (1000 rows), 33.2 and 33.1 for 64 x 200
+// (2000), 20.2 and 18.6 for 16 x 256 (2000); and where a few rows leave all
+// entries to one block, 344 and 37.6 for 56 x 256.
+constexpr int kGramPerBlock = 200000;
 constexpr int kWideT = 64, kWideR = 5, kWideThreads = 1024;
 // Floats of LDS: the most that a shape within cp_tile_rows takes, for every
 // shape (a block fills its compute unit's registers anyway, and LDS that is not
@@ -654,8 +662,9 @@ int cp_num_blocks(int n_rows, int D, int K, int max_blocks) {
   return ntiles < max_blocks ? (ntiles < 1 ? 1 : ntiles) : max_blocks;
 }
 
-bool cp_reduce_forms_gram(int D, int K) {
-  return cp_mfma_tile_rows(D, K) == 0 && D * K >= kGramOnceDK;
+bool cp_reduce_forms_gram(int D, int K, int nblk) {
+  return cp_mfma_tile_rows(D, K) == 0 && D * K >= kGramOnceDK &&
+         (long long)K * K * (D + 128) <= (long long)kGramPerBlock * nblk;
 }
 
 hipError_t launch_cp_reduce(const float* X, int n_rows, const float* Phi, int D, int K, int nblk,

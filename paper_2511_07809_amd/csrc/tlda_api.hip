@@ -803,7 +803,7 @@ tlda_status tlda_cp_step(tlda_ctx* c, const float* X, int32_t n_rows, const int3
   tlda_status st = ensure_partial(c, (size_t)nblk * D * K);
   if (st != TLDA_OK) return st;
   float* g = grad ? grad : c->cp.grad;
-  const bool gram = !is_bf16(c) && tlda::cp_reduce_forms_gram(D, K);
+  const bool gram = !is_bf16(c) && tlda::cp_reduce_forms_gram(D, K, nblk);
   HIP_OK(c, timing_start(c));
   if (is_bf16(c))
     HIP_OK(c, tlda::launch_cp_reduce_bf16(X, n_rows, Phi, D, K, nblk, c->cp.partial, c->cp.phi0,

@@ -316,9 +316,9 @@ int whiten_chunks(int V, int Dp);
 // CP step
 // The reduction kernels also copy Phi into phi_copy (D*K floats), which the
 // finish kernel reads while it writes Phi.
-// gsq: where cp_reduce_forms_gram(D, K) holds, the K x K squared Gram entries
-// of Phi for the finish, else NULL
-bool cp_reduce_forms_gram(int D, int K);
+// gsq: where cp_reduce_forms_gram(D, K, nblk) holds, the K x K squared Gram
+// entries of Phi for the finish, else NULL
+bool cp_reduce_forms_gram(int D, int K, int nblk);
 hipError_t launch_cp_reduce(const float* X, int n_rows, const float* Phi, int D, int K, int nblk,
                             float* partial, float* phi_copy, double* gsq, hipStream_t s);
 // n = sum of counts[0 .. ncounts), or n_default when counts is NULL; gsq

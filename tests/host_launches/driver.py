@@ -209,6 +209,24 @@ def check_encoder_tiles_fit_what_they_hold():
         LIB.tlda_mlp_destroy(m)
 
 
+def check_few_blocks_do_not_form_the_gram_entries():
+    """Past 128 columns or topics the reduction forms the finish's squared Gram
+    entries only where enough blocks share them; else a launch of its own does."""
+    FAKE.fake_keep_args(b"k_cp_reduce_wide(", 9)
+    for D, K in ((56, 256), (16, 256), (130, 110), (200, 70), (256, 56)):
+        h = context(400, K, D)
+        Phi = np.zeros((D, K), dtype=np.float32)
+        X = np.zeros((100000, D), dtype=np.float32)
+        for n, apart in ((1, True), (65, True), (16384, False), (100000, False)):
+            FAKE.fake_clear()
+            assert LIB.tlda_cp_step(h, X.ctypes.data, n, None, 0.0, Phi.ctypes.data, None) == 0
+            names = [base(k) for k, _ in launches()]
+            assert names[0] == "k_cp_reduce_wide"
+            assert ("k_gram_sq" in names) == apart, (D, K, n, names)
+            assert (FAKE.fake_arg(0, 8) == 0) == apart, (D, K, n)
+        LIB.tlda_destroy(h)
+
+
 def check_steps_only_launch():
     """A step on a warm context makes no runtime call beyond its launches that
     would cost host time on every one of them: no function attributes."""

@@ -31,6 +31,7 @@ def stand_in(tmp_path_factory):
     "classic_step_after_a_failed_allocation",
     "encoder_forward_takes_any_number_of_rows",
     "encoder_tiles_fit_what_they_hold",
+    "few_blocks_do_not_form_the_gram_entries",
     "steps_only_launch",
 ])
 def test_host_launches(stand_in, check):
