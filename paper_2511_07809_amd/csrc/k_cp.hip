@@ -6,7 +6,7 @@
 // the D x D x D tensor is never formed.
 //
 // The reductions (k_cp_reduce_mfma up to D, K of 128, k_cp_reduce_wide past
-// that): each block walks a fixed set of row tiles (tile b, b + nblk, ...),
+// that, k_cp_reduce_narrow for few columns of it): each block walks a fixed set of row tiles (tile b, b + nblk, ...),
 // forms S = X_t Phi and adds X_t^T S^2 to its own R1, and writes that partial;
 // the row partition depends only on n_rows, so the reduction order is fixed.
 #include "tlda_internal.h"
@@ -15,7 +15,8 @@ namespace tlda {
 namespace {
 
 // ---------------------------------------------------------------------------
-// FP32 matrix-core reduction (D, K <= 128 after padding to 16).  Per row tile (T rows of X staged in LDS):
+// FP32 matrix-core reduction (D, K <= 128 after padding to 16).  Per row tile
+// (T rows of X staged in LDS):
 //   S = X_t Phi      with v_mfma_f32_16x16x4_f32; each wave owns S column
 //                    tiles ct = wave, wave + 4, ... and keeps the Phi
 //                    fragments of those columns in registers for the whole
@@ -298,6 +299,124 @@ __global__ void __launch_bounds__(kWideThreads) k_cp_reduce_wide(
       for (int r = 0; r < 4; ++r) {
         const int d = t / nct * 16 + 4 * l4 + r;
         if (d < D && k < K) out[d * K + k] = acc[q][r];
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The same for few columns and more than 128 topics, where the matrix cores'
+// 16-wide tiles would be mostly padding: 256 threads, the vector ALUs, padded
+// to 4.  Phi (D x K, resident in LDS for the whole block) and the X tile of T
+// rows give S = X_t Phi with 4 x 4 register blocking, S is squared in LDS, and
+// R1 += X_t^T S^2 accumulates in registers (a thread owns up to kVecR 4 x 4
+// blocks of R1; room for 4 makes three blocks a CU, and fewer partials for the
+// finish: with 2, 39.0 against 32.7 us for 200000 rows of 1 x 192).
+// ---------------------------------------------------------------------------
+constexpr int kVecThreads = 256, kVecR = 4;
+constexpr int kVecD = 20;   // (D / 4) (K / 4) <= 256 kVecR
+
+__global__ void __launch_bounds__(kVecThreads) k_cp_reduce_narrow(
+    const float* __restrict__ X, int n_rows, const float* __restrict__ Phi, int D, int K, int T,
+    int nblk, float* __restrict__ partial, float* __restrict__ phi_copy) {
+  extern __shared__ float smem[];
+  const int Dq = (D + 3) & ~3, Kq = (K + 3) & ~3;
+  float* Ps = smem;                 // [Dq][Kq]
+  float* Xs = Ps + Dq * Kq;         // [T][Dq]
+  float* Ss = Xs + T * Dq;          // [T][Kq]
+  const int tid = threadIdx.x;
+  for (int e = blockIdx.x * kVecThreads + tid; e < D * K; e += nblk * kVecThreads)
+    phi_copy[e] = Phi[e];
+  for (int e = tid; e < Dq * Kq; e += kVecThreads) {
+    const int d = e / Kq, k = e % Kq;
+    Ps[e] = (d < D && k < K) ? Phi[d * K + k] : 0.f;
+  }
+  const int nkb = Kq / 4, ndb = Dq / 4;
+  const int nSb = (T / 4) * nkb;     // 4x4 blocks of S
+  const int nRb = ndb * nkb;         // 4x4 blocks of R1
+  float acc[kVecR][4][4];
+#pragma unroll
+  for (int q = 0; q < kVecR; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[q][i][j] = 0.f;
+
+  const int ntiles = (n_rows + T - 1) / T;
+  for (int tile = blockIdx.x; tile < ntiles; tile += nblk) {
+    __syncthreads();
+    const int r0 = tile * T;
+    for (int e = tid; e < T * Dq; e += kVecThreads) {
+      const int r = e / Dq, d = e % Dq;
+      const int gr = r0 + r;
+      Xs[e] = (gr < n_rows && d < D) ? X[(size_t)gr * D + d] : 0.f;
+    }
+    __syncthreads();
+    // S = X_t Phi, squared
+    for (int bidx = tid; bidx < nSb; bidx += kVecThreads) {
+      const int rb = bidx / nkb, kb = bidx % nkb;
+      float s[4][4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[i][j] = 0.f;
+      const float* x0 = Xs + (rb * 4) * Dq;
+      for (int d = 0; d < Dq; ++d) {
+        const float4 p = *reinterpret_cast<const float4*>(Ps + d * Kq + kb * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float xv = x0[i * Dq + d];
+          s[i][0] = fmaf(xv, p.x, s[i][0]);
+          s[i][1] = fmaf(xv, p.y, s[i][1]);
+          s[i][2] = fmaf(xv, p.z, s[i][2]);
+          s[i][3] = fmaf(xv, p.w, s[i][3]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float4 o;
+        o.x = s[i][0] * s[i][0];
+        o.y = s[i][1] * s[i][1];
+        o.z = s[i][2] * s[i][2];
+        o.w = s[i][3] * s[i][3];
+        *reinterpret_cast<float4*>(Ss + (rb * 4 + i) * Kq + kb * 4) = o;
+      }
+    }
+    __syncthreads();
+    // R1 += X_t^T S^2
+#pragma unroll
+    for (int q = 0; q < kVecR; ++q) {
+      const int bidx = tid + q * kVecThreads;
+      if (bidx >= nRb) break;
+      const int db = bidx / nkb, kb = bidx % nkb;
+      for (int r = 0; r < T; ++r) {
+        const float4 xv = *reinterpret_cast<const float4*>(Xs + r * Dq + db * 4);
+        const float4 sv = *reinterpret_cast<const float4*>(Ss + r * Kq + kb * 4);
+        const float xa[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[q][i][0] = fmaf(xa[i], sv.x, acc[q][i][0]);
+          acc[q][i][1] = fmaf(xa[i], sv.y, acc[q][i][1]);
+          acc[q][i][2] = fmaf(xa[i], sv.z, acc[q][i][2]);
+          acc[q][i][3] = fmaf(xa[i], sv.w, acc[q][i][3]);
+        }
+      }
+    }
+  }
+  float* out = partial + (size_t)blockIdx.x * D * K;
+#pragma unroll
+  for (int q = 0; q < kVecR; ++q) {
+    const int bidx = tid + q * kVecThreads;
+    if (bidx >= nRb) break;
+    const int db = bidx / nkb, kb = bidx % nkb;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int d = db * 4 + i;
+      if (d >= D) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = kb * 4 + j;
+        if (k < K) out[d * K + k] = acc[q][i][j];
       }
     }
   }
@@ -609,6 +728,27 @@ int cp_tile_rows(int D, int K) {
   return 0;
 }
 
+// Whether a batch takes it: from how many rows on it is the faster one (steps,
+// vector against matrix cores; past 4 columns the matrix kernel's constant part
+// is the smaller).  4 x 160: 16.4 and 19.6 us at 40001 rows, 15.4 and 16.4 at
+// 20000, 14.1 and 12.7 at 1000; 1 x 256: 10.8 and 13.0 at one row, 36 and 64 at
+// 200000.  8 x 129: 42 and 50 at 200000, equal at 40001, 16.6 and 13.2 at 1000;
+// 8 x 192: 53 and 55 at 200000, 24.1 and 21.4 at 40001; 8 x 256: 52 and 66.
+// At 200000 rows 12 x 129: 48 and 50, 16 x 129: 59 and 51, 17 x 129: 63 and 67,
+// 17 x 160: 78 and 70.
+bool cp_narrow(int D, int K, int n_rows) {
+  if (K <= 128 || D > kVecD) return false;
+  if (D <= 4) return K > 232 || n_rows > 16384;
+  if (D <= 8) return K > 216 || n_rows > (K <= 180 ? 80000 : 160000);
+  return n_rows > 160000 && ((D <= 12 && K <= 160) || (D > 16 && K <= 144));
+}
+
+// LDS bytes of the narrow reduction: Phi and its row tiles of X and S.
+size_t cp_narrow_lds(int D, int K) {
+  const size_t dq = (D + 3) & ~3, kq = (K + 3) & ~3;
+  return sizeof(float) * (dq * kq + cp_tile_rows(D, K) * (dq + kq));
+}
+
 // Padded size of a dimension for the matrix-core reduction: the smallest of
 // 16, 32, 64, 112, 128 that holds it (0: too large).
 int mfma_bucket(int n) {
@@ -630,7 +770,7 @@ int cp_mfma_tile_rows(int D, int K) {
   return (size_t)64 * (dq + kq + 8) * sizeof(float) <= 49152 ? 64 : 32;
 }
 
-int cp_resident_blocks(int D, int K, int num_cu) {
+int cp_resident_blocks(int D, int K, int n_rows, int num_cu) {
   const int Tm = cp_mfma_tile_rows(D, K);
   int per_cu = 0;
   hipError_t e = hipSuccess;
@@ -649,6 +789,9 @@ int cp_resident_blocks(int D, int K, int num_cu) {
 #undef TLDA_OCC
   } else {
     per_cu = 1;   // 16 waves of up to 128 registers
+    if (cp_narrow(D, K, n_rows))
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_cp_reduce_narrow, kVecThreads,
+                                                        cp_narrow_lds(D, K));
   }
   if (e != hipSuccess || per_cu < 1) per_cu = 1;
   return per_cu * num_cu;
@@ -657,13 +800,13 @@ int cp_resident_blocks(int D, int K, int num_cu) {
 int cp_num_blocks(int n_rows, int D, int K, int max_blocks) {
   if (max_blocks <= 0) max_blocks = 1024;
   const int Tm = cp_mfma_tile_rows(D, K);
-  const int T = Tm > 0 ? Tm : kWideT;
+  const int T = Tm > 0 ? Tm : cp_narrow(D, K, n_rows) ? cp_tile_rows(D, K) : kWideT;
   const int ntiles = (n_rows + T - 1) / T;
   return ntiles < max_blocks ? (ntiles < 1 ? 1 : ntiles) : max_blocks;
 }
 
-bool cp_reduce_forms_gram(int D, int K, int nblk) {
-  return cp_mfma_tile_rows(D, K) == 0 && D * K >= kGramOnceDK &&
+bool cp_reduce_forms_gram(int D, int K, int n_rows, int nblk) {
+  return cp_mfma_tile_rows(D, K) == 0 && !cp_narrow(D, K, n_rows) && D * K >= kGramOnceDK &&
          (long long)K * K * (D + 128) <= (long long)kGramPerBlock * nblk;
 }
 
@@ -686,6 +829,10 @@ hipError_t launch_cp_reduce(const float* X, int n_rows, const float* Phi, int D,
     TLDA_MFMA_ROW(16) TLDA_MFMA_ROW(32) TLDA_MFMA_ROW(64) TLDA_MFMA_ROW(112) TLDA_MFMA_ROW(128)
 #undef TLDA_MFMA_ROW
 #undef TLDA_MFMA
+  } else if (cp_narrow(D, K, n_rows)) {
+    const int T = cp_tile_rows(D, K);
+    launch_main(k_cp_reduce_narrow, dim3(nblk), dim3(kVecThreads), (unsigned)cp_narrow_lds(D, K),
+                s, X, n_rows, Phi, D, K, T, nblk, partial, phi_copy);
   } else {
     if (cp_wide_lds_floats(D, K) > kWideLds) return hipErrorInvalidValue;
     launch_main(k_cp_reduce_wide, dim3(nblk), dim3(kWideThreads), 0, s, X, n_rows, Phi, D, K, nblk,

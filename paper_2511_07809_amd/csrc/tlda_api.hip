@@ -796,14 +796,18 @@ tlda_status tlda_cp_step(tlda_ctx* c, const float* X, int32_t n_rows, const int3
   if (is_bf16(c)) {
     nblk = bf16_grid(c, 1, n_rows);
   } else {
-    if (c->tune.cp_max_blocks <= 0)
-      c->tune.cp_max_blocks = tlda::cp_resident_blocks(D, K, c->num_cu);
-    nblk = tlda::cp_num_blocks(n_rows, D, K, c->tune.cp_max_blocks);
+    int most = c->tune.cp_max_blocks;
+    if (most <= 0) {
+      int& resident = c->tune.cp_resident[tlda::cp_narrow(D, K, n_rows) ? 1 : 0];
+      if (resident <= 0) resident = tlda::cp_resident_blocks(D, K, n_rows, c->num_cu);
+      most = resident;
+    }
+    nblk = tlda::cp_num_blocks(n_rows, D, K, most);
   }
   tlda_status st = ensure_partial(c, (size_t)nblk * D * K);
   if (st != TLDA_OK) return st;
   float* g = grad ? grad : c->cp.grad;
-  const bool gram = !is_bf16(c) && tlda::cp_reduce_forms_gram(D, K, nblk);
+  const bool gram = !is_bf16(c) && tlda::cp_reduce_forms_gram(D, K, n_rows, nblk);
   HIP_OK(c, timing_start(c));
   if (is_bf16(c))
     HIP_OK(c, tlda::launch_cp_reduce_bf16(X, n_rows, Phi, D, K, nblk, c->cp.partial, c->cp.phi0,

@@ -107,8 +107,10 @@ struct EigScratch {
 struct Tuning {
   int cp_max_blocks = 0;
   int fused_blocks = 0;
-  int fused_resident[2] = {0, 0};     // cached occupancy rounds of the FP32 fused kernels: the
-                                      // one of large batches, the one of small ones
+  int cp_resident[2] = {0, 0};        // cached occupancy rounds of the FP32 reductions from X: the
+                                      // matrix-core one, the one for few columns
+  int fused_resident[2] = {0, 0};     // and of the FP32 fused kernels: the one of large batches,
+                                      // the one of small ones
   int bf16_blocks = 0;
   int bf16_resident[3] = {0, 0, 0};   // cached occupancy rounds of the BF16 kernels
   int whiten_v4 = 0;
@@ -316,9 +318,9 @@ int whiten_chunks(int V, int Dp);
 // CP step
 // The reduction kernels also copy Phi into phi_copy (D*K floats), which the
 // finish kernel reads while it writes Phi.
-// gsq: where cp_reduce_forms_gram(D, K, nblk) holds, the K x K squared Gram
+// gsq: where cp_reduce_forms_gram(D, K, n_rows, nblk) holds, the K x K squared Gram
 // entries of Phi for the finish, else NULL
-bool cp_reduce_forms_gram(int D, int K, int nblk);
+bool cp_reduce_forms_gram(int D, int K, int n_rows, int nblk);
 hipError_t launch_cp_reduce(const float* X, int n_rows, const float* Phi, int D, int K, int nblk,
                             float* partial, float* phi_copy, double* gsq, hipStream_t s);
 // n = sum of counts[0 .. ncounts), or n_default when counts is NULL; gsq
@@ -395,8 +397,10 @@ hipError_t launch_cp_reduce_bf16(const float* X, int n_rows, const float* Phi, i
                                  int nblk, float* partial, float* phi_copy, hipStream_t s);
 hipError_t launch_whiten_bf16(const tlda_csr_batch& b, const uint16_t* W16, const float* mw16,
                               int Dh, int D, int nblk, float* X, int* block_counts, hipStream_t s);
-// One full round of resident CP-reduction blocks on this device.
-int cp_resident_blocks(int D, int K, int num_cu);
+// One full round of resident blocks of this batch's CP reduction on this device.
+int cp_resident_blocks(int D, int K, int n_rows, int num_cu);
+// Whether a batch takes the reduction for few columns (another grid).
+bool cp_narrow(int D, int K, int n_rows);
 // classic-moment CP step (FP32, D, K <= 128): Z = W Phi, r = Phi^T mw32 and
 // phi_copy = Phi, then the per-block data-term partials divided by c3 and the
 // kept counts (block_counts[0 .. nblk)).

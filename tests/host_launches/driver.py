@@ -227,6 +227,36 @@ def check_few_blocks_do_not_form_the_gram_entries():
         LIB.tlda_destroy(h)
 
 
+def check_few_columns_take_the_narrow_reduction():
+    """Past 128 topics, few columns take the reduction that does not pad them to
+    16; its grid and the other's do not depend on the batch before."""
+    FAKE.fake_occupancy(b"k_cp_reduce_narrow", 3)
+    Phi = np.zeros(20 * 256, dtype=np.float32)
+    X = ctypes.c_void_p(1 << 20)   # never read
+
+    def reduction(h, n):
+        FAKE.fake_clear()
+        assert LIB.tlda_cp_step(h, X, n, None, 0.0, Phi.ctypes.data, None) == 0
+        return base(FAKE.fake_kernel(0).decode()), FAKE.fake_grid(0, 0)
+
+    narrow, wide = "k_cp_reduce_narrow", "k_cp_reduce_wide"
+    for D, K, n, want in ((1, 256, 1, narrow), (4, 233, 1, narrow), (4, 232, 16384, wide),
+                          (4, 129, 16385, narrow), (5, 217, 1, narrow), (8, 180, 80000, wide),
+                          (8, 180, 80001, narrow), (8, 181, 160000, wide), (8, 216, 160001, narrow),
+                          (12, 160, 160001, narrow), (12, 161, 500000, wide), (16, 129, 500000, wide),
+                          (20, 144, 160001, narrow), (20, 144, 160000, wide), (21, 129, 500000, wide)):
+        seen = []
+        for order in ((n, 7), (7, n)):
+            h = context(400, K, D)
+            got = {rows: reduction(h, rows) for rows in order}
+            assert got[n][0] == want, (D, K, n, got)
+            seen.append(got)
+            LIB.tlda_destroy(h)
+        assert seen[0] == seen[1], seen
+        if n > 100000:
+            assert seen[0][n][1] == (3 if want == narrow else 1) * NUM_CU, seen
+
+
 def check_steps_only_launch():
     """A step on a warm context makes no runtime call beyond its launches that
     would cost host time on every one of them: no function attributes."""

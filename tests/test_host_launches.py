@@ -32,6 +32,7 @@ def stand_in(tmp_path_factory):
     "encoder_forward_takes_any_number_of_rows",
     "encoder_tiles_fit_what_they_hold",
     "few_blocks_do_not_form_the_gram_entries",
+    "few_columns_take_the_narrow_reduction",
     "steps_only_launch",
 ])
 def test_host_launches(stand_in, check):
