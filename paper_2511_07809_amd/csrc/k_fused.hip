@@ -1023,12 +1023,16 @@ namespace {
 bool fused_wide(int D, int K) { return mfma_bucket(D) > 64 || mfma_bucket(K) > 64; }
 }  // namespace
 
-bool fused_small(int D, int K, int n_rows) {
-  return mfma_bucket(D) <= 32 && mfma_bucket(K) <= 64 && D > 0 && n_rows <= kFusedSmallRows;
+// (Past 32 topics the products of its many tiles count as well, and a document
+// has to have some words to be worth it: 16384 documents at 16 x 60 take 12.7 us
+// with it and 11.4 without at 3 words, 12.6 and 11.9 at 8, 12.6 and 13.5 at 16.)
+bool fused_small(int D, int K, int n_rows, int nnz) {
+  return mfma_bucket(D) <= 32 && mfma_bucket(K) <= 64 && D > 0 && n_rows <= kFusedSmallRows &&
+         (K <= 32 || n_rows <= 12288 || nnz >= 12 * n_rows);
 }
 
-int fused_tile_rows(int D, int K, int n_rows) {
-  if (fused_small(D, K, n_rows)) return kSmallTile;
+int fused_tile_rows(int D, int K, int n_rows, int nnz) {
+  if (fused_small(D, K, n_rows, nnz)) return kSmallTile;
   if (mfma_bucket(D) >= 64 && mfma_bucket(K) >= 64) return 48;   // the hybrid kernel
   return fused_wide(D, K) ? 32 : cp_mfma_tile_rows(D, K);        // 8-wave : 4-wave
 }
@@ -1079,11 +1083,11 @@ hipError_t launch_whiten_cp(const tlda_csr_batch& b, const float* W32, const flo
     return launch_hyb<64, 64, 16, 16>(b, W32, mw32, D, Dp, Dt, tail_base, Phi, K, nblk, partial,
                                       block_counts, Xout, phi_copy, gsq, s);
   }
-  const int T = fused_tile_rows(D, K, b.n_rows);
+  const int T = fused_tile_rows(D, K, b.n_rows, b.nnz);
   int G = Dp / 4;   // lanes per document: Dp is 4, 8, 16, 32 or 64 here
   if (G < 1) G = 1;
   if (G > 16) G = 16;
-  if (fused_small(D, K, b.n_rows)) {
+  if (fused_small(D, K, b.n_rows, b.nnz)) {
 #define TLDA_SMALL(DQ_, KQ_)                                                                     \
   if (dq == DQ_ && kq == KQ_)                                                                    \
     return launch_fused_small<DQ_, KQ_>(G, b, W32, mw32, D, Dp, Phi, K, nblk, partial,           \

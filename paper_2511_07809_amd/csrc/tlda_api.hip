@@ -459,9 +459,9 @@ tlda_status fused_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float* 
   if (is_bf16(c)) {
     nblk = bf16_grid(c, 0, b->n_rows);
   } else {
-    const int T = tlda::fused_tile_rows(D, K, b->n_rows);
+    const int T = tlda::fused_tile_rows(D, K, b->n_rows, b->nnz);
     const int ntiles = (b->n_rows + T - 1) / T;
-    st = fused_grid(c, tlda::fused_small(D, K, b->n_rows), &nblk);
+    st = fused_grid(c, tlda::fused_small(D, K, b->n_rows, b->nnz), &nblk);
     if (st != TLDA_OK) return st;
     if (ntiles < nblk) nblk = ntiles;
     if (nblk > 2 * tlda::kWhitenBlockCounts) nblk = 2 * tlda::kWhitenBlockCounts;
@@ -480,7 +480,7 @@ tlda_status fused_step(tlda_ctx* c, const tlda_csr_batch* b, float beta, float* 
   // kGramOnceDK entries)
   const bool gram_in_kernel =
       is_bf16(c) || (tlda::fused_forms_gram(D, K) &&
-                     (D * K >= tlda::kGramOnceDK || tlda::fused_tile_rows(D, K, b->n_rows) == 48));
+                     (D * K >= tlda::kGramOnceDK || tlda::fused_tile_rows(D, K, b->n_rows, b->nnz) == 48));
   st = begin_use(c, b);
   if (st != TLDA_OK) return st;
   HIP_OK(c, timing_start(c));
@@ -1660,7 +1660,7 @@ tlda_status tlda_graph_capture_steps(tlda_ctx* c, const tlda_csr_batch* batches,
     // buffer that the graph writes)
     int large = 0, small = 0;
     tlda_status st = fused_grid(c, false, &large);
-    if (st == TLDA_OK && tlda::fused_small(D, K, 1)) st = fused_grid(c, true, &small);
+    if (st == TLDA_OK && tlda::fused_small(D, K, 1, 0)) st = fused_grid(c, true, &small);
     if (st != TLDA_OK) return st;
     const int nblk = std::min(std::max(large, small), 2 * tlda::kWhitenBlockCounts);
     need = (size_t)nblk * D * K;

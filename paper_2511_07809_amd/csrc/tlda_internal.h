@@ -342,8 +342,8 @@ int cp_mfma_tile_rows(int D, int K);
 bool fused_supported(int D, int K, int Dp);
 // Whether a batch takes the small-batch instance (never past kFusedSmallRows rows).
 constexpr int kFusedSmallRows = 16384;
-bool fused_small(int D, int K, int n_rows);
-int fused_tile_rows(int D, int K, int n_rows);   // row tile of the fused kernel for this batch
+bool fused_small(int D, int K, int n_rows, int nnz);
+int fused_tile_rows(int D, int K, int n_rows, int nnz);   // row tile of this batch's kernel
 // With partial == nullptr, launch_whiten_cp only stores in *block_counts how
 // many blocks of the kernel it would launch for this batch can be resident on
 // one CU.

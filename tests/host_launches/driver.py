@@ -257,6 +257,21 @@ def check_few_columns_take_the_narrow_reduction():
             assert seen[0][n][1] == (3 if want == narrow else 1) * NUM_CU, seen
 
 
+def check_short_documents_of_many_topics_keep_the_tall_tiles():
+    """Past 32 topics, a batch of more than 12288 documents takes 16-row tiles only
+    if its documents have words enough."""
+    for D, K, n, words, small in ((16, 60, 16384, 3, False), (16, 60, 16384, 12, True),
+                                  (16, 60, 12288, 3, True), (4, 33, 12289, 11, False),
+                                  (16, 32, 16384, 3, True), (32, 64, 16385, 20, False)):
+        h = context(400, K, D)
+        assert set_whitening(h, 400, D) == 0
+        kernel, grid = step(h, batch(n, words), D, K)[0]
+        rows = int(kernel.split("<")[1].split(",")[2])
+        assert (rows == 16) == small, (D, K, n, words, kernel)
+        assert grid == min((n + rows - 1) // rows, 2 * NUM_CU)
+        LIB.tlda_destroy(h)
+
+
 def check_steps_only_launch():
     """A step on a warm context makes no runtime call beyond its launches that
     would cost host time on every one of them: no function attributes."""

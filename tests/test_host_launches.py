@@ -33,6 +33,7 @@ def stand_in(tmp_path_factory):
     "encoder_tiles_fit_what_they_hold",
     "few_blocks_do_not_form_the_gram_entries",
     "few_columns_take_the_narrow_reduction",
+    "short_documents_of_many_topics_keep_the_tall_tiles",
     "steps_only_launch",
 ])
 def test_host_launches(stand_in, check):
