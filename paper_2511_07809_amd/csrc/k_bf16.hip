@@ -542,10 +542,11 @@ __global__ void __launch_bounds__(64 * NW, 4) k_cp_bf16_multi(
     default: break;
   }
 #undef TLDA_MULTI
-  // The slice's squared Gram entries, once: formed by every block of the finish
-  // for its own entries they were most of its time (24 slices, D = K = 50 at
-  // most: finish 28 -> 17 us, this kernel 241 -> 243).
-  gram_entries(d.Phi, d.D, d.K, blk * 64 * NW + threadIdx.x, d.nblk * 64 * NW, d.gsq);
+  // The slice's squared Gram entries, once, where the plan says so: formed by
+  // every block of the finish for its own entries they were most of its time (24
+  // slices, D = K = 50 at most: finish 28 -> 17 us, this kernel 241 -> 243).
+  if (d.gsq != nullptr)
+    gram_entries(d.Phi, d.D, d.K, blk * 64 * NW + threadIdx.x, d.nblk * 64 * NW, d.gsq);
 }
 
 struct Bf16Args {

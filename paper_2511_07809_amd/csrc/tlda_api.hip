@@ -1330,9 +1330,14 @@ tlda_status multi_layout(tlda_multi* m, int total_blocks) {
   const int tr = tlda::multi_tile_rows(m->tile);
   std::vector<int> tiles(m->n);
   long long all_tiles = 0;
+  auto finish_blocks = [](const tlda::SliceStep& d) {
+    return (d.D * d.K + tlda::kFinishEntries - 1) / tlda::kFinishEntries;
+  };
+  int all_fin = 0;
   for (int i = 0; i < m->n; ++i) {
     tiles[i] = (m->rows[i] + tr - 1) / tr;
     all_tiles += tiles[i];
+    all_fin += finish_blocks(m->host[i]);
   }
   if (total_blocks <= 0) total_blocks = tlda::cp_bf16_multi_per_cu(m->tile) * m->num_cu;
   std::vector<tlda::SliceStep> tab = m->host;
@@ -1347,8 +1352,18 @@ tlda_status multi_layout(tlda_multi* m, int total_blocks) {
     d.blk0 = (int)blk_slice.size();
     for (int b = 0; b < nb; ++b) blk_slice.push_back(i);
     d.fin0 = (int)fin_slice.size();
-    const int nf = (d.D * d.K + tlda::kFinishEntries - 1) / tlda::kFinishEntries;
-    for (int b = 0; b < nf; ++b) fin_slice.push_back(i);
+    for (int b = 0; b < finish_blocks(d); ++b) fin_slice.push_back(i);
+    // The reduction forms the squared Gram entries of Phi where the finish would
+    // be long at it: more finish blocks than two rounds of compute units, or few
+    // enough entries a wave (at about D + 128 an entry) to cost the reduction
+    // less.  Steps at D = K = 50, 1000 documents a slice, by the reduction and by
+    // the finish: one slice 21.4 and 18.9 us, 2 slices 23.1 and 22.0, 4 slices 25.5
+    // and 25.7, 12 slices 37.3 and 44.5, 64 slices 115 and 167; one slice of 4000
+    // documents 19.0 and 19.4, of 20000 21.7 and 22.9; at D = K = 10 64 slices 24.5
+    // and 24.9, one 13.7 and 13.4.
+    const double share =
+        (double)d.K * d.K * (d.D + 128) / ((double)nb * tlda::multi_tile_waves(m->tile));
+    if (d.D * d.K < 256 || (all_fin < 2 * m->num_cu && share > 2000.0)) d.gsq = nullptr;
     need_p += (size_t)nb * d.D * d.K;
     need_c += (size_t)nb;
     max_dk = std::max(max_dk, d.D * d.K);

@@ -205,7 +205,8 @@ struct SliceStep {
   int Dh, D, K, shape;
   float* Phi;            // read by the reduction (copied to phi_copy), written by the finish
   float* phi_copy;
-  double* gsq;           // [K][K] squared Gram entries of Phi, from the reduction
+  double* gsq;           // [K][K] squared Gram entries of Phi, from the reduction (NULL: the
+                         // finish forms the ones it needs)
   float* partial;        // [nblk][D][K]
   int* block_counts;     // [nblk]
   int nblk, blk0, fin0;

@@ -272,6 +272,43 @@ def check_short_documents_of_many_topics_keep_the_tall_tiles():
         LIB.tlda_destroy(h)
 
 
+def check_small_plans_leave_the_gram_entries_to_the_finish():
+    """A slice's table entry names a buffer for the squared Gram entries only where
+    forming them in the reduction is the faster way."""
+    FAKE.fake_keep_args(b"k_cp_bf16_multi<", 2)
+    stride, at_nblk, at_gsq = 168, 104, 80   # of the device table's entries
+
+    def gsq(slices, n, K):
+        ctxs = []
+        for _ in range(slices):
+            h = context(400, K, K, tl.TLDA_BF16)
+            assert set_whitening(h, 400, K) == 0
+            ctxs.append(h)
+        Phi = np.zeros((slices, K * K), dtype=np.float32)
+        bs = (tl.tlda_csr_batch * slices)(*[batch(n)] * slices)
+        P = (ctypes.c_void_p * slices)(*[Phi[i].ctypes.data for i in range(slices)])
+        betas = (ctypes.c_float * slices)()
+        plan = ctypes.c_void_p()
+        assert LIB.tlda_multi_create(slices, (ctypes.c_void_p * slices)(*ctxs), bs, P, betas, None,
+                                     ctypes.byref(plan)) == 0
+        FAKE.fake_clear()
+        assert LIB.tlda_multi_step(plan) == 0
+        table, blocks, got = FAKE.fake_arg(0, 0), 0, []
+        for i in range(slices):
+            at = table + stride * i
+            blocks += ctypes.c_int32.from_address(at + at_nblk).value
+            got.append(ctypes.c_uint64.from_address(at + at_gsq).value != 0)
+        assert blocks == FAKE.fake_grid(0, 0)   # (the table is read where it should be)
+        LIB.tlda_multi_destroy(plan)
+        for h in ctxs:
+            LIB.tlda_destroy(h)
+        return got
+
+    assert gsq(1, 1000, 50) == [False] and gsq(2, 1000, 50) == [False] * 2
+    assert gsq(1, 20000, 50) == [True] and gsq(1, 4000, 50) == [True]
+    assert gsq(12, 1000, 50) == [True] * 12 and gsq(64, 1000, 10) == [False] * 64
+
+
 def check_steps_only_launch():
     """A step on a warm context makes no runtime call beyond its launches that
     would cost host time on every one of them: no function attributes."""

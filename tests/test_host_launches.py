@@ -34,6 +34,7 @@ def stand_in(tmp_path_factory):
     "few_blocks_do_not_form_the_gram_entries",
     "few_columns_take_the_narrow_reduction",
     "short_documents_of_many_topics_keep_the_tall_tiles",
+    "small_plans_leave_the_gram_entries_to_the_finish",
     "steps_only_launch",
 ])
 def test_host_launches(stand_in, check):
