@@ -226,16 +226,25 @@ __global__ void __launch_bounds__(256) k_infer_G(const double* __restrict__ A, i
 // from then on, so an unchanged number is an unchanged set, and the last tau is
 // the exact threshold of it.
 //
-// Documents finish at different iterations: a wave takes new ones from the
+// Documents finish at different iterations: a wave takes new ones from its
 // queue when kRefill columns are free (the b = A^T x of new documents costs
-// about an iteration for the whole wave).
+// about an iteration for the whole wave).  There are kInferQueues queues, each
+// with every kInferQueues-th 16 rows and every kInferQueues-th wave: one address
+// takes an atomic every 14 ns, which held 300000 rows at 262 us where they had
+// few iterations to do (2 topics, no iteration: 266 us with one queue, 39 with
+// 16, 80 with a wave per document; 5 topics, 20 iterations: 282, 156, 1490).
 //
 // Bound: the vector ALUs (the projection) and the FP32 matrix cores (4 TM
 // steps of TM tiles an iteration) about alike; two waves or more per SIMD
-// overlap them (up to 64 topics, where G's fragments stay in registers; past
-// that a wave takes a SIMD's registers alone).  65536 documents of 50 topics, up
-// to 200 iterations: 1.16 ms (6.5 with a lane per topic and the products as
-// sums over lanes).
+// overlap them (up to 64 topics, where G's fragments stay in registers).  65536
+// documents of 50 topics, up to 200 iterations: 1.16 ms (6.5 with a lane per
+// topic and the products as sums over lanes).  Past 64 topics a wave has a
+// SIMD's registers to itself, does not fit them (up to 128 topics 540 bytes a
+// lane in scratch memory, past that 528) and takes G from the caches in every
+// iteration.  It is still the faster way: 300000 documents, 60 iterations, 65
+// topics 11.1 ms (44.5 with a wave per document), 100 27 (63), 120 55 (72),
+// 128 with D = 30 52 (122); 65536 documents, 200 iterations, 256 topics 205 ms
+// (370).
 //
 // given: the start point is read from `out` (e.g. an encoder's output on the
 // simplex) instead of the uniform 1/K.
@@ -265,12 +274,16 @@ __global__ void __launch_bounds__(64, TM <= 4 ? 2 : 1) k_infer(
     const float* __restrict__ X, int n_rows, const float* __restrict__ A32,
     const float* __restrict__ Gf, const float* __restrict__ step32, int D, int K, int max_iter,
     float tol, float* __restrict__ out, bool given, bool gap_rule, float gap_tol, int min_steps,
-    int* __restrict__ n_stepped, unsigned* __restrict__ queue) {
+    int* __restrict__ n_stepped, unsigned* __restrict__ queues) {
   constexpr bool kRegs = TM <= 4;   // G's fragments in registers
   const int lane = threadIdx.x, l16 = lane & 15, q = lane >> 4;
   const int nt = (K + 15) / 16;                        // tiles of topics (<= TM)
   const int last = min(4, K - 16 * (nt - 1));          // steps of the last tile with topics < K
   const float step = step32[0];
+  const unsigned own = blockIdx.x % kInferQueues;
+  unsigned* queue = queues + own * kInferQueueStride;
+  // the row of this wave's queue's entry e
+  auto queued = [&](unsigned e) { return e / 16 * (16 * kInferQueues) + 16 * own + e % 16; };
   float gf[kRegs ? TM * TM * 4 : 1];
   if (kRegs) {
 #pragma unroll
@@ -298,8 +311,8 @@ __global__ void __launch_bounds__(64, TM <= 4 ? 2 : 1) k_infer(
       unsigned base = 0;
       if (lane == 0) base = atomicAdd(queue, (unsigned)nfree);
       base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-      drained = base + nfree >= (unsigned)n_rows;
-      const unsigned mine = base + __popc(free & ((1u << l16) - 1u));
+      drained = queued(base + nfree) >= (unsigned)n_rows;
+      const unsigned mine = queued(base + __popc(free & ((1u << l16) - 1u)));
       const bool fresh = row < 0 && mine < (unsigned)n_rows;
       if (fresh) {
         row = (int)mine;
@@ -496,7 +509,7 @@ hipError_t launch_inference_setup(const double* W, const double* m, const double
   return launch_top_eig(G, K < D ? K : D, step32, s);
 }
 
-// *queue must be zero.  As many waves as the 256 compute units hold: three per
+// The queues must be zero.  As many waves as the 256 compute units hold: three per
 // SIMD with G in registers up to 64 topics, one past that.
 static hipError_t launch_infer_k(const float* X, int n_rows, const float* A32, const float* Gf,
                                  const float* step32, int D, int K, int max_iter, float tol,
@@ -507,7 +520,8 @@ static hipError_t launch_infer_k(const float* X, int n_rows, const float* A32, c
   const dim3 grid(waves < most ? waves : most);
 #define TLDA_INFER(tm)                                                                           \
   hipLaunchKernelGGL(k_infer<tm>, grid, dim3(64), 0, s, X, n_rows, A32, Gf, step32, D, K,        \
-                     max_iter, tol, theta, given, gap_rule, gap_tol, min_steps, n_stepped, reinterpret_cast<unsigned*>(queue))
+                     max_iter, tol, theta, given, gap_rule, gap_tol, min_steps, n_stepped,        \
+                     reinterpret_cast<unsigned*>(queue))
   if (K <= 16) TLDA_INFER(1);
   else if (K <= 32) TLDA_INFER(2);
   else if (K <= 64) TLDA_INFER(4);

@@ -578,7 +578,8 @@ void destroy_all(tlda_ctx* c) {
   dfree(c->cp.gsq);
   dfree(c->cp.Z); dfree(c->cp.rz); dfree(c->cp.Z16);
   dfree(c->post); dfree(c->postA); dfree(c->postG); dfree(c->postP);
-  dfree(c->A32); dfree(c->Gf); dfree(c->step32); dfree(c->dev_flags); dfree(c->block_counts);
+  dfree(c->A32); dfree(c->Gf); dfree(c->step32); dfree(c->dev_flags); dfree(c->queues);
+  dfree(c->block_counts);
   for (auto& s : c->slots) {
     if (s.free_) (void)hipEventSynchronize(s.free_);
     dfree(s.row_ptr); dfree(s.col_idx); dfree(s.val); dfree(s.col16); dfree(s.val16);
@@ -684,8 +685,10 @@ tlda_status tlda_create(const tlda_config* cfg, void* hip_stream, tlda_ctx** out
             dalloc(&ctx->post, tlda::unwhiten_scratch_doubles(c.V, c.K)) == hipSuccess &&
             dalloc(&ctx->postP, tlda::project_scratch_doubles(c.V, c.D, c.K)) == hipSuccess &&
             dalloc(&ctx->postA, D * K) == hipSuccess && dalloc(&ctx->postG, K * K) == hipSuccess &&
-            dalloc(&ctx->A32, D * K) == hipSuccess && dalloc(&ctx->Gf, (K + 15) / 16 * 16 * ((K + 15) / 16 * 16)) == hipSuccess &&
+            dalloc(&ctx->A32, D * K) == hipSuccess &&
+            dalloc(&ctx->Gf, ((K + 15) / 16 * 16) * ((K + 15) / 16 * 16)) == hipSuccess &&
             dalloc(&ctx->step32, 1) == hipSuccess && dalloc(&ctx->dev_flags, 4) == hipSuccess &&
+            dalloc(&ctx->queues, tlda::kInferQueueInts) == hipSuccess &&
             dalloc(&ctx->block_counts, 2 * tlda::kWhitenBlockCounts) == hipSuccess;
   if (ok && (c.flags & TLDA_BF16))
     ok = dalloc(&ctx->wh.W16, V * (size_t)ctx->Dh) == hipSuccess &&
@@ -917,11 +920,11 @@ tlda_status tlda_infer_doc_topics_whitened(tlda_ctx* c, const float* X, int32_t 
   CHECK_ARG(c, c->wh.ready, TLDA_ERR_STATE, "no whitening matrix yet");
   if (n_rows == 0) return TLDA_OK;
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
-  HIP_OK(c, launch_zero(c->dev_flags, 4 * sizeof(int), c->stream));
+  HIP_OK(c, launch_zero(c->queues, tlda::kInferQueueInts * sizeof(int), c->stream));
   HIP_OK(c, tlda::launch_inference_setup(c->wh.W, c->wh.m, mu, V, D, K, c->postP, c->postA,
                                          c->postG, c->A32, c->Gf, c->step32, c->stream));
   HIP_OK(c, tlda::launch_infer(X, n_rows, c->A32, c->Gf, c->step32, D, K, max_iter, tol,
-                               theta_out, c->dev_flags + 1, c->stream));
+                               theta_out, c->queues, c->stream));
   return TLDA_OK;
 }
 
@@ -1269,7 +1272,7 @@ tlda_status tlda_infer_doc_topics_mlp(tlda_ctx* c, tlda_mlp* m, const float* X, 
   HIP_OK(c, launch_zero(ns, sizeof(int32_t), c->stream));
   if (n_rows == 0) return TLDA_OK;
   const int V = c->cfg.V, D = c->cfg.D, K = c->cfg.K;
-  HIP_OK(c, launch_zero(c->dev_flags + 1, sizeof(int), c->stream));
+  HIP_OK(c, launch_zero(c->queues, tlda::kInferQueueInts * sizeof(int), c->stream));
   HIP_OK(c, tlda::launch_inference_setup(c->wh.W, c->wh.m, mu, V, D, K, c->postP, c->postA,
                                          c->postG, c->A32, c->Gf, c->step32, c->stream));
   if (m != nullptr) {
@@ -1281,7 +1284,7 @@ tlda_status tlda_infer_doc_topics_mlp(tlda_ctx* c, tlda_mlp* m, const float* X, 
   }
   HIP_OK(c, tlda::launch_infer_gap(X, n_rows, c->A32, c->Gf, c->step32, D, K, m != nullptr,
                                    gap_tol, min_steps, max_iter, theta_out, ns,
-                                   c->dev_flags + 1, c->stream));
+                                   c->queues, c->stream));
   return TLDA_OK;
 }
 

@@ -15,6 +15,10 @@ namespace tlda {
 // Floats of the allocation-free step's partial buffer (16 MiB per device).
 constexpr size_t kNoAllocFloats = size_t(4) << 20;
 
+// The inference solve's row queues, each counter on a cache line of its own.
+constexpr int kInferQueues = 16, kInferQueueStride = 32;
+constexpr int kInferQueueInts = kInferQueues * kInferQueueStride;
+
 // Per-block count scratch: the whitening and the moment kernels cap their
 // grids at this many blocks (the moment kernel stores two counts per block).
 constexpr int kWhitenBlockCounts = 2048;
@@ -156,8 +160,9 @@ struct tlda_ctx {
   float* A32 = nullptr;       // [D][K]
   float* Gf = nullptr;        // A^T A in fragment order, K padded to 16
   float* step32 = nullptr;    // [1]
-  int* dev_flags = nullptr;   // [4] CSR validation and inference words: 0, 1 validation, 1
-                              // the solve's queue, 2 kept rows, 3 stepped rows
+  int* dev_flags = nullptr;   // [4] CSR validation and inference words: 0, 1 validation, 2 kept
+                              // rows, 3 stepped rows
+  int* queues = nullptr;      // [kInferQueueInts] the inference solve's queues
   int* block_counts = nullptr;  // [2 * kWhitenBlockCounts] per-block document counts
   // timing hook: event pairs recorded around the main kernel of each hot-path call
   hipEvent_t* t_start = nullptr;
@@ -466,7 +471,8 @@ hipError_t launch_project(const double* W, const double* m, const double* mu, in
                           double* part, double* A, float* A32, hipStream_t s);
 // step = 1 / (largest eigenvalue of the n x n positive semidefinite G), n <= 128
 hipError_t launch_top_eig(const double* G, int n, float* step, hipStream_t s);
-// queue: a zeroed device counter, which the solve's waves take rows from
+// queue: kInferQueueInts zeroed device counters, which the solve's waves take
+// rows from
 hipError_t launch_infer(const float* X, int n_rows, const float* A32, const float* Gf,
                         const float* step32, int D, int K, int max_iter, float tol,
                         float* theta, int* queue, hipStream_t s);
