@@ -242,9 +242,9 @@ __global__ void __launch_bounds__(256) k_infer_G(const double* __restrict__ A, i
 // SIMD's registers to itself, does not fit them (up to 128 topics 540 bytes a
 // lane in scratch memory, past that 528) and takes G from the caches in every
 // iteration.  It is still the faster way: 300000 documents, 60 iterations, 65
-// topics 11.1 ms (44.5 with a wave per document), 100 27 (63), 120 55 (72),
-// 128 with D = 30 52 (122); 65536 documents, 200 iterations, 256 topics 205 ms
-// (370).
+// topics 11.1 ms (44 with a wave per document), 100 27 (63), 120 55 (72),
+// 128 with D = 30 52 (122); 65536 documents, 200 iterations, 256 topics 220 ms
+// (384).
 //
 // given: the start point is read from `out` (e.g. an encoder's output on the
 // simplex) instead of the uniform 1/K.
