@@ -169,6 +169,19 @@ tlda_status fused_grid(tlda_ctx* c, bool small, int* blocks) {
   return TLDA_OK;
 }
 
+// Blocks of the FP32 reduction from X: the tuned number, or one full round of
+// resident blocks of the kernel that this batch takes.
+int cp_grid(tlda_ctx* c, int n_rows) {
+  const int D = c->cfg.D, K = c->cfg.K;
+  int most = c->tune.cp_max_blocks;
+  if (most <= 0) {
+    int& resident = c->tune.cp_resident[tlda::cp_narrow(D, K, n_rows) ? 1 : 0];
+    if (resident <= 0) resident = tlda::cp_resident_blocks(D, K, n_rows, c->num_cu);
+    most = resident;
+  }
+  return tlda::cp_num_blocks(n_rows, D, K, most);
+}
+
 tlda_status ensure_partial(tlda_ctx* c, size_t need) {
   if (c->cp.cap < need) {
     HIP_OK(c, hipStreamSynchronize(c->stream));
@@ -799,13 +812,7 @@ tlda_status tlda_cp_step(tlda_ctx* c, const float* X, int32_t n_rows, const int3
   if (is_bf16(c)) {
     nblk = bf16_grid(c, 1, n_rows);
   } else {
-    int most = c->tune.cp_max_blocks;
-    if (most <= 0) {
-      int& resident = c->tune.cp_resident[tlda::cp_narrow(D, K, n_rows) ? 1 : 0];
-      if (resident <= 0) resident = tlda::cp_resident_blocks(D, K, n_rows, c->num_cu);
-      most = resident;
-    }
-    nblk = tlda::cp_num_blocks(n_rows, D, K, most);
+    nblk = cp_grid(c, n_rows);
   }
   tlda_status st = ensure_partial(c, (size_t)nblk * D * K);
   if (st != TLDA_OK) return st;
@@ -1661,29 +1668,28 @@ tlda_status tlda_graph_capture_steps(tlda_ctx* c, const tlda_csr_batch* batches,
   CHECK_ARG(c, std::isfinite(beta), TLDA_ERR_ARG, "beta is not finite");
   // everything that may synchronise or allocate happens before the capture:
   // argument and content checks, and the largest partial buffer
-  int max_rows = 0;
   for (int i = 0; i < n; ++i) {
     tlda_status st = check_batch(c, &batches[i]);
     if (st != TLDA_OK) return st;
     CHECK_ARG(c, batches[i].slot < 0, TLDA_ERR_ARG, "staged batches are not captured");
     st = validate_content(c, &batches[i]);
     if (st != TLDA_OK) return st;
-    max_rows = std::max(max_rows, (int)batches[i].n_rows);
   }
-  size_t need = 0;
+  // (room for the full grid of every kernel that this context's steps take,
+  // whatever their batches: none may regrow the buffer that the graph writes)
+  constexpr int kAnyRows = 1 << 30;
+  int nblk = 0;
   if (is_bf16(c)) {
-    need = (size_t)bf16_grid(c, 0, max_rows) * D * K;
+    nblk = std::max(bf16_grid(c, 0, kAnyRows), bf16_grid(c, 1, kAnyRows));
   } else {
-    // (room for either instance's full grid: a later step must not regrow the
-    // buffer that the graph writes)
     int large = 0, small = 0;
     tlda_status st = fused_grid(c, false, &large);
     if (st == TLDA_OK && tlda::fused_small(D, K, 1, 0)) st = fused_grid(c, true, &small);
     if (st != TLDA_OK) return st;
-    const int nblk = std::min(std::max(large, small), 2 * tlda::kWhitenBlockCounts);
-    need = (size_t)nblk * D * K;
+    nblk = std::max(std::min(std::max(large, small), 2 * tlda::kWhitenBlockCounts),
+                    cp_grid(c, kAnyRows));
   }
-  tlda_status st = ensure_partial(c, need);
+  tlda_status st = ensure_partial(c, (size_t)nblk * D * K);
   if (st != TLDA_OK) return st;
   HIP_OK(c, hipStreamSynchronize(c->stream));
   tlda_graph* g = new (std::nothrow) tlda_graph();

@@ -116,6 +116,32 @@ def check_captured_steps_never_regrow_their_partials():
     LIB.tlda_destroy(h)
 
 
+def check_no_step_regrows_what_a_graph_writes():
+    """A graph captured over small batches keeps its partials when the context
+    then steps larger ones, from the batch or from X."""
+    FAKE.fake_occupancy(b"k_cp_reduce_mfma<", 6)
+    freed = []
+    for D, K, flags in ((5, 5, 0), (50, 50, 0), (100, 100, 0), (16, 100, 0), (50, 50, tl.TLDA_BF16),
+                        (100, 100, tl.TLDA_BF16)):
+        V = 400
+        Phi = np.zeros((D, K), dtype=np.float32)
+        h = context(V, K, D, flags)
+        assert set_whitening(h, V, D) == 0
+        small, large = batch(1000, 1), batch(300000, 1)
+        g = ctypes.c_void_p()
+        arr = (tl.tlda_csr_batch * 1)(small)
+        assert LIB.tlda_graph_capture_steps(h, arr, 1, 0.0, Phi.ctypes.data, ctypes.byref(g)) == 0
+        before = FAKE.fake_frees()
+        step(h, large, D, K)
+        assert LIB.tlda_cp_step(h, ctypes.c_void_p(1 << 20), 300000, None, 0.0, Phi.ctypes.data,
+                                None) == 0
+        if FAKE.fake_frees() != before:
+            freed.append((D, K, flags))
+        LIB.tlda_graph_destroy(g)
+        LIB.tlda_destroy(h)
+    assert not freed, freed
+
+
 def check_rebase_after_a_failed_allocation():
     """Out of memory anywhere in keeping the previous whitening leaves a context
     whose next whitening and rebase work: no kernel gets a null buffer."""

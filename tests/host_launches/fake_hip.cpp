@@ -26,6 +26,7 @@ std::vector<std::pair<std::string, int>> g_occupancy;  // substring, blocks
 std::map<std::string, int> g_n_args;
 long long g_fail_malloc = -1;                          // mallocs until one fails
 int g_set_attribute = 0;
+int g_frees = 0;                                       // of device memory
 int g_last_error = 0;
 
 std::string name_of(const void* f) {
@@ -70,6 +71,7 @@ const char* fake_query(int i) { return g_queries[i].c_str(); }
 void fake_occupancy(const char* part, int blocks) { g_occupancy.push_back({part, blocks}); }
 void fake_keep_args(const char* part, int n) { g_n_args[part] = n; }
 void fake_fail_malloc(long long after) { g_fail_malloc = after; }
+int fake_frees() { return g_frees; }
 int fake_set_attribute() { return g_set_attribute; }
 
 // ---- the runtime ----
@@ -129,6 +131,7 @@ int hipMalloc(void** p, size_t bytes) {
   return *p ? 0 : 2;
 }
 int hipFree(void* p) {
+  ++g_frees;
   std::free(p);
   return 0;
 }
