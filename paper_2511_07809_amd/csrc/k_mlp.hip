@@ -692,19 +692,43 @@ int pad64(int n) { return (n + 63) / 64 * 64; }
 
 }  // namespace
 
+// LDS of k_forward: halves a document in the two buffers, bytes of a block.
+static int forward_lda(int D, int H) { return std::max(pad32(D), pad32(H)) + 8; }
+static int forward_ldb(int H, int K) { return std::max(pad32(H), 2 * pad32(K)) + 8; }
+static size_t forward_lds(int D, int H, int K, int docs) {
+  return (size_t)docs * (forward_lda(D, H) + forward_ldb(H, K)) * sizeof(uint16_t);
+}
+// and of k_train
+static int train_lda(int D, int H) { return std::max(pad32(D), pad32(H)) + 8; }
+static size_t train_lds(int D, int H, int K) {
+  return (size_t)16 * (3 * train_lda(D, H) + pad32(K) + 8) * sizeof(uint16_t) +
+         16 * (pad32(K) + 4) * sizeof(float);
+}
+constexpr size_t kForwardLds = 80 * 1024;   // two blocks on a compute unit
+static auto train_kernel(int H) {
+  return H <= 32 * kWaves ? k_train<1> : H <= 64 * kWaves ? k_train<2> : k_train<4>;
+}
+
 // Dynamic LDS past the default 64 KB (of the compute unit's 160) has to be
-// allowed; once, when an encoder is made, and for any encoder's widths.
-hipError_t mlp_allow_lds() {
-  const void* kernels[] = {
-      reinterpret_cast<const void*>(k_forward<1>), reinterpret_cast<const void*>(k_forward<2>),
-      reinterpret_cast<const void*>(k_forward<4>), reinterpret_cast<const void*>(k_train<1>),
-      reinterpret_cast<const void*>(k_train<2>),   reinterpret_cast<const void*>(k_train<4>)};
-  for (const void* k : kernels) {
-    const hipError_t e =
-        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+// allowed; once, when an encoder is made, for the kernels that need it (any
+// encoder's need, since the permission is the kernel's).
+hipError_t mlp_allow_lds(int D, int H, int K) {
+  auto allow = [](const void* kernel, size_t bytes) {
+    return bytes <= 64 * 1024 ? hipSuccess
+                              : hipFuncSetAttribute(
+                                    kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  };
+  auto forward = [&](auto kernel, int docs) {
+    const size_t bytes = forward_lds(D, H, K, docs);
+    return docs > 16 && bytes > kForwardLds
+               ? hipSuccess
+               : allow(reinterpret_cast<const void*>(kernel), bytes);
+  };
+  hipError_t e = forward(k_forward<4>, 64);
+  if (e == hipSuccess) e = forward(k_forward<2>, 32);
+  if (e == hipSuccess) e = forward(k_forward<1>, 16);
+  if (e != hipSuccess) return e;
+  return allow(reinterpret_cast<const void*>(train_kernel(H)), train_lds(D, H, K));
 }
 
 size_t mlp_param_count(int d_in, int hidden, int k_out) {
@@ -727,18 +751,16 @@ size_t mlp_tile_halves(int d_in, int hidden, int k_out, int max_batch) {
 hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta) {
   if (n <= 0) return hipSuccess;
   const int D = m.d_in, H = m.hidden, K = m.k_out;
-  const int lda = std::max(pad32(D), pad32(H)) + 8;
-  const int ldb = std::max(pad32(H), 2 * pad32(K)) + 8;
+  const int lda = forward_lda(D, H), ldb = forward_ldb(H, K);
   const Frags f = frags_of(m);
   // 64 documents a block while the grid still fills the 256 compute units
   // twice over and two blocks' LDS fits on one; 32 or 16 below that, or for
   // wide layers
-  auto bytes = [&](int docs) { return (size_t)docs * (lda + ldb) * sizeof(uint16_t); };
   int nt = 1;
-  if (bytes(64) <= 80 * 1024 && n >= 64 * 512) nt = 4;
-  else if (bytes(32) <= 80 * 1024 && n >= 32 * 512) nt = 2;
+  if (forward_lds(D, H, K, 64) <= kForwardLds && n >= 64 * 512) nt = 4;
+  else if (forward_lds(D, H, K, 32) <= kForwardLds && n >= 32 * 512) nt = 2;
   auto kernel = nt == 4 ? k_forward<4> : nt == 2 ? k_forward<2> : k_forward<1>;
-  const size_t lds = bytes(16 * nt);
+  const size_t lds = forward_lds(D, H, K, 16 * nt);
   // a launch takes fewer than 2^32 work items
   const int64_t docs = 16 * nt, most = ((int64_t(1) << 32) / kThreads - 1) * docs;
   for (int64_t r = 0; r < n; r += most) {
@@ -765,12 +787,12 @@ static hipError_t train_partials(tlda_mlp& m, const float* X, const float* T, in
   o.d1 = o.h2 + (size_t)pad64(H) * o.ld;
   o.d2 = o.d1 + (size_t)pad64(H) * o.ld;
   o.d3 = o.d2 + (size_t)pad64(H) * o.ld;
-  const int Kp = pad32(K), lda = std::max(pad32(D), pad32(H)) + 8;
-  const size_t lds = (size_t)16 * (3 * lda + Kp + 8) * sizeof(uint16_t) + 16 * (Kp + 4) * sizeof(float);
+  const int lda = train_lda(D, H);
+  const size_t lds = train_lds(D, H, K);
   const dim3 grid(c.chunk_pad / 16, c.splits);
   const Frags f = frags_of(m);
   const float inv_b = 1.0f / (float)n;
-  auto kernel = H <= 32 * kWaves ? k_train<1> : H <= 64 * kWaves ? k_train<2> : k_train<4>;
+  auto kernel = train_kernel(H);
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, m.stream, X, T, n, D, H, K, lda, f, o, inv_b,
                      m.row_loss);
   const hipError_t e = hipGetLastError();

@@ -1158,7 +1158,7 @@ tlda_status tlda_mlp_create(int32_t d_in, int32_t hidden, int32_t k_out, int32_t
   if (d_in < 1 || d_in > TLDA_MLP_MAX_WIDTH || hidden < 1 || hidden > TLDA_MLP_MAX_WIDTH ||
       k_out < 1 || k_out > TLDA_MAX_K || max_batch < 1)
     return TLDA_ERR_SHAPE;
-  if (tlda::mlp_allow_lds() != hipSuccess) return TLDA_ERR_DEVICE;
+  if (tlda::mlp_allow_lds(d_in, hidden, k_out) != hipSuccess) return TLDA_ERR_DEVICE;
   tlda_mlp* m = new (std::nothrow) tlda_mlp();
   if (!m) return TLDA_ERR_OOM;
   m->d_in = d_in;

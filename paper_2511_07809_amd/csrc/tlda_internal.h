@@ -436,7 +436,7 @@ size_t mlp_bias_floats(int hidden, int k_out);
 size_t mlp_workspace_floats(int d_in, int hidden, int k_out, int max_batch);
 size_t mlp_tile_halves(int d_in, int hidden, int k_out, int max_batch);
 // what the kernels below need on the current device before their first launch
-hipError_t mlp_allow_lds();
+hipError_t mlp_allow_lds(int d_in, int hidden, int k_out);
 // forward pass of n rows: theta = softmax(...) (FP32 [n][k_out])
 hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta);
 // gradients and loss of the mean cross-entropy of n <= max_batch rows against
