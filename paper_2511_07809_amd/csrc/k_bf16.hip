@@ -513,9 +513,9 @@ __global__ void __launch_bounds__(64 * (MODE == kWhitenOnly ? 4 : bf16_waves(DQ,
 // whitening, D, K and Phi) in one launch: block b serves slice blk_slice[b],
 // as block b - blk0 of that slice's nblk blocks.  One LDS allocation of the
 // largest shape (D, K <= 64) serves every slice.  Four waves per SIMD: the Gram
-// entries at the end would take 4-wave blocks to three (263 us).  Tile shape: TR documents
-// per row tile, NW waves per block (the plan's autotuner picks among the
-// instances below).
+// entries at the end would take 4-wave blocks to three (263 us in the same
+// trace).  Tile shape: TR documents per row tile, NW waves per block (the plan's
+// autotuner picks among the instances below).
 template <int TR, int NW>
 __global__ void __launch_bounds__(64 * NW, 4) k_cp_bf16_multi(
     const SliceStep* __restrict__ sl, const int* __restrict__ blk_slice) {
@@ -544,7 +544,8 @@ __global__ void __launch_bounds__(64 * NW, 4) k_cp_bf16_multi(
 #undef TLDA_MULTI
   // The slice's squared Gram entries, once, where the plan says so: formed by
   // every block of the finish for its own entries they were most of its time (24
-  // slices, D = K = 50 at most: finish 28 -> 17 us, this kernel 241 -> 243).
+  // slices, D = K = 50 at most, in a kernel trace, where a pass takes a quarter
+  // longer than among others: finish 28 -> 17 us, this kernel 241 -> 243).
   if (d.gsq != nullptr)
     gram_entries(d.Phi, d.D, d.K, blk * 64 * NW + threadIdx.x, d.nblk * 64 * NW, d.gsq);
 }

@@ -456,6 +456,12 @@ __global__ void __launch_bounds__(1024) k_jacobi(double* __restrict__ A, double*
 // at i (i + 1) / 2 + j.  A thread owns the 2 x 2 blocks at the rows of pair a
 // and the columns of pair b > a of the same (a, b) in every round, at most MAXB.
 // rot: [sweeps][m - 1][half] rotations (c, s); *n_sweeps: sweeps that rotated.
+// The rotations take 3.6 ms at p = 200 and 0.5 at p = 100, the vectors 0.29 and
+// 0.1 (58 and 1.42 ms when one block kept matrix and vectors, the larger one in
+// memory): a round is two barriers and one pair per thread, a serial chain.
+// Past p = 200 the triangle does not fit LDS and k_jacobi keeps both in memory:
+// the refresh at V = 5000, D = 100 takes 10 ms with p = 200 and 108 with 201
+// (143 both before).
 constexpr int kRotP = 200, kRotThreads = 1024, kMaxSweeps = 60;
 
 __device__ __forceinline__ int tri(int i, int j) {
@@ -478,13 +484,6 @@ __device__ __forceinline__ int2 circle_pair(int r, int k, int m) {
     ++j;
   }
   return i < j ? make_int2(i, j) : make_int2(j, i);
-}
-
-// 1 / sqrt(x), x > 0: the hardware estimate and one third-order step
-__device__ __forceinline__ double inv_sqrt(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = fma(-x * y, y, 1.0);
-  return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // Barrier for LDS data alone: __syncthreads would also wait for the rotations
@@ -615,9 +614,6 @@ __global__ void __launch_bounds__(kRotThreads) k_jacobi_rot(const double* __rest
   for (int i = tid; i < p; i += kRotThreads) ev[i] = A[tri(i, i)];
 }
 
-// The rotations take 3.6 ms at p = 200 and 0.5 at p = 100, the vectors 0.29 and
-// 0.1 (58 and 1.42 ms when one block kept matrix and vectors, the larger one in
-// memory): a round is two barriers and one pair per thread, a serial chain.
 // Z = the product of k_jacobi_rot's rotations: one wave per row of Z, the row
 // in LDS, lane l taking pairs l and l + 64 of every round; the next round's
 // rotations are on their way while this one's are applied.

@@ -68,16 +68,6 @@ __device__ __forceinline__ doublex4 tile_mfma(doublex4 a, doublex4 b, doublex4 a
   return acc;
 }
 
-// 1 / sqrt(d) for d > 0: the hardware estimate (about 2^-23 relative) and one
-// third-order step, to within an ulp or two, in a sixth of the dependent
-// instructions of a division by a square root; a chain of p of these is what
-// the factorisation waits for.
-__device__ __forceinline__ double inv_sqrt(double d) {
-  const double y = __builtin_amdgcn_rsq(d);
-  const double e = fma(-d * y, y, 1.0);
-  return fma(y * e, fma(0.375, e, 0.5), y);
-}
-
 // One wave: the Cholesky factor of the 16 x 16 tile `a` (row-major in LDS)
 // and the inverse of its transpose.  Lanes 0-15 (and 32-47) hold a column of
 // the tile, lanes 16-31 a column of the identity, and both take the same
@@ -170,10 +160,15 @@ constexpr int panel_tiles(int n) {
   return nb;
 }
 
-// Where the diagonal of R spans less than this, the block's columns come out of
-// one Cholesky-QR pass orthonormal to about 1e-16 / kWell^2 = 1e-8, and the
-// iteration goes on without the second (the cold refresh at V = 20000, p = 200
-// takes 263 ms with it everywhere, 244 without it there).
+// Where the diagonal of R spans less than this, the iteration goes on without
+// the second Cholesky-QR pass (the cold refresh at V = 20000, p = 200 takes 263
+// ms with it everywhere, 244 without it there).  Between iterations only the
+// span of the block matters, which one pass leaves as it is; its columns need
+// not be orthonormal, just far from dependent.  With G + s I = R^T R they come
+// out with Q^T Q = I - s R^-T R^-1, off by s / sigma_min(R)^2: about 1e-4 at this
+// limit with the shift s of 1e-12 of the largest diagonal entry.  (The diagonal
+// of an unpivoted R only estimates its condition, so this is a rule of thumb; the
+// last iteration before the projection always runs both passes.)
 constexpr double kWell = 1e-4;
 
 // The factor, tiles in registers: one block of NW waves, tile t = tile_at(i, j)
@@ -731,10 +726,9 @@ static int gram_chunks(int V, const GramShape& g, int blocks) {
   const int want = blocks / g.units(), most = (V + 63) / 64;
   return want < 1 ? 1 : want < most ? want : most;
 }
-// 1024 blocks are four waves per SIMD of the 256 compute units; half of them
-// for the one product of an inference, whose scratch every context keeps.
-// Blocks of the tall products: four a CU for the refresh's, whose tile rows are
-// several units; two for the projection's, whose chunks the sum reads again.
+// Blocks of the tall products: four a CU (four waves per SIMD) for the refresh's,
+// whose tile rows are several units; two for the one projection of an inference,
+// whose chunks the sum reads again and whose scratch every context keeps.
 constexpr int kGramBlocks = 1024, kProjectBlocks = 512;
 
 // The chunks alone; their number to nz.

@@ -946,8 +946,8 @@ hipError_t launch_wide(const tlda_csr_batch& b, const float* W32, const float* m
 // Small batches of narrow shapes: 16 lanes per document whatever G is, and
 // 16-row tiles.  With G lanes (2 at D = 5) a document's nonzeros go 8 at a
 // time, two round trips each, and 1000 documents are 16 blocks: latency is all
-// there is (11.3 us for 1000 documents of 33 words); 16 lanes take 64 of them at
-// once, on 63 blocks.  Steps at D = K = 5, 51 tokens: 15.0 -> 9.3 us for 1000
+// there is (11.3 us for 1000 documents of 33 words); 16 lanes take P = 16 / G
+// times as many at once (64 at D = 5), on 63 blocks.  Steps at D = K = 5, 51 tokens: 15.0 -> 9.3 us for 1000
 // documents, 16.0 -> 12.6 for 16 000; at 30 000 both take 17.3 and at 60 000
 // this takes 25.0 against 21.9 (the lanes' redundant reads then count; at D = 20
 // the two cross between 30 000 and 60 000 as well).

@@ -12,6 +12,16 @@
 
 namespace tlda {
 
+// 1 / sqrt(d) for d > 0: the hardware estimate (about 2^-23 relative) and one
+// third-order step, to within an ulp or two, in a sixth of the dependent
+// instructions of a division by a square root, a chain of which the Cholesky
+// pivots and the rotations wait for.
+__device__ __forceinline__ double inv_sqrt(double d) {
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-d * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
 // Floats of the allocation-free step's partial buffer (16 MiB per device).
 constexpr size_t kNoAllocFloats = size_t(4) << 20;
 
@@ -133,7 +143,8 @@ struct CpScratch {
   float* Z = nullptr;         // [V][Kp] W Phi of the classic-moment step
   float* rz = nullptr;        // [Kp]    Phi^T W^T M1 of the classic-moment step
   uint16_t* Z16 = nullptr;    // [V][Kh] bf16(W16 Phi) of the BF16 classic-moment step
-  double* gsq = nullptr;      // [K][K] squared Gram entries of Phi (large D x K only)
+  double* gsq = nullptr;      // [K][K] squared Gram entries of Phi: of steps with D K >=
+                              // kGramOnceDK, and of kernels that form them at any size
 };
 
 }  // namespace tlda
@@ -294,8 +305,8 @@ hipError_t launch_gram(const double* A, const double* B, double* G, int V, int p
                        double* part, hipStream_t s);
 // Binv <- R^-1 with A^T A + shift_rel max diag(A^T A) I = R^T R (R upper; p <=
 // 512); *info |= 1 on a pivot that is not positive; *well (or NULL) tells
-// whether one Cholesky-QR pass with it leaves the block's columns orthonormal
-// to 1e-8.  Here and below: nothing is done where *skip is set (skip may be NULL)
+// whether the diagonal of R spans little enough for one Cholesky-QR pass with it
+// to do between iterations, where only the block's span matters.  Here and below: nothing is done where *skip is set (skip may be NULL)
 size_t chol_scratch_doubles(int p);
 hipError_t launch_gram_chol(const double* A, double* G, int V, int p, double* part,
                             double shift_rel, double* scratch, double* Binv, int* info,
