@@ -175,9 +175,10 @@ __global__ void __launch_bounds__(kThreads) k_classic_z(const float* __restrict_
 //
 // What bounds it: issue slots and the latency of the gathers.  131072 documents
 // of 20 words at D = K = 50, V = 20000 (2.52 million nonzeros, 1.35 GB through
-// L2) take 293 us: the matrix cores are busy for 140 of them, the vector ALU
-// for about 75 (per nonzero row two offsets, two readlanes, four operations for
-// L, s and q, three for the reduction row).  Tiles of 16 documents per block of
+// L2) take 265 us among other steps (288 in a kernel trace, where each launch
+// waits): the matrix cores are busy for 140 of them, the vector ALU for about 75
+// (per nonzero row two offsets, two readlanes, four operations for L, s and q,
+// three for the reduction row).  Tiles of 16 documents per block of
 // four waves, with Z gathered twice, staged in LDS and a barrier per 16 rows,
 // took 475 us.  Z rows kept in LDS between the phases took 350 us: 20 KB a wave
 // leave two waves per SIMD, where a ring of 12 KB leaves three.  A 64-bit
