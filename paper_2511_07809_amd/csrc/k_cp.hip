@@ -7,8 +7,9 @@
 //
 // The reductions (k_cp_reduce_mfma up to D, K of 128, k_cp_reduce_wide past
 // that, k_cp_reduce_narrow for few columns of it): each block walks a fixed set
-// of row tiles (tile b, b + nblk, ...), forms S = X_t Phi and adds X_t^T S^2 to its own R1, and writes that partial;
-// the row partition depends only on n_rows, so the reduction order is fixed.
+// of row tiles (tile b, b + nblk, ...), forms S = X_t Phi and adds X_t^T S^2 to
+// its own R1, and writes that partial; the row partition depends only on n_rows,
+// so the reduction order is fixed.
 #include "tlda_internal.h"
 
 namespace tlda {
