@@ -240,8 +240,9 @@ __device__ inline float softmax_row(float* z, int K, int j) {
 // theta = softmax(...) for a tile of 16 NT documents.  LDS: two activation
 // buffers of 16 NT documents, each as wide as what it holds: lda halves for the
 // rows of X and the second hidden layer, ldb for the first and the logits in
-// FP32.
-template <int NT>
+// FP32.  WIDE: D > kWideInput (an instance of its own: beside each other the two
+// ways in cost the narrow one 0.3%).
+template <int NT, bool WIDE>
 __global__ void __launch_bounds__(kThreads) k_forward(const float* __restrict__ X, int64_t n_rows,
                                                       int D, int H, int K, int lda, int ldb,
                                                       Frags f, float* __restrict__ theta) {
@@ -253,7 +254,7 @@ __global__ void __launch_bounds__(kThreads) k_forward(const float* __restrict__ 
   const int Dp = pad32(D), Hp = pad32(H), Kp = pad32(K);
   const int64_t row0 = (int64_t)blockIdx.x * docs;
   const int rows = (int)min((int64_t)docs, n_rows - row0);
-  if (D > kWideInput)
+  if (WIDE)
     load_wide_rows<docs>(X + row0 * D, rows, D, Dp, buf[0], lda);
   else
     load_rows(X + row0 * D, rows, docs, D, Dp, buf[0], lda);
@@ -705,6 +706,11 @@ static size_t train_lds(int D, int H, int K) {
          16 * (pad32(K) + 4) * sizeof(float);
 }
 constexpr size_t kForwardLds = 80 * 1024;   // two blocks on a compute unit
+static auto forward_kernel(int D, int nt) {
+  if (D > kWideInput)
+    return nt == 4 ? k_forward<4, true> : nt == 2 ? k_forward<2, true> : k_forward<1, true>;
+  return nt == 4 ? k_forward<4, false> : nt == 2 ? k_forward<2, false> : k_forward<1, false>;
+}
 static auto train_kernel(int H) {
   return H <= 32 * kWaves ? k_train<1> : H <= 64 * kWaves ? k_train<2> : k_train<4>;
 }
@@ -718,15 +724,12 @@ hipError_t mlp_allow_lds(int D, int H, int K) {
                               : hipFuncSetAttribute(
                                     kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   };
-  auto forward = [&](auto kernel, int docs) {
-    const size_t bytes = forward_lds(D, H, K, docs);
-    return docs > 16 && bytes > kForwardLds
-               ? hipSuccess
-               : allow(reinterpret_cast<const void*>(kernel), bytes);
-  };
-  hipError_t e = forward(k_forward<4>, 64);
-  if (e == hipSuccess) e = forward(k_forward<2>, 32);
-  if (e == hipSuccess) e = forward(k_forward<1>, 16);
+  hipError_t e = hipSuccess;
+  for (int nt = 1; nt <= 4 && e == hipSuccess; nt *= 2) {
+    const size_t bytes = forward_lds(D, H, K, 16 * nt);
+    if (nt == 1 || bytes <= kForwardLds)
+      e = allow(reinterpret_cast<const void*>(forward_kernel(D, nt)), bytes);
+  }
   if (e != hipSuccess) return e;
   return allow(reinterpret_cast<const void*>(train_kernel(H)), train_lds(D, H, K));
 }
@@ -759,7 +762,7 @@ hipError_t mlp_forward(tlda_mlp& m, const float* X, int64_t n, float* theta) {
   int nt = 1;
   if (forward_lds(D, H, K, 64) <= kForwardLds && n >= 64 * 512) nt = 4;
   else if (forward_lds(D, H, K, 32) <= kForwardLds && n >= 32 * 512) nt = 2;
-  auto kernel = nt == 4 ? k_forward<4> : nt == 2 ? k_forward<2> : k_forward<1>;
+  auto kernel = forward_kernel(D, nt);
   const size_t lds = forward_lds(D, H, K, 16 * nt);
   // a launch takes fewer than 2^32 work items
   const int64_t docs = 16 * nt, most = ((int64_t(1) << 32) / kThreads - 1) * docs;

@@ -211,7 +211,7 @@ def check_encoder_forward_takes_any_number_of_rows():
             row = 0
             for i, (kernel, grid) in enumerate(launches()):
                 assert base(kernel) == "k_forward"
-                docs = 16 * int(kernel.split("k_forward<")[1].split(">")[0])
+                docs = 16 * int(kernel.split("k_forward<")[1].split(",")[0])
                 assert FAKE.fake_arg(i, 0) == X + 4 * d_in * row
                 assert FAKE.fake_arg(i, 8) == theta + 4 * k_out * row, (i, kernel)
                 rows = FAKE.fake_arg(i, 1)
